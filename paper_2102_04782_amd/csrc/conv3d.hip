@@ -3,7 +3,10 @@
 // Where the 3-D problem IS a 2-D problem - a filter that does not extend in height and width (time-only filters and
 // pointwise layers: depth becomes the row axis and a whole frame the column axis), or a volume of depth one - the entry
 // points hand it to the 2-D entry points, matrix-core kernels included; the views involved are pure reinterpretations of
-// the NCDHW tensors.  Every other layer (3 x 3 x 3 and friends) runs on direct integer kernels: v_dot4_i32_i8 forms where
+// the NCDHW tensors.  Other layers of some size with groups = 1 run on the matrix cores too: forward and data gradient as
+// chunks of the 2-D tile kernel's contraction axis (conv_mfma_halo.hip, D3), the filter gradient of 3 x 3 frames as the
+// 2-D filter gradient of the layer's frames (below).  What is left - small or grouped layers, other extents and strides -
+// runs on direct integer kernels: v_dot4_i32_i8 forms where
 // the shapes allow it (k3_fwd_dot, k3_bwd_data_dot: 16 channels per load against filter rows that are uniform across the
 // wave; k3_bwd_filter_dot: four positions of a row per load, unit stride and dilation along w, filters of at most
 // 3 x 3 x 3), and one-multiply-at-a-time kernels for everything else.  The filter of such a layer is stored three times:
@@ -411,6 +414,155 @@ __global__ __launch_bounds__(kBlock) void k3_bwd_filter_dot(Geo3 g, CnhwView X, 
     }
 }
 
+// ---------------------------------------------------------------------------------------------
+// Filter gradient on the matrix cores.  For one depth tap the product is the 2-D filter gradient of the layer's frames:
+//     dW[co][ci][kd] = sum over (n, od) of the correlation of frame (n, od) of G with frame (n, od*sD + kd*dD - pD) of X ,
+// so the 2-D kernels (conv_mfma_dw32.hip) serve once the operands sit in their slots.  The carriers' channel-major planes
+// are dense rows, without the zero bytes those kernels rely on, so both operands are copied into the 2-D layouts of the
+// problem "every frame an image": the sample's depth padding becomes zero frames (shared between samples at unit stride,
+// like the padding of rows and images), a depth stride one copy of the activation per phase, and a depth tap the distance
+// of a whole number of frames.  The copies' rows are made a multiple of four bytes long (a few columns of zeros): a dword
+// of a copy then lies in one row and is one byte-aligned load, and a thread decodes its position once for 16 bytes.
+// ---------------------------------------------------------------------------------------------
+struct Relayout {
+    const int8_t* src;
+    int8_t* dst;
+    int64_t src_chan_pitch, src_lead;            // dense rows: element (n, z, h, w) of a channel at lead + ((n*D + z)*H + h)*W + w
+    int C, N, D, H, W;
+    int Dq, sD, pD;                              // frame slots per sample; slot q of depth phase r holds depth q*sD + r - pD
+    int64_t chan_pitch, plane_pitch, depth_pitch;   // of the destination; depth_pitch from one depth phase to the next
+    int lead, img_rows, row_pitch, ph_h, ph_w, org_h, org_w;
+    int lead_imgs;                               // whole images that cover the leading zeros
+    int per_plane;                               // workgroups per (channel, phase) plane
+    int blocks;
+    FastDiv div_slot, div_pitch, div_dq;
+};
+
+__device__ __forceinline__ void relayout(const Relayout& L, int b) {
+    const int plane = b / L.per_plane, jb = b - plane * L.per_plane;
+    const int phases = L.ph_h * L.ph_w;
+    const int c = (plane / phases) % L.C, ph = plane % phases, r = plane / (phases * L.C);
+    const int ph_h = ph / L.ph_w, ph_w = ph % L.ph_w;
+    const uint32_t slot = (uint32_t)(L.img_rows * L.row_pitch);
+    const int8_t* src = L.src + (int64_t)c * L.src_chan_pitch + L.src_lead;
+    int8_t* dst = L.dst + r * L.depth_pitch + (int64_t)c * L.chan_pitch + (int64_t)ph * L.plane_pitch;
+    // first byte of the frame in slot `img` of this depth phase, or -1 where the slot holds none
+    auto frame = [&](int img) -> int64_t {
+        const int n = (int)fdiv((uint32_t)max(img, 0), L.div_dq);
+        const int z = (img - n * L.Dq) * L.sD + r - L.pD;
+        return img >= 0 && n < L.N && (unsigned)z < (unsigned)L.D ? ((int64_t)n * L.D + z) * L.H * L.W : -1;
+    };
+    const int64_t at = ((int64_t)jb * kBlock + threadIdx.x) * 16;
+    if (at >= L.plane_pitch) return;
+    // the first of the thread's four dwords; the lead and the row pitch are multiples of four, so a dword lies in one row
+    const uint32_t o = (uint32_t)((int)at - L.lead) + (uint32_t)L.lead_imgs * slot;
+    const uint32_t q = fdiv(o, L.div_slot);
+    const uint32_t rem = o - q * slot;
+    int row = (int)fdiv(rem, L.div_pitch);
+    int col = (int)(rem - (uint32_t)row * (uint32_t)L.row_pitch);
+    int img = (int)q - L.lead_imgs;
+    int64_t f = frame(img);
+    int h = row * L.ph_h + ph_h - L.org_h, w = col * L.ph_w + ph_w - L.org_w;
+    uint32_t v[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+        const bool rok = f >= 0 && (unsigned)h < (unsigned)L.H;
+        // columns of the dword that exist: bytes before column 0 or behind the last one belong to other rows and are cleared
+        v[u] = 0;
+        if (L.ph_w == 1) {
+            if (rok && w > -4 && w < L.W) {
+                uint32_t raw;
+                __builtin_memcpy(&raw, src + f + h * L.W + w, 4);   // (the plane's zero halo reaches further than three bytes)
+                const int lo = max(0, -w), hi = min(4, L.W - w);    // 0 <= lo < hi <= 4
+                v[u] = raw & (0xFFFFFFFFu << (8 * lo)) & (0xFFFFFFFFu >> (32 - 8 * hi));
+            }
+        } else {
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+                if (rok && (unsigned)(w + i * L.ph_w) < (unsigned)L.W) v[u] |= (uint32_t)(uint8_t)src[f + h * L.W + w + i * L.ph_w] << (8 * i);
+        }
+        col += 4;
+        w += 4 * L.ph_w;
+        if (col == L.row_pitch) {
+            col = 0;
+            w = ph_w - L.org_w;
+            h += L.ph_h;
+            if (++row == L.img_rows) {
+                row = 0;
+                h = ph_h - L.org_h;
+                f = frame(++img);
+            }
+        }
+    }
+    *reinterpret_cast<uint4*>(dst + at) = make_uint4(v[0], v[1], v[2], v[3]);
+}
+
+__global__ __launch_bounds__(kBlock) void k3_relayout(Relayout a, Relayout b) {
+    if ((int)blockIdx.x < a.blocks) relayout(a, (int)blockIdx.x);
+    else relayout(b, (int)blockIdx.x - a.blocks);
+}
+
+// The two-dimensional problem of a layer's frames, the operands' places in the workspace, and what remains of the 3-D layer.
+struct Dw3Plan {
+    bool ok;
+    daq_conv_desc frames;      // every frame slot an image
+    daq_layout Lg, Lx;         // of the copies of vq and q(X)
+    int64_t off_g, off_x, bytes;
+    int Dq;
+    DwDepth depth;
+};
+
+// From this many multiply-accumulates on: the copies and the reduction are two launches more than the dot4 kernel's one, whose
+// rate is about 17 TOP/s (3 x 3 x 3, 32 -> 32, 4 x 16 x 16, 28 M: 52 against 65 us for the three calls of a backward step, which
+// at that size are bound by their launches; 64 -> 128, 4 x 8 x 8, 57 M: 140 against 59 us).
+constexpr int64_t kDw3MinMacs = (int64_t)40 << 20;
+
+Dw3Plan dw3_plan(const daq_conv3d_desc& d) {
+    Dw3Plan p{};
+    const Geo3 g = geo3_of(d);
+    if (d.groups != 1 || d.strideD > 8 || (int64_t)g.N * g.Do * g.Ho * g.Wo * g.Cout * g.Cin * g.kD * g.kH * g.kW < kDw3MinMacs) return p;
+    p.Dq = std::max(g.sD == 1 ? g.Din + g.pD : (int)ceil_div(g.Din + 2 * g.pD, g.sD), g.Do);
+    const int64_t frames = (int64_t)g.N * p.Dq, reach = (int64_t)(g.kD - 1) * g.dD / g.sD;
+    if (frames + reach >= ((int64_t)1 << 24)) return p;
+    p.frames = daq_conv_desc{(int)frames, g.Cin, g.Hin, g.Win, g.Cout, g.kH, g.kW, g.sH, g.sW, g.pH, g.pW, g.dH, g.dW, 1};
+    for (int extra = 0; extra < 16; ++extra, ++p.frames.Win) {   // columns of zeros that make the row pitch a multiple of four
+        daq_conv_desc longer = p.frames;                         // the activation has the frames the last depth tap reaches
+        longer.N += (int)reach;
+        if (daq_layout_vq(&p.frames, &p.Lg) != DAQ_OK || daq_layout_qx_cnhw(&longer, &p.Lx) != DAQ_OK) return p;
+        if (p.Lg.row_pitch % 4 == 0 && p.Lx.row_pitch % 4 == 0) break;
+    }
+    if (p.Lg.row_pitch % 4 || p.Lx.row_pitch % 4) return p;
+    const int64_t lim = (int64_t)1 << 31;
+    if (p.Lg.bytes >= lim || p.Lx.bytes * g.sD >= lim || !bwd_filter_lds_supported(p.frames, g.kD)) return p;
+    p.off_g = 256 + (int64_t)bwd_filter_lds_ws_bytes(p.frames, g.kD);
+    p.off_x = p.off_g + round_up(p.Lg.bytes, 256);
+    p.bytes = p.off_x + round_up(p.Lx.bytes * g.sD, 256);
+    p.depth = DwDepth{g.kD, g.dD, g.sD, p.Lx.chan_pitch, p.Lx.plane_pitch, p.Lx.bytes};
+    p.ok = true;
+    return p;
+}
+
+Relayout relayout_of(const daq_layout& from, const daq_layout& to, const int8_t* src, int8_t* dst, int N, int D, int H, int Dq, int sD, int pD) {
+    Relayout r{};
+    r.src = src; r.dst = dst;
+    r.src_chan_pitch = from.chan_pitch; r.src_lead = from.lead;
+    r.C = from.C; r.N = N; r.D = D; r.H = H; r.W = from.W;
+    r.Dq = Dq; r.sD = sD; r.pD = pD;
+    r.chan_pitch = to.chan_pitch; r.plane_pitch = to.plane_pitch; r.depth_pitch = to.bytes;
+    // an activation's lead ends with the padding columns of its first row; they are decoded as columns, so that rows start on dwords
+    const int adj = (int)(to.lead & 3);
+    r.lead = (int)to.lead - adj; r.img_rows = to.img_rows; r.row_pitch = to.row_pitch;
+    r.ph_h = to.phases_h; r.ph_w = to.phases_w; r.org_h = to.org_h; r.org_w = to.org_w + adj;
+    const int64_t slot = (int64_t)to.img_rows * to.row_pitch;
+    r.lead_imgs = (int)ceil_div(to.lead, slot);
+    r.per_plane = (int)ceil_div(to.plane_pitch, 16 * kBlock);
+    r.blocks = r.per_plane * r.C * r.ph_h * r.ph_w * sD;
+    r.div_slot = make_fastdiv((uint32_t)slot);
+    r.div_pitch = make_fastdiv((uint32_t)to.row_pitch);
+    r.div_dq = make_fastdiv((uint32_t)Dq);
+    return r;
+}
+
 // The two channel-contraction copies of the filter from its plain codes (the buffer behind the plain copy is zero).
 __global__ __launch_bounds__(kBlock) void k3_pack_w(const int8_t* __restrict__ plain, int Cout, int Cin, int groups, int taps, W3 L,
                                                     int8_t* __restrict__ out) {
@@ -505,9 +657,12 @@ extern "C" size_t daq_conv3d_workspace_bytes(daq_op op, const daq_conv3d_desc* d
     if (kind == 1) return daq_workspace_bytes(op, &cx);
     switch (op) {
         case DAQ_OP_QUANTIZE_GRAD: return daq_workspace_bytes(DAQ_OP_QUANTIZE_GRAD, &cg);
-        case DAQ_OP_CONV_FWD: return daq_workspace_bytes(DAQ_OP_CONV_FWD, &cx);
-        case DAQ_OP_CONV_BWD_DATA:
-        case DAQ_OP_CONV_BWD_FILTER: return 256;
+        case DAQ_OP_CONV_FWD: return daq_workspace_bytes(DAQ_OP_CONV_FWD, &cx) + conv3d_halo_ws_bytes(false, *desc);
+        case DAQ_OP_CONV_BWD_DATA: return 256 + conv3d_halo_ws_bytes(true, *desc);
+        case DAQ_OP_CONV_BWD_FILTER: {
+            const Dw3Plan p = dw3_plan(*desc);
+            return p.ok ? (size_t)p.bytes : 256;
+        }
         default: return 0;
     }
 }
@@ -551,6 +706,8 @@ extern "C" daq_status daq_conv3d_fwd_int8(const daq_conv3d_desc* desc, const flo
     DAQ_LAUNCH("pack_w", st, hipLaunchKernelGGL(k3_quant_plain, dim3((unsigned)ceil_div(wb, kBlock)), dim3(kBlock), 0, st, W, nw, bits, s_w, qw, wb));
     DAQ_LAUNCH("pack_w", st, hipLaunchKernelGGL(k3_pack_w, dim3((unsigned)ceil_div(nw, kBlock)), dim3(kBlock), 0, st, qw, g.Cout, g.Cin,
                                                 g.groups, taps, L3, qw));
+    if (conv3d_halo_ws_bytes(false, *desc))
+        return conv3d_fwd_halo(*desc, qx_nhwc, qw + L3.off_fwd, s_x, s_w, Y, acc_out, static_cast<char*>(workspace) + daq_workspace_bytes(DAQ_OP_CONV_FWD, &cx), st);
     const int64_t px = (int64_t)g.N * g.Do * g.Ho * g.Wo;
     if (dot_channels_ok(g.groups, g.cig, g.cog) && ceil_div(px, kBlock) < ((int64_t)1 << 31) && ceil_div(g.Cout, kCoT) <= 65535) {
         const dim3 grid((unsigned)ceil_div(px, kBlock), (unsigned)ceil_div(g.Cout, kCoT));
@@ -575,11 +732,15 @@ extern "C" daq_status daq_conv3d_bwd_data_int8(const daq_conv3d_desc* desc, cons
     if (kind == 1) return daq_conv_bwd_data_int8(&cx, qg, s_global, qw, s_w, dX, acc_out, workspace, workspace_bytes, stream);
     if (!qg || !s_global || !qw || !s_w || !dX) return DAQ_ERR_INVALID_ARG;
     if (!a16(qg) || !a16(qw) || !a16(dX) || !a16(acc_out)) return DAQ_ERR_INVALID_ARG;
-    if (!ws_ok(workspace, workspace_bytes, 256)) return DAQ_ERR_WORKSPACE;
+    if (!ws_ok(workspace, workspace_bytes, daq_conv3d_workspace_bytes(DAQ_OP_CONV_BWD_DATA, desc))) return DAQ_ERR_WORKSPACE;
     daq_layout Lg;
     if (daq_layout_qg(&cg, &Lg) != DAQ_OK || Lg.kind != DAQ_LAYOUT_NHWC) return DAQ_ERR_UNSUPPORTED;
     const Geo3 g = geo3_of(*desc);
     hipStream_t st = (hipStream_t)stream;
+    if (conv3d_halo_ws_bytes(true, *desc)) {
+        const W3 L3 = w3_of(g.Cout, g.Cin, g.groups, g.kD * g.kH * g.kW);
+        return conv3d_bwd_data_halo(*desc, qg, s_global, qw + L3.off_bwd, s_w, dX, acc_out, workspace, st);
+    }
     const int64_t px = (int64_t)g.N * g.Din * g.Hin * g.Win;
     // the contraction runs over the output channels of a group here: the roles of the two channel counts are exchanged
     if (dot_channels_ok(g.groups, g.cog, g.cig) && ceil_div(px, kBlock) < ((int64_t)1 << 31) && ceil_div(g.Cin, kCoT) <= 65535) {
@@ -606,11 +767,19 @@ extern "C" daq_status daq_conv3d_bwd_filter_int8(const daq_conv3d_desc* desc, co
     if (kind == 1) return daq_conv_bwd_filter_int8(&cx, qx_cnhw, s_x, vq, s_chan, dW, acc_out, workspace, workspace_bytes, stream);
     if (!qx_cnhw || !s_x || !vq || !s_chan || !dW) return DAQ_ERR_INVALID_ARG;
     if (!a16(qx_cnhw) || !a16(vq) || ((uintptr_t)dW & 3u) || ((uintptr_t)acc_out & 3u)) return DAQ_ERR_INVALID_ARG;
-    if (!ws_ok(workspace, workspace_bytes, 256)) return DAQ_ERR_WORKSPACE;
+    if (!ws_ok(workspace, workspace_bytes, daq_conv3d_workspace_bytes(DAQ_OP_CONV_BWD_FILTER, desc))) return DAQ_ERR_WORKSPACE;
     daq_layout Lx, Lg;
     if (daq_layout_qx_cnhw(&cx, &Lx) != DAQ_OK || daq_layout_vq(&cg, &Lg) != DAQ_OK) return DAQ_ERR_UNSUPPORTED;
     const Geo3 g = geo3_of(*desc);
     hipStream_t st = (hipStream_t)stream;
+    const Dw3Plan p = dw3_plan(*desc);
+    if (p.ok) {
+        int8_t* ws = static_cast<int8_t*>(workspace);
+        const Relayout rg = relayout_of(Lg, p.Lg, vq, ws + p.off_g, g.N, g.Do, g.Ho, p.Dq, 1, 0);
+        const Relayout rx = relayout_of(Lx, p.Lx, qx_cnhw, ws + p.off_x, g.N, g.Din, g.Hin, p.Dq, g.sD, g.pD);
+        DAQ_LAUNCH("conv3d_relayout", st, hipLaunchKernelGGL(k3_relayout, dim3((unsigned)(rg.blocks + rx.blocks)), dim3(kBlock), 0, st, rg, rx));
+        return conv_bwd_filter_lds(p.frames, ws + p.off_x, s_x, ws + p.off_g, s_chan, dW, acc_out, workspace, st, nullptr, false, &p.depth);
+    }
     if (g.sW == 1 && g.dW == 1 && g.kD <= 3 && g.kH <= 3 && g.kW <= 3 && (int64_t)g.N * g.Do * g.Ho < ((int64_t)1 << 31) &&
         (int64_t)g.Cout * g.cig < ((int64_t)1 << 31)) {
         DAQ_LAUNCH("conv3d_bwd_filter_dot", st,

@@ -54,8 +54,24 @@ struct Dw32Args {
     const float* s_x;
     const float* s_chan;
     float* dW;
-    int32_t* acc_out;    int bf16;              // dW is bfloat16 storage
+    int32_t* acc_out;
+    int bf16;             // dW is bfloat16 storage
+    // 3-D layers: depth tap kd = blockIdx.y is the same product against the activation's frames kd * dD further on (all
+    // 0 / taps / 0 for a 2-D layer, whose grid has one row)
+    int dD, sD, taps_all;
+    int64_t x_frame, x_depth_phase;   // bytes from a frame to the next, and from a depth-stride phase to the next
+    int64_t part_kd;                  // int32 entries of the partial tiles of one depth tap
 };
+
+// The launch's share for depth tap blockIdx.y: where it reads the activation and where it leaves its results.
+__device__ __forceinline__ void dw_depth(Dw32Args& p, int taps) {
+    const int kd = blockIdx.y;
+    if (kd == 0) return;
+    p.x += (int64_t)((kd * p.dD) % p.sD) * p.x_depth_phase + (int64_t)((kd * p.dD) / p.sD) * p.x_frame;
+    p.part += kd * p.part_kd;
+    p.dW += kd * taps;   // (3-D results are fp32)
+    if (p.acc_out) p.acc_out += kd * taps;
+}
 
 __device__ __forceinline__ int alignbyte(int hi, int lo, int sh) {
     return (int)__builtin_amdgcn_alignbyte((unsigned)hi, (unsigned)lo, (unsigned)sh);
@@ -112,6 +128,7 @@ __global__ __launch_bounds__(64 * WM * WN * WK) void k_dw32(Dw32Args p) {
     constexpr int B_MAX = S2 ? 5 : 4 * WN * 256 / NT;  // 16-byte units of the activation tile per thread, at most
     extern __shared__ __align__(16) int8_t lds[];
 
+    dw_depth(p, kT);
     const int tid = threadIdx.x, lane = tid % kWave;
     const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
     const int wk = wave % WK, wn = (wave / WK) % WN, wm = wave / (WK * WN);
@@ -354,11 +371,12 @@ __global__ __launch_bounds__(64 * WM * WN * WK) void k_dw32(Dw32Args p) {
             const int row = wave + WAVES * i, co = co0 + row;
             if (co >= p.Cout) break;
             const float sc = sx * (sc_row[i] / 127.0f);
-            const int64_t off = ((int64_t)co * p.Cin + ci0) * kT;
+            const int64_t off = ((int64_t)co * p.Cin + ci0) * p.taps_all;
             for (int j = lane; j < ncol; j += kWave) {
                 const int v = red[row * ROWW + j];
-                store_result(p.dW, off + j, (float)v * sc, p.bf16);
-                if (p.acc_out) p.acc_out[off + j] = v;
+                const int64_t at = off + (p.taps_all == kT ? j : (j / kT) * p.taps_all + j % kT);   // (a depth tap's nine results, then the next ci's)
+                store_result(p.dW, at, (float)v * sc, p.bf16);
+                if (p.acc_out) p.acc_out[at] = v;
             }
         }
         return;
@@ -378,7 +396,7 @@ __global__ __launch_bounds__(64 * WM * WN * WK) void k_dw32(Dw32Args p) {
     for (int r = 0; r < 16; ++r) {
         const int co = co0 + wm * 32 + 8 * (r >> 2) + 4 * lh + (r & 3);
         if (co < p.Cout) {
-            const int64_t off = ((int64_t)co * p.Cin + ci) * kT;
+            const int64_t off = ((int64_t)co * p.Cin + ci) * p.taps_all;
             const float sc = sx * (p.s_chan[co] / 127.0f);
 #pragma unroll
             for (int t = 0; t < kT; ++t) {
@@ -395,6 +413,12 @@ __global__ __launch_bounds__(64 * WM * WN * WK) void k_dw32(Dw32Args p) {
 // and keeps all of its loads in flight - no LDS, no barrier.
 __global__ __launch_bounds__(256) void k_dw_reduce(DwTail t) {
     __shared__ int32_t l_sum[4 * kWave];
+    if (blockIdx.y > 0) {   // depth tap of a 3-D layer
+        const int entries = t.blocks;
+        t.part += (int64_t)blockIdx.y * entries * t.splits * kWave;
+        t.dW += blockIdx.y * t.taps;
+        if (t.acc_out) t.acc_out += blockIdx.y * t.taps;
+    }
     if (t.splits > kDwReducePerWave) {
         dw_reduce_role(t, (int)blockIdx.x, l_sum);
         return;
@@ -441,6 +465,7 @@ __global__ __launch_bounds__(64 * WM * WN * WK) void k_dw11(Dw32Args p) {
     static_assert(NT % UPR == 0, "a thread's units all sit in the same 16-byte column of their rows");
     extern __shared__ __align__(16) int8_t lds[];
 
+    dw_depth(p, 1);
     const int tid = threadIdx.x, lane = tid % kWave;
     const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
     const int wk = wave % WK, wn = (wave / WK) % WN, wm = wave / (WK * WN);
@@ -653,7 +678,7 @@ __global__ __launch_bounds__(64 * WM * WN * WK) void k_dw11(Dw32Args p) {
             const int co = co0 + wm * 64 + 32 * (q / 32) + 8 * (r >> 2) + 4 * lh + (r & 3);
             const int ci = ci0 + wn * 64 + 32 * ((q / 16) % 2) + l32;
             if (co < p.Cout && ci < p.Cin) {
-                const int64_t off = (int64_t)co * p.Cin + ci;   // 32 lanes = 32 consecutive ci: 128-byte runs
+                const int64_t off = ((int64_t)co * p.Cin + ci) * p.taps_all;   // 32 lanes = 32 consecutive ci: 128-byte runs (2-D)
                 const float sc = WK > 1 ? sc_own[q % 8] : p.s_chan[co];
                 store_result(p.dW, off, (float)v * (sx * (sc / 127.0f)), p.bf16);
                 if (p.acc_out) p.acc_out[off] = v;
@@ -692,7 +717,8 @@ void choose_bands(Plan32& pl, int bm, int bn) {
     pl.blocks = (int64_t)kXcd * pl.band_m * pl.band_n;
 }
 
-Plan32 make_plan32(const daq_conv_desc& d) {
+// depth: depth taps of a 3-D layer (its frames are the images of `d`); the launch has that many times the tiles
+Plan32 make_plan32(const daq_conv_desc& d, int depth = 1) {
     Plan32 pl{};
     if (d.groups != 1) return pl;
     const bool unit = d.strideH == 1 && d.strideW == 1 && d.dilH == 1 && d.dilW == 1;
@@ -715,7 +741,7 @@ Plan32 make_plan32(const daq_conv_desc& d) {
         pl.tiles_m = (int)ceil_div(d.Cout, 64 * pl.wm);
         pl.tiles_n = (int)ceil_div(d.Cin, 64 * pl.wn);
         const int64_t tiles = (int64_t)pl.tiles_m * pl.tiles_n;
-        int64_t s = ceil_div(256, tiles);
+        int64_t s = ceil_div(256, tiles * depth);
         s = std::min<int64_t>(s, std::max(1, pl.nchunks / 2));
         pl.splits = (int)std::max<int64_t>(1, s);
         // One chunk per LDS stage.  (Two chunks per barrier were measured on the late ResNet-50 layers: the K loop of a
@@ -749,7 +775,7 @@ Plan32 make_plan32(const daq_conv_desc& d) {
     pl.tiles_m = (int)ceil_div(d.Cout, bm);
     pl.tiles_n = (int)ceil_div(d.Cin, bn);
     const int64_t tiles = (int64_t)pl.tiles_m * pl.tiles_n;
-    int64_t s = ceil_div(256, tiles);
+    int64_t s = ceil_div(256, tiles * depth);
     s = std::min<int64_t>(s, std::max(1, pl.nchunks / 2));
     pl.splits = (int)std::max<int64_t>(1, s);
     const size_t stage = (size_t)bm * kPA + (size_t)(pl.s2 ? 4 : 1) * bn * pl.pb;
@@ -764,8 +790,8 @@ Plan32 make_plan32(const daq_conv_desc& d) {
 }
 
 template <int WM, int WN, int WK, int PF, bool S2 = false>
-daq_status launch32(const Plan32& pl, const Dw32Args& a, int wq4, hipStream_t st) {
-    const dim3 grid((unsigned)pl.blocks);
+daq_status launch32(const Plan32& pl, const Dw32Args& a, int wq4, hipStream_t st, int depth) {
+    const dim3 grid((unsigned)pl.blocks, (unsigned)depth);
 #define DAQ_DW32_CASE(Q)                                                                                          \
     if (wq4 == Q) {                                                                                               \
         auto kern = k_dw32<Q, WM, WN, WK, PF, S2>;                                                                    \
@@ -782,18 +808,19 @@ daq_status launch32(const Plan32& pl, const Dw32Args& a, int wq4, hipStream_t st
 
 }  // namespace
 
-bool bwd_filter_lds_supported(const daq_conv_desc& d) { return make_plan32(d).ok; }
+bool bwd_filter_lds_supported(const daq_conv_desc& d, int depth) { return make_plan32(d, depth).ok; }
 
-size_t bwd_filter_lds_ws_bytes(const daq_conv_desc& d) {
-    const Plan32 pl = make_plan32(d);
+size_t bwd_filter_lds_ws_bytes(const daq_conv_desc& d, int depth) {
+    const Plan32 pl = make_plan32(d, depth);
     if (!pl.ok || pl.splits == 1) return 0;
-    return (size_t)round_up(pl.part_slots * pl.splits * 4, 256);
+    return (size_t)round_up(pl.part_slots * pl.splits * depth * 4, 256);
 }
 
 daq_status conv_bwd_filter_lds(const daq_conv_desc& d, const int8_t* qx, const float* s_x, const int8_t* vq,
-                               const float* s_chan, float* dW, int32_t* acc, void* ws, hipStream_t st, DwTail* defer, bool bf16) {
+                               const float* s_chan, float* dW, int32_t* acc, void* ws, hipStream_t st, DwTail* defer, bool bf16, const DwDepth* dp) {
     if (defer) defer->blocks = 0;
-    const Plan32 pl = make_plan32(d);
+    const int depth = dp ? dp->kD : 1;
+    const Plan32 pl = make_plan32(d, depth);
     if (!pl.ok) return DAQ_ERR_UNSUPPORTED;
     daq_layout Lx, Lg;
     if (daq_layout_qx_cnhw(&d, &Lx) != DAQ_OK || daq_layout_vq(&d, &Lg) != DAQ_OK) return DAQ_ERR_INVALID_ARG;
@@ -819,9 +846,22 @@ daq_status conv_bwd_filter_lds(const daq_conv_desc& d, const int8_t* qx, const f
     a.dW = dW;
     a.acc_out = acc;
     a.bf16 = bf16 ? 1 : 0;
+    const int taps = pl.k11 ? 1 : kT;
+    a.taps_all = taps * depth;
+    a.sD = 1;
+    if (dp) {
+        // the activation's buffer holds more frames than the gradient's and as many copies as the depth stride
+        a.dD = dp->dD;
+        a.sD = dp->sD;
+        a.x_chan_pitch = dp->x_chan_pitch;
+        a.x_plane_pitch = dp->x_plane_pitch;
+        a.x_frame = (int64_t)Lx.img_rows * Lx.row_pitch;
+        a.x_depth_phase = dp->x_depth_phase;
+        a.part_kd = pl.part_slots * pl.splits;
+    }
     const int wq4 = Lx.row_pitch & 3;
     if (pl.k11) {
-        const dim3 grid((unsigned)pl.blocks);
+        const dim3 grid((unsigned)pl.blocks, (unsigned)depth);
         if (pl.wk == 1) {
             auto kern = k_dw11<2, 2, 1, 1, 1>;
             if (hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)pl.lds_bytes) != hipSuccess)
@@ -834,23 +874,23 @@ daq_status conv_bwd_filter_lds(const daq_conv_desc& d, const int8_t* qx, const f
             DAQ_LAUNCH("conv_bwd_filter_dw11", st, hipLaunchKernelGGL(kern, grid, dim3(512), pl.lds_bytes, st, a));
         }
         if (pl.splits > 1 && defer && dw_tail_worthwhile((int)(pl.part_slots / kWave), pl.splits))
-            *defer = DwTail{a.part, (int)(pl.part_slots / kWave), pl.splits, pl.tiles_n, pl.wm, pl.wn, d.Cout, d.Cin, 1, s_x, s_chan, dW, acc, bf16 ? 1 : 0};
+            *defer = DwTail{a.part, (int)(pl.part_slots / kWave), pl.splits, pl.tiles_n, pl.wm, pl.wn, d.Cout, d.Cin, 1, s_x, s_chan, dW, acc, bf16 ? 1 : 0, taps * depth};
         else if (pl.splits > 1) {
-            const DwTail t{a.part, (int)(pl.part_slots / kWave), pl.splits, pl.tiles_n, pl.wm, pl.wn, d.Cout, d.Cin, 1, s_x, s_chan, dW, acc, bf16 ? 1 : 0};
+            const DwTail t{a.part, (int)(pl.part_slots / kWave), pl.splits, pl.tiles_n, pl.wm, pl.wn, d.Cout, d.Cin, 1, s_x, s_chan, dW, acc, bf16 ? 1 : 0, taps * depth};
             const unsigned blocks = pl.splits > kDwReducePerWave ? (unsigned)t.blocks : (unsigned)ceil_div(t.blocks, 4);
-            DAQ_LAUNCH("dw_reduce", st, hipLaunchKernelGGL(k_dw_reduce, dim3(blocks), dim3(256), 0, st, t));
+            DAQ_LAUNCH("dw_reduce", st, hipLaunchKernelGGL(k_dw_reduce, dim3(blocks, (unsigned)depth), dim3(256), 0, st, t));
         }
         return DAQ_OK;
     }
-    const daq_status rc = pl.s2 ? launch32<1, 1, 8, 2, true>(pl, a, wq4, st)
-                          : pl.wk == 1 ? launch32<2, 2, 1, 1>(pl, a, wq4, st) : launch32<1, 1, 8, 3>(pl, a, wq4, st);
+    const daq_status rc = pl.s2 ? launch32<1, 1, 8, 2, true>(pl, a, wq4, st, depth)
+                          : pl.wk == 1 ? launch32<2, 2, 1, 1>(pl, a, wq4, st, depth) : launch32<1, 1, 8, 3>(pl, a, wq4, st, depth);
     if (rc != DAQ_OK) return rc;
     if (pl.splits > 1 && defer && dw_tail_worthwhile((int)(pl.part_slots / kWave), pl.splits)) {
-        *defer = DwTail{a.part, (int)(pl.part_slots / kWave), pl.splits, pl.tiles_n, pl.wm, pl.wn, d.Cout, d.Cin, 9, s_x, s_chan, dW, acc, bf16 ? 1 : 0};
+        *defer = DwTail{a.part, (int)(pl.part_slots / kWave), pl.splits, pl.tiles_n, pl.wm, pl.wn, d.Cout, d.Cin, 9, s_x, s_chan, dW, acc, bf16 ? 1 : 0, taps * depth};
     } else if (pl.splits > 1) {
-        const DwTail t{a.part, (int)(pl.part_slots / kWave), pl.splits, pl.tiles_n, pl.wm, pl.wn, d.Cout, d.Cin, 9, s_x, s_chan, dW, acc, bf16 ? 1 : 0};
+        const DwTail t{a.part, (int)(pl.part_slots / kWave), pl.splits, pl.tiles_n, pl.wm, pl.wn, d.Cout, d.Cin, 9, s_x, s_chan, dW, acc, bf16 ? 1 : 0, taps * depth};
         const unsigned blocks = pl.splits > kDwReducePerWave ? (unsigned)t.blocks : (unsigned)ceil_div(t.blocks, 4);
-        DAQ_LAUNCH("dw_reduce", st, hipLaunchKernelGGL(k_dw_reduce, dim3(blocks), dim3(256), 0, st, t));
+        DAQ_LAUNCH("dw_reduce", st, hipLaunchKernelGGL(k_dw_reduce, dim3(blocks, (unsigned)depth), dim3(256), 0, st, t));
     }
     return DAQ_OK;
 }

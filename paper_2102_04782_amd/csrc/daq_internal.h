@@ -165,14 +165,20 @@ daq_status conv_fwd_mfma(const daq_conv_desc& d, const int8_t* qx_nhwc, const in
 
 
 // conv_mfma_dw32.hip: 3 x 3 unit-stride filter gradient on the 32x32x32 MFMA, operands staged through LDS
-bool bwd_filter_lds_supported(const daq_conv_desc& d);
-size_t bwd_filter_lds_ws_bytes(const daq_conv_desc& d);
+// A 3-D layer is the 2-D problem of its frames, `depth` times over: depth tap kd pairs the gradient's frames with the
+// activation's frames (kd * dD) / sD further on in depth-stride phase (kd * dD) % sD of the buffer.
+struct DwDepth {
+    int kD, dD, sD;
+    int64_t x_chan_pitch, x_plane_pitch, x_depth_phase;
+};
+bool bwd_filter_lds_supported(const daq_conv_desc& d, int depth = 1);
+size_t bwd_filter_lds_ws_bytes(const daq_conv_desc& d, int depth = 1);
 // With `defer`, a K-split launch leaves its last stage (sum of the partial tiles, de-quantization) undone and
 // describes it in *defer (blocks == 0: nothing is left) for a later kernel's extra workgroups, see dw_tail.h.
 struct DwTail;
 daq_status conv_bwd_filter_lds(const daq_conv_desc& d, const int8_t* qx, const float* s_x, const int8_t* vq,
                                const float* s_chan, float* dW, int32_t* acc, void* ws, hipStream_t st,
-                               DwTail* defer = nullptr, bool bf16 = false);
+                               DwTail* defer = nullptr, bool bf16 = false, const DwDepth* dp = nullptr);
 
 // conv_mfma_halo.hip: halo-tile form of the channel-contracting kernel (unit stride; stride 2 for the data gradient)
 bool bwd_data_halo_supported(const daq_conv_desc& d);
@@ -184,6 +190,12 @@ daq_status conv_bwd_data_halo(const daq_conv_desc& d, const int8_t* qg, const fl
 bool fwd_halo_supported(const daq_conv_desc& d);
 daq_status conv_fwd_halo(const daq_conv_desc& d, const int8_t* qx_nhwc, const int8_t* qw, const float* s_x,
                          const float* s_w, float* Y, int32_t* acc, hipStream_t st);
+// 3-D layers on the same kernel.  The workspace holds the filter in fragment order; 0 bytes: the layer stays on the kernels of conv3d.hip.
+size_t conv3d_halo_ws_bytes(bool backward, const daq_conv3d_desc& d);
+daq_status conv3d_bwd_data_halo(const daq_conv3d_desc& d, const int8_t* qg, const float* s_g, const int8_t* w_bwd, const float* s_w, float* dX,
+                                int32_t* acc, void* frag, hipStream_t st);
+daq_status conv3d_fwd_halo(const daq_conv3d_desc& d, const int8_t* qx, const int8_t* w_fwd, const float* s_x, const float* s_w, float* Y,
+                           int32_t* acc, void* frag, hipStream_t st);
 
 // conv_depthwise.hip: groups == channels, both operands channel-major
 bool depthwise_dx_supported(const daq_conv_desc& d);

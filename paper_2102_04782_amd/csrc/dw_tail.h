@@ -26,6 +26,7 @@ struct DwTail {
     float* dW;
     int32_t* acc_out;
     int bf16;              // dW is bfloat16 storage
+    int taps_all;          // elements of dW from one (co, ci) to the next: `taps`, or kD * taps where depth tap kd is grid row blockIdx.y
 };
 
 // Whether the role should replace the reduction launch: one workgroup per entry, each with more than 32 splits.
@@ -47,11 +48,11 @@ __device__ __forceinline__ int64_t dw_tail_element(const DwTail& t, int e, int l
         // register r of tap slot/16: row (co) 8*(r/4) + 4*(lane/32) + r%4, column (ci) lane%32
         co = (tm * t.wm_n + wm) * 32 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
         ci = (tn * t.wn_n + wn) * 32 + (lane & 31);
-        off = ((int64_t)co * t.Cin + ci) * 9 + slot / 16;
+        off = ((int64_t)co * t.Cin + ci) * t.taps_all + slot / 16;
     } else {
         co = (tm * t.wm_n + wm) * 64 + 32 * (slot / 32) + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
         ci = (tn * t.wn_n + wn) * 64 + 32 * ((slot / 16) % 2) + (lane & 31);
-        off = (int64_t)co * t.Cin + ci;
+        off = ((int64_t)co * t.Cin + ci) * t.taps_all;
     }
     return (co < t.Cout && ci < t.Cin) ? off : -1;
 }

@@ -29,6 +29,19 @@ LAYERS = {
     "grouped16": ((1, 32, 3, 6, 5, 48, 3, 3, 3, 1, 1, 1, 1, 1, 1, 1, 1, 1, 2), 0),      # whole 16-channel records per group: dot4 forms
     "wide_rows": ((1, 20, 3, 5, 23, 33, 3, 3, 3, 1, 1, 1, 1, 1, 1, 1, 1, 1, 1), 0),     # rows that are not a multiple of four positions
     "h_strided": ((2, 6, 6, 9, 10, 10, 3, 3, 3, 2, 2, 1, 1, 1, 1, 1, 1, 1, 1), 0),      # strides in depth and height, unit stride along w
+    # large enough for the matrix-core forms (conv_mfma_halo.hip D3, the filter gradient of the frames): odd images, channel
+    # counts off every tile, frames whose depth taps fall off either end
+    "mc_3x3x3": ((2, 44, 6, 16, 15, 72, 3, 3, 3, 1, 1, 1, 1, 1, 1, 1, 1, 1, 1), 0),     # 256-pixel tiles, nine constant taps
+    "mc_7x7": ((3, 160, 4, 7, 7, 96, 3, 3, 3, 1, 1, 1, 1, 1, 1, 1, 1, 1, 1), 0),        # several frames per tile, several chunks per depth tap
+    "mc_thin": ((2, 20, 5, 21, 19, 136, 3, 3, 3, 1, 1, 1, 1, 1, 1, 1, 1, 1, 1), 0),     # at most 32 result channels
+    "mc_r128": ((1, 128, 16, 64, 64, 16, 1, 3, 3, 1, 1, 1, 0, 1, 1, 1, 1, 1, 1), 0),    # 128-row tiles; one depth tap
+    "mc_no_pad": ((2, 64, 7, 14, 13, 48, 3, 3, 3, 1, 1, 1, 0, 0, 0, 1, 1, 1, 1), 0),    # output volume smaller than the input's
+    "mc_deep_pad": ((2, 48, 4, 12, 12, 56, 3, 3, 3, 1, 1, 1, 2, 1, 1, 2, 1, 1, 1), 0),  # depth dilation 2
+    "mc_s2": ((4, 64, 5, 17, 16, 80, 3, 3, 3, 1, 2, 2, 1, 1, 1, 1, 1, 1, 1), 0),        # stride 2 in height and width: parity classes, phase planes
+    "mc_depth_s2": ((2, 64, 9, 14, 12, 64, 3, 3, 3, 2, 1, 1, 1, 1, 1, 1, 1, 1, 1), 0),  # stride 2 in depth only
+    "mc_all_s2": ((4, 64, 8, 18, 18, 96, 3, 3, 3, 2, 2, 2, 1, 1, 1, 1, 1, 1, 1), 0),    # in all three
+    "mc_taps15": ((2, 64, 5, 14, 14, 48, 3, 5, 3, 1, 1, 1, 1, 2, 1, 1, 1, 1, 1), 0),    # run-time tap list in the data gradient
+    "mc_1x1_s2": ((4, 128, 6, 20, 20, 128, 3, 1, 1, 1, 2, 2, 1, 0, 0, 1, 1, 1, 1), 0),  # no height or width extent, but a stride there
     "big_pad": ((1, 4, 4, 5, 6, 5, 3, 3, 3, 1, 1, 1, 2, 2, 2, 1, 1, 1, 1), 0),          # padding wider than the filter's reach
 }
 
