@@ -18,6 +18,7 @@
 // can also be split across workgroups: partial tiles are written with coalesced stores and summed
 // by k_dw_reduce.
 #include <algorithm>
+#include <type_traits>
 
 #include "daq_internal.h"
 #include "dw_tail.h"
@@ -71,6 +72,15 @@ __device__ __forceinline__ void dw_depth(Dw32Args& p, int taps) {
     p.part += kd * p.part_kd;
     p.dW += kd * taps;   // (3-D results are fp32)
     if (p.acc_out) p.acc_out += kd * taps;
+}
+
+// f(0), f(1), ... f(N - 1) with constant arguments.
+template <int N, int I = 0, typename F>
+__device__ __forceinline__ void ring_round(F f) {
+    if constexpr (I < N) {
+        f(std::integral_constant<int, I>{});
+        ring_round<N, I + 1>(f);
+    }
 }
 
 __device__ __forceinline__ int alignbyte(int hi, int lo, int sh) {
@@ -217,11 +227,8 @@ __global__ __launch_bounds__(64 * WM * WN * WK) void k_dw32(Dw32Args p) {
 
     const int arow = (wm * 32 + l32) * kPA + 16 * lh;
     const int brow = A_BYTES + (wn * 32 + l32) * p.pb + 16 * lh;
-    for (int base = c_begin; base < c_end; base += PF) {
-#pragma unroll
-      for (int u = 0; u < PF; ++u) {
-        const int chunk = base + u;
-        if (chunk >= c_end) break;   // uniform
+    auto step = [&](int chunk, auto ring_step) {
+        constexpr int u = ring_step;   // position in the ring: a constant, so that the sets stay in registers
         const int buf = (chunk - c_begin) & 1;
         const int8_t* A = lds + buf * STAGE + arow;
         const int8_t* B = lds + buf * STAGE + brow;
@@ -303,8 +310,13 @@ __global__ __launch_bounds__(64 * WM * WN * WK) void k_dw32(Dw32Args p) {
         store_chunk(buf ^ 1, (u + 1) % PF);
         load_chunk(chunk + 1 + PF, (u + 1) % PF);
         __syncthreads();
-      }
-    }
+    };
+    // Whole rounds of the ring first, without an exit in between: at the head of a loop that can be left and entered
+    // half-way round, the compiler no longer knows which loads are the oldest and waits for all of them (measured on this
+    // one: every third chunk waited for a load issued right before it).
+    int chunk = c_begin;
+    for (; chunk + PF <= c_end; chunk += PF) ring_round<PF>([&](auto u) { step(chunk + (int)u, u); });
+    ring_round<PF - 1>([&](auto u) { if (chunk + (int)u < c_end) step(chunk + (int)u, u); });
 
     // register r of a 32 x 32 tile: row (co) 8*(r/4) + 4*lh + r%4, column (ci) l32; slot = tap*16 + r
     constexpr int SLOTS = kT * 16;
@@ -698,6 +710,24 @@ struct Plan32 {
     int64_t part_slots;   // int32 entries of one split's partial tiles
 };
 
+// K splits across workgroups.  A workgroup fills a CU (its combine area, or the four stages of the direct-to-LDS form, is
+// 130 KB of LDS), so a launch of more than 256 runs in rounds, and 264 take as long as 512; a split launch is followed by
+// the reduction, which costs a launch and the partial tiles' way to memory and back.  The split that minimises
+//     rounds * (chunks of a workgroup * t_chunk + t_fixed) + (reduction, if any)
+// with the measured times: 0.75 us per chunk for nine taps and 0.45 us for one, 4 us of prologue, combine and stores, 5 us for
+// a reduction and its launch, partial tiles at 3 TB/s.  (64 -> 64, 3 x 3 x 3 on 8 x 56 x 56: 22 splits were 264 workgroups,
+// 57 us; 21 are 252.  16 -> 16, 3 x 3 on 16 x 16, batch 4: five chunks, one split, no reduction.)
+int choose_splits(int64_t tiles, int nchunks, double t_chunk, double tile_bytes) {
+    double best = 0.0;
+    int best_s = 1;
+    for (int s = 1; s <= nchunks && (s == 1 || tiles * s <= 4 * 256); ++s) {
+        const double rounds = (double)ceil_div(tiles * s, 256);
+        const double t = rounds * ((double)ceil_div(nchunks, s) * t_chunk + 4.0) + (s > 1 ? 5.0 + 2.0 * (double)tiles * s * tile_bytes / 3e6 : 0.0);
+        if (s == 1 || t < best) { best = t; best_s = s; }
+    }
+    return best_s;
+}
+
 // Rectangles per split for 1, 2 or 4 splits (8, 4 or 2 XCDs share a split): the cut of the tile grid that makes an
 // XCD touch the fewest operand rows, rows of the two operands weighted by their tile heights.
 void choose_bands(Plan32& pl, int bm, int bn) {
@@ -741,9 +771,7 @@ Plan32 make_plan32(const daq_conv_desc& d, int depth = 1) {
         pl.tiles_m = (int)ceil_div(d.Cout, 64 * pl.wm);
         pl.tiles_n = (int)ceil_div(d.Cin, 64 * pl.wn);
         const int64_t tiles = (int64_t)pl.tiles_m * pl.tiles_n;
-        int64_t s = ceil_div(256, tiles * depth);
-        s = std::min<int64_t>(s, std::max(1, pl.nchunks / 2));
-        pl.splits = (int)std::max<int64_t>(1, s);
+        pl.splits = pl.wk == 1 ? 1 : choose_splits(tiles * depth, pl.nchunks, 0.45, 64 * 64 * 4);
         // One chunk per LDS stage.  (Two chunks per barrier were measured on the late ResNet-50 layers: the K loop of a
         // workgroup - 13 chunks of 32 KiB in 7 us on every CU at once, bound by the staging through registers and LDS and
         // its two waits per chunk - gets a quarter shorter per byte, and the first stage arrives that much later.)
@@ -775,9 +803,7 @@ Plan32 make_plan32(const daq_conv_desc& d, int depth = 1) {
     pl.tiles_m = (int)ceil_div(d.Cout, bm);
     pl.tiles_n = (int)ceil_div(d.Cin, bn);
     const int64_t tiles = (int64_t)pl.tiles_m * pl.tiles_n;
-    int64_t s = ceil_div(256, tiles * depth);
-    s = std::min<int64_t>(s, std::max(1, pl.nchunks / 2));
-    pl.splits = (int)std::max<int64_t>(1, s);
+    pl.splits = pl.wk == 1 ? 1 : choose_splits(tiles * depth, pl.nchunks, 0.75, 32 * 32 * kT * 4);
     const size_t stage = (size_t)bm * kPA + (size_t)(pl.s2 ? 4 : 1) * bn * pl.pb;
     // hand-over area of the parallel combine: [owner][source][slot][lane]
     const int rounds = pl.wk > 4 ? 2 : 1;

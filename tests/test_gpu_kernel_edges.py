@@ -1,0 +1,34 @@
+"""Sizes at which a kernel's loop or a dispatch rule turns over, against the oracle (integers exactly, see test_gpu_parity)."""
+import numpy as np
+import pytest
+
+from paper_2102_04782_amd import workloads as wl
+from test_gpu_parity import run_convs_on_codes
+
+pytestmark = pytest.mark.gpu
+
+
+def on_random_codes(layer, seed):
+    rng = np.random.default_rng(seed)
+    qX = rng.integers(-127, 128, layer.x_shape).astype(np.int8)
+    qW = rng.integers(-127, 128, layer.w_shape).astype(np.int8)
+    qG = rng.integers(-127, 128, layer.y_shape).astype(np.int8)
+    s_c = (10.0 ** rng.uniform(-4, -1, layer.Cout)).astype(np.float32)
+    run_convs_on_codes(layer, qX, qW, qG, 2.5, 0.11, 0.03, s_c)
+
+
+@pytest.mark.parametrize("batch", [1, 4, 8, 12, 16, 20, 24])
+@pytest.mark.parametrize("stride", [1, 2])
+def test_filter_gradient_ring_remainders(batch, stride):
+    """3 x 3: one to seven 256-byte chunks of the flat axis, all in one workgroup: whole rounds of the load ring and every
+    remainder."""
+    on_random_codes(wl.Layer("ring", batch, 20, 7 * stride, 7 * stride, 24, 3, 3, stride, 1), 40 + batch)
+
+
+@pytest.mark.parametrize("layer", [
+    wl.Layer("t3x5", 6, 160, 20, 20, 96, 3, 3, 1, 1),        # 15 tiles: 17 splits fill the chip, 18 would need a second round
+    wl.Layer("t1x1_odd", 5, 200, 17, 17, 344, 1, 1, 1, 0),   # 24 tiles of 64 x 64
+    wl.Layer("t130", 2, 416, 10, 10, 320, 3, 3, 1, 1),       # 130 tiles: two rounds cannot pay, one split
+], ids=lambda l: l.name)
+def test_filter_gradient_splits(layer):
+    on_random_codes(layer, 77)
