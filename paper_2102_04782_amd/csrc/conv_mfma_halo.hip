@@ -584,15 +584,21 @@ struct StreamArgs {
     const float* s_a;
     const float* s_b;
     float* out;
+    uint32_t out_bytes;   // STORE 1 and 2
     int32_t* acc_out;
-    int nt;
     DwTail tail;          // tail.blocks > 0: that many workgroups behind the first main_blocks finish a deferred filter gradient
     int main_blocks;
     int bf16;             // the result is bfloat16 storage
 };
 
 // KS = 32-byte contraction steps (cp <= 32 * KS)
-template <int KS>
+// STORE: how the results leave.  1 (fp32) and 2 (bfloat16, even planes): through a buffer descriptor, an offset past its extent
+// for pixels and rows that do not exist, so that every group issues the same number of stores with no branch between them.
+// Loads and stores retire in order, and only with that number known can the compiler wait for the next group's pixel
+// fragments alone; behind branches it waits for everything, i.e. for the group's own stores to reach memory.
+// (ResNet-50, batch 64, backward of the layer: 256 -> 64 at 56 x 56 114 -> 105 us, 256 -> 128 at 56 x 56 167 -> 140,
+// 512 -> 256 at 28 x 28 100 -> 93.)  0: any result (accumulators too, bfloat16 on odd planes, 2 GiB and more).
+template <int KS, int STORE, bool NT>
 __global__ __launch_bounds__(256) void k_dx_1x1_stream(StreamArgs p) {
     __shared__ int32_t l_role[256];
     if (p.tail.blocks > 0 && (int)blockIdx.x >= p.main_blocks) {   // uniform
@@ -611,6 +617,8 @@ __global__ __launch_bounds__(256) void k_dx_1x1_stream(StreamArgs p) {
     const __amdgpu_buffer_rsrc_t rs_src = __builtin_amdgcn_make_buffer_rsrc((void*)p.src, 0, (int)p.src_bytes, 0x00020000);
     const __amdgpu_buffer_rsrc_t rs_w = __builtin_amdgcn_make_buffer_rsrc((void*)p.wfrag, 0, (int)p.wfrag_bytes, 0x00020000);
     const float scale = (*p.s_a / 127.0f) * (*p.s_b / 127.0f);
+    const __amdgpu_buffer_rsrc_t rs_out = __builtin_amdgcn_make_buffer_rsrc((void*)p.out, 0, (int)p.out_bytes, 0x00020000);
+    const bool rows_full = 64 * rp + 64 <= p.Crow;   // uniform
 
     v4i A[2][KS];
 #pragma unroll
@@ -631,6 +639,8 @@ __global__ __launch_bounds__(256) void k_dx_1x1_stream(StreamArgs p) {
     };
     v4i B[KS];
     fetch(s, B);
+    // the loop is entered with nothing on its way, so that its head waits as its own back edge needs
+    __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0)
     for (uint32_t grp = s; grp < p.groups; grp += (uint32_t)p.S) {
         v4i Bn[KS];
         fetch(grp + (uint32_t)p.S, Bn);
@@ -643,7 +653,34 @@ __global__ __launch_bounds__(256) void k_dx_1x1_stream(StreamArgs p) {
             for (int ks = 0; ks < KS; ++ks) acc[j] = __builtin_amdgcn_mfma_i32_32x32x32_i8(A[j][ks], B[ks], acc[j], 0, 0, 0);
         }
         const uint32_t P = grp * 32u + (uint32_t)l32;
-        if (P < p.total_px) {
+        if constexpr (STORE != 0) {
+            const uint32_t n = fdiv(P < p.total_px ? P : 0u, p.div_hw);
+            const uint32_t r0 = P - n * (uint32_t)p.HW;
+            constexpr uint32_t EB = STORE == 1 ? 4 : 2;
+            const uint32_t row_bytes = (uint32_t)p.HW * EB;
+            const bool odd = l32 & 1;
+            const int lane_row = 64 * rp + 4 * lh + (STORE == 2 && odd ? 1 : 0);   // bfloat16: see below
+            const uint32_t at = ((n * (uint32_t)p.Crow + (uint32_t)lane_row) * (uint32_t)p.HW + r0 - (STORE == 2 && odd ? 1u : 0u)) * EB;
+            const uint32_t voff = P < p.total_px ? at : kOob;
+#pragma unroll
+            for (int j = 0; j < 2; ++j)
+#pragma unroll
+                for (int r = 0; r < 16; r += STORE) {
+                    const int dr = 32 * j + 8 * (r >> 2) + (r & 3);
+                    const uint32_t v = (rows_full | (lane_row + dr < p.Crow)) ? voff : kOob;
+                    if constexpr (STORE == 1) {
+                        const int w = __builtin_bit_cast(int, (float)acc[j][r] * scale);
+                        __builtin_amdgcn_raw_buffer_store_b32(w, rs_out, (int)v, (int)((uint32_t)dr * row_bytes), NT ? 2 : 0);   // 2: streaming
+                    } else {
+                        // lanes 2k and 2k+1 hold pixels r0 (even) and r0 + 1 of one plane: they trade values, and the even
+                        // lane stores the pair of row dr, the odd lane that of row dr + 1, one aligned dword each
+                        const uint32_t v0 = bf16_bits((float)acc[j][r] * scale), v1 = bf16_bits((float)acc[j][r + 1] * scale);
+                        const uint32_t got = (uint32_t)__builtin_amdgcn_mov_dpp((int)(odd ? v0 : v1), 0xB1, 0xF, 0xF, false);
+                        const int w = (int)(odd ? (got | (v1 << 16)) : (v0 | (got << 16)));
+                        __builtin_amdgcn_raw_buffer_store_b32(w, rs_out, (int)v, (int)((uint32_t)dr * row_bytes), NT ? 2 : 0);   // 2: streaming
+                    }
+                }
+        } else if (P < p.total_px) {
             const uint32_t n = fdiv(P, p.div_hw);
             const uint32_t r0 = P - n * (uint32_t)p.HW;
 #pragma unroll
@@ -665,7 +702,7 @@ __global__ __launch_bounds__(256) void k_dx_1x1_stream(StreamArgs p) {
                             const int dr = 8 * (r >> 2) + (r & 3) + (odd ? 1 : 0);
                             if (rowbase + dr < p.Crow) {
                                 uint32_t* z = reinterpret_cast<uint32_t*>(ob + (int64_t)dr * p.HW - (odd ? 1 : 0));
-                                if (p.nt) __builtin_nontemporal_store(word, z);
+                                if (NT) __builtin_nontemporal_store(word, z);
                                 else *z = word;
                             }
                         }
@@ -683,7 +720,7 @@ __global__ __launch_bounds__(256) void k_dx_1x1_stream(StreamArgs p) {
                     const int dr = 8 * (r >> 2) + (r & 3);
                     if (rowbase + dr >= p.Crow) continue;
                     float* z = p.out + at + (int64_t)dr * p.HW;
-                    if (p.nt) __builtin_nontemporal_store((float)acc[j][r] * scale, z);
+                    if (NT) __builtin_nontemporal_store((float)acc[j][r] * scale, z);
                     else *z = (float)acc[j][r] * scale;
                     if (p.acc_out) p.acc_out[at + (int64_t)dr * p.HW] = acc[j][r];
                 }
@@ -1079,16 +1116,25 @@ daq_status launch_stream(const char* name, const daq_conv_desc& d, const daq_lay
     a.s_a = s_a; a.s_b = s_b;
     a.out = out; a.acc_out = acc;
     a.bf16 = bf16 ? 1 : 0;
-    a.nt = (int64_t)d.N * rows * a.HW * (bf16 ? 2 : 4) >= kStreamBytes;
     const int64_t wgs = (int64_t)a.RP * ceil_div(a.S, 4);
     if (tail) a.tail = *tail;
     a.main_blocks = (int)wgs;
     const dim3 grid((unsigned)(wgs + a.tail.blocks));
-#define DAQ_STREAM(KSV) DAQ_LAUNCH(name, st, hipLaunchKernelGGL((k_dx_1x1_stream<KSV>), grid, dim3(256), 0, st, a))
-    if (ks <= 1) DAQ_STREAM(1);
-    else if (ks <= 2) DAQ_STREAM(2);
-    else if (ks <= 4) DAQ_STREAM(4);
-    else DAQ_STREAM(8);
+    const int64_t out_bytes = (int64_t)d.N * rows * a.HW * (bf16 ? 2 : 4);
+    const int store = acc || out_bytes >= ((int64_t)1 << 31) || (bf16 && (a.HW & 1)) ? 0 : bf16 ? 2 : 1;
+    const bool nt = stream_result(out_bytes, (int64_t)a.HW * (bf16 ? 2 : 4));
+    a.out_bytes = store ? (uint32_t)out_bytes : 0u;
+#define DAQ_STREAM(KSV)                                                                                                          \
+    {                                                                                                                            \
+        auto kern = store == 1 ? (nt ? k_dx_1x1_stream<KSV, 1, true> : k_dx_1x1_stream<KSV, 1, false>)                          \
+                    : store == 2 ? (nt ? k_dx_1x1_stream<KSV, 2, true> : k_dx_1x1_stream<KSV, 2, false>)                        \
+                                 : (nt ? k_dx_1x1_stream<KSV, 0, true> : k_dx_1x1_stream<KSV, 0, false>);                       \
+        DAQ_LAUNCH(name, st, hipLaunchKernelGGL(kern, grid, dim3(256), 0, st, a));                                               \
+    }
+    if (ks <= 1) DAQ_STREAM(1)
+    else if (ks <= 2) DAQ_STREAM(2)
+    else if (ks <= 4) DAQ_STREAM(4)
+    else DAQ_STREAM(8)
 #undef DAQ_STREAM
     return DAQ_OK;
 }
@@ -1112,7 +1158,7 @@ daq_status conv_bwd_data_halo(const daq_conv_desc& d, const int8_t* qg, const fl
     g.a.wfrag = qw + Lw.off_bwd_frag;
     g.a.s_a = s_w; g.a.s_b = s_g;
     g.a.out = dX; g.a.acc_out = acc;
-    g.a.nt = !bf16 && (int64_t)d.N * d.Cin * d.Hin * d.Win * 4 >= kStreamBytes;
+    g.a.nt = !bf16 && stream_result((int64_t)d.N * d.Cin * d.Hin * d.Win * 4, (int64_t)d.Hin * d.Win * 4);
     return launch(g, st, kBwdNames);
 }
 
@@ -1131,7 +1177,7 @@ daq_status conv_fwd_halo(const daq_conv_desc& d, const int8_t* qx, const int8_t*
     g.a.wfrag = qw + Lw.off_fwd_frag;
     g.a.s_a = s_x; g.a.s_b = s_w;
     g.a.out = Y; g.a.acc_out = acc;
-    g.a.nt = (int64_t)d.N * d.Cout * daq_out_h(&d) * daq_out_w(&d) * 4 >= kStreamBytes;
+    g.a.nt = stream_result((int64_t)d.N * d.Cout * daq_out_h(&d) * daq_out_w(&d) * 4, (int64_t)daq_out_h(&d) * daq_out_w(&d) * 4);
     return launch(g, st, kFwdNames);
 }
 

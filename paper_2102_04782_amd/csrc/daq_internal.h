@@ -16,6 +16,9 @@ constexpr float kTinyScale = 7.888609052210118e-31f;  // 2^-100: below this a sc
 // produced instead of at the end of the kernel, and without evicting the int8 operands the next kernels read.
 // Smaller results stay in the write-back caches, which is faster for them (measured: 12.8 MB slower, 25.7 MB faster).
 constexpr int64_t kStreamBytes = (int64_t)24 << 20;
+// And only where a result plane is a whole number of 64-byte half-lines: the pieces of a line that two tiles share otherwise
+// reach memory one by one (1 x 1, 1024 -> 256 at 14 x 14, batch 64, planes of 784 bytes, data gradient: 17 against 24 us).
+inline bool stream_result(int64_t bytes, int64_t plane_bytes) { return bytes >= kStreamBytes && plane_bytes % 64 == 0; }
 constexpr int kKAlign = 256;         // the flattened (n,h,w) axis of a CNHW buffer is padded to this many bytes
 
 inline int64_t round_up(int64_t v, int64_t m) { return (v + m - 1) / m * m; }
