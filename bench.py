@@ -491,7 +491,7 @@ def sweep_forward(args, dev) -> int:
     layers = wl.config_layers(args.config)
     steps = max(3, min(args.steps, 20))
     seen, rows_out = {}, []
-    tot = {"conv": 0.0, "quantize_x": 0.0, "quantize_w": 0.0}
+    tot = {"conv": 0.0, "quantize": 0.0}
     for li, L in enumerate(layers):
         key = L.desc_fields()
         if key not in seen:
@@ -510,14 +510,12 @@ def sweep_forward(args, dev) -> int:
             rows, _ = prof_rows_us(daq.prof_end(), steps)
             t = {k: us * n for k, (us, n) in rows.items()}
             conv = sum(v for k, v in t.items() if k.startswith("conv"))
-            qw = t.get("pack_w", 0.0)
-            seen[key] = (conv, sum(t.values()) - conv - qw, qw)
+            seen[key] = (conv, sum(t.values()) - conv)
             del X, W, out
-        conv, qx, qw = seen[key]
+        conv, quantize = seen[key]
         tot["conv"] += conv
-        tot["quantize_x"] += qx
-        tot["quantize_w"] += qw
-        rows_out.append({"layer": L.name, "conv_us": round(conv, 1), "quantize_us": round(qx + qw, 1)})
+        tot["quantize"] += quantize
+        rows_out.append({"layer": L.name, "conv_us": round(conv, 1), "quantize_us": round(quantize, 1)})
     total = sum(tot.values())
     print(json.dumps({"metric": "forward entry point, kernel time (HIP events)", "value": round(1e-3 * total, 4), "unit": "ms",
                       "higher_is_better": False, "n_gpus": 1, "data": "synthetic", "dtype": "int8",

@@ -28,9 +28,7 @@ extern "C" daq_status daq_conv_fwd_int8_ex(const daq_conv_desc* desc, const floa
     daq_status rc = quantize_activation_check(*desc, X);   // nothing is launched for a tensor the quantizers cannot take
     if (rc != DAQ_OK) return rc;
     hipStream_t st = (hipStream_t)stream;
-    rc = quantize_activation(*desc, X, qx_nhwc, qx_cnhw, s_x, workspace, st, schedule);
-    if (rc != DAQ_OK) return rc;
-    rc = quantize_filter(*desc, W, qw_packed, s_w, workspace, st);
+    rc = quantize_forward(*desc, X, qx_nhwc, qx_cnhw, s_x, W, qw_packed, s_w, workspace, st, schedule);
     if (rc != DAQ_OK) return rc;
     if (fwd_halo_supported(*desc)) return conv_fwd_halo(*desc, qx_nhwc, qw_packed, s_x, s_w, Y, acc_out, st);
     if (depthwise_fwd_supported(*desc)) return conv_fwd_depthwise(*desc, qx_cnhw, qw_packed, s_x, s_w, Y, acc_out, st);

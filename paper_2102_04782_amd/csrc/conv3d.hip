@@ -694,9 +694,9 @@ extern "C" daq_status daq_conv3d_fwd_int8(const daq_conv3d_desc* desc, const flo
     daq_layout Ln;
     if (daq_layout_qx_nhwc(&cx, &Ln) != DAQ_OK) return DAQ_ERR_UNSUPPORTED;
     hipStream_t st = (hipStream_t)stream;
-    rc = quantize_activation(cx, X, qx_nhwc, qx_cnhw, s_x, workspace, st, DAQ_SCHEDULE_AUTO);
+    rc = quantize_forward(cx, X, qx_nhwc, qx_cnhw, s_x, nullptr, nullptr, nullptr, workspace, st, DAQ_SCHEDULE_AUTO);
     if (rc != DAQ_OK) return rc;
-    uint32_t* bits = (uint32_t*)workspace + 32;
+    uint32_t* bits = (uint32_t*)workspace + kFwdWsFree;
     const Geo3 g = geo3_of(*desc);
     const int taps = g.kD * g.kH * g.kW;
     const W3 L3 = w3_of(g.Cout, g.Cin, g.groups, taps);

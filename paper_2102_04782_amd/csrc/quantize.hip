@@ -43,6 +43,7 @@ struct QuantWs {
     uint32_t* part_cnt;   // [C][cgroups]  #{|g| > sigma} seen by counting workgroup p of the channel's block
     int chunks;           // 4096-element chunks of one channel
     int slabs;            // statistics workgroups (partials) per channel
+    int part_n;           // entries of part_max whose maximum is the scale of the per-tensor copy (C * slabs)
     int tiles;            // 64-pixel tiles of the flattened (n, h*w) axis
     int cgroups;          // counting workgroups per block of 64 channels
     int scheme;           // daq_scheme the launches of this call follow
@@ -57,6 +58,7 @@ QuantWs carve_quant_ws(void* base, int C, int N, int HW) {
     w.chunks = (int)ceil_div(Mstats, kStatsElems);
     const int iters = (int)ceil_div(w.chunks, kMaxSlabs);
     w.slabs = (int)ceil_div(w.chunks, iters);
+    w.part_n = C * w.slabs;
     w.tiles = (int)ceil_div(M, kWave);
     const int cb = (int)ceil_div(C, 64);
     const int want = std::max(1, kCountGrid / cb);
@@ -207,11 +209,6 @@ __device__ __forceinline__ uint32_t wave_sum_u32(uint32_t v) {
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) v += __shfl_down(v, o);
     return v;
-}
-
-__global__ void k_fill_u32(uint32_t* p, int64_t n, uint32_t v) {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) p[i] = v;
 }
 
 // Fixed-shape workgroup reduction of (max, sum, sum); the result is valid in thread 0.
@@ -390,19 +387,18 @@ __device__ __forceinline__ uint32_t quad_swap(uint32_t v) {
 // final decision), quantizes with it and stores the bytes of the real elements; the packing pass, which takes the
 // decision, then only rewrites the channels whose guess was wrong (and writes the padding).  A correct guess saves
 // the third sweep over dY for that channel; a wrong one costs nothing but the bytes written here.
-template <typename T, bool STOCH, bool WRITE_QG, bool COUNT, bool EARLY = false>
-__global__ __launch_bounds__(kBlock, 4) void k_count_qg(const T* __restrict__ g, int N, int C, int HW, int c_pitch,
-                                                     FastDiv div_hw, QuantWs ws, const float* __restrict__ scale_ptr,
-                                                     int8_t* __restrict__ qg, uint64_t seed,
-                                                     const float* __restrict__ s_state, float* __restrict__ s_global,
-                                                     EarlyVq ev, int qg_tail) {
+// `bid`: the workgroup's number among those of this role (the forward pass launches it with other roles, k_fwd_quant).
+template <typename T, bool STOCH, bool WRITE_QG, bool COUNT, bool EARLY>
+__device__ __forceinline__ void count_qg_role(const int bid, const T* __restrict__ g, int N, int C, int HW, int c_pitch, FastDiv div_hw,
+                                              const QuantWs& ws, int8_t* __restrict__ qg, uint64_t seed, const float* __restrict__ s_state,
+                                              float* __restrict__ s_global, const EarlyVq& ev, int qg_tail) {
     __shared__ float l_sigma[64];
     __shared__ float l_inv[64];
     __shared__ float l_max[kBlock / kWave];
     __shared__ __align__(16) int8_t l_tile[64 * 80];
     const int tid = threadIdx.x, wave = tid / kWave, lane = tid % kWave;
-    const int p = blockIdx.x % ws.cgroups;
-    const int cb = blockIdx.x / ws.cgroups;
+    const int p = bid % ws.cgroups;
+    const int cb = bid / ws.cgroups;
     // A last block of at most 32 channels (thin tensors; channel counts like 96 or 144) has one or two groups of 16 channels,
     // and two or three of the four waves would idle.  Its waves take four (or two) different pixel tiles instead, and
     // since the block's share of an NHWC record is then 16 (or 32) bytes, a lane's codes are that share (or half of it):
@@ -463,13 +459,10 @@ __global__ __launch_bounds__(kBlock, 4) void k_count_qg(const T* __restrict__ g,
     };
     fetch(t_first, x, n_cur, px_cur, v_cur);
 
-    // scale of the global copy: max_c |g|max from the statistics pass, or an explicit per-tensor scale
-    float sg = 0.0f;
-    if (scale_ptr) {
-        sg = *scale_ptr;
-    } else {
+    // scale of the global copy: the maximum over the partials of the launch before
+    {
         float m = 0.0f;
-        const int total = C * ws.slabs;
+        const int total = ws.part_n;
         for (int base = 0; base < total; base += 8 * kBlock) {
             float v[8];
 #pragma unroll
@@ -495,22 +488,20 @@ __global__ __launch_bounds__(kBlock, 4) void k_count_qg(const T* __restrict__ g,
         // layer-wise clipping compares every element with the standard deviation of the whole tensor
         l_sigma[tid] = ws.scheme == DAQ_SCHEME_MCS ? ws.layer[2] : sig;
     }
-    // forward pass (nothing is counted, the scale is given): the channel-major copy takes the same per-tensor scale
-    if (!COUNT && EARLY && tid < 64) l_inv[tid] = inv_scale(sg);
     __syncthreads();
-    if (!scale_ptr) sg = fmaxf(fmaxf(l_max[0], l_max[1]), fmaxf(l_max[2], l_max[3]));
+    float sg = fmaxf(fmaxf(l_max[0], l_max[1]), fmaxf(l_max[2], l_max[3]));
     const float sg_raw = sg;
     if (!(sg >= kTinyScale)) sg = 0.0f;
-    if (COUNT && blockIdx.x == 0) {
+    if (COUNT && bid == 0) {
         // the clip state is overwritten by the packing pass: keep what this iteration started from
         for (int i = tid; i < C; i += kBlock) ws.s_prev[i] = s_state[i];
     }
-    if (!scale_ptr && blockIdx.x == 0 && tid == 0) {
+    if (bid == 0 && tid == 0) {
         *s_global = sg;
         ws.layer[0] = sg_raw;
     }
     // the NHWC buffer is a multiple of 256 bytes long: the bytes behind the last pixel hold no element and are zero
-    if (WRITE_QG && blockIdx.x == 0 && tid < qg_tail) qg[(int64_t)M * c_pitch + tid] = 0;
+    if (WRITE_QG && bid == 0 && tid < qg_tail) qg[(int64_t)M * c_pitch + tid] = 0;
     const float inv = inv_scale(sg);
     // sigma of the wave's 16 channels.  Lanes without a pixel and channels past C hold x = 0, and
     // 0 > sigma is false for every sigma >= 0, so the comparison needs no validity mask.
@@ -522,7 +513,7 @@ __global__ __launch_bounds__(kBlock, 4) void k_count_qg(const T* __restrict__ g,
 
     float inv_c[16];
 #pragma unroll
-    for (int i = 0; i < 16; ++i) inv_c[i] = EARLY ? uniform(l_inv[c0 - cb * 64 + i]) : 0.0f;
+    for (int i = 0; i < 16; ++i) inv_c[i] = EARLY ? (COUNT ? uniform(l_inv[c0 - cb * 64 + i]) : inv) : 0.0f;   // forward: one scale
 
     uint32_t cnt[16];   // wave-uniform counters
 #pragma unroll
@@ -627,9 +618,17 @@ __global__ __launch_bounds__(kBlock, 4) void k_count_qg(const T* __restrict__ g,
         }
         if (ws.scheme == DAQ_SCHEME_MCS) {   // uniform: one population; its count is the sum over all counting waves
             const uint32_t all = wave_sum_u32(mine_ok ? mine : 0u);
-            if (lane == 0) ws.layer_cnt[blockIdx.x * (kBlock / kWave) + wave] = all;
+            if (lane == 0) ws.layer_cnt[bid * (kBlock / kWave) + wave] = all;
         }
     }
+}
+
+template <typename T, bool STOCH, bool WRITE_QG, bool COUNT, bool EARLY = false>
+__global__ __launch_bounds__(kBlock, 4) void k_count_qg(const T* __restrict__ g, int N, int C, int HW, int c_pitch, FastDiv div_hw,
+                                                        QuantWs ws, int8_t* __restrict__ qg, uint64_t seed,
+                                                        const float* __restrict__ s_state, float* __restrict__ s_global, EarlyVq ev,
+                                                        int qg_tail) {
+    count_qg_role<T, STOCH, WRITE_QG, COUNT, EARLY>((int)blockIdx.x, g, N, C, HW, c_pitch, div_hw, ws, qg, seed, s_state, s_global, ev, qg_tail);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -777,25 +776,34 @@ __device__ __forceinline__ float clip_value(const QuantWs& ws, const ClipArgs& c
     return s;
 }
 
+// Scale of a per-tensor copy from the partial maxima of the launch before (fixed tree; every thread gets it).  Called by
+// all kBlock threads; `l` is kBlock / kWave floats of LDS.
+__device__ __forceinline__ float fold_scale(const float* __restrict__ part, int n, float* l) {
+    float m = 0.0f;
+    for (int i = threadIdx.x; i < n; i += kBlock) m = fmaxf(m, part[i]);
+    m = wave_max(m);
+    if (threadIdx.x % kWave == 0) l[threadIdx.x / kWave] = m;
+    __syncthreads();
+    return fmaxf(fmaxf(l[0], l[1]), fmaxf(l[2], l[3]));
+}
+
 struct PackArgs {
     FastDiv div_slot, div_pitch;
     int per_chan;          // workgroups per (channel, phase) plane
     int lead_imgs;         // whole images that cover the leading zeros
-    int per_channel_scale; // scale[c] instead of scale[0] (ignored with CLIP)
+    int part_n;            // > 0: the scale is the maximum of that many partials behind the scale pointer (ignored with CLIP)
     uint32_t tensor;       // random stream id
     uint64_t seed;
 };
 
 template <typename T, bool STOCH, bool CLIP>
-__global__ __launch_bounds__(kBlock) void k_pack_cnhw(const T* __restrict__ src, CnhwView L,
-                                                      const float* __restrict__ scale, int8_t* __restrict__ dst,
-                                                      PackArgs pa, QuantWs ws, ClipArgs ca) {
+__device__ __forceinline__ void pack_cnhw_role(const int b, const int phase, const T* __restrict__ src, const CnhwView& L,
+                                               const float* __restrict__ scale, int8_t* __restrict__ dst, const PackArgs& pa,
+                                               const QuantWs& ws, const ClipArgs& ca) {
     __shared__ uint32_t l_cnt[kBlock / kWave];
-    const int b = blockIdx.x;
     const int xcd = b % kXcd, q = b / kXcd;
     const int c = (q / pa.per_chan) * kXcd + xcd;  // channel c runs on XCD c % 8
     const int jb = q % pa.per_chan;                // block of 1024 dwords along the flattened axis
-    const int phase = blockIdx.z;
     if (c >= L.C) return;
     const int tid = threadIdx.x;
     const int ph = phase / L.phases_w, pw = phase % L.phases_w;
@@ -852,7 +860,7 @@ __global__ __launch_bounds__(kBlock) void k_pack_cnhw(const T* __restrict__ src,
 
     float s;
     if (CLIP) s = clip_value(ws, ca, c, (double)L.N * (double)L.H * (double)L.W, jb == 0 && phase == 0, l_cnt);
-    else s = pa.per_channel_scale ? scale[c] : scale[0];
+    else s = pa.part_n ? fold_scale(scale, pa.part_n, reinterpret_cast<float*>(l_cnt)) : scale[0];
     const float inv = inv_scale(s);
 
     // Padding positions were read as 0.0f and quantize to code 0 in either rounding mode
@@ -869,6 +877,12 @@ __global__ __launch_bounds__(kBlock) void k_pack_cnhw(const T* __restrict__ src,
     }
 }
 
+template <typename T, bool STOCH, bool CLIP>
+__global__ __launch_bounds__(kBlock) void k_pack_cnhw(const T* __restrict__ src, CnhwView L, const float* __restrict__ scale,
+                                                      int8_t* __restrict__ dst, PackArgs pa, QuantWs ws, ClipArgs ca) {
+    pack_cnhw_role<T, STOCH, CLIP>((int)blockIdx.x, (int)blockIdx.z, src, L, scale, dst, pa, ws, ca);
+}
+
 // ---------------------------------------------------------------------------------------------
 // S5, channel-major copy, fast path for unsplit layouts (one stride phase) whose row length is a
 // multiple of V = 4 or 2.  Source driven: a thread loads V consecutive floats of one row with one
@@ -883,7 +897,7 @@ struct RowsArgs {
     FastDiv div_hwv, div_wv, div_prb;
     int per_chan;          // blocks of 1024 element groups per channel
     int grid_per_chan;     // data workgroups per channel (one more zeroes the padding); fewer than per_chan: they loop
-    int per_channel_scale;
+    int part_n;            // as in PackArgs
     int early;             // the counting pass has written the real elements of channels whose class it guessed
     uint32_t tensor;
     uint64_t seed;
@@ -906,11 +920,9 @@ __device__ __forceinline__ void store_codes(int8_t* p, uint32_t w) {
 }
 
 template <typename T, bool STOCH, bool CLIP, int V>
-__global__ __launch_bounds__(kBlock) void k_pack_rows(const T* __restrict__ src, CnhwView L,
-                                                      const float* __restrict__ scale, int8_t* __restrict__ dst,
-                                                      RowsArgs pa, QuantWs ws, ClipArgs ca) {
+__device__ __forceinline__ void pack_rows_role(const int b, const T* __restrict__ src, const CnhwView& L, const float* __restrict__ scale,
+                                               int8_t* __restrict__ dst, const RowsArgs& pa, const QuantWs& ws, const ClipArgs& ca) {
     __shared__ uint32_t l_cnt[kBlock / kWave];
-    const int b = blockIdx.x;
     const int xcd = b % kXcd, q = b / kXcd;
     const int c = (q / (pa.grid_per_chan + 1)) * kXcd + xcd;  // channel c runs on XCD c % 8
     const int jb0 = q % (pa.grid_per_chan + 1);
@@ -958,8 +970,7 @@ __global__ __launch_bounds__(kBlock) void k_pack_rows(const T* __restrict__ src,
         }
     }
     if (CLIP && !pa.early) s = clip_value(ws, ca, c, (double)L.N * (double)L.H * (double)L.W, jb0 == 0, l_cnt);
-    else if (!CLIP) s = pa.per_channel_scale ? scale[c] : scale[0];
-    const float inv = inv_scale(s);
+    float inv = CLIP ? inv_scale(s) : 0.0f;
 
     const uint32_t HW = (uint32_t)(L.H * L.W), HWV = HW / V, WV = (uint32_t)L.W / V;
     const uint32_t groups = (uint32_t)L.N * HWV;
@@ -1005,6 +1016,8 @@ __global__ __launch_bounds__(kBlock) void k_pack_rows(const T* __restrict__ src,
         }
     }
 
+    // a given scale is folded while the loads are in flight (without `early` there is one pass)
+    if constexpr (!CLIP) inv = inv_scale(pa.part_n ? fold_scale(scale, pa.part_n, reinterpret_cast<float*>(l_cnt)) : scale[0]);
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
         uint32_t bits[4] = {0u, 0u, 0u, 0u};
@@ -1027,6 +1040,12 @@ __global__ __launch_bounds__(kBlock) void k_pack_rows(const T* __restrict__ src,
         }
     }
   }
+}
+
+template <typename T, bool STOCH, bool CLIP, int V>
+__global__ __launch_bounds__(kBlock) void k_pack_rows(const T* __restrict__ src, CnhwView L, const float* __restrict__ scale,
+                                                      int8_t* __restrict__ dst, RowsArgs pa, QuantWs ws, ClipArgs ca) {
+    pack_rows_role<T, STOCH, CLIP, V>((int)blockIdx.x, src, L, scale, dst, pa, ws, ca);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -1232,35 +1251,45 @@ __global__ __launch_bounds__(TH, NU <= 8 ? (VEC4 ? 6 : 8) : 4) void k_chan_resid
 // ---------------------------------------------------------------------------------------------
 // per-tensor helpers for the forward pass
 // ---------------------------------------------------------------------------------------------
-// max |x| of a tensor into *bits (the bit pattern of a non-negative float orders like the float).  One atomic per
-// workgroup: atomics on one address are served one after the other (about 10 ns each), so a kernel that ends every
-// wave with one spends longer on them than on the tensor.  16-byte loads, four in flight per thread.
-__global__ __launch_bounds__(kBlock) void k_absmax(const float* __restrict__ x, int64_t n, uint32_t* bits) {
+// max |x| of X and of W in one launch: the first bx workgroups sweep X, the next bw sweep W, each stores its maximum as one
+// partial, and whoever needs the scale folds the partials (an atomic per workgroup on one address is served one after the
+// other, about 10 ns each, and needs a cleared word first).  Eight 16-byte loads in flight per thread; a load past the end
+// reads the last quad again, which changes no maximum.  (64 x 64 x 56 x 56: 19 us with atomics, 10 us here, 5.1 TB/s.)
+constexpr int kAbsmaxBlocksX = 512, kAbsmaxBlocksW = 256;   // a plain read loop is fastest with 512 workgroups on this chip
+struct AbsmaxArgs {
+    const float* x[2];
+    int64_t n[2];
+    int blocks[2];
+    float* part[2];
+};
+__global__ __launch_bounds__(kBlock) void k_absmax(AbsmaxArgs a) {
     __shared__ float l_m[kBlock / kWave];
+    const bool second = (int)blockIdx.x >= a.blocks[0];
+    const int b = (int)blockIdx.x - (second ? a.blocks[0] : 0);
+    const float* __restrict__ x = second ? a.x[1] : a.x[0];
+    const int64_t n = second ? a.n[1] : a.n[0];
+    const int64_t stride = (int64_t)(second ? a.blocks[1] : a.blocks[0]) * kBlock;
     float m = 0.0f;
     const int64_t n4 = ((uintptr_t)x & 15u) ? 0 : n / 4;   // whole aligned quads; the rest goes element by element
-    const int64_t stride = (int64_t)gridDim.x * kBlock;
     const float4* x4 = reinterpret_cast<const float4*>(x);
-    int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-    for (; i + 3 * stride < n4; i += 4 * stride) {
-        float4 v[4];
+    for (int64_t i = (int64_t)b * kBlock + threadIdx.x; i < n4; i += 8 * stride) {
+        float4 v[8];
 #pragma unroll
-        for (int u = 0; u < 4; ++u) v[u] = x4[i + u * stride];
+        for (int u = 0; u < 8; ++u) v[u] = x4[std::min(i + u * stride, n4 - 1)];
 #pragma unroll
-        for (int u = 0; u < 4; ++u) m = fmaxf(m, fmaxf(fmaxf(fabsf(v[u].x), fabsf(v[u].y)), fmaxf(fabsf(v[u].z), fabsf(v[u].w))));
+        for (int u = 0; u < 8; ++u) m = fmaxf(m, fmaxf(fmaxf(fabsf(v[u].x), fabsf(v[u].y)), fmaxf(fabsf(v[u].z), fabsf(v[u].w))));
     }
-    for (; i < n4; i += stride) {
-        const float4 v = x4[i];
-        m = fmaxf(m, fmaxf(fmaxf(fabsf(v.x), fabsf(v.y)), fmaxf(fabsf(v.z), fabsf(v.w))));
+    for (int64_t j = 4 * n4 + (int64_t)b * kBlock + threadIdx.x; j < n; j += 8 * stride) {
+        float v[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) v[u] = x[std::min(j + u * stride, n - 1)];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) m = fmaxf(m, fabsf(v[u]));
     }
-    for (int64_t j = 4 * n4 + (int64_t)blockIdx.x * kBlock + threadIdx.x; j < n; j += stride) m = fmaxf(m, fabsf(x[j]));
     m = wave_max(m);
     if (threadIdx.x % kWave == 0) l_m[threadIdx.x / kWave] = m;
     __syncthreads();
-    if (threadIdx.x == 0) {
-        for (int w = 1; w < kBlock / kWave; ++w) m = fmaxf(m, l_m[w]);
-        atomicMax(bits, __float_as_uint(m));
-    }
+    if (threadIdx.x == 0) (second ? a.part[1] : a.part[0])[b] = fmaxf(fmaxf(l_m[0], l_m[1]), fmaxf(l_m[2], l_m[3]));
 }
 
 // Scale of the per-tensor copy from the per-channel maxima of the channel-resident pass (one workgroup).
@@ -1278,38 +1307,171 @@ __global__ __launch_bounds__(kBlock) void k_fold_max(QuantWs ws, int C, float* _
     }
 }
 
-__global__ void k_scale_from_bits(const uint32_t* bits, float* s) {
-    const float v = __uint_as_float(*bits);
-    *s = (v >= kTinyScale) ? v : 0.0f;
+// q(W) in its arrangements (see daq_wpack_layout), every byte of the buffer written once, zeros included.
+struct PackWArgs {
+    const float* w;
+    int8_t* out;
+    float* s_w;
+    const float* part;     // partial maxima of |W|
+    int part_n;
+    int Cout, Cin, groups, taps, cig, cog;
+    int chunks, ci_tiles;  // groups == 1: tap chunks and 32-channel tiles of the grid
+    int blocks;            // workgroups of this role; 0: no filter
+    FastDiv div_run, div_tap, div_runl, div_tapl;   // (32 * taps of a chunk, taps of a chunk), the last chunk's own
+    daq_wpack_layout L;
+};
+constexpr int kWTaps = 9;                   // taps a workgroup takes at once
+constexpr int kWPlane = 32 * 32 + 16;       // bytes of a tap's 32 x 32 codes in LDS; the 16 spread the taps over the banks
+
+// One group: a workgroup takes 32 x 32 channels (the tile of the fragment order) x up to nine taps.  Its weights are
+// runs of 32 * taps consecutive floats, all loads in flight at once; the codes go to LDS in both orders, [co][ci] and
+// [ci][co], and leave as 16-byte units: whole KiB of the two fragment copies, 32-byte runs of the other two.  (Scattering
+// each code to five places in byte stores behind a fill of the buffer: 3 x 3, 272 -> 912, fill 12.6 and packing 24.7 us.)
+template <int NT>
+__device__ __forceinline__ void pack_w_tile(const int b, const PackWArgs& a, float* l_red, int8_t* l_f, int8_t* l_b) {
+    const int tid = threadIdx.x;
+    const int tc = b % a.chunks, tile = b / a.chunks;
+    const int ct = tile / a.ci_tiles, it = tile - ct * a.ci_tiles;
+    const int co0 = 32 * ct, ci0 = 32 * it, t0 = tc * kWTaps;
+    const bool last = tc + 1 == a.chunks;
+    const int nt = NT == 1 ? 1 : min(kWTaps, a.taps - t0);
+    const FastDiv div_run = last ? a.div_runl : a.div_run, div_tap = last ? a.div_tapl : a.div_tap;
+    // element e of the tile: weight index (~0: none there) and place in LDS, tap << 10 | co << 5 | ci (~0: past the tile)
+    auto place = [&](uint32_t e, uint32_t& at, uint32_t& pl) {
+        const uint32_t co = fdiv(e, div_run), r = e - co * (uint32_t)(32 * nt), ci = fdiv(r, div_tap), t = r - ci * (uint32_t)nt;
+        const bool ok = co < 32u && co0 + (int)co < a.Cout && ci0 + (int)ci < a.Cin;
+        at = ok ? (uint32_t)((co0 + (int)co) * a.cig + ci0 + (int)ci) * (uint32_t)a.taps + (uint32_t)t0 + t : ~0u;
+        pl = co < 32u ? t << 10 | co << 5 | ci : ~0u;
+    };
+    float x[4 * NT];
+    uint32_t at, pl;
+#pragma unroll
+    for (int k = 0; k < 4 * NT; ++k) {
+        place((uint32_t)tid + kBlock * k, at, pl);
+        x[k] = ldf_or_zero(a.w + at, at != ~0u);
+    }
+    const float s = fold_scale(a.part, a.part_n, l_red);
+    if (b == 0 && tid == 0) *a.s_w = s >= kTinyScale ? s : 0.0f;
+    const float inv = inv_scale(s);
+    uint32_t e0 = (uint32_t)tid;
+    asm volatile("" : "+v"(e0));   // the places are worked out again: kept since the loads, they would spill
+#pragma unroll
+    for (int k = 0; k < 4 * NT; ++k) {
+        place(e0 + kBlock * k, at, pl);
+        const int8_t code = at != ~0u ? (int8_t)quant_code<false>(x[k], inv, 0u) : (int8_t)0;
+        if (at != ~0u) a.out[a.L.off_plain + at] = code;
+        if (pl != ~0u) {
+            const uint32_t t = pl >> 10, co = pl >> 5 & 31u, ci = pl & 31u;
+            l_f[t * kWPlane + co * 32 + ci] = code;
+            l_b[t * kWPlane + ci * 32 + co] = code;
+        }
+    }
+    __syncthreads();
+    const int rbf = (a.Cout + 31) / 32, rbb = (a.Cin + 31) / 32;
+    for (int u = tid; u < nt * 64; u += kBlock) {
+        const int t = u >> 6, h = (u >> 5) & 1, row = u & 31;
+        const int64_t tap = t0 + t;
+        const uint4 f = *reinterpret_cast<const uint4*>(l_f + t * kWPlane + row * 32 + 16 * h);
+        const uint4 g = *reinterpret_cast<const uint4*>(l_b + t * kWPlane + row * 32 + 16 * h);
+        if (co0 + row < a.Cout && ci0 + 16 * h < a.L.cig_pitch)
+            *reinterpret_cast<uint4*>(a.out + a.L.off_fwd + (tap * a.Cout + co0 + row) * a.L.cig_pitch + ci0 + 16 * h) = f;
+        if (ci0 + row < a.Cin && co0 + 16 * h < a.L.cog_pitch)
+            *reinterpret_cast<uint4*>(a.out + a.L.off_bwd + (tap * a.Cin + ci0 + row) * a.L.cog_pitch + co0 + 16 * h) = g;
+        const int in_tile = h * 512 + row * 16;
+        if (ct < rbf)
+            *reinterpret_cast<uint4*>(a.out + a.L.off_fwd_frag + (((((int64_t)(ci0 >> 6) * a.taps + tap) * rbf + ct) * 2 + (it & 1)) << 10) + in_tile) = f;
+        if (it < rbb)
+            *reinterpret_cast<uint4*>(a.out + a.L.off_bwd_frag + (((((int64_t)(co0 >> 6) * a.taps + tap) * rbb + it) * 2 + (ct & 1)) << 10) + in_tile) = g;
+    }
+    if (b == 0) {   // the bytes between the copies
+        const int64_t z0 = (int64_t)a.Cout * a.cig * a.taps, z1 = a.L.off_fwd + (int64_t)a.taps * a.Cout * a.L.cig_pitch,
+                      z2 = a.L.off_bwd + (int64_t)a.taps * a.Cin * a.L.cog_pitch;
+        if (z0 + tid < a.L.off_fwd) a.out[z0 + tid] = 0;
+        if (z1 + tid < a.L.off_bwd) a.out[z1 + tid] = 0;
+        if (z2 + tid < a.L.off_fwd_frag) a.out[z2 + tid] = 0;
+    }
 }
 
-// q(W) in its three arrangements (see daq_wpack_layout); the buffer is zero-filled beforehand.
-__global__ __launch_bounds__(kBlock) void k_pack_w(const float* __restrict__ W, const float* __restrict__ s_w,
-                                                   int Cout, int Cin, int groups, int kH, int kW,
-                                                   daq_wpack_layout L, int8_t* __restrict__ out) {
-    const int cig = Cin / groups, cog = Cout / groups, taps = kH * kW;
-    const int64_t total = (int64_t)Cout * cig * taps;
-    const int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-    if (i >= total) return;
-    const int tap = (int)(i % taps);
-    const int cl = (int)((i / taps) % cig);
-    const int co = (int)(i / ((int64_t)taps * cig));
-    const int g = co / cog, col = co % cog;
-    const int ci = g * cig + cl;
-    const float inv = inv_scale(*s_w);
-    const int8_t code = (int8_t)quant_code<false>(W[i], inv, 0u);
-    out[L.off_plain + i] = code;
-    out[L.off_fwd + ((int64_t)tap * Cout + co) * L.cig_pitch + cl] = code;
-    out[L.off_bwd + ((int64_t)tap * Cin + ci) * L.cog_pitch + col] = code;
-    if (groups == 1) {
-        // fragment order: element (tap, row, k) of a copy with RB row blocks
-        auto frag = [&](int row, int k, int RB) -> int64_t {
-            return ((((int64_t)(k >> 6) * taps + tap) * RB + (row >> 5)) * 2 + ((k & 63) >> 5)) * 1024 +
-                   ((((k & 31) >> 4) * 32 + (row & 31)) * 16) + (k & 15);
-        };
-        out[L.off_fwd_frag + frag(co, ci, (Cout + 31) / 32)] = code;
-        out[L.off_bwd_frag + frag(ci, co, (Cin + 31) / 32)] = code;
+// Grouped layers: a thread writes 16 bytes of one of the three copies.  Their weights are few.
+__device__ __forceinline__ void pack_w_units(const int b, const PackWArgs& a, float* l_red) {
+    const int64_t o = 16 * ((int64_t)b * kBlock + threadIdx.x);
+    const int64_t n = (int64_t)a.Cout * a.cig * a.taps;
+    int64_t first = -1, step = 0;   // weight of the unit's first byte, distance to the next one's, how many bytes hold a weight
+    int count = 0;
+    if (o < a.L.off_fwd) {
+        first = o;
+        step = 1;
+        count = (int)std::max<int64_t>(0, std::min<int64_t>(16, n - o));
+    } else if (o < a.L.off_bwd) {
+        const int64_t q = (o - a.L.off_fwd) / 16, upr = a.L.cig_pitch / 16, row = q / upr, k0 = 16 * (q - row * upr);
+        const int64_t tap = row / a.Cout, co = row - tap * a.Cout;
+        first = (co * a.cig + k0) * a.taps + tap;
+        step = a.taps;
+        count = tap < a.taps ? (int)std::min<int64_t>(16, a.cig - k0) : 0;
+    } else if (o < a.L.bytes) {
+        const int64_t q = (o - a.L.off_bwd) / 16, upr = a.L.cog_pitch / 16, row = q / upr, k0 = 16 * (q - row * upr);
+        const int64_t tap = row / a.Cin, ci = row - tap * a.Cin, grp = ci / a.cig;
+        first = ((grp * a.cog + k0) * a.cig + (ci - grp * a.cig)) * a.taps + tap;
+        step = (int64_t)a.cig * a.taps;
+        count = tap < a.taps ? (int)std::min<int64_t>(16, a.cog - k0) : 0;
     }
+    float x[16];
+#pragma unroll
+    for (int i = 0; i < 16; ++i) x[i] = ldf_or_zero(a.w + first + i * step, i < count);
+    const float s = fold_scale(a.part, a.part_n, l_red);
+    if (b == 0 && threadIdx.x == 0) *a.s_w = s >= kTinyScale ? s : 0.0f;
+    const float inv = inv_scale(s);
+    uint32_t c[16];
+#pragma unroll
+    for (int i = 0; i < 16; ++i) c[i] = i < count ? (uint32_t)quant_code<false>(x[i], inv, 0u) : 0u;
+    if (o < a.L.bytes)
+        *reinterpret_cast<uint4*>(a.out + o) = make_uint4(pack4(c[0], c[1], c[2], c[3]), pack4(c[4], c[5], c[6], c[7]),
+                                                          pack4(c[8], c[9], c[10], c[11]), pack4(c[12], c[13], c[14], c[15]));
+}
+
+// Everything the forward pass quantizes, in one launch behind k_absmax: q(W), the two copies of q(X).  The three are
+// independent of each other, and most layers are small: the launches and the gaps between them cost more than the bytes
+// (eleven launches a forward pass with a launch for each step; three with the product now.  3 x 3, 128 -> 128 at 28 x 28,
+// batch 8, whole pass: 39.8 -> 26.7 us; 1 x 1, 64 -> 256 at 56 x 56, batch 64: 91 -> 66; 416 -> 320 3 x 3 at 21 x 21: 59 -> 36).
+// Each role starts at a multiple of eight workgroups, so that its own mapping to the XCDs holds.
+// EARLY: the NHWC role writes both copies from one read of X, the channel-major role only the zeros round about the rows.
+// V: elements per thread of the source-driven channel-major role, 0: the output-driven one.
+struct FwdQuantArgs {
+    const float* x;
+    int8_t *nhwc, *cnhw;
+    float* s_x;
+    int N, C, HW, c_pitch, tail;
+    int w_blocks, x_blocks;   // of the first two roles, rounded up to a multiple of eight
+    int phase_blocks;         // output-driven channel-major role: workgroups per stride phase
+    FastDiv div_hw;
+    CnhwView Lc;
+    PackArgs pa;
+    RowsArgs ra;
+    EarlyVq ev;
+    QuantWs ws;
+    PackWArgs w;
+};
+template <bool EARLY, int V>
+__global__ __launch_bounds__(kBlock, 4) void k_fwd_quant(FwdQuantArgs a) {
+    __shared__ float l_red[kBlock / kWave];
+    __shared__ __align__(16) int8_t l_w[2 * kWTaps * kWPlane];
+    int b = (int)blockIdx.x;
+    if (b < a.w_blocks) {   // uniform, as all branches below
+        if (b >= a.w.blocks) return;
+        if (a.w.groups > 1) pack_w_units(b, a.w, l_red);
+        else if (a.w.taps == 1) pack_w_tile<1>(b, a.w, l_red, l_w, l_w + kWTaps * kWPlane);
+        else pack_w_tile<kWTaps>(b, a.w, l_red, l_w, l_w + kWTaps * kWPlane);
+        return;
+    }
+    b -= a.w_blocks;
+    if (b < a.x_blocks) {
+        if (b >= (a.C + 63) / 64 * a.ws.cgroups) return;
+        count_qg_role<float, false, true, false, EARLY>(b, a.x, a.N, a.C, a.HW, a.c_pitch, a.div_hw, a.ws, a.nhwc, 0, nullptr, a.s_x, a.ev, a.tail);
+        return;
+    }
+    b -= a.x_blocks;
+    if constexpr (V > 0) pack_rows_role<float, false, false, V>(b, a.x, a.Lc, a.ws.part_max, a.cnhw, a.ra, a.ws, ClipArgs{});
+    else pack_cnhw_role<float, false, false>(b % a.phase_blocks, b / a.phase_blocks, a.x, a.Lc, a.ws.part_max, a.cnhw, a.pa, a.ws, ClipArgs{});
 }
 
 // grid of k_pack_cnhw: x enumerates (channel, block of 1024 dwords) with the channel's XCD in the low bits,
@@ -1318,13 +1480,13 @@ int pack_per_chan(const daq_layout& L) { return (int)ceil_div(L.plane_pitch / 4,
 dim3 pack_grid(const daq_layout& L) {
     return dim3((unsigned)(round_up(L.C, kXcd) * pack_per_chan(L)), 1u, (unsigned)(L.phases_h * L.phases_w));
 }
-PackArgs pack_args(const daq_layout& L, int per_channel_scale, uint32_t tensor, uint64_t seed) {
+PackArgs pack_args(const daq_layout& L, int part_n, uint32_t tensor, uint64_t seed) {
     PackArgs pa{};
     pa.div_slot = make_fastdiv((uint32_t)(L.img_rows * L.row_pitch));
     pa.div_pitch = make_fastdiv((uint32_t)L.row_pitch);
     pa.per_chan = pack_per_chan(L);
     pa.lead_imgs = (int)ceil_div(L.lead, (int64_t)L.img_rows * L.row_pitch);
-    pa.per_channel_scale = per_channel_scale;
+    pa.part_n = part_n;
     pa.tensor = tensor;
     pa.seed = seed;
     return pa;
@@ -1356,13 +1518,29 @@ int rows_vector(const daq_layout& Ld, const void* src, int elem_bytes = 4) {
     return 0;
 }
 
+RowsArgs rows_args(const daq_layout& Ld, int v, bool early, int part_n, uint32_t tensor, uint64_t seed) {
+    RowsArgs ra{};
+    const uint32_t hwv = (uint32_t)(Ld.H * Ld.W / v);
+    ra.div_hwv = make_fastdiv(hwv);
+    ra.div_wv = make_fastdiv((uint32_t)(Ld.W / v));
+    ra.div_prb = make_fastdiv((uint32_t)std::max(1, (Ld.img_rows - Ld.H) * Ld.row_pitch));
+    ra.per_chan = (int)ceil_div((int64_t)Ld.N * hwv, 4 * kBlock);
+    ra.grid_per_chan = early ? std::min(ra.per_chan, 16) : ra.per_chan;
+    ra.part_n = part_n;
+    ra.early = early ? 1 : 0;
+    ra.tensor = tensor;
+    ra.seed = seed;
+    return ra;
+}
+int64_t rows_blocks(const daq_layout& Ld, const RowsArgs& ra) { return round_up(Ld.C, kXcd) * (ra.grid_per_chan + 1); }
+
 // Launches the channel-major packing of one fp32 NCHW tensor: the source-driven row kernel when the
 // layout allows it, the output-driven kernel otherwise.
 // With dst2 the same pass also writes a second copy quantized with the per-tensor scale scale2 (random stream
 // tensor2); *fused tells whether that happened - the output-driven kernel writes one copy per launch.
 template <typename T>
 daq_status launch_pack(const char* name, bool stoch, bool clip, const T* src, const daq_layout& Ld,
-                       const float* scale, int per_channel_scale, int8_t* dst, uint32_t tensor, uint64_t seed,
+                       const float* scale, int8_t* dst, uint32_t tensor, uint64_t seed,
                        const QuantWs& ws, const ClipArgs& ca, hipStream_t st, int8_t* dst2 = nullptr,
                        const float* scale2 = nullptr, uint32_t tensor2 = 0, bool* fused = nullptr, bool early = false) {
     if (fused) *fused = false;
@@ -1370,22 +1548,12 @@ daq_status launch_pack(const char* name, bool stoch, bool clip, const T* src, co
     const int v = rows_vector(Ld, src, (int)sizeof(T));
     if (early && !v) return DAQ_ERR_INVALID_ARG;   // the caller checks rows_vector before it asks for the early copy
     if (v) {
-        RowsArgs ra{};
-        const uint32_t hwv = (uint32_t)(Ld.H * Ld.W / v);
-        ra.div_hwv = make_fastdiv(hwv);
-        ra.div_wv = make_fastdiv((uint32_t)(Ld.W / v));
-        ra.div_prb = make_fastdiv((uint32_t)std::max(1, (Ld.img_rows - Ld.H) * Ld.row_pitch));
-        ra.per_chan = (int)ceil_div((int64_t)Ld.N * hwv, 4 * kBlock);
-        ra.grid_per_chan = early ? std::min(ra.per_chan, 16) : ra.per_chan;
-        ra.per_channel_scale = per_channel_scale;
-        ra.early = early ? 1 : 0;
-        ra.tensor = tensor;
-        ra.seed = seed;
+        RowsArgs ra = rows_args(Ld, v, early, 0, tensor, seed);
         ra.dst2 = dst2;
         ra.scale2 = scale2;
         ra.tensor2 = tensor2;
         if (fused) *fused = dst2 != nullptr;
-        const dim3 grid((unsigned)(round_up(Ld.C, kXcd) * (ra.grid_per_chan + 1)));
+        const dim3 grid((unsigned)rows_blocks(Ld, ra));
 #define DAQ_ROWS(S, CL, VV) \
     DAQ_LAUNCH(name, st, hipLaunchKernelGGL((k_pack_rows<T, S, CL, VV>), grid, dim3(kBlock), 0, st, src, V, scale, dst, ra, ws, ca))
         if (v == 4) {
@@ -1399,7 +1567,7 @@ daq_status launch_pack(const char* name, bool stoch, bool clip, const T* src, co
         return DAQ_OK;
     }
     if (!pack_supported(Ld)) return DAQ_ERR_UNSUPPORTED;
-    const PackArgs pa = pack_args(Ld, per_channel_scale, tensor, seed);
+    const PackArgs pa = pack_args(Ld, 0, tensor, seed);
     const dim3 grid = pack_grid(Ld);
 #define DAQ_PACK(S, CL) \
     DAQ_LAUNCH(name, st, hipLaunchKernelGGL((k_pack_cnhw<T, S, CL>), grid, dim3(kBlock), 0, st, src, V, scale, dst, pa, ws, ca))
@@ -1415,7 +1583,10 @@ size_t quantize_grad_ws_bytes(const daq_conv_desc& d) {
     return (size_t)carve_quant_ws(nullptr, d.Cout, d.N, daq_out_h(&d) * daq_out_w(&d)).total_bytes;
 }
 
-size_t fwd_quant_ws_bytes(const daq_conv_desc&) { return 256; }
+// Forward workspace, in floats: the partial maxima of X, those of W, what the shared quantizer code writes beside its
+// results, and room for the callers of 3-D layers (kFwdWsFree).
+size_t fwd_quant_ws_bytes(const daq_conv_desc&) { return 4096; }
+static_assert(kAbsmaxBlocksX + kAbsmaxBlocksW + 8 <= kFwdWsFree && kFwdWsFree + 8 <= 4096 / 4, "forward workspace");
 
 // ---------------------------------------------------------------------------------------------
 // forward-side quantization of X (two layouts) and W (packed)
@@ -1430,61 +1601,78 @@ daq_status quantize_activation_check(const daq_conv_desc& d, const float* X) {
     return DAQ_OK;
 }
 
-daq_status quantize_activation(const daq_conv_desc& d, const float* X, int8_t* qx_nhwc, int8_t* qx_cnhw, float* s_x,
-                               void* wsp, hipStream_t st, daq_schedule schedule) {
+daq_status quantize_forward(const daq_conv_desc& d, const float* X, int8_t* qx_nhwc, int8_t* qx_cnhw, float* s_x, const float* W,
+                            int8_t* qw, float* s_w, void* wsp, hipStream_t st, daq_schedule schedule) {
     const daq_status ok = quantize_activation_check(d, X);
     if (ok != DAQ_OK) return ok;
-    uint32_t* bits = (uint32_t*)wsp;
-    const int64_t n = (int64_t)d.N * d.Cin * d.Hin * d.Win;
-    DAQ_LAUNCH("fill", st, hipLaunchKernelGGL(k_fill_u32, dim3(1), dim3(64), 0, st, bits, (int64_t)1, 0u));
-    const int blocks = (int)std::min<int64_t>(ceil_div(n, kBlock * 16), 1024);
-    DAQ_LAUNCH("absmax", st, hipLaunchKernelGGL(k_absmax, dim3(blocks), dim3(kBlock), 0, st, X, n, bits));
-    DAQ_LAUNCH("scale", st, hipLaunchKernelGGL(k_scale_from_bits, dim3(1), dim3(1), 0, st, bits, s_x));
-
     daq_layout Ln, Lc;
     if (daq_layout_qx_nhwc(&d, &Ln) != DAQ_OK || daq_layout_qx_cnhw(&d, &Lc) != DAQ_OK) return DAQ_ERR_INVALID_ARG;
-    const int HW = d.Hin * d.Win;
-    const int CB = (int)ceil_div(d.Cin, 64);
-    QuantWs geo = carve_quant_ws(nullptr, d.Cin, d.N, HW);  // only the tile geometry is used: nothing is counted here
-    // Unit-stride layers whose channel-major layout the row kernel serves: one sweep over X writes both copies (the
-    // mechanism of the early per-channel copy of dY, with the per-tensor scale), then the padding bytes are filled in.
-    // (by default from 8 Mi elements on: below that the two lean passes are faster, as for dY)
-    const bool want_early = schedule == DAQ_SCHEDULE_EARLY_COPY || (schedule == DAQ_SCHEDULE_AUTO && n >= ((int64_t)8 << 20));
-    if (want_early && rows_vector(Lc, X) != 0 && Lc.lead + (int64_t)d.N * Lc.img_rows * Lc.row_pitch < ((int64_t)1 << 32)) {
-        const EarlyVq ev{qx_cnhw, Lc.chan_pitch, (int32_t)Lc.lead, Lc.img_rows, Lc.row_pitch, Lc.W, make_fastdiv((uint32_t)Lc.W),
-                         0.0f, 0.0f, 0.0f, Lc.W % 4 == 0 ? 1 : 0};
-        DAQ_LAUNCH("quant_both", st,
-                   hipLaunchKernelGGL((k_count_qg<float, false, true, false, true>), dim3(CB * geo.cgroups), dim3(kBlock), 0, st, X,
-                                      d.N, d.Cin, HW, Ln.c_pitch, make_fastdiv((uint32_t)HW), geo, (const float*)s_x, qx_nhwc,
-                                      (uint64_t)0, (const float*)nullptr, (float*)nullptr, ev, nhwc_tail(Ln)));
-        return launch_pack("pad_cnhw", false, false, X, Lc, (const float*)s_x, 0, qx_cnhw, 0u, 0, geo, ClipArgs{}, st, nullptr, nullptr,
-                           0, nullptr, true);
-    }
-    DAQ_LAUNCH("quant_nhwc", st,
-               hipLaunchKernelGGL((k_count_qg<float, false, true, false>), dim3(CB * geo.cgroups), dim3(kBlock), 0, st, X, d.N,
-                                  d.Cin, HW, Ln.c_pitch, make_fastdiv((uint32_t)HW), geo, (const float*)s_x, qx_nhwc,
-                                  (uint64_t)0, (const float*)nullptr, (float*)nullptr, EarlyVq{}, nhwc_tail(Ln)));
-    const daq_status prc = launch_pack("pack_cnhw", false, false, X, Lc, (const float*)s_x, 0, qx_cnhw, 0u, 0, geo, ClipArgs{}, st);
-    if (prc != DAQ_OK) return prc;
-    return DAQ_OK;
-}
+    float* part = (float*)wsp;
+    const int taps = d.kH * d.kW;
+    const int64_t n = (int64_t)d.N * d.Cin * d.Hin * d.Win, nw = W ? (int64_t)d.Cout * (d.Cin / d.groups) * taps : 0;
+    AbsmaxArgs m{};
+    m.x[0] = X; m.n[0] = n; m.part[0] = part;
+    m.x[1] = W; m.n[1] = nw; m.part[1] = part + kAbsmaxBlocksX;
+    m.blocks[0] = (int)std::min<int64_t>(ceil_div(n, kBlock * 32), kAbsmaxBlocksX);
+    m.blocks[1] = (int)std::min<int64_t>(ceil_div(nw, kBlock * 32), kAbsmaxBlocksW);
+    DAQ_LAUNCH("absmax", st, hipLaunchKernelGGL(k_absmax, dim3((unsigned)(m.blocks[0] + m.blocks[1])), dim3(kBlock), 0, st, m));
 
-daq_status quantize_filter(const daq_conv_desc& d, const float* W, int8_t* qw, float* s_w, void* wsp,
-                           hipStream_t st) {
-    uint32_t* bits = (uint32_t*)wsp + 16;
-    daq_wpack_layout L;
-    if (daq_layout_qw(&d, &L) != DAQ_OK) return DAQ_ERR_INVALID_ARG;
-    const int64_t n = (int64_t)d.Cout * (d.Cin / d.groups) * d.kH * d.kW;
-    DAQ_LAUNCH("fill", st, hipLaunchKernelGGL(k_fill_u32, dim3(1), dim3(64), 0, st, bits, (int64_t)1, 0u));
-    DAQ_LAUNCH("fill", st,
-               hipLaunchKernelGGL(k_fill_u32, dim3((unsigned)ceil_div(L.bytes / 4, kBlock)), dim3(kBlock), 0, st,
-                                  (uint32_t*)qw, L.bytes / 4, 0u));
-    const int blocks = (int)std::min<int64_t>(ceil_div(n, kBlock * 16), 1024);
-    DAQ_LAUNCH("absmax", st, hipLaunchKernelGGL(k_absmax, dim3(blocks), dim3(kBlock), 0, st, W, n, bits));
-    DAQ_LAUNCH("scale", st, hipLaunchKernelGGL(k_scale_from_bits, dim3(1), dim3(1), 0, st, bits, s_w));
-    DAQ_LAUNCH("pack_w", st,
-               hipLaunchKernelGGL(k_pack_w, dim3((unsigned)ceil_div(n, kBlock)), dim3(kBlock), 0, st, W,
-                                  (const float*)s_w, d.Cout, d.Cin, d.groups, d.kH, d.kW, L, qw));
+    const int HW = d.Hin * d.Win;
+    FwdQuantArgs a{};
+    a.x = X; a.nhwc = qx_nhwc; a.cnhw = qx_cnhw; a.s_x = s_x;
+    a.N = d.N; a.C = d.Cin; a.HW = HW; a.c_pitch = Ln.c_pitch; a.tail = nhwc_tail(Ln);
+    a.div_hw = make_fastdiv((uint32_t)HW);
+    a.Lc = cnhw_view(Lc);
+    a.ws = carve_quant_ws(nullptr, d.Cin, d.N, HW);  // only the tile geometry is used: nothing is counted here
+    a.ws.part_max = part;
+    a.ws.part_n = m.blocks[0];
+    a.ws.layer = part + kAbsmaxBlocksX + kAbsmaxBlocksW;
+    a.x_blocks = (int)round_up(ceil_div(d.Cin, 64) * a.ws.cgroups, kXcd);
+    // Unit-stride layers whose channel-major layout the row kernel serves: one sweep over X writes both copies (the
+    // mechanism of the early per-channel copy of dY, with the per-tensor scale), and only the padding bytes are left.
+    // (by default from 8 Mi elements on: below that the two lean passes are faster, as for dY)
+    const int v = rows_vector(Lc, X);
+    const bool early = (schedule == DAQ_SCHEDULE_EARLY_COPY || (schedule == DAQ_SCHEDULE_AUTO && n >= ((int64_t)8 << 20))) && v != 0 &&
+                       Lc.lead + (int64_t)d.N * Lc.img_rows * Lc.row_pitch < ((int64_t)1 << 32);
+    int64_t c_blocks;
+    if (v) {
+        a.ra = rows_args(Lc, v, early, a.ws.part_n, 0u, 0);
+        c_blocks = rows_blocks(Lc, a.ra);
+    } else {
+        a.pa = pack_args(Lc, a.ws.part_n, 0u, 0);
+        const dim3 g = pack_grid(Lc);
+        a.phase_blocks = (int)g.x;
+        c_blocks = (int64_t)g.x * g.z;
+    }
+    if (early)
+        a.ev = EarlyVq{qx_cnhw, Lc.chan_pitch, (int32_t)Lc.lead, Lc.img_rows, Lc.row_pitch, Lc.W, make_fastdiv((uint32_t)Lc.W),
+                       0.0f, 0.0f, 0.0f, Lc.W % 4 == 0 ? 1 : 0};
+    if (W) {
+        PackWArgs& w = a.w;
+        if (daq_layout_qw(&d, &w.L) != DAQ_OK) return DAQ_ERR_INVALID_ARG;
+        w.w = W; w.out = qw; w.s_w = s_w; w.part = m.part[1]; w.part_n = m.blocks[1];
+        w.Cout = d.Cout; w.Cin = d.Cin; w.groups = d.groups; w.taps = taps;
+        w.cig = d.Cin / d.groups; w.cog = d.Cout / d.groups;
+        if (d.groups == 1) {
+            w.chunks = (int)ceil_div(taps, kWTaps);
+            w.ci_tiles = 2 * (int)ceil_div(d.Cin, 64);
+            const int first = std::min(taps, kWTaps), last = taps - (w.chunks - 1) * kWTaps;
+            w.div_run = make_fastdiv((uint32_t)(32 * first)); w.div_tap = make_fastdiv((uint32_t)first);
+            w.div_runl = make_fastdiv((uint32_t)(32 * last)); w.div_tapl = make_fastdiv((uint32_t)last);
+            w.blocks = 2 * (int)ceil_div(d.Cout, 64) * w.ci_tiles * w.chunks;
+        } else {
+            w.blocks = (int)ceil_div(w.L.bytes, 16 * kBlock);
+        }
+        a.w_blocks = (int)round_up(w.blocks, kXcd);
+    }
+    const int64_t blocks = a.w_blocks + a.x_blocks + c_blocks;
+    if (blocks >= ((int64_t)1 << 31)) return DAQ_ERR_UNSUPPORTED;
+#define DAQ_FWD_QUANT(E, VV) DAQ_LAUNCH("quant_fwd", st, hipLaunchKernelGGL((k_fwd_quant<E, VV>), dim3((unsigned)blocks), dim3(kBlock), 0, st, a))
+    if (early) { if (v == 4) DAQ_FWD_QUANT(true, 4); else DAQ_FWD_QUANT(true, 2); }
+    else if (v == 4) DAQ_FWD_QUANT(false, 4);
+    else if (v == 2) DAQ_FWD_QUANT(false, 2);
+    else DAQ_FWD_QUANT(false, 0);
+#undef DAQ_FWD_QUANT
     return DAQ_OK;
 }
 
@@ -1566,7 +1754,6 @@ daq_status quantize_grad_impl(const daq_conv_desc* desc, const T* dY, float* s_s
 
     const FastDiv div_hw = make_fastdiv((uint32_t)HW);
     const int CB = (int)ceil_div(C, 64);
-    const float* no_scale = nullptr;
 
     // Channels that fit in LDS: one read of dY serves statistics, count, decision and the per-channel copy
     // (k_chan_resident); the global copy follows in the counting kernel's copy-only form.
@@ -1582,6 +1769,7 @@ daq_status quantize_grad_impl(const daq_conv_desc* desc, const T* dY, float* s_s
     // but it saves a launch, and ResNet-50's backward pass as a whole measured 1 % faster with it than without.)
     if (!given && resident_ok && (schedule == DAQ_SCHEDULE_CHANNEL_RESIDENT || schedule == DAQ_SCHEDULE_AUTO)) {
         ws.slabs = 1;   // one |g|max partial per channel
+        ws.part_n = C;
         const ResArgs ra{div_hw, make_fastdiv((uint32_t)Wo), N, C, HW, k, A, lambda, keys};
         const ClipArgs ca{k, A, lambda, s_state, s_chan, cls, stats};
         // planes without padding between rows and images hold element m at byte lead + m
@@ -1611,13 +1799,13 @@ daq_status quantize_grad_impl(const daq_conv_desc* desc, const T* dY, float* s_s
         if (!qg_nhwc) {
             // depthwise layers: the per-tensor copy is channel-major too; its scale is folded from the channel maxima first
             DAQ_LAUNCH("fold_max", st, hipLaunchKernelGGL(k_fold_max, dim3(1), dim3(kBlock), 0, st, ws, C, s_global));
-            return launch_pack("pack_qg", stoch, false, dY, Lv, s_global, 0, qg, 1u, keys, ws, ClipArgs{}, st);
+            return launch_pack("pack_qg", stoch, false, dY, Lv, s_global, qg, 1u, keys, ws, ClipArgs{}, st);
         }
         const dim3 cgrid((unsigned)(CB * ws.cgroups));
 #define DAQ_COPY_LAUNCH(S)                                                                                           \
     DAQ_LAUNCH("global_copy", st,                                                                                    \
                hipLaunchKernelGGL((k_count_qg<T, S, true, false, false>), cgrid, dim3(kBlock), 0, st, dY, N, C, HW, Lg.c_pitch, \
-                                  div_hw, ws, no_scale, qg, keys, (const float*)s_state, s_global, EarlyVq{}, nhwc_tail(Lg)))
+                                  div_hw, ws, qg, keys, (const float*)s_state, s_global, EarlyVq{}, nhwc_tail(Lg)))
         if (stoch) DAQ_COPY_LAUNCH(true);
         else DAQ_COPY_LAUNCH(false);
 #undef DAQ_COPY_LAUNCH
@@ -1630,6 +1818,7 @@ daq_status quantize_grad_impl(const daq_conv_desc* desc, const T* dY, float* s_s
     const FastDiv div_g4 = make_fastdiv((uint32_t)((HW + 3) / 4));
     if (given) {
         ws.slabs = 1;
+        ws.part_n = C;
         ws.part_max = const_cast<float*>(given->absmax);   // the consumers only read the partials
         ws.part_s1 = const_cast<double*>(given->sum);
         ws.part_s2 = const_cast<double*>(given->sumsq);
@@ -1663,7 +1852,7 @@ daq_status quantize_grad_impl(const daq_conv_desc* desc, const T* dY, float* s_s
 #define DAQ_COUNT_LAUNCH(S, Q, E)                                                                                    \
     DAQ_LAUNCH("count_qg", st,                                                                                       \
                hipLaunchKernelGGL((k_count_qg<T, S, Q, true, E>), cgrid, dim3(kBlock), 0, st, dY, N, C, HW,             \
-                                  qg_nhwc ? Lg.c_pitch : 0, div_hw, ws, no_scale, qg, keys, (const float*)s_state,   \
+                                  qg_nhwc ? Lg.c_pitch : 0, div_hw, ws, qg, keys, (const float*)s_state,   \
                                   s_global, ev, qg_nhwc ? nhwc_tail(Lg) : 0))
     if (early) {
         if (stoch) DAQ_COUNT_LAUNCH(true, true, true);
@@ -1691,11 +1880,11 @@ daq_status quantize_grad_impl(const daq_conv_desc* desc, const T* dY, float* s_s
         if (stream_follows(side, st) != DAQ_OK) return DAQ_ERR_HIP;
         sp = side;
     }
-    rc = launch_pack("pack_vq", stoch, true, dY, Lv, nullptr, 1, vq, 0u, keys, ws, ca, sp, qg_nhwc ? nullptr : qg, s_global,
+    rc = launch_pack("pack_vq", stoch, true, dY, Lv, nullptr, vq, 0u, keys, ws, ca, sp, qg_nhwc ? nullptr : qg, s_global,
                      1u, &fused, early);
     if (rc != DAQ_OK) return rc;
     if (!qg_nhwc && !fused)
-        rc = launch_pack("pack_qg", stoch, false, dY, Lv, s_global, 0, qg, 1u, keys, ws, ClipArgs{}, st);
+        rc = launch_pack("pack_qg", stoch, false, dY, Lv, s_global, qg, 1u, keys, ws, ClipArgs{}, st);
     if (rc == DAQ_OK && side && !qg_nhwc && stream_follows(side, st) != DAQ_OK) return DAQ_ERR_HIP;
     return rc;
 }

@@ -2,8 +2,9 @@
 import numpy as np
 import pytest
 
+from paper_2102_04782_amd import binding as daq
 from paper_2102_04782_amd import workloads as wl
-from test_gpu_parity import run_convs_on_codes
+from test_gpu_parity import check_forward, run_convs_on_codes
 
 pytestmark = pytest.mark.gpu
 
@@ -32,3 +33,19 @@ def test_filter_gradient_ring_remainders(batch, stride):
 ], ids=lambda l: l.name)
 def test_filter_gradient_splits(layer):
     on_random_codes(layer, 77)
+
+
+@pytest.mark.parametrize("layer", [
+    wl.Layer("one", 1, 1, 1, 1, 1, 1, 1, 1, 0),             # one element of everything
+    wl.Layer("tile_less1", 2, 31, 9, 9, 33, 3, 3, 1, 1),    # one short of a 32-channel tile, one past it
+    wl.Layer("tile_past", 2, 65, 6, 6, 32, 1, 1, 1, 0),     # a second 64-channel block of the contraction axis
+    wl.Layer("two_taps", 3, 40, 7, 7, 70, 1, 2, 1, 0),
+    wl.Layer("ten_taps", 2, 33, 8, 12, 34, 2, 5, 1, 2),     # a chunk of nine taps and one of one
+    wl.Layer("stem", 2, 3, 15, 15, 33, 7, 7, 2, 3),         # 49 taps: five chunks of nine, one of four
+    wl.Layer("grouped", 2, 36, 6, 8, 54, 3, 3, 1, 1, groups=2),
+    wl.Layer("depthwise", 2, 33, 5, 6, 33, 3, 3, 2, 1, groups=33),
+], ids=lambda l: l.name)
+@pytest.mark.parametrize("schedule", [None, daq.SCHEDULE_EARLY_COPY])
+def test_forward_quantization_tiles(layer, schedule):
+    """q(W) in all arrangements and both copies of q(X), byte for byte."""
+    check_forward(layer, 91, schedule)
