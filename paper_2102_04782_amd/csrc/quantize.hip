@@ -1062,23 +1062,28 @@ __global__ __launch_bounds__(kBlock) void k_pack_rows(const T* __restrict__ src,
 constexpr int64_t kResidentMaxLds = 96 * 1024;   // bytes of a channel's int8 plane (the LDS image)
 
 struct ResArgs {
-    FastDiv div_hw, div_w;
+    FastDiv div_u, div_w;  // div_u: load units of a plane
     int N, C, HW;
     float k, A, lambda;
     uint64_t seed;         // the keys of stochastic rounding (round_keys)
 };
 
-// A load unit is four consecutive elements of one plane (VEC4: planes of a multiple of four elements in a 16-byte
-// aligned fp32 tensor) or one element; a thread holds NU units, a workgroup has TH threads.
-// FLAT (with VEC4): the plane has no padding between rows or images (1 x 1 layers), so element m of the channel sits at
+// A load unit is four consecutive elements of one plane (VEC4, planes of at least four elements) or one element; a thread
+// holds NU units, a workgroup has TH threads.  TAIL: the plane is not a multiple of four long, and its last unit is moved
+// back to end with it: the elements it shares with the unit before are zeroed for the statistics and not written again.
+// Every load is then 16 (bfloat16: 8) consecutive bytes at the alignment of an element, and a plane of 49 takes 13 of them
+// instead of 49.  (512 -> 2048 1 x 1 at 7 x 7, batch 128, bfloat16: 27 us with a load an element, 22.5 here.)
+// FLAT (without TAIL): the plane has no padding between rows or images (1 x 1 layers), so element m of the channel sits at
 // byte lead + m and a unit's four codes are one aligned dword of the plane: they go straight to memory, no LDS image.
-template <typename T, bool STOCH, bool VEC4, int NU, int TH, bool FLAT = false>
-__global__ __launch_bounds__(TH, NU <= 8 ? (VEC4 ? 6 : 8) : 4) void k_chan_resident(const T* __restrict__ g, CnhwView L, int8_t* __restrict__ vq,
+template <typename T, bool STOCH, bool VEC4, int NU, bool FLAT, bool TAIL>
+__global__ __launch_bounds__(1024, NU <= 2 ? 8 : NU <= 8 ? 6 : 4) void k_chan_resident(const T* __restrict__ g, CnhwView L, int8_t* __restrict__ vq,
                                                       ResArgs ra, QuantWs ws, ClipArgs ca) {
     extern __shared__ __align__(16) int8_t l_img[];   // the channel's plane as it will sit in memory
-    __shared__ float l_mx[TH / kWave];
-    __shared__ double l_s1[TH / kWave], l_s2[TH / kWave];
-    __shared__ uint32_t l_cnt[TH / kWave];
+    constexpr int kMaxWaves = 1024 / kWave;
+    __shared__ float l_mx[kMaxWaves];
+    __shared__ double l_s1[kMaxWaves], l_s2[kMaxWaves];
+    __shared__ uint32_t l_cnt[kMaxWaves];
+    const int TH = (int)blockDim.x;
     __shared__ float l_bc[4];   // |g|max, mean, sigma, clip value
     // workgroup b runs on XCD b % 8: an XCD takes a contiguous eighth of the channels, whose planes are neighbours in
     // every image and share cache lines where a plane is not a whole number of them
@@ -1090,24 +1095,43 @@ __global__ __launch_bounds__(TH, NU <= 8 ? (VEC4 ? 6 : 8) : 4) void k_chan_resid
     constexpr uint32_t EB = sizeof(T);
     constexpr int PER = VEC4 ? 4 : 1;
     const __amdgpu_buffer_rsrc_t rs = f32_rsrc(g, (uint32_t)M * (uint32_t)ra.C * EB);
-    const int units = (M + PER - 1) / PER;
-    const uint32_t skip = (uint32_t)(ra.C - 1) * (uint32_t)HW, first = (uint32_t)c * (uint32_t)HW;   // the other channels' planes of an image
+    const uint32_t upp = (uint32_t)(HW + PER - 1) / PER, units = (uint32_t)ra.N * upp;   // load units of a plane, of the channel
+    // unit q -> image, first element in its plane (TAIL: after the move back), leading elements that belong to the unit before
+    auto place = [&](uint32_t q, uint32_t& n, uint32_t& i, uint32_t& dup) {
+        n = fdiv(q, ra.div_u);
+        const uint32_t at = (q - n * upp) * PER;
+        i = TAIL ? min(at, (uint32_t)HW - 4u) : at;
+        dup = at - i;
+    };
+    // a thread's number again, for the compiler a new one: the places are worked out afresh in every phase, kept they would spill
+    auto again = [&]() {
+        uint32_t t = (uint32_t)tid;
+        asm volatile("" : "+v"(t));
+        return t;
+    };
+    auto index = [&](uint32_t n, uint32_t i) { return (n * (uint32_t)ra.C + (uint32_t)c) * (uint32_t)HW + i; };   // NCHW
 
+    const float s_prev = ca.s_state[c];   // needed by one thread, late: requested with the channel, its latency does not show
     // ---- S1: the channel comes in, all loads of the thread in flight at once ----
     float x[NU][PER];
 #pragma unroll
     for (int u = 0; u < NU; ++u) {
-        const int q = u * TH + tid;
+        const uint32_t q = (uint32_t)(u * TH + tid);
         const bool ok = q < units;
-        const uint32_t m = ok ? (uint32_t)q * PER : 0u;
-        const uint32_t n = fdiv(m, ra.div_hw);
-        const uint32_t off = ok ? (m + n * skip + first) * EB : kOobOff;   // NCHW index (n*C + c)*HW + (m - n*HW)
-        if constexpr (VEC4) {
-            const v4u raw = __builtin_amdgcn_raw_buffer_load_b128(rs, (int)off, 0, 0);
+        uint32_t n, i, dup;
+        place(ok ? q : 0u, n, i, dup);
+        if constexpr (VEC4 && EB == 4) {
+            const v4u raw = __builtin_amdgcn_raw_buffer_load_b128(rs, (int)(ok ? index(n, i) * EB : kOobOff), 0, 0);
 #pragma unroll
             for (int e = 0; e < 4; ++e) x[u][e] = __uint_as_float(raw[e]);
+        } else if constexpr (VEC4) {
+            const uint4 raw = ld4_or_zero<T>(g + index(n, i), ok);
+            x[u][0] = __uint_as_float(raw.x);
+            x[u][1] = __uint_as_float(raw.y);
+            x[u][2] = __uint_as_float(raw.z);
+            x[u][3] = __uint_as_float(raw.w);
         } else {
-            x[u][0] = buf_ld<T>(rs, off, 0u);
+            x[u][0] = buf_ld<T>(rs, ok ? index(n, i) * EB : kOobOff, 0u);
         }
     }
     if constexpr (STOCH) __builtin_amdgcn_sched_barrier(0);   // every load of the channel is requested before the hashes below start
@@ -1116,15 +1140,16 @@ __global__ __launch_bounds__(TH, NU <= 8 ? (VEC4 ? 6 : 8) : 4) void k_chan_resid
     // thread in half k % 2 of word k / 2).
     uint32_t draw[STOCH ? (NU * PER + 1) / 2 : 1];
     if constexpr (STOCH) {
+        const uint32_t tid2 = again();
 #pragma unroll
         for (int k = 0; k < NU * PER; k += 2) {
             uint32_t h[2] = {0u, 0u};
 #pragma unroll
             for (int t = 0; t < 2 && k + t < NU * PER; ++t) {
                 const int u = (k + t) / PER, e = (k + t) % PER;
-                const uint32_t m = (uint32_t)(u * TH + tid) * PER;   // (units past the channel hash a number nobody uses)
-                const uint32_t n = fdiv(m, ra.div_hw);
-                h[t] = fmix32((m + n * skip + first + (uint32_t)e) ^ (uint32_t)ra.seed);
+                uint32_t n, i, dup;
+                place((uint32_t)(u * TH) + tid2, n, i, dup);   // (units past the channel hash a number nobody uses)
+                h[t] = fmix32((index(n, i) + (uint32_t)e) ^ (uint32_t)ra.seed);
             }
             draw[k / 2] = (h[0] >> 16) | (h[1] & 0xffff0000u);   // the per-channel copy draws from the upper half of the hash
         }
@@ -1141,14 +1166,30 @@ __global__ __launch_bounds__(TH, NU <= 8 ? (VEC4 ? 6 : 8) : 4) void k_chan_resid
         const int k = u * PER + e;
         return (k & 1) ? draw[k / 2] >> 16 : draw[k / 2] & 0xffffu;
     };
+    uint32_t dups = 0;   // TAIL: leading elements of unit u that belong to the unit before, two bits each
+    if constexpr (TAIL) {
+        const uint32_t tid2 = again();
+#pragma unroll
+        for (int u = 0; u < NU; ++u) {
+            uint32_t n, i, dup;
+            place((uint32_t)(u * TH) + tid2, n, i, dup);
+            dups |= dup << (2 * u);
+        }
+    }
+    // element e of unit u as the statistics see it
+    auto own = [&](int u, int e) -> float {
+        if (!TAIL || e == 3) return x[u][e];
+        return (dups >> (2 * u) & 3u) > (uint32_t)e ? 0.0f : x[u][e];
+    };
     float mx = 0.0f;
     double s1 = 0.0, s2 = 0.0;
 #pragma unroll
     for (int u = 0; u < NU; ++u)
 #pragma unroll
         for (int e = 0; e < PER; ++e) {   // units past the channel were read as zeros and change nothing
-            mx = fmaxf(mx, fabsf(x[u][e]));
-            const double a = x[u][e];
+            const float v = own(u, e);
+            mx = fmaxf(mx, fabsf(v));
+            const double a = v;
             s1 += a;
             s2 = __builtin_fma(a, a, s2);   // the square of a widened fp32 is exact in fp64: the same sum as s2 + a * a, one instruction
         }
@@ -1178,7 +1219,7 @@ __global__ __launch_bounds__(TH, NU <= 8 ? (VEC4 ? 6 : 8) : 4) void k_chan_resid
 #pragma unroll
     for (int u = 0; u < NU; ++u)
 #pragma unroll
-        for (int e = 0; e < PER; ++e) cnt += (uint32_t)__popcll(__ballot(fabsf(x[u][e]) > sigma));
+        for (int e = 0; e < PER; ++e) cnt += (uint32_t)__popcll(__ballot(fabsf(own(u, e)) > sigma));
     if (lane == 0) l_cnt[wave] = cnt;
     __syncthreads();
     if (tid == 0) {
@@ -1186,7 +1227,7 @@ __global__ __launch_bounds__(TH, NU <= 8 ? (VEC4 ? 6 : 8) : 4) void k_chan_resid
         for (int w = 1; w < TH / kWave; ++w) cnt += l_cnt[w];
         const double Md = (double)ra.N * (double)HW;
         const int klass = ((double)cnt > (double)ra.lambda * Md) ? DAQ_CLASS_GAUSS : DAQ_CLASS_INVT;
-        const float sc = clip_rule(klass, gm, ca.s_state[c], ra.k, ra.A);
+        const float sc = clip_rule(klass, gm, s_prev, ra.k, ra.A);
         l_bc[3] = sc;
         ca.s_state[c] = sc;
         ca.s_chan[c] = (sc >= kTinyScale) ? sc : 0.0f;
@@ -1203,40 +1244,49 @@ __global__ __launch_bounds__(TH, NU <= 8 ? (VEC4 ? 6 : 8) : 4) void k_chan_resid
     const float inv = inv_scale(l_bc[3]);
 
     if constexpr (FLAT) {
-        // ---- S5, plane without padding: a unit's four codes are dword q of the plane's payload ----
-        uint32_t* plane32 = reinterpret_cast<uint32_t*>(vq + (int64_t)c * L.chan_pitch);   // chan_pitch is a multiple of 256
-        uint32_t* pay = plane32 + (L.lead >> 2);
+        // ---- S5, plane without padding: a unit's four codes are four consecutive bytes of the plane's payload ----
+        // (TAIL: at any byte; what a unit shares with the one before it, both write the same)
+        int8_t* plane = vq + (int64_t)c * L.chan_pitch;
+        const uint32_t tid2 = again(), payload = (uint32_t)M;
 #pragma unroll
         for (int u = 0; u < NU; ++u) {
-            const int q = u * TH + tid;
+            const uint32_t q = (uint32_t)(u * TH) + tid2;
             if (q < units) {
                 uint32_t b[4];
 #pragma unroll
                 for (int e = 0; e < 4; ++e) b[e] = quant_bits<STOCH>(x[u][e], inv, draw_of(u, e));
-                pay[q] = pack4(b[0], b[1], b[2], b[3]);
+                const uint32_t w = pack4(b[0], b[1], b[2], b[3]);
+                if constexpr (TAIL) {
+                    uint32_t n, i, dup;
+                    place(q, n, i, dup);
+                    __builtin_memcpy(plane + (uint32_t)L.lead + n * (uint32_t)HW + i, &w, 4);
+                } else {
+                    reinterpret_cast<uint32_t*>(plane + L.lead)[q] = w;
+                }
             }
         }
-        // the zeros in front of and behind the payload
-        const int head = (int)(L.lead >> 2), tail = head + units, total = (int)(L.plane_pitch >> 2);
-        for (int i = tid; i < head; i += TH) plane32[i] = 0u;
-        for (int i = tail + tid; i < total; i += TH) plane32[i] = 0u;
+        // the zeros in front of and behind the payload (the plane and its lead are whole dwords, the payload need not be)
+        const uint32_t head = (uint32_t)L.lead, tail = head + payload, total = (uint32_t)L.plane_pitch;
+        for (uint32_t t = 4u * tid; t < head; t += 4u * TH) *reinterpret_cast<uint32_t*>(plane + t) = 0u;
+        const uint32_t tail4 = (tail + 3u) & ~3u;
+        if (TAIL && tid < (int)(tail4 - tail)) plane[tail + tid] = 0;
+        for (uint32_t t = tail4 + 4u * tid; t < total; t += 4u * TH) *reinterpret_cast<uint32_t*>(plane + t) = 0u;
         return;
     }
     // ---- S5: the per-channel codes go to their places in the plane image ----
-    const uint32_t slot = (uint32_t)(L.img_rows * L.row_pitch);
+    const uint32_t slot = (uint32_t)(L.img_rows * L.row_pitch), tid2 = again();
 #pragma unroll
     for (int u = 0; u < NU; ++u) {
-        const int q = u * TH + tid;
+        const uint32_t q = (uint32_t)(u * TH) + tid2;
         if (q < units) {
-            const uint32_t m = (uint32_t)q * PER;
-            const uint32_t n = fdiv(m, ra.div_hw);
-            const uint32_t px = m - n * (uint32_t)HW;
+            uint32_t n, px, dup;
+            place(q, n, px, dup);
             uint32_t r = fdiv(px, ra.div_w);
             uint32_t col = px - r * (uint32_t)L.W;
             uint32_t pos = (uint32_t)L.lead + n * slot + r * (uint32_t)L.row_pitch + col;
 #pragma unroll
             for (int e = 0; e < PER; ++e) {
-                l_img[pos] = (int8_t)quant_bits<STOCH>(x[u][e], inv, draw_of(u, e));
+                if (!TAIL || e == 3 || (uint32_t)e >= dup) l_img[pos] = (int8_t)quant_bits<STOCH>(x[u][e], inv, draw_of(u, e));
                 const bool wrap = ++col == (uint32_t)L.W;   // a unit stays inside its image, but may run on into the next row
                 col = wrap ? 0u : col;
                 pos += wrap ? (uint32_t)(L.row_pitch - L.W) + 1u : 1u;
@@ -1757,11 +1807,16 @@ daq_status quantize_grad_impl(const daq_conv_desc* desc, const T* dY, float* s_s
 
     // Channels that fit in LDS: one read of dY serves statistics, count, decision and the per-channel copy
     // (k_chan_resident); the global copy follows in the counting kernel's copy-only form.
-    // a workgroup of 512 threads x 8 or 16 load units, or 1024 x 16, holds the channel; a unit is four elements where planes are a
-    // multiple of four elements long in a 16-byte aligned fp32 tensor, else one element
-    const bool res_v4 = sizeof(T) == 4 && HW % 4 == 0 && ((uintptr_t)dY & 15u) == 0;
-    const int64_t res_units = ceil_div((int64_t)N * HW, res_v4 ? 4 : 1);
-    const bool res_small = res_units <= 8 * 512, res_mid = res_units <= 16 * 512;
+    // A workgroup holds the channel, 2, 4, 8 or 16 units to a thread, as many waves as that takes.  A wave's work is serial, some
+    // 100 instructions a unit, so while the chip has room for the waves fewer units are faster (16 channels of 832 units: 7.2, 7.4,
+    // 8.2, 11.0 us with 2, 4, 8, 16); once it is full, waves with more loads in flight are (2048 channels of 1664 units: 31.5, 24.5,
+    // 22.4, 24.6 us; 512 channels of 1664: 10.5, 10.2, 10.6, 14.0; 1024 of 832: 10.8, 10.3, 10.2, 11.9).
+    const bool res_v4 = HW >= 4;   // dword-aligned 16-byte loads run at full rate, as in the statistics sweep
+    const int res_upp = res_v4 ? (HW + 3) / 4 : HW;
+    const int64_t res_units = (int64_t)N * res_upp;
+    auto res_fits = [&](int nu) { return res_units <= nu * 1024 && C * ceil_div(res_units, nu * kWave) <= 6144; };   // 24 waves a CU
+    const int res_nu = res_fits(2) ? 2 : res_fits(4) ? 4 : res_fits(8) || res_units <= 8 * 512 ? 8 : 16;
+    const int res_th = (int)round_up(ceil_div(res_units, res_nu), kWave);
     const bool resident_ok = scheme == DAQ_SCHEME_DAQ && res_units <= 16 * 1024 && Lv.plane_pitch <= kResidentMaxLds &&
                              (Lv.plane_pitch & 15) == 0 && (Lv.chan_pitch & 15) == 0;
     // (The 1024-thread form runs one workgroup per CU, whose load, count and packing phases follow each other with nothing
@@ -1770,28 +1825,37 @@ daq_status quantize_grad_impl(const daq_conv_desc* desc, const T* dY, float* s_s
     if (!given && resident_ok && (schedule == DAQ_SCHEDULE_CHANNEL_RESIDENT || schedule == DAQ_SCHEDULE_AUTO)) {
         ws.slabs = 1;   // one |g|max partial per channel
         ws.part_n = C;
-        const ResArgs ra{div_hw, make_fastdiv((uint32_t)Wo), N, C, HW, k, A, lambda, keys};
+        const ResArgs ra{make_fastdiv((uint32_t)res_upp), make_fastdiv((uint32_t)Wo), N, C, HW, k, A, lambda, keys};
         const ClipArgs ca{k, A, lambda, s_state, s_chan, cls, stats};
         // planes without padding between rows and images hold element m at byte lead + m
         const bool res_flat = res_v4 && Lv.row_pitch == Lv.W && Lv.img_rows == Lv.H && (Lv.lead & 3) == 0 && (Lv.plane_pitch & 3) == 0 &&
                               Lv.lead + (int64_t)N * HW <= Lv.plane_pitch;
         const size_t lds = res_flat ? 0 : (size_t)Lv.plane_pitch;
-#define DAQ_RES_LAUNCH(S, V, NUV, THV)                                                                               \
-    if (V && res_flat) {                                                                                             \
-        DAQ_LAUNCH("chan_resident", st, hipLaunchKernelGGL((k_chan_resident<T, S, V, NUV, THV, V>), dim3((unsigned)round_up(C, kXcd)), dim3(THV), 0, st, dY, cnhw_view(Lv), vq, ra, ws, ca)); \
-    } else {                                                                                                         \
-        auto kern = k_chan_resident<T, S, V, NUV, THV>;                                                              \
-        if (hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess) \
+        const dim3 rgrid((unsigned)round_up(C, kXcd));
+#define DAQ_RES_LAUNCH(S, V, NUV, FL, TL)                                                                            \
+    {                                                                                                                \
+        auto kern = k_chan_resident<T, S, V, NUV, FL, TL>;                                                           \
+        if (!FL && hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess) \
             return DAQ_ERR_HIP;                                                                                      \
-        DAQ_LAUNCH("chan_resident", st, hipLaunchKernelGGL(kern, dim3((unsigned)round_up(C, kXcd)), dim3(THV), lds, st, dY, cnhw_view(Lv), vq, ra, ws, ca)); \
+        DAQ_LAUNCH("chan_resident", st, hipLaunchKernelGGL(kern, rgrid, dim3((unsigned)res_th), lds, st, dY, cnhw_view(Lv), vq, ra, ws, ca)); \
     }
-#define DAQ_RES_SIZE(S, V) { if (res_small) DAQ_RES_LAUNCH(S, V, 8, 512) else if (res_mid) DAQ_RES_LAUNCH(S, V, 16, 512) else DAQ_RES_LAUNCH(S, V, 16, 1024) }
-        if constexpr (sizeof(T) == 4) {
-            if (stoch) { if (res_v4) DAQ_RES_SIZE(true, true) else DAQ_RES_SIZE(true, false) }
-            else { if (res_v4) DAQ_RES_SIZE(false, true) else DAQ_RES_SIZE(false, false) }
-        } else {
-            if (stoch) DAQ_RES_SIZE(true, false) else DAQ_RES_SIZE(false, false)
-        }
+#define DAQ_RES_FORM(S, NUV)                                                                                         \
+    {                                                                                                                \
+        if (!res_v4) DAQ_RES_LAUNCH(S, false, NUV, false, false)                                                     \
+        else if (res_flat && HW % 4 == 0) DAQ_RES_LAUNCH(S, true, NUV, true, false)                                  \
+        else if (res_flat) DAQ_RES_LAUNCH(S, true, NUV, true, true)                                                  \
+        else if (HW % 4 == 0) DAQ_RES_LAUNCH(S, true, NUV, false, false)                                             \
+        else DAQ_RES_LAUNCH(S, true, NUV, false, true)                                                               \
+    }
+#define DAQ_RES_SIZE(S)                                                                                              \
+    {                                                                                                                \
+        if (res_nu == 2) DAQ_RES_FORM(S, 2)                                                                          \
+        else if (res_nu == 4) DAQ_RES_FORM(S, 4)                                                                     \
+        else if (res_nu == 8) DAQ_RES_FORM(S, 8)                                                                     \
+        else DAQ_RES_FORM(S, 16)                                                                                     \
+    }
+        if (stoch) DAQ_RES_SIZE(true) else DAQ_RES_SIZE(false)
+#undef DAQ_RES_FORM
 #undef DAQ_RES_SIZE
 #undef DAQ_RES_LAUNCH
         // the per-channel copy, its scales, classes and clip state are complete here; the global copy follows on `st`
