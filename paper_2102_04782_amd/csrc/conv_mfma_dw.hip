@@ -832,8 +832,7 @@ daq_status launch_dw(const Plan& pl, const DwArgs& a, int wq4, hipStream_t st) {
 #define DAQ_DW_CASE(Q)                                                                                            \
     if (wq4 == Q) {                                                                                               \
         auto kern = k_dw_mfma<KH, KW, Q, WGK, NB, PF>;                                                            \
-        if (hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize,                    \
-                                (int)pl.lds_bytes) != hipSuccess)                                                 \
+        if (!allow_lds((const void*)kern, pl.lds_bytes))                                                 \
             return DAQ_ERR_HIP;                                                                                   \
         DAQ_LAUNCH("conv_bwd_filter_frag", st, hipLaunchKernelGGL(kern, grid, dim3(256), pl.lds_bytes, st, a));   \
         return DAQ_OK;                                                                                            \
@@ -849,8 +848,7 @@ daq_status launch_dw_direct(const Plan& pl, const DwArgs& a, int wq4, hipStream_
 #define DAQ_DW_CASE(Q)                                                                                            \
     if (wq4 == Q) {                                                                                               \
         auto kern = k_dw_direct<KH, KW, Q, NB, PFD>;                                                              \
-        if (hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize,                    \
-                                (int)pl.lds_bytes) != hipSuccess)                                                 \
+        if (!allow_lds((const void*)kern, pl.lds_bytes))                                                 \
             return DAQ_ERR_HIP;                                                                                   \
         DAQ_LAUNCH("conv_bwd_filter_direct_frag", st, hipLaunchKernelGGL(kern, grid, dim3(256), pl.lds_bytes, st, a));   \
         return DAQ_OK;                                                                                            \
@@ -864,7 +862,7 @@ template <int TW, int NB, int PFD, bool WTAPS, int WAVES>
 daq_status launch_dw_taps(const Plan& pl, const DwArgs& a, const TapTable& tt, hipStream_t st) {
     const dim3 grid((unsigned)(pl.tiles_m * pl.tiles_n * pl.splits));
     auto kern = k_dw_taps<TW, NB, PFD, WTAPS, WAVES>;
-    if (hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)pl.lds_bytes) != hipSuccess)
+    if (!allow_lds((const void*)kern, pl.lds_bytes))
         return DAQ_ERR_HIP;
     DAQ_LAUNCH("conv_bwd_filter_taps", st, hipLaunchKernelGGL(kern, grid, dim3(64 * WAVES), pl.lds_bytes, st, a, tt));
     return DAQ_OK;

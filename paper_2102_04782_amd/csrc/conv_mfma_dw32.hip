@@ -821,8 +821,7 @@ daq_status launch32(const Plan32& pl, const Dw32Args& a, int wq4, hipStream_t st
 #define DAQ_DW32_CASE(Q)                                                                                          \
     if (wq4 == Q) {                                                                                               \
         auto kern = k_dw32<Q, WM, WN, WK, PF, S2>;                                                                    \
-        if (hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize,                    \
-                                (int)pl.lds_bytes) != hipSuccess)                                                 \
+        if (!allow_lds((const void*)kern, pl.lds_bytes))                                                 \
             return DAQ_ERR_HIP;                                                                                   \
         DAQ_LAUNCH("conv_bwd_filter_dw32", st, hipLaunchKernelGGL(kern, grid, dim3(64 * WM * WN * WK), pl.lds_bytes, st, a)); \
         return DAQ_OK;                                                                                            \
@@ -890,12 +889,12 @@ daq_status conv_bwd_filter_lds(const daq_conv_desc& d, const int8_t* qx, const f
         const dim3 grid((unsigned)pl.blocks, (unsigned)depth);
         if (pl.wk == 1) {
             auto kern = k_dw11<2, 2, 1, 1, 1>;
-            if (hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)pl.lds_bytes) != hipSuccess)
+            if (!allow_lds((const void*)kern, pl.lds_bytes))
                 return DAQ_ERR_HIP;
             DAQ_LAUNCH("conv_bwd_filter_dw11", st, hipLaunchKernelGGL(kern, grid, dim3(256), pl.lds_bytes, st, a));
         } else {
             auto kern = k_dw11<1, 1, 8, 3, 1, true>;
-            if (hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)pl.lds_bytes) != hipSuccess)
+            if (!allow_lds((const void*)kern, pl.lds_bytes))
                 return DAQ_ERR_HIP;
             DAQ_LAUNCH("conv_bwd_filter_dw11", st, hipLaunchKernelGGL(kern, grid, dim3(512), pl.lds_bytes, st, a));
         }

@@ -919,8 +919,7 @@ daq_status launch(Geometry& g, hipStream_t st, const HaloNames& names) {
 #define DAQ_HALO_CASE(WRV, DBV, WV)                                                                                  \
     {                                                                                                                \
         auto kern = a.stride == 2 ? k_conv_halo<WRV, DBV, 2, WV> : k_conv_halo<WRV, DBV, 1, WV>;                     \
-        if (hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)g.lds_bytes) !=  \
-            hipSuccess)                                                                                              \
+        if (!allow_lds((const void*)kern, g.lds_bytes))                                                                                              \
             return DAQ_ERR_HIP;                                                                                      \
         DAQ_LAUNCH(name, st, hipLaunchKernelGGL(kern, grid, dim3(64 * WV), g.lds_bytes, st, a));                     \
     }
@@ -934,14 +933,14 @@ daq_status launch(Geometry& g, hipStream_t st, const HaloNames& names) {
     if (ring1) {
         auto kern = a.stride == 2 ? (g.px == kPxWg ? k_conv_halo<1, true, 2, 4, 1> : k_conv_halo<1, true, 2, 4, 1, 2, 128>)
                                   : (g.px == kPxWg ? k_conv_halo<1, true, 1, 4, 1> : k_conv_halo<1, true, 1, 4, 1, 2, 128>);
-        if (hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)g.lds_bytes) != hipSuccess)
+        if (!allow_lds((const void*)kern, g.lds_bytes))
             return DAQ_ERR_HIP;
         DAQ_LAUNCH(names.k1, st, hipLaunchKernelGGL(kern, grid, dim3(256), g.lds_bytes, st, a));
         return DAQ_OK;
     }
     if (taps9_applies(g)) {
         auto kern = g.px == kPxWg ? k_conv_halo<1, true, 1, 4, 9> : k_conv_halo<1, true, 1, 4, 9, 2, 128>;
-        if (hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)g.lds_bytes) != hipSuccess)
+        if (!allow_lds((const void*)kern, g.lds_bytes))
             return DAQ_ERR_HIP;
         DAQ_LAUNCH(names.k9, st, hipLaunchKernelGGL(kern, grid, dim3(256), g.lds_bytes, st, a));
         return DAQ_OK;
@@ -955,8 +954,7 @@ daq_status launch(Geometry& g, hipStream_t st, const HaloNames& names) {
 #define DAQ_HALO_NARROW(DBV)                                                                                         \
     {                                                                                                                \
         auto kern = a.stride == 2 ? k_conv_halo<1, DBV, 2, 4, 0, 1> : k_conv_halo<1, DBV, 1, 4, 0, 1>;               \
-        if (hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)g.lds_bytes) !=  \
-            hipSuccess)                                                                                              \
+        if (!allow_lds((const void*)kern, g.lds_bytes))                                                                                              \
             return DAQ_ERR_HIP;                                                                                      \
         DAQ_LAUNCH(name, st, hipLaunchKernelGGL(kern, grid, dim3(256), g.lds_bytes, st, a));                         \
     }
@@ -1079,7 +1077,7 @@ daq_status launch3(Plan3& pl, const int8_t* filter, void* frag, const char* name
                 : a.Crow <= 32 && pl.g.px == kPxWg ? k_conv_halo<1, true, 1, 4, 0, 1, kPxWg, true>
                 : taps9_applies(pl.g) ? (pl.g.px == kPxWg ? k_conv_halo<1, true, 1, 4, 9, 2, kPxWg, true> : k_conv_halo<1, true, 1, 4, 9, 2, 128, true>)
                                       : k_conv_halo<1, true, 1, 4, 0, 2, kPxWg, true>;
-    if (hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)pl.g.lds_bytes) != hipSuccess) return DAQ_ERR_HIP;
+    if (!allow_lds((const void*)kern, pl.g.lds_bytes)) return DAQ_ERR_HIP;
     DAQ_LAUNCH(name, st, hipLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3(r128 ? 512 : 256), pl.g.lds_bytes, st, a));
     return DAQ_OK;
 }

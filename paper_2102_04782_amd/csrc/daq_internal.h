@@ -41,6 +41,12 @@ void prof_pop(hipStream_t s);                     // records the stop event
         if (hipGetLastError() != hipSuccess) return DAQ_ERR_HIP; \
     } while (0)
 
+// Dynamic LDS beyond 64 KiB has to be asked for, kernel by kernel and on every device; below that (48 KiB here: some kernels
+// have a static part as well) the call would only cost host time, in launches that are often shorter than it takes to make them.
+inline bool allow_lds(const void* kernel, size_t bytes) {
+    return bytes <= 48 * 1024 || hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes) == hipSuccess;
+}
+
 // ---- predicated loads without control flow ------------------------------------------------
 // A load guarded by an `if` becomes an exec-masked branch with a full memory wait at its join, and a
 // select applied to the loaded value makes the compiler wait right behind the load; either way a

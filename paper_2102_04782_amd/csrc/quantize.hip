@@ -1835,7 +1835,7 @@ daq_status quantize_grad_impl(const daq_conv_desc* desc, const T* dY, float* s_s
 #define DAQ_RES_LAUNCH(S, V, NUV, FL, TL)                                                                            \
     {                                                                                                                \
         auto kern = k_chan_resident<T, S, V, NUV, FL, TL>;                                                           \
-        if (!FL && hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess) \
+        if (!FL && !allow_lds((const void*)kern, lds)) \
             return DAQ_ERR_HIP;                                                                                      \
         DAQ_LAUNCH("chan_resident", st, hipLaunchKernelGGL(kern, rgrid, dim3((unsigned)res_th), lds, st, dY, cnhw_view(Lv), vq, ra, ws, ca)); \
     }
