@@ -92,6 +92,9 @@ extern "C" daq_status daq_conv_bwd_int8(const daq_conv_desc* desc, const int8_t*
     void* ws_d = static_cast<char*>(workspace) + need_f;   // need_f is a multiple of 256
     if (bwd_filter_lds_supported(*desc) && bwd_data_halo_supported(*desc)) {
         hipStream_t st = (hipStream_t)stream;
+        daq_status both;
+        if (conv_bwd_both_small(*desc, qx_cnhw, s_x, vq, s_chan, dW, dW_acc, qg, s_global, qw_packed, s_w, dX, dX_acc, workspace, st, both))
+            return both;
         DwTail tail{};
         const daq_status rc = conv_bwd_filter_lds(*desc, qx_cnhw, s_x, vq, s_chan, dW, dW_acc, workspace, st, &tail);
         if (rc != DAQ_OK) return rc;

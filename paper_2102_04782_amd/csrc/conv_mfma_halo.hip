@@ -20,14 +20,12 @@
 #include <algorithm>
 
 #include "daq_internal.h"
+#include "dw32_role.h"
 #include "dw_tail.h"
 
 namespace daq {
 
 namespace {
-
-typedef int v4i __attribute__((ext_vector_type(4)));
-typedef int v16i __attribute__((ext_vector_type(16)));
 
 constexpr int kPxWg = 256;         // destination pixels per workgroup (128 in the small-tile form of 1 x 1 filters)
 constexpr int kKc = 64;            // contraction bytes per step (two MFMA K-steps of 32)
@@ -93,8 +91,8 @@ __device__ __forceinline__ v4i buffer_load16(__amdgpu_buffer_rsrc_t rsrc, uint32
 // frame of the sample (zeros where there is none), so the depth taps are further chunks of the contraction axis - chunk
 // kd * nkc_frame + kc - and nothing else in the loop changes; the filter copy is in the same order (k_frag3 writes it).
 // (3 x 3 x 3, 64 -> 64, 8 x 56 x 56, batch 8, data gradient: 365 us with dot products, 49 us here, 0.9 POP/s.)
-template <int WR, bool DB, int ST, int WAVES, int TAPS = 0, int NX = 2, int PX = kPxWg, bool D3 = false>
-__global__ __launch_bounds__(64 * WAVES, (TAPS == 1 || NX == 1 || PX < kPxWg) ? 2 : 1) void k_conv_halo(HaloArgs p) {
+template <int WR, bool DB, int ST, int WAVES, int TAPS, int NX, int PX, bool D3>
+__device__ __forceinline__ void halo_role(const HaloArgs& p, const uint32_t bid) {
     constexpr int ROWS = 64 * WR;
     constexpr int WPX = WAVES / WR;
     constexpr int SPT = 16 * WAVES;   // window slots one pass of the workgroup stages (four lanes per slot)
@@ -102,11 +100,10 @@ __global__ __launch_bounds__(64 * WAVES, (TAPS == 1 || NX == 1 || PX < kPxWg) ? 
     constexpr int BF = PXW / 32;
     extern __shared__ __align__(16) int8_t lds[];   // one or two window buffers of S slots
 
-    if (p.tail.blocks > 0 && (int)blockIdx.x >= p.main_blocks) {   // uniform
-        dw_reduce_role(p.tail, (int)blockIdx.x - p.main_blocks, reinterpret_cast<int32_t*>(lds));
+    if (p.tail.blocks > 0 && (int)bid >= p.main_blocks) {   // uniform
+        dw_reduce_role(p.tail, (int)bid - p.main_blocks, reinterpret_cast<int32_t*>(lds));
         return;
     }
-    const uint32_t bid = blockIdx.x;
     const int tid = threadIdx.x, wave = tid / kWave, lane = tid % kWave;
     const int l32 = lane & 31, lh = lane >> 5;
     const int wr = wave % WR, wp = wave / WR;
@@ -562,6 +559,11 @@ __global__ __launch_bounds__(64 * WAVES, (TAPS == 1 || NX == 1 || PX < kPxWg) ? 
     }
 }
 
+template <int WR, bool DB, int ST, int WAVES, int TAPS = 0, int NX = 2, int PX = kPxWg, bool D3 = false>
+__global__ __launch_bounds__(64 * WAVES, (TAPS == 1 || NX == 1 || PX < kPxWg) ? 2 : 1) void k_conv_halo(HaloArgs p) {
+    halo_role<WR, DB, ST, WAVES, TAPS, NX, PX, D3>(p, blockIdx.x);
+}
+
 // ---------------------------------------------------------------------------------------------
 // 1 x 1 data gradient (and forward pass) at unit stride with a short contraction axis (at most 256 channels: for the
 // data gradient the projection layers of MobileNetV2 and the 1 x 1 layers of ResNet-50 that reduce to 64 - 256 channels).  Such a layer is a few
@@ -1000,6 +1002,46 @@ Geometry plan_fwd(const daq_conv_desc& d) {
 }
 
 // ---------------------------------------------------------------------------------------------
+// Both gradients of a small layer in one launch.  They do not depend on each other, and a layer whose two kernels together
+// have no more workgroups than the chip has CUs gains nothing from running them one after the other: each is a chain of
+// latencies (prologue, a few chunks, combine, stores; 6 to 10 us), most CUs idle, and a launch between them.  The first
+// w_blocks workgroups work on the filter gradient, those from x_first on (a multiple of eight, so that either part's own
+// mapping to the XCDs holds) on the data gradient, with the first four of their eight waves.  All are resident at once: at
+// most 256, each with a CU's LDS to itself.
+// (Backward step, quantizer included: 16 -> 16 3 x 3 at 16 x 16, batch 4, 24.8 -> 18.3 us; 100 -> 70 3 x 3 at 29 x 31, batch
+// 5, 28.7 -> 22.4; 53 -> 592 1 x 1 stride 2 at 53 x 53, batch 3, 32 -> 23.)
+// ---------------------------------------------------------------------------------------------
+enum BothForm { kBothRing1, kBothTaps9, kBothOneChunk, kBothNarrow, kBothRing1S2, kBothNone };   // of the tile kernel
+constexpr int kBothBlocks = 256;
+
+template <int KIND, int FORM>
+__global__ __launch_bounds__(512, 1) void k_bwd_both(Dw32Args w, HaloArgs x, int w_blocks, int x_first) {
+    const int b = (int)blockIdx.x;
+    if (b < x_first) {   // uniform
+        if (b >= w_blocks) return;
+        if constexpr (KIND < 4) dw32_role<KIND, 1, 1, 8, 3, false>(w, b);
+        else dw11_role<1, 1, 8, 3, 1, true>(w, b);
+        return;
+    }
+    if (threadIdx.x >= 256) return;   // (a barrier waits for the waves that are still there)
+    const uint32_t bid = (uint32_t)(b - x_first);
+    if constexpr (FORM == kBothRing1) halo_role<1, true, 1, 4, 1, 2, 128, false>(x, bid);
+    else if constexpr (FORM == kBothTaps9) halo_role<1, true, 1, 4, 9, 2, 128, false>(x, bid);
+    else if constexpr (FORM == kBothOneChunk) halo_role<1, false, 1, 4, 0, 2, kPxWg, false>(x, bid);
+    else if constexpr (FORM == kBothNarrow) halo_role<1, false, 1, 4, 0, 1, kPxWg, false>(x, bid);
+    else halo_role<1, true, 2, 4, 1, 2, 128, false>(x, bid);
+}
+
+BothForm both_form(const Geometry& g) {
+    const HaloArgs& a = g.a;
+    if (!g.ok || g.rows != 64) return kBothNone;
+    if (ring1_applies(g)) return g.px != 128 ? kBothNone : a.stride == 2 ? kBothRing1S2 : kBothRing1;
+    if (taps9_applies(g)) return g.px == 128 ? kBothTaps9 : kBothNone;
+    if (g.px != kPxWg || a.double_buffer || a.stride != 1) return kBothNone;
+    return a.Crow <= 32 ? kBothNarrow : kBothOneChunk;
+}
+
+// ---------------------------------------------------------------------------------------------
 // 3-D layers (forms D3 of the tile kernel).  The filter of such a layer is stored [tap][row][contraction, a multiple of 16]
 // with tap = (kd*kH + kh)*kW + kw; a lane of the tile kernel would collect its fragment from 32 rows a pitch apart, a
 // quarter of the rate of one contiguous KiB, and every workgroup reads the whole filter.  So the filter is put into
@@ -1158,6 +1200,49 @@ daq_status conv_bwd_data_halo(const daq_conv_desc& d, const int8_t* qg, const fl
     g.a.out = dX; g.a.acc_out = acc;
     g.a.nt = !bf16 && stream_result((int64_t)d.N * d.Cin * d.Hin * d.Win * 4, (int64_t)d.Hin * d.Win * 4);
     return launch(g, st, kBwdNames);
+}
+
+bool conv_bwd_both_small(const daq_conv_desc& d, const int8_t* qx, const float* s_x, const int8_t* vq, const float* s_chan, float* dW,
+                         int32_t* dW_acc, const int8_t* qg, const float* s_g, const int8_t* qw, const float* s_w, float* dX, int32_t* dX_acc,
+                         void* ws, hipStream_t st, daq_status& rc) {
+    Geometry g = plan_bwd(d);
+    const BothForm form = both_form(g);
+    if (form == kBothNone) return false;
+    const int64_t x_blocks = blocks_per_row_tile(g.a) * ceil_div(g.a.Crow, 64);
+    if (x_blocks > kBothBlocks - 8) return false;
+    const double x_us = form == kBothTaps9 ? 5.0 + 1.0 * (double)ceil_div(g.a.cp, kKc) : 4.5 + 0.35 * (double)ceil_div(g.a.cp, kKc);
+    DwBeside w;
+    if (!bwd_filter_beside(d, qx, s_x, vq, s_chan, dW, dW_acc, ws, kBothBlocks - (int)x_blocks, x_us, w)) return false;
+    daq_wpack_layout Lw;
+    if (daq_layout_qw(&d, &Lw) != DAQ_OK) return false;
+    HaloArgs& a = g.a;
+    a.src = qg;
+    a.wfrag = qw + Lw.off_bwd_frag;
+    a.s_a = s_w;
+    a.s_b = s_g;
+    a.out = dX;
+    a.acc_out = dX_acc;
+    a.main_blocks = (int)x_blocks;
+    const int x_first = (int)round_up(w.blocks, kXcd);
+    const dim3 grid((unsigned)(x_first + x_blocks));
+    const size_t lds = std::max(w.lds_bytes, g.lds_bytes);
+    auto run = [&]() -> daq_status {
+#define DAQ_BOTH(K, F)                                                                                                \
+    if (w.kind == K && form == F) {                                                                                  \
+        auto kern = k_bwd_both<K, F>;                                                                                \
+        if (!allow_lds((const void*)kern, lds)) return DAQ_ERR_HIP;                                                  \
+        DAQ_LAUNCH("conv_bwd_both", st, hipLaunchKernelGGL(kern, grid, dim3(512), lds, st, w.a, a, w.blocks, x_first)); \
+        return w.tail.blocks > 0 ? launch_dw_reduce(w.tail, 1, st) : DAQ_OK;                                         \
+    }
+#define DAQ_BOTH33(F) DAQ_BOTH(0, F) DAQ_BOTH(1, F) DAQ_BOTH(2, F) DAQ_BOTH(3, F)
+        DAQ_BOTH33(kBothTaps9) DAQ_BOTH33(kBothOneChunk) DAQ_BOTH33(kBothNarrow)
+        DAQ_BOTH(4, kBothRing1) DAQ_BOTH(4, kBothOneChunk) DAQ_BOTH(4, kBothNarrow) DAQ_BOTH(4, kBothRing1S2)
+#undef DAQ_BOTH33
+#undef DAQ_BOTH
+        return DAQ_ERR_UNSUPPORTED;
+    };
+    rc = run();
+    return rc != DAQ_ERR_UNSUPPORTED;   // nothing was launched
 }
 
 bool fwd_halo_supported(const daq_conv_desc& d) { return plan_fwd(d).ok; }

@@ -196,6 +196,11 @@ bool bwd_data_halo_supported(const daq_conv_desc& d);
 daq_status conv_bwd_data_halo(const daq_conv_desc& d, const int8_t* qg, const float* s_g, const int8_t* qw,
                               const float* s_w, float* dX, int32_t* acc, hipStream_t st, const DwTail* tail = nullptr,
                               bool bf16 = false);
+// Both gradients of a small layer in one launch (and a reduction, if the filter gradient is split); false: the layer has no
+// such form, and nothing was launched.
+bool conv_bwd_both_small(const daq_conv_desc& d, const int8_t* qx, const float* s_x, const int8_t* vq, const float* s_chan, float* dW,
+                         int32_t* dW_acc, const int8_t* qg, const float* s_g, const int8_t* qw, const float* s_w, float* dX, int32_t* dX_acc,
+                         void* ws, hipStream_t st, daq_status& rc);
 bool fwd_halo_supported(const daq_conv_desc& d);
 daq_status conv_fwd_halo(const daq_conv_desc& d, const int8_t* qx_nhwc, const int8_t* qw, const float* s_x,
                          const float* s_w, float* Y, int32_t* acc, hipStream_t st);

@@ -29,6 +29,8 @@ struct DwTail {
     int taps_all;          // elements of dW from one (co, ci) to the next: `taps`, or kD * taps where depth tap kd is grid row blockIdx.y
 };
 
+daq_status launch_dw_reduce(const DwTail& t, int depth, hipStream_t st);   // the same as a launch of its own
+
 // Whether the role should replace the reduction launch: one workgroup per entry, each with more than 32 splits.
 inline bool dw_tail_worthwhile(int entries, int splits) { return splits > 32 && entries <= 4096; }
 

@@ -49,3 +49,18 @@ def test_filter_gradient_splits(layer):
 def test_forward_quantization_tiles(layer, schedule):
     """q(W) in all arrangements and both copies of q(X), byte for byte."""
     check_forward(layer, 91, schedule)
+
+
+@pytest.mark.parametrize("layer", [
+    wl.Layer("both_narrow", 2, 16, 9, 10, 20, 3, 3, 1, 1),       # one contraction chunk, at most 32 result channels
+    wl.Layer("both_chunk", 3, 48, 11, 12, 40, 3, 3, 1, 1),       # one chunk, 64-row tiles
+    wl.Layer("both_taps9", 4, 70, 9, 15, 130, 3, 3, 1, 1),       # several chunks
+    wl.Layer("both_split", 24, 33, 14, 13, 65, 3, 3, 1, 1),      # the filter gradient split, its reduction a launch of its own
+    wl.Layer("both_1x1", 3, 100, 9, 9, 150, 1, 1, 1, 0),
+    wl.Layer("both_1x1_chunk", 4, 40, 10, 11, 50, 1, 1, 1, 0),
+    wl.Layer("both_1x1_s2", 3, 40, 13, 12, 90, 1, 1, 2, 0),
+    wl.Layer("both_248", 31, 60, 32, 16, 24, 3, 3, 1, 1),        # 62 tiles of the data gradient
+    wl.Layer("both_past", 62, 60, 32, 32, 24, 3, 3, 1, 1),       # 248: the last one to have room beside it
+], ids=lambda l: l.name)
+def test_both_gradients_of_a_small_layer(layer):
+    on_random_codes(layer, 55)
