@@ -471,6 +471,7 @@ __global__ __launch_bounds__(256) void k_dw_direct(DwArgs p) {
 // Rows past Cout / Cin and unused tap slots compute on valid memory and are never stored.
 // ---------------------------------------------------------------------------------------------
 constexpr int kMaxTapSlots = 56;
+constexpr double kTapLoad = 0.4;   // us a K step of a workgroup takes for each of a wave's byte-aligned operand loads, which bound it
 struct TapTable {
     int64_t off[kMaxTapSlots];   // byte offset of the tap's window start inside an activation channel
     int id[kMaxTapSlots];        // kh*kW + kw, or -1 for an unused slot
@@ -577,24 +578,36 @@ __global__ __launch_bounds__(64 * WAVES) void k_dw_taps(DwArgs p, TapTable tt) {
         }
     };
 
+    // Whole rounds of the ring, then what has been loaded by then.  Every step of a round issues the same loads (past the end the last
+    // step's again, which the caches absorb): with a condition around them the compiler cannot count what is in flight
+    // and waits for everything in every step, the latency of memory.  (With the split count below: 3 -> 96 7 x 7 stride 2 at 15 x 15,
+    // batch 7, 48.8 -> 11.2 us; 32 -> 384 5 x 5 at 29 x 32 97 -> 25; 176 -> 128 5 x 5 at 27 x 31, batch 28, 386 -> 118.)
+    auto multiply = [&](int u) {
 #pragma unroll
-    for (int i = 0; i < PFD; ++i)
-        if (s_begin + i < s_end) load_step(s_begin + i, i);
-
-    for (int base = s_begin; base < s_end; base += PFD) {
+        for (int t = 0; t < NT; ++t)
 #pragma unroll
-        for (int u = 0; u < PFD; ++u) {
-            const int s = base + u;
-            if (s < s_end) {
+            for (int m = 0; m < 4; ++m)
+                acc[m][t] = __builtin_amdgcn_mfma_i32_16x16x64_i8(ra[u][m], rb[u][t], acc[m][t], 0, 0, 0);
+    };
+    if (s_begin < s_end) {
 #pragma unroll
-                for (int t = 0; t < NT; ++t)
-#pragma unroll
-                    for (int m = 0; m < 4; ++m)
-                        acc[m][t] = __builtin_amdgcn_mfma_i32_16x16x64_i8(ra[u][m], rb[u][t], acc[m][t], 0, 0, 0);
-                if (s + PFD < s_end) load_step(s + PFD, u);
-            }
+        for (int i = 0; i < PFD; ++i) {
+            load_step(min(s_begin + i, s_end - 1), i);
+            __builtin_amdgcn_sched_barrier(0);   // keep the steps in program order
         }
     }
+    int base = s_begin;
+    for (; base + PFD < s_end; base += PFD) {
+#pragma unroll
+        for (int u = 0; u < PFD; ++u) {
+            multiply(u);
+            load_step(min(base + u + PFD, s_end - 1), u);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    }
+#pragma unroll
+    for (int u = 0; u < PFD; ++u)
+        if (base + u < s_end) multiply(u);   // uniform per wave
 
     const float sx = *p.s_x / 127.0f;
     const int T = tt.T;
@@ -751,23 +764,27 @@ Plan make_general_plan(const daq_conv_desc& d) {
     const bool rowmode = T > 9 && d.Cin * d.kW <= 32 && d.kH <= 8 && d.kW <= 8;
     if (rowmode) { pl.row_kw = d.kW; pl.tw = 2; pl.nb = 2; pl.wtaps = true; pl.pf = 3; }   // taps = kh, two per wave
     else if (T == 1) { pl.tw = 1; pl.nb = 4; pl.wtaps = false; pl.pf = 4; }
-    else if (T <= 9) { pl.tw = 9; pl.nb = 1; pl.wtaps = false; pl.pf = 3; }
+    else if (T <= 9) { pl.tw = T <= 3 ? 3 : T <= 5 ? 5 : T <= 7 ? 7 : 9; pl.nb = 1; pl.wtaps = false; pl.pf = 3; }
     else { pl.tw = 7; pl.nb = 1; pl.wtaps = true; pl.pf = 2; }   // 4 waves up to 28 taps, 8 waves beyond
     pl.wgk = pl.wtaps ? 1 : 4;
     pl.tiles_m = (int)ceil_div(d.Cout, kBM);
     pl.tiles_n = pl.row_kw ? 1 : (int)ceil_div(d.Cin, 16 * pl.nb);
     const int64_t tiles = (int64_t)pl.tiles_m * pl.tiles_n;
     const int64_t nsteps = (int64_t)pl.nchunks * (kKC / 64);
-    int64_t s = ceil_div(512, tiles);
-    const int64_t max_by_steps = std::max<int64_t>(1, nsteps / (pl.wtaps ? 2 : 8));   // at least two steps per wave
-    if (s > max_by_steps) s = max_by_steps;
-    // partial tiles are written and read once: keep that below ~2x the operand bytes
-    const int64_t operand = (int64_t)d.Cout * Lg.plane_pitch + (int64_t)d.Cin * Lg.plane_pitch * d.strideH * d.strideW;
     const int64_t Tp = pl.row_kw ? d.kH : T;   // tap slots of the partial layout
-    const int64_t tile_bytes = tiles * kBM * 16 * pl.nb * Tp * 4;
-    const int64_t max_by_traffic = std::max<int64_t>(1, operand / tile_bytes);
-    if (s > max_by_traffic) s = max_by_traffic;
-    pl.splits = (int)std::max<int64_t>(1, s);
+    // K splits: the number that minimises
+    //     rounds over the CUs * (steps of a wave * t_step + t_fixed) + (reduction and its launch, if any)
+    // with partial tiles on their way at 3 TB/s.  A CU is as fast with one workgroup as with two (its byte-aligned loads bound it:
+    // 3 -> 64 7 x 7 stride 2 at 112 x 112, batch 64, 16 steps in 32 us).  (Bounded by the bytes of the operands instead, as
+    // before, a tiny stem ran in two workgroups.)
+    const double tile_bytes = (double)(kBM * 16 * pl.nb * Tp * 4);
+    double best = 0.0;
+    pl.splits = 1;
+    for (int64_t s = 1; s <= std::max<int64_t>(1, nsteps / (pl.wtaps ? 2 : 8)) && (s == 1 || tiles * s <= 1024); ++s) {   // two steps a wave
+        const double steps = (double)ceil_div(nsteps, pl.wtaps ? s : 4 * s);
+        const double us = (double)ceil_div(tiles * s, 256) * (steps * kTapLoad * pl.tw * pl.nb + 4.0) + (s > 1 ? 5.0 + 2.0 * (double)tiles * (double)s * tile_bytes / 3e6 : 0.0);
+        if (s == 1 || us < best) { best = us; pl.splits = (int)s; }
+    }
     pl.lds_bytes = pl.wtaps ? 256 : (size_t)12 * pl.nb * pl.tw * 4 * kWave * 4;
     if (pl.lds_bytes > 160 * 1024) return pl;
     pl.part_slots = tiles * 16 * pl.nb * Tp * kWave;
@@ -942,7 +959,10 @@ daq_status conv_bwd_filter_mfma(const daq_conv_desc& d, const int8_t* qx, const 
         const TapTable tt = make_tap_table(d, Lx, pl);
         if (pl.row_kw) rc = launch_dw_taps<2, 2, 3, true, 4>(pl, a, tt, st);
         else if (pl.tw == 1) rc = launch_dw_taps<1, 4, 4, false, 4>(pl, a, tt, st);
-        else if (pl.tw == 9) rc = launch_dw_taps<9, 1, 3, false, 4>(pl, a, tt, st);
+        else if (T <= 3) rc = launch_dw_taps<3, 1, 3, false, 4>(pl, a, tt, st);
+        else if (T <= 5) rc = launch_dw_taps<5, 1, 3, false, 4>(pl, a, tt, st);
+        else if (T <= 7) rc = launch_dw_taps<7, 1, 3, false, 4>(pl, a, tt, st);
+        else if (T <= 9) rc = launch_dw_taps<9, 1, 3, false, 4>(pl, a, tt, st);
         else if (T <= 28) rc = launch_dw_taps<7, 1, 2, true, 4>(pl, a, tt, st);
         else rc = launch_dw_taps<7, 1, 2, true, 8>(pl, a, tt, st);
     } else {

@@ -64,3 +64,11 @@ def test_forward_quantization_tiles(layer, schedule):
 ], ids=lambda l: l.name)
 def test_both_gradients_of_a_small_layer(layer):
     on_random_codes(layer, 55)
+
+
+@pytest.mark.parametrize("kH,kW,pad,stride", [(1, 2, 0, 1), (2, 2, 1, 1), (5, 1, 0, 1), (2, 3, 1, 2), (7, 1, 2, 1), (2, 4, 1, 1), (2, 5, 0, 1), (4, 7, 2, 1),
+                                              (5, 6, 2, 1), (7, 7, 3, 2)])
+@pytest.mark.parametrize("batch", [1, 5, 13])
+def test_filter_gradient_of_any_extent(kH, kW, pad, stride, batch):
+    """Tap counts at both sides of the kernel's forms; K steps from fewer than the load ring holds to several rounds of it."""
+    on_random_codes(wl.Layer("taps", batch, 3 if kH == 7 and kW == 7 else 20, 12, 11, 70, kH, kW, stride, pad), 60 + batch)
