@@ -351,7 +351,7 @@ __global__ __launch_bounds__(kBlock) void k_dwise_dx_any(DxArgs p) {
 // Workgroup (c, slab) sweeps its part of the axis 4096 bytes at a time: a thread takes 16 aligned
 // bytes of G and, for every tap, the 16 activation bytes at the tap's offset (byte aligned; the nine
 // windows of a 3 x 3 filter overlap almost entirely, so they come from the same cache lines).
-// Partial sums go to [c][slab][t]; k_dwise_dw_reduce adds the slabs and de-quantizes.
+// Partial sums go to [c][slab][t]; k_dwise_dw_reduce adds the slabs and de-quantizes.  One slab writes the result itself.
 // ---------------------------------------------------------------------------------------------
 constexpr int kDwTaps = 9;
 struct DwiseDwArgs {
@@ -362,6 +362,11 @@ struct DwiseDwArgs {
     int64_t off[kDwTaps];  // unused slots repeat slot 0 (computed, never stored)
     int T, C, slabs;
     int32_t* part;         // [C][slabs][kDwTaps]
+    const float* s_x;      // these five with one slab, whose workgroup writes the result itself
+    const float* s_chan;
+    float* dW;
+    int32_t* acc_out;
+    int bf16;
 };
 
 // ROWS3 >= 0: 3 x 3 filter at unit stride and dilation with row_pitch mod 4 == ROWS3 - the three windows of a filter
@@ -435,8 +440,15 @@ __global__ __launch_bounds__(kBlock) void k_dwise_dw(DwiseDwArgs p) {
         if (tid % kWave == 0) l_red[tid / kWave][t] = v;
     }
     __syncthreads();
-    if (tid < kDwTaps)
-        p.part[((int64_t)c * p.slabs + slab) * kDwTaps + tid] = l_red[0][tid] + l_red[1][tid] + l_red[2][tid] + l_red[3][tid];
+    if (tid >= kDwTaps) return;
+    const int sum = l_red[0][tid] + l_red[1][tid] + l_red[2][tid] + l_red[3][tid];
+    if (p.slabs > 1) {
+        p.part[((int64_t)c * p.slabs + slab) * kDwTaps + tid] = sum;
+    } else if (tid < p.T) {   // the whole channel: no reduction launch
+        const int i = c * p.T + tid;
+        store_result(p.dW, i, (float)sum * ((*p.s_x / 127.0f) * (p.s_chan[c] / 127.0f)), p.bf16);
+        if (p.acc_out) p.acc_out[i] = sum;
+    }
 }
 
 // One wave per filter element: its lanes take the slabs (independent loads, all in flight), then a shuffle tree.
@@ -464,6 +476,10 @@ int log2_exact(int v) {
 
 int dw_slabs(const daq_conv_desc& d, int64_t klen) {
     const int64_t iters = ceil_div(klen, kDwSlabBytes);
+    // A launch for the sums costs more than four iterations (192 channels, 3 x 3 at 22 x 22, batch 29, backward 35 -> 27 us, the
+    // launch that folded the channel maxima of the global copy saved as well).  A register ring for the next iteration's
+    // loads was no gain: 96 channels, stride 2 at 112 x 112, batch 128, 62 -> 66 us, fewer waves resident.
+    if (iters <= 4) return 1;
     int64_t s = ceil_div(2048, d.Cout);
     if (s > iters) s = iters;
     if (s > 256) s = 256;
@@ -677,6 +693,7 @@ daq_status conv_bwd_filter_depthwise(const daq_conv_desc& d, const int8_t* qx, c
     a.C = d.Cout;
     a.slabs = dw_slabs(d, Lg.plane_pitch);
     a.part = reinterpret_cast<int32_t*>(reinterpret_cast<char*>(ws) + 256);
+    a.s_x = s_x; a.s_chan = s_chan; a.dW = dW; a.acc_out = acc; a.bf16 = bf16 ? 1 : 0;
     // window start of every tap inside an activation channel (stride-phase plane + shift), as in the dense kernel
     for (int t = 0; t < kDwTaps; ++t) a.off[t] = 0;
     for (int kh = 0; kh < d.kH; ++kh)
@@ -694,6 +711,7 @@ daq_status conv_bwd_filter_depthwise(const daq_conv_desc& d, const int8_t* qx, c
     else if (q4 == 2) DAQ_LAUNCH("conv_bwd_filter_depthwise", st, hipLaunchKernelGGL(k_dwise_dw<2>, grid, dim3(kBlock), 0, st, a));
     else if (q4 == 3) DAQ_LAUNCH("conv_bwd_filter_depthwise", st, hipLaunchKernelGGL(k_dwise_dw<3>, grid, dim3(kBlock), 0, st, a));
     else DAQ_LAUNCH("conv_bwd_filter_depthwise", st, hipLaunchKernelGGL(k_dwise_dw<-1>, grid, dim3(kBlock), 0, st, a));
+    if (a.slabs == 1) return DAQ_OK;
     DAQ_LAUNCH("dw_reduce", st,
                hipLaunchKernelGGL(k_dwise_dw_reduce, dim3((unsigned)ceil_div(d.Cout * a.T, kBlock / kWave)), dim3(kBlock), 0, st,
                                   a.part, d.Cout, a.slabs, a.T, s_x, s_chan, dW, acc, bf16 ? 1 : 0));

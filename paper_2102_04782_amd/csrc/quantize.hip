@@ -787,11 +787,24 @@ __device__ __forceinline__ float fold_scale(const float* __restrict__ part, int 
     return fmaxf(fmaxf(l[0], l[1]), fmaxf(l[2], l[3]));
 }
 
+// The scale of a per-tensor copy: a value, or the maximum of part_n partials, which `first` (one workgroup) publishes.
+__device__ __forceinline__ float given_scale(const float* __restrict__ scale, int part_n, float* publish, float* publish_raw, bool first, float* l) {
+    if (!part_n) return scale[0];
+    const float s = fold_scale(scale, part_n, l);
+    if (publish && first && threadIdx.x == 0) {
+        *publish = s >= kTinyScale ? s : 0.0f;
+        *publish_raw = s;
+    }
+    return s;
+}
+
 struct PackArgs {
     FastDiv div_slot, div_pitch;
     int per_chan;          // workgroups per (channel, phase) plane
     int lead_imgs;         // whole images that cover the leading zeros
     int part_n;            // > 0: the scale is the maximum of that many partials behind the scale pointer (ignored with CLIP)
+    float* publish;        // where the first workgroup leaves that scale (two floats: as reported, as found), or null
+    float* publish_raw;
     uint32_t tensor;       // random stream id
     uint64_t seed;
 };
@@ -860,7 +873,7 @@ __device__ __forceinline__ void pack_cnhw_role(const int b, const int phase, con
 
     float s;
     if (CLIP) s = clip_value(ws, ca, c, (double)L.N * (double)L.H * (double)L.W, jb == 0 && phase == 0, l_cnt);
-    else s = pa.part_n ? fold_scale(scale, pa.part_n, reinterpret_cast<float*>(l_cnt)) : scale[0];
+    else s = given_scale(scale, pa.part_n, pa.publish, pa.publish_raw, c == 0 && jb == 0 && phase == 0, reinterpret_cast<float*>(l_cnt));
     const float inv = inv_scale(s);
 
     // Padding positions were read as 0.0f and quantize to code 0 in either rounding mode
@@ -897,7 +910,9 @@ struct RowsArgs {
     FastDiv div_hwv, div_wv, div_prb;
     int per_chan;          // blocks of 1024 element groups per channel
     int grid_per_chan;     // data workgroups per channel (one more zeroes the padding); fewer than per_chan: they loop
-    int part_n;            // as in PackArgs
+    int part_n;            // this and the next two as in PackArgs
+    float* publish;
+    float* publish_raw;
     int early;             // the counting pass has written the real elements of channels whose class it guessed
     uint32_t tensor;
     uint64_t seed;
@@ -1017,7 +1032,8 @@ __device__ __forceinline__ void pack_rows_role(const int b, const T* __restrict_
     }
 
     // a given scale is folded while the loads are in flight (without `early` there is one pass)
-    if constexpr (!CLIP) inv = inv_scale(pa.part_n ? fold_scale(scale, pa.part_n, reinterpret_cast<float*>(l_cnt)) : scale[0]);
+    if constexpr (!CLIP)
+        inv = inv_scale(given_scale(scale, pa.part_n, pa.publish, pa.publish_raw, c == 0 && jb == 0, reinterpret_cast<float*>(l_cnt)));
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
         uint32_t bits[4] = {0u, 0u, 0u, 0u};
@@ -1342,21 +1358,6 @@ __global__ __launch_bounds__(kBlock) void k_absmax(AbsmaxArgs a) {
     if (threadIdx.x == 0) (second ? a.part[1] : a.part[0])[b] = fmaxf(fmaxf(l_m[0], l_m[1]), fmaxf(l_m[2], l_m[3]));
 }
 
-// Scale of the per-tensor copy from the per-channel maxima of the channel-resident pass (one workgroup).
-__global__ __launch_bounds__(kBlock) void k_fold_max(QuantWs ws, int C, float* __restrict__ s_global) {
-    __shared__ float l_m[kBlock / kWave];
-    float m = 0.0f;
-    for (int i = threadIdx.x; i < C; i += kBlock) m = fmaxf(m, ws.part_max[i]);
-    m = wave_max(m);
-    if (threadIdx.x % kWave == 0) l_m[threadIdx.x / kWave] = m;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        m = fmaxf(fmaxf(l_m[0], l_m[1]), fmaxf(l_m[2], l_m[3]));
-        ws.layer[0] = m;
-        *s_global = (m >= kTinyScale) ? m : 0.0f;
-    }
-}
-
 // q(W) in its arrangements (see daq_wpack_layout), every byte of the buffer written once, zeros included.
 struct PackWArgs {
     const float* w;
@@ -1370,11 +1371,12 @@ struct PackWArgs {
     FastDiv div_run, div_tap, div_runl, div_tapl;   // (32 * taps of a chunk, taps of a chunk), the last chunk's own
     daq_wpack_layout L;
 };
-constexpr int kWTaps = 9;                   // taps a workgroup takes at once
+constexpr int kWTaps = 3;                   // taps a workgroup takes at once: twelve weights a thread
 constexpr int kWPlane = 32 * 32 + 16;       // bytes of a tap's 32 x 32 codes in LDS; the 16 spread the taps over the banks
 
-// One group: a workgroup takes 32 x 32 channels (the tile of the fragment order) x up to nine taps.  Its weights are
-// runs of 32 * taps consecutive floats, all loads in flight at once; the codes go to LDS in both orders, [co][ci] and
+// One group: a workgroup takes 32 x 32 channels (the tile of the fragment order) x up to three taps, twelve weights a thread,
+// all loads in flight at once (nine taps, whose weights are contiguous, made each thread's work a chain of 36: 3 x 3, 128 ->
+// 128 at 28 x 28, batch 8, forward 26.7 us against 17.7); the codes go to LDS in both orders, [co][ci] and
 // [ci][co], and leave as 16-byte units: whole KiB of the two fragment copies, 32-byte runs of the other two.  (Scattering
 // each code to five places in byte stores behind a fill of the buffer: 3 x 3, 272 -> 912, fill 12.6 and packing 24.7 us.)
 template <int NT>
@@ -1592,13 +1594,16 @@ template <typename T>
 daq_status launch_pack(const char* name, bool stoch, bool clip, const T* src, const daq_layout& Ld,
                        const float* scale, int8_t* dst, uint32_t tensor, uint64_t seed,
                        const QuantWs& ws, const ClipArgs& ca, hipStream_t st, int8_t* dst2 = nullptr,
-                       const float* scale2 = nullptr, uint32_t tensor2 = 0, bool* fused = nullptr, bool early = false) {
+                       const float* scale2 = nullptr, uint32_t tensor2 = 0, bool* fused = nullptr, bool early = false, int part_n = 0,
+                       float* publish = nullptr) {
     if (fused) *fused = false;
     const CnhwView V = cnhw_view(Ld);
     const int v = rows_vector(Ld, src, (int)sizeof(T));
     if (early && !v) return DAQ_ERR_INVALID_ARG;   // the caller checks rows_vector before it asks for the early copy
     if (v) {
-        RowsArgs ra = rows_args(Ld, v, early, 0, tensor, seed);
+        RowsArgs ra = rows_args(Ld, v, early, part_n, tensor, seed);
+        ra.publish = publish;
+        ra.publish_raw = ws.layer;
         ra.dst2 = dst2;
         ra.scale2 = scale2;
         ra.tensor2 = tensor2;
@@ -1617,7 +1622,9 @@ daq_status launch_pack(const char* name, bool stoch, bool clip, const T* src, co
         return DAQ_OK;
     }
     if (!pack_supported(Ld)) return DAQ_ERR_UNSUPPORTED;
-    const PackArgs pa = pack_args(Ld, 0, tensor, seed);
+    PackArgs pa = pack_args(Ld, part_n, tensor, seed);
+    pa.publish = publish;
+    pa.publish_raw = ws.layer;
     const dim3 grid = pack_grid(Ld);
 #define DAQ_PACK(S, CL) \
     DAQ_LAUNCH(name, st, hipLaunchKernelGGL((k_pack_cnhw<T, S, CL>), grid, dim3(kBlock), 0, st, src, V, scale, dst, pa, ws, ca))
@@ -1861,9 +1868,9 @@ daq_status quantize_grad_impl(const daq_conv_desc* desc, const T* dY, float* s_s
         // the per-channel copy, its scales, classes and clip state are complete here; the global copy follows on `st`
         if (side && stream_follows(side, st) != DAQ_OK) return DAQ_ERR_HIP;
         if (!qg_nhwc) {
-            // depthwise layers: the per-tensor copy is channel-major too; its scale is folded from the channel maxima first
-            DAQ_LAUNCH("fold_max", st, hipLaunchKernelGGL(k_fold_max, dim3(1), dim3(kBlock), 0, st, ws, C, s_global));
-            return launch_pack("pack_qg", stoch, false, dY, Lv, s_global, qg, 1u, keys, ws, ClipArgs{}, st);
+            // depthwise layers: the per-tensor copy is channel-major too; its workgroups fold the channel maxima themselves
+            return launch_pack("pack_qg", stoch, false, dY, Lv, ws.part_max, qg, 1u, keys, ws, ClipArgs{}, st, nullptr, nullptr, 0, nullptr, false,
+                               ws.part_n, s_global);
         }
         const dim3 cgrid((unsigned)(CB * ws.cgroups));
 #define DAQ_COPY_LAUNCH(S)                                                                                           \
