@@ -118,10 +118,8 @@ inline uint64_t round_keys(uint64_t seed) {
     const uint32_t lo = (uint32_t)seed, hi = (uint32_t)(seed >> 32);
     return (uint64_t)fmix32(lo ^ fmix32(hi ^ 0x9E3779B9u));
 }
-__device__ __forceinline__ uint32_t rng_u(uint64_t keys, uint32_t tensor, uint32_t idx) {
-    const uint32_t h = fmix32(idx ^ (uint32_t)keys);
-    return tensor == 0u ? h >> 16 : h & 0xFFFFu;
-}
+__device__ __forceinline__ uint32_t draw_half(uint32_t h, uint32_t tensor) { return tensor == 0u ? h >> 16 : h & 0xFFFFu; }
+__device__ __forceinline__ uint32_t rng_u(uint64_t keys, uint32_t tensor, uint32_t idx) { return draw_half(fmix32(idx ^ (uint32_t)keys), tensor); }
 
 // 127/s, or 0 when the scale is treated as zero (then every code is 0).
 __device__ __forceinline__ float inv_scale(float s) { return (s >= kTinyScale) ? 127.0f / s : 0.0f; }
@@ -1031,6 +1029,16 @@ __device__ __forceinline__ void pack_rows_role(const int b, const T* __restrict_
         }
     }
 
+    uint32_t hash[4][V];   // of the elements: the two copies draw from its two halves
+    if constexpr (STOCH) {
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+#pragma unroll
+            for (int i = 0; i < V; ++i) {
+                hash[u][i] = fmix32((eoff[u] / EB + i) ^ (uint32_t)pa.seed);
+                asm volatile("" : "+v"(hash[u][i]));   // computed once, not once a copy
+            }
+    }
     // a given scale is folded while the loads are in flight (without `early` there is one pass)
     if constexpr (!CLIP)
         inv = inv_scale(given_scale(scale, pa.part_n, pa.publish, pa.publish_raw, c == 0 && jb == 0, reinterpret_cast<float*>(l_cnt)));
@@ -1038,7 +1046,7 @@ __device__ __forceinline__ void pack_rows_role(const int b, const T* __restrict_
     for (int u = 0; u < 4; ++u) {
         uint32_t bits[4] = {0u, 0u, 0u, 0u};
 #pragma unroll
-        for (int i = 0; i < V; ++i) bits[i] = quant_bits<STOCH>(x[u][i], inv, STOCH ? rng_u(pa.seed, pa.tensor, eoff[u] / EB + i) : 0u);
+        for (int i = 0; i < V; ++i) bits[i] = quant_bits<STOCH>(x[u][i], inv, STOCH ? draw_half(hash[u][i], pa.tensor) : 0u);
         if (live[u]) store_codes<V>(plane + doff[u], pack4(bits[0], bits[1], bits[2], bits[3]));
         if (row_end[u])
             for (int k = 0; k < padw; ++k) plane[doff[u] + V + k] = 0;
@@ -1049,7 +1057,7 @@ __device__ __forceinline__ void pack_rows_role(const int b, const T* __restrict_
         for (int u = 0; u < 4; ++u) {
             uint32_t bits[4] = {0u, 0u, 0u, 0u};
 #pragma unroll
-            for (int i = 0; i < V; ++i) bits[i] = quant_bits<STOCH>(x[u][i], inv2, STOCH ? rng_u(pa.seed, pa.tensor2, eoff[u] / EB + i) : 0u);
+            for (int i = 0; i < V; ++i) bits[i] = quant_bits<STOCH>(x[u][i], inv2, STOCH ? draw_half(hash[u][i], pa.tensor2) : 0u);
             if (live[u]) store_codes<V>(plane2 + doff[u], pack4(bits[0], bits[1], bits[2], bits[3]));
             if (row_end[u])
                 for (int k = 0; k < padw; ++k) plane2[doff[u] + V + k] = 0;
