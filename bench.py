@@ -97,6 +97,8 @@ def kernel_work(layer, d, name: str, dy_bytes: float, dx_bytes: float, qg_nhwc: 
         return E_Y + E_W + dx_bytes * E_X, ops
     if name.startswith("conv_bwd_filter"):
         return E_X + E_Y + 4.0 * E_W, ops
+    if name == "conv_bwd_both":
+        return 2.0 * E_Y + E_W + (dx_bytes + 1.0) * E_X + 4.0 * E_W, 2.0 * ops
     return 0.0, 0.0
 
 
@@ -585,7 +587,7 @@ def sweep(args, dev) -> int:
             seen[key] = (wall_us,
                          sum(v for k, v in t.items() if k in QUANT_KERNELS),
                          sum(v for k, v in t.items() if k.startswith("conv_bwd_filter") or k == "dw_reduce"),
-                         sum(v for k, v in t.items() if k.startswith("conv_bwd_data")))
+                         sum(v for k, v in t.items() if k.startswith("conv_bwd_data") or k == "conv_bwd_both"))
             del s
         wall_us, q_us, dw_us, dx_us = seen[key]
         tot_wall += wall_us
