@@ -536,7 +536,16 @@ Dw3Plan dw3_plan(const daq_conv3d_desc& d) {
     if (p.Lg.bytes >= lim || p.Lx.bytes * g.sD >= lim || !bwd_filter_lds_supported(p.frames, g.kD)) return p;
     p.off_g = 256 + (int64_t)bwd_filter_lds_ws_bytes(p.frames, g.kD);
     p.off_x = p.off_g + round_up(p.Lg.bytes, 256);
-    p.bytes = p.off_x + round_up(p.Lx.bytes * g.sD, 256);
+    // The kernel walks every row as far as the gradient's chunks reach, for a depth tap from a frame further on, and the copy's
+    // own rounding to chunks need not cover that: behind the last row of the last phase it may read bytes of no copy (they meet
+    // zeros of the gradient), which have to be the workspace's.
+    int64_t end = p.Lx.bytes * g.sD;
+    const int64_t frame = (int64_t)p.Lx.img_rows * p.Lx.row_pitch, row = p.Lx.bytes - p.Lx.plane_pitch + bwd_filter_lds_row_bytes(p.frames, g.kD);
+    for (int kd = 0; kd < g.kD; ++kd) {
+        const int64_t at = (int64_t)kd * g.dD;
+        end = std::max(end, at % g.sD * p.Lx.bytes + at / g.sD * frame + row);
+    }
+    p.bytes = p.off_x + round_up(end, 256);
     p.depth = DwDepth{g.kD, g.dD, g.sD, p.Lx.chan_pitch, p.Lx.plane_pitch, p.Lx.bytes};
     p.ok = true;
     return p;

@@ -272,6 +272,11 @@ size_t bwd_filter_lds_ws_bytes(const daq_conv_desc& d, int depth) {
     return (size_t)round_up(pl.part_slots * pl.splits * depth * 4, 256);
 }
 
+int64_t bwd_filter_lds_row_bytes(const daq_conv_desc& d, int depth) {
+    const Plan32 pl = make_plan32(d, depth);
+    return (int64_t)(pl.nchunks - 1) * kKC + (pl.k11 ? kKC : 16 * pl.b_units);
+}
+
 daq_status conv_bwd_filter_lds(const daq_conv_desc& d, const int8_t* qx, const float* s_x, const int8_t* vq,
                                const float* s_chan, float* dW, int32_t* acc, void* ws, hipStream_t st, DwTail* defer, bool bf16, const DwDepth* dp) {
     if (defer) defer->blocks = 0;

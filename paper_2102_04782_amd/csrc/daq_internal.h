@@ -182,6 +182,7 @@ struct DwDepth {
 };
 bool bwd_filter_lds_supported(const daq_conv_desc& d, int depth = 1);
 size_t bwd_filter_lds_ws_bytes(const daq_conv_desc& d, int depth = 1);
+int64_t bwd_filter_lds_row_bytes(const daq_conv_desc& d, int depth = 1);   // read of an activation row, from its start on (a supported layer's)
 // With `defer`, a K-split launch leaves its last stage (sum of the partial tiles, de-quantization) undone and
 // describes it in *defer (blocks == 0: nothing is left) for a later kernel's extra workgroups, see dw_tail.h.
 struct DwTail;

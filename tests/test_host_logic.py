@@ -3,6 +3,8 @@ logic (layouts, workspace sizes, argument validation) behaves.  No kernel is lau
 import ctypes as C
 import os
 import re
+import shutil
+import subprocess
 
 import numpy as np
 import pytest
@@ -187,6 +189,19 @@ def test_workspace_and_validation_without_a_gpu():
     assert b16(dY=None) == daq.ERR_INVALID_ARG and b16(dY=odd) == daq.ERR_INVALID_ARG and b16(scheme=9) == daq.ERR_INVALID_ARG
     assert b16(wsb=8) == daq.ERR_WORKSPACE
     assert daq.status_string(daq.ERR_WORKSPACE).startswith("workspace")
+
+
+@pytest.mark.skipif(shutil.which("hipcc") is None, reason="no hipcc")
+def test_frame_copies_of_3d_layers_stay_inside_the_workspace(tmp_path):
+    exe = str(tmp_path / "frame_copies")
+    pkg = os.path.join(ROOT, "paper_2102_04782_amd")
+    cmd = ["hipcc", "--offload-arch=gfx950", "-O1", "-std=c++17", "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops", "-Wno-unused-function",
+           "-Wno-pass-failed", "-I", os.path.join(ROOT, "include"), "-I", os.path.join(pkg, "csrc"), os.path.join(ROOT, "tests", "host", "frame_copies.hip"),
+           "-o", exe, "-L" + pkg, "-ldaq", "-Wl,-rpath," + pkg]
+    res = subprocess.run(cmd, capture_output=True, text=True, timeout=600)
+    assert res.returncode == 0, res.stderr[-4000:]
+    run = subprocess.run([exe], capture_output=True, text=True, timeout=600)
+    assert run.returncode == 0, run.stdout + run.stderr
 
 
 def test_workload_tables():
