@@ -63,12 +63,12 @@ extern "C" daq_status daq_conv_bwd_filter_int8(const daq_conv_desc* desc, const 
                                                void* workspace, size_t workspace_bytes, void* stream) {
     if (!desc_valid(desc) || !qx_cnhw || !s_x || !vq || !s_chan || !dW) return DAQ_ERR_INVALID_ARG;
     if (!a16(qx_cnhw) || !a16(vq) || !a4(dW) || !a4(acc_out)) return DAQ_ERR_INVALID_ARG;
-    const size_t need = daq_workspace_bytes(DAQ_OP_CONV_BWD_FILTER, desc);
-    if (need == 0) return DAQ_ERR_UNSUPPORTED;
-    if (!ws_ok(workspace, workspace_bytes, need)) return DAQ_ERR_WORKSPACE;
+    if (!plannable(desc)) return DAQ_ERR_UNSUPPORTED;
+    const Plan32 pl = make_plan32(*desc);
+    if (!ws_ok(workspace, workspace_bytes, bwd_filter_ws_bytes(*desc, pl))) return DAQ_ERR_WORKSPACE;
     hipStream_t st = (hipStream_t)stream;
-    if (bwd_filter_lds_supported(*desc))
-        return conv_bwd_filter_lds(*desc, qx_cnhw, s_x, vq, s_chan, dW, acc_out, workspace, st);
+    if (pl.ok)
+        return conv_bwd_filter_lds(*desc, pl, qx_cnhw, s_x, vq, s_chan, dW, acc_out, workspace, st);
     if (bwd_filter_mfma_supported(*desc))
         return conv_bwd_filter_mfma(*desc, qx_cnhw, s_x, vq, s_chan, dW, acc_out, workspace, st);
     if (depthwise_dw_supported(*desc))
@@ -85,18 +85,18 @@ extern "C" daq_status daq_conv_bwd_int8(const daq_conv_desc* desc, const int8_t*
         return DAQ_ERR_INVALID_ARG;
     if (!a16(qx_cnhw) || !a16(vq) || !a4(dW) || !a4(dW_acc) || !a16(qg) || !a16(qw_packed) || !a16(dX) || !a16(dX_acc))
         return DAQ_ERR_INVALID_ARG;
-    const size_t need_f = daq_workspace_bytes(DAQ_OP_CONV_BWD_FILTER, desc);
-    const size_t need_d = daq_workspace_bytes(DAQ_OP_CONV_BWD_DATA, desc);
-    if (need_f == 0 || need_d == 0) return DAQ_ERR_UNSUPPORTED;
+    if (!plannable(desc)) return DAQ_ERR_UNSUPPORTED;
+    const Plan32 pl = make_plan32(*desc);
+    const size_t need_f = bwd_filter_ws_bytes(*desc, pl), need_d = daq_workspace_bytes(DAQ_OP_CONV_BWD_DATA, desc);
     if (!ws_ok(workspace, workspace_bytes, need_f + need_d)) return DAQ_ERR_WORKSPACE;
     void* ws_d = static_cast<char*>(workspace) + need_f;   // need_f is a multiple of 256
-    if (bwd_filter_lds_supported(*desc) && bwd_data_halo_supported(*desc)) {
+    if (pl.ok && bwd_data_halo_supported(*desc)) {
         hipStream_t st = (hipStream_t)stream;
         daq_status both;
-        if (conv_bwd_both_small(*desc, qx_cnhw, s_x, vq, s_chan, dW, dW_acc, qg, s_global, qw_packed, s_w, dX, dX_acc, workspace, st, both))
+        if (conv_bwd_both_small(*desc, pl, qx_cnhw, s_x, vq, s_chan, dW, dW_acc, qg, s_global, qw_packed, s_w, dX, dX_acc, workspace, st, both))
             return both;
         DwTail tail{};
-        const daq_status rc = conv_bwd_filter_lds(*desc, qx_cnhw, s_x, vq, s_chan, dW, dW_acc, workspace, st, &tail);
+        const daq_status rc = conv_bwd_filter_lds(*desc, pl, qx_cnhw, s_x, vq, s_chan, dW, dW_acc, workspace, st, &tail);
         if (rc != DAQ_OK) return rc;
         return conv_bwd_data_halo(*desc, qg, s_global, qw_packed, s_w, dX, dX_acc, st, tail.blocks > 0 ? &tail : nullptr);
     }
@@ -129,13 +129,13 @@ extern "C" daq_status daq_conv_bwd_filter_int8_bf16(const daq_conv_desc* desc, c
                                                     void* workspace, size_t workspace_bytes, void* stream) {
     if (!desc_valid(desc) || !qx_cnhw || !s_x || !vq || !s_chan || !dW_bf16) return DAQ_ERR_INVALID_ARG;
     if (!a16(qx_cnhw) || !a16(vq) || ((uintptr_t)dW_bf16 & 1u)) return DAQ_ERR_INVALID_ARG;
-    const size_t need = daq_workspace_bytes(DAQ_OP_CONV_BWD_FILTER, desc);
-    if (need == 0) return DAQ_ERR_UNSUPPORTED;
-    if (!ws_ok(workspace, workspace_bytes, need)) return DAQ_ERR_WORKSPACE;
+    if (!plannable(desc)) return DAQ_ERR_UNSUPPORTED;
+    const Plan32 pl = make_plan32(*desc);
+    if (!ws_ok(workspace, workspace_bytes, bwd_filter_ws_bytes(*desc, pl))) return DAQ_ERR_WORKSPACE;
     hipStream_t st = (hipStream_t)stream;
     float* out = reinterpret_cast<float*>(dW_bf16);
-    if (bwd_filter_lds_supported(*desc))
-        return conv_bwd_filter_lds(*desc, qx_cnhw, s_x, vq, s_chan, out, nullptr, workspace, st, nullptr, true);
+    if (pl.ok)
+        return conv_bwd_filter_lds(*desc, pl, qx_cnhw, s_x, vq, s_chan, out, nullptr, workspace, st, nullptr, true);
     if (bwd_filter_mfma_supported(*desc))
         return conv_bwd_filter_mfma(*desc, qx_cnhw, s_x, vq, s_chan, out, nullptr, workspace, st, true);
     if (depthwise_dw_supported(*desc))

@@ -507,6 +507,7 @@ struct Dw3Plan {
     bool ok;
     daq_conv_desc frames;      // every frame slot an image
     daq_layout Lg, Lx;         // of the copies of vq and q(X)
+    Plan32 pl;                 // of the product
     int64_t off_g, off_x, bytes;
     int Dq;
     DwDepth depth;
@@ -533,14 +534,16 @@ Dw3Plan dw3_plan(const daq_conv3d_desc& d) {
     }
     if (p.Lg.row_pitch % 4 || p.Lx.row_pitch % 4) return p;
     const int64_t lim = (int64_t)1 << 31;
-    if (p.Lg.bytes >= lim || p.Lx.bytes * g.sD >= lim || !bwd_filter_lds_supported(p.frames, g.kD)) return p;
-    p.off_g = 256 + (int64_t)bwd_filter_lds_ws_bytes(p.frames, g.kD);
+    if (p.Lg.bytes >= lim || p.Lx.bytes * g.sD >= lim) return p;
+    p.pl = make_plan32(p.frames, g.kD);
+    if (!p.pl.ok) return p;
+    p.off_g = 256 + (int64_t)bwd_filter_lds_ws_bytes(p.pl, g.kD);
     p.off_x = p.off_g + round_up(p.Lg.bytes, 256);
     // The kernel walks every row as far as the gradient's chunks reach, for a depth tap from a frame further on, and the copy's
     // own rounding to chunks need not cover that: behind the last row of the last phase it may read bytes of no copy (they meet
     // zeros of the gradient), which have to be the workspace's.
     int64_t end = p.Lx.bytes * g.sD;
-    const int64_t frame = (int64_t)p.Lx.img_rows * p.Lx.row_pitch, row = p.Lx.bytes - p.Lx.plane_pitch + bwd_filter_lds_row_bytes(p.frames, g.kD);
+    const int64_t frame = (int64_t)p.Lx.img_rows * p.Lx.row_pitch, row = p.Lx.bytes - p.Lx.plane_pitch + bwd_filter_lds_row_bytes(p.pl);
     for (int kd = 0; kd < g.kD; ++kd) {
         const int64_t at = (int64_t)kd * g.dD;
         end = std::max(end, at % g.sD * p.Lx.bytes + at / g.sD * frame + row);
@@ -550,6 +553,8 @@ Dw3Plan dw3_plan(const daq_conv3d_desc& d) {
     p.ok = true;
     return p;
 }
+
+size_t dw3_ws_bytes(const Dw3Plan& p) { return p.ok ? (size_t)p.bytes : 256; }
 
 Relayout relayout_of(const daq_layout& from, const daq_layout& to, const int8_t* src, int8_t* dst, int N, int D, int H, int Dq, int sD, int pD) {
     Relayout r{};
@@ -668,10 +673,7 @@ extern "C" size_t daq_conv3d_workspace_bytes(daq_op op, const daq_conv3d_desc* d
         case DAQ_OP_QUANTIZE_GRAD: return daq_workspace_bytes(DAQ_OP_QUANTIZE_GRAD, &cg);
         case DAQ_OP_CONV_FWD: return daq_workspace_bytes(DAQ_OP_CONV_FWD, &cx) + conv3d_halo_ws_bytes(false, *desc);
         case DAQ_OP_CONV_BWD_DATA: return 256 + conv3d_halo_ws_bytes(true, *desc);
-        case DAQ_OP_CONV_BWD_FILTER: {
-            const Dw3Plan p = dw3_plan(*desc);
-            return p.ok ? (size_t)p.bytes : 256;
-        }
+        case DAQ_OP_CONV_BWD_FILTER: return dw3_ws_bytes(dw3_plan(*desc));
         default: return 0;
     }
 }
@@ -776,18 +778,18 @@ extern "C" daq_status daq_conv3d_bwd_filter_int8(const daq_conv3d_desc* desc, co
     if (kind == 1) return daq_conv_bwd_filter_int8(&cx, qx_cnhw, s_x, vq, s_chan, dW, acc_out, workspace, workspace_bytes, stream);
     if (!qx_cnhw || !s_x || !vq || !s_chan || !dW) return DAQ_ERR_INVALID_ARG;
     if (!a16(qx_cnhw) || !a16(vq) || ((uintptr_t)dW & 3u) || ((uintptr_t)acc_out & 3u)) return DAQ_ERR_INVALID_ARG;
-    if (!ws_ok(workspace, workspace_bytes, daq_conv3d_workspace_bytes(DAQ_OP_CONV_BWD_FILTER, desc))) return DAQ_ERR_WORKSPACE;
+    const Dw3Plan p = dw3_plan(*desc);
+    if (!ws_ok(workspace, workspace_bytes, dw3_ws_bytes(p))) return DAQ_ERR_WORKSPACE;
     daq_layout Lx, Lg;
     if (daq_layout_qx_cnhw(&cx, &Lx) != DAQ_OK || daq_layout_vq(&cg, &Lg) != DAQ_OK) return DAQ_ERR_UNSUPPORTED;
     const Geo3 g = geo3_of(*desc);
     hipStream_t st = (hipStream_t)stream;
-    const Dw3Plan p = dw3_plan(*desc);
     if (p.ok) {
         int8_t* ws = static_cast<int8_t*>(workspace);
         const Relayout rg = relayout_of(Lg, p.Lg, vq, ws + p.off_g, g.N, g.Do, g.Ho, p.Dq, 1, 0);
         const Relayout rx = relayout_of(Lx, p.Lx, qx_cnhw, ws + p.off_x, g.N, g.Din, g.Hin, p.Dq, g.sD, g.pD);
         DAQ_LAUNCH("conv3d_relayout", st, hipLaunchKernelGGL(k3_relayout, dim3((unsigned)(rg.blocks + rx.blocks)), dim3(kBlock), 0, st, rg, rx));
-        return conv_bwd_filter_lds(p.frames, ws + p.off_x, s_x, ws + p.off_g, s_chan, dW, acc_out, workspace, st, nullptr, false, &p.depth);
+        return conv_bwd_filter_lds(p.frames, p.pl, ws + p.off_x, s_x, ws + p.off_g, s_chan, dW, acc_out, workspace, st, nullptr, false, &p.depth);
     }
     if (g.sW == 1 && g.dW == 1 && g.kD <= 3 && g.kH <= 3 && g.kW <= 3 && (int64_t)g.N * g.Do * g.Ho < ((int64_t)1 << 31) &&
         (int64_t)g.Cout * g.cig < ((int64_t)1 << 31)) {

@@ -778,13 +778,8 @@ Plan make_general_plan(const daq_conv_desc& d) {
     // 3 -> 64 7 x 7 stride 2 at 112 x 112, batch 64, 16 steps in 32 us).  (Bounded by the bytes of the operands instead, as
     // before, a tiny stem ran in two workgroups.)
     const double tile_bytes = (double)(kBM * 16 * pl.nb * Tp * 4);
-    double best = 0.0;
-    pl.splits = 1;
-    for (int64_t s = 1; s <= std::max<int64_t>(1, nsteps / (pl.wtaps ? 2 : 8)) && (s == 1 || tiles * s <= 1024); ++s) {   // two steps a wave
-        const double steps = (double)ceil_div(nsteps, pl.wtaps ? s : 4 * s);
-        const double us = (double)ceil_div(tiles * s, 256) * (steps * kTapLoad * pl.tw * pl.nb + 4.0) + (s > 1 ? 5.0 + 2.0 * (double)tiles * (double)s * tile_bytes / 3e6 : 0.0);
-        if (s == 1 || us < best) { best = us; pl.splits = (int)s; }
-    }
+    pl.splits = cheapest_split(SplitModel{ceil_div(nsteps, pl.wtaps ? 1 : 4), tiles, std::min<int64_t>(nsteps / (pl.wtaps ? 2 : 8), 1024 / tiles),   // two steps a wave
+                                          kTapLoad * pl.tw * pl.nb, 4.0, 0.0, 5.0, 2.0 * (double)tiles * tile_bytes / 3e6});
     pl.lds_bytes = pl.wtaps ? 256 : (size_t)12 * pl.nb * pl.tw * 4 * kWave * 4;
     if (pl.lds_bytes > 160 * 1024) return pl;
     pl.part_slots = tiles * 16 * pl.nb * Tp * kWave;

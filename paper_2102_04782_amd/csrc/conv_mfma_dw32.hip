@@ -73,17 +73,6 @@ __global__ __launch_bounds__(64 * WM * WN * WK) void k_dw11(Dw32Args p) {
     dw11_role<WM, WN, WK, PF, CH, DMA>(p, (int)blockIdx.x);
 }
 
-struct Plan32 {
-    bool ok;
-    bool k11;             // 1 x 1 filter: the plain GEMM kernel
-    bool s2;              // 3 x 3 filter at stride 2: four stride-phase planes per input channel
-    int wm, wn, wk, splits, tiles_m, tiles_n, nchunks, pb, b_units, ch;
-    int bands_m, bands_n, band_m, band_n;   // rectangles of the tile grid per K split when there are 1, 2 or 4 splits (else 0)
-    int64_t blocks;       // workgroups of the launch
-    size_t lds_bytes;
-    int64_t part_slots;   // int32 entries of one split's partial tiles
-};
-
 // K splits across workgroups.  A workgroup fills a CU (its combine area, or the four stages of the direct-to-LDS form, is
 // 130 KB of LDS), so a launch of more than 256 runs in rounds, and 264 take as long as 512; a split launch is followed by
 // the reduction, which costs a launch and the partial tiles' way to memory and back.  The split that minimises
@@ -92,14 +81,7 @@ struct Plan32 {
 // a reduction and its launch, partial tiles at 3 TB/s.  (64 -> 64, 3 x 3 x 3 on 8 x 56 x 56: 22 splits were 264 workgroups,
 // 57 us; 21 are 252.  16 -> 16, 3 x 3 on 16 x 16, batch 4: five chunks, one split, no reduction.)
 int choose_splits(int64_t tiles, int nchunks, double t_chunk, double tile_bytes) {
-    double best = 0.0;
-    int best_s = 1;
-    for (int s = 1; s <= nchunks && (s == 1 || tiles * s <= 4 * 256); ++s) {
-        const double rounds = (double)ceil_div(tiles * s, 256);
-        const double t = rounds * ((double)ceil_div(nchunks, s) * t_chunk + 4.0) + (s > 1 ? 5.0 + 2.0 * (double)tiles * s * tile_bytes / 3e6 : 0.0);
-        if (s == 1 || t < best) { best = t; best_s = s; }
-    }
-    return best_s;
+    return cheapest_split(SplitModel{nchunks, tiles, 4 * 256 / tiles, t_chunk, 4.0, 0.0, 5.0, 2.0 * (double)tiles * tile_bytes / 3e6});
 }
 
 // Rectangles per split for 1, 2 or 4 splits (8, 4 or 2 XCDs share a split): the cut of the tile grid that makes an
@@ -121,8 +103,9 @@ void choose_bands(Plan32& pl, int bm, int bn) {
     pl.blocks = (int64_t)kXcd * pl.band_m * pl.band_n;
 }
 
-// depth: depth taps of a 3-D layer (its frames are the images of `d`); the launch has that many times the tiles
-Plan32 make_plan32(const daq_conv_desc& d, int depth = 1) {
+}  // namespace
+
+Plan32 make_plan32(const daq_conv_desc& d, int depth) {
     Plan32 pl{};
     if (d.groups != 1) return pl;
     const bool unit = d.strideH == 1 && d.strideW == 1 && d.dilH == 1 && d.dilW == 1;
@@ -188,6 +171,8 @@ Plan32 make_plan32(const daq_conv_desc& d, int depth = 1) {
     pl.ok = true;
     return pl;
 }
+
+namespace {
 
 Dw32Args fill_args(const Plan32& pl, const daq_conv_desc& d, const daq_layout& Lx, const daq_layout& Lg, const int8_t* qx, const float* s_x,
                    const int8_t* vq, const float* s_chan, float* dW, int32_t* acc, void* ws, bool bf16, const DwDepth* dp) {
@@ -264,24 +249,17 @@ daq_status launch32(const Plan32& pl, const Dw32Args& a, int wq4, hipStream_t st
 
 }  // namespace
 
-bool bwd_filter_lds_supported(const daq_conv_desc& d, int depth) { return make_plan32(d, depth).ok; }
-
-size_t bwd_filter_lds_ws_bytes(const daq_conv_desc& d, int depth) {
-    const Plan32 pl = make_plan32(d, depth);
+size_t bwd_filter_lds_ws_bytes(const Plan32& pl, int depth) {
     if (!pl.ok || pl.splits == 1) return 0;
     return (size_t)round_up(pl.part_slots * pl.splits * depth * 4, 256);
 }
 
-int64_t bwd_filter_lds_row_bytes(const daq_conv_desc& d, int depth) {
-    const Plan32 pl = make_plan32(d, depth);
-    return (int64_t)(pl.nchunks - 1) * kKC + (pl.k11 ? kKC : 16 * pl.b_units);
-}
+int64_t bwd_filter_lds_row_bytes(const Plan32& pl) { return (int64_t)(pl.nchunks - 1) * kKC + (pl.k11 ? kKC : 16 * pl.b_units); }
 
-daq_status conv_bwd_filter_lds(const daq_conv_desc& d, const int8_t* qx, const float* s_x, const int8_t* vq,
+daq_status conv_bwd_filter_lds(const daq_conv_desc& d, const Plan32& pl, const int8_t* qx, const float* s_x, const int8_t* vq,
                                const float* s_chan, float* dW, int32_t* acc, void* ws, hipStream_t st, DwTail* defer, bool bf16, const DwDepth* dp) {
     if (defer) defer->blocks = 0;
     const int depth = dp ? dp->kD : 1;
-    const Plan32 pl = make_plan32(d, depth);
     if (!pl.ok) return DAQ_ERR_UNSUPPORTED;
     daq_layout Lx, Lg;
     if (daq_layout_qx_cnhw(&d, &Lx) != DAQ_OK || daq_layout_vq(&d, &Lg) != DAQ_OK) return DAQ_ERR_INVALID_ARG;
@@ -308,21 +286,15 @@ daq_status conv_bwd_filter_lds(const daq_conv_desc& d, const int8_t* qx, const f
     return finish(pl, tail_of(pl, a, d, depth), defer, depth, st);
 }
 
-bool bwd_filter_beside(const daq_conv_desc& d, const int8_t* qx, const float* s_x, const int8_t* vq, const float* s_chan, float* dW, int32_t* acc,
-                       void* ws, int max_blocks, double other_us, DwBeside& out) {
-    Plan32 pl = make_plan32(d);
+bool bwd_filter_beside(const daq_conv_desc& d, Plan32 pl, const int8_t* qx, const float* s_x, const int8_t* vq, const float* s_chan, float* dW,
+                       int32_t* acc, void* ws, int max_blocks, double other_us, DwBeside& out) {
     daq_layout Lx, Lg;
     if (!pl.ok || pl.wk != 8 || pl.s2 || daq_layout_qx_cnhw(&d, &Lx) != DAQ_OK || daq_layout_vq(&d, &Lg) != DAQ_OK) return false;
     const int64_t tiles = (int64_t)pl.tiles_m * pl.tiles_n;
+    if (tiles > max_blocks) return false;
     const double t_chunk = pl.k11 ? 0.45 : 0.75;
-    double best = 0.0;
-    int best_s = 0;
-    for (int s = 1; s <= pl.splits && tiles * s <= max_blocks; ++s) {   // the workspace holds pl.splits partial tiles
-        const double t = std::max((double)ceil_div(pl.nchunks, s) * t_chunk + 4.0, other_us) + (s > 1 ? 5.0 : 0.0);
-        if (!best_s || t < best) { best = t; best_s = s; }
-    }
-    if (!best_s) return false;
-    pl.splits = best_s;
+    // (the workspace holds pl.splits partial tiles)
+    pl.splits = cheapest_split(SplitModel{pl.nchunks, tiles, std::min<int64_t>(pl.splits, max_blocks / tiles), t_chunk, 4.0, other_us, 5.0, 0.0});
     choose_bands(pl, pl.k11 ? 64 : 32, pl.k11 ? 64 : 32);
     if (pl.blocks > max_blocks) {   // rectangles of unequal size pad the grid
         pl.bands_m = pl.bands_n = 0;

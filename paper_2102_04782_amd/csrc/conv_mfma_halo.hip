@@ -1202,7 +1202,7 @@ daq_status conv_bwd_data_halo(const daq_conv_desc& d, const int8_t* qg, const fl
     return launch(g, st, kBwdNames);
 }
 
-bool conv_bwd_both_small(const daq_conv_desc& d, const int8_t* qx, const float* s_x, const int8_t* vq, const float* s_chan, float* dW,
+bool conv_bwd_both_small(const daq_conv_desc& d, const Plan32& plan_w, const int8_t* qx, const float* s_x, const int8_t* vq, const float* s_chan, float* dW,
                          int32_t* dW_acc, const int8_t* qg, const float* s_g, const int8_t* qw, const float* s_w, float* dX, int32_t* dX_acc,
                          void* ws, hipStream_t st, daq_status& rc) {
     Geometry g = plan_bwd(d);
@@ -1212,7 +1212,7 @@ bool conv_bwd_both_small(const daq_conv_desc& d, const int8_t* qx, const float* 
     if (x_blocks > kBothBlocks - 8) return false;
     const double x_us = form == kBothTaps9 ? 5.0 + 1.0 * (double)ceil_div(g.a.cp, kKc) : 4.5 + 0.35 * (double)ceil_div(g.a.cp, kKc);
     DwBeside w;
-    if (!bwd_filter_beside(d, qx, s_x, vq, s_chan, dW, dW_acc, ws, kBothBlocks - (int)x_blocks, x_us, w)) return false;
+    if (!bwd_filter_beside(d, plan_w, qx, s_x, vq, s_chan, dW, dW_acc, ws, kBothBlocks - (int)x_blocks, x_us, w)) return false;
     daq_wpack_layout Lw;
     if (daq_layout_qw(&d, &Lw) != DAQ_OK) return false;
     HaloArgs& a = g.a;

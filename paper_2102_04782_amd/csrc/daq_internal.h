@@ -24,7 +24,17 @@ constexpr int kKAlign = 256;         // the flattened (n,h,w) axis of a CNHW buf
 inline int64_t round_up(int64_t v, int64_t m) { return (v + m - 1) / m * m; }
 inline int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
 
+// Into how many parts to split the n steps of each of a launch's tiles, when a CU holds one workgroup at a time:
+//     rounds over the CUs * max(steps of the longest part * t_step + t_fixed, t_floor) + (several parts: t_reduce + parts * t_part) .
+// The count with the least of it, the smallest of equals, at most `limit`.
+struct SplitModel {
+    int64_t n, tiles, limit;
+    double t_step, t_fixed, t_floor, t_reduce, t_part;
+};
+int cheapest_split(const SplitModel& m, int* tried = nullptr);
+
 bool desc_valid(const daq_conv_desc* d);
+bool plannable(const daq_conv_desc* d);   // valid, and of a size the kernels' indices hold
 inline bool is_depthwise(const daq_conv_desc& d) { return d.groups > 1 && d.groups == d.Cin && d.groups == d.Cout; }
 
 // ---- profiling hooks (prof.hip) ------------------------------------------------------------
@@ -180,13 +190,24 @@ struct DwDepth {
     int kD, dD, sD;
     int64_t x_chan_pitch, x_plane_pitch, x_depth_phase;
 };
-bool bwd_filter_lds_supported(const daq_conv_desc& d, int depth = 1);
-size_t bwd_filter_lds_ws_bytes(const daq_conv_desc& d, int depth = 1);
-int64_t bwd_filter_lds_row_bytes(const daq_conv_desc& d, int depth = 1);   // read of an activation row, from its start on (a supported layer's)
+struct Plan32 {
+    bool ok;              // these kernels serve the layer; an entry point makes its plan once and hands it on
+    bool k11;             // 1 x 1 filter: the plain GEMM kernel
+    bool s2;              // 3 x 3 filter at stride 2: four stride-phase planes per input channel
+    int wm, wn, wk, splits, tiles_m, tiles_n, nchunks, pb, b_units, ch;
+    int bands_m, bands_n, band_m, band_n;   // rectangles of the tile grid per K split when there are 1, 2 or 4 splits (else 0)
+    int64_t blocks;       // workgroups of the launch
+    size_t lds_bytes;
+    int64_t part_slots;   // int32 entries of one split's partial tiles
+};
+// depth: depth taps of a 3-D layer (its frames are the images of `d`); the launch has that many times the tiles
+Plan32 make_plan32(const daq_conv_desc& d, int depth = 1);
+size_t bwd_filter_lds_ws_bytes(const Plan32& pl, int depth = 1);
+int64_t bwd_filter_lds_row_bytes(const Plan32& pl);   // read of an activation row, from its start on
 // With `defer`, a K-split launch leaves its last stage (sum of the partial tiles, de-quantization) undone and
 // describes it in *defer (blocks == 0: nothing is left) for a later kernel's extra workgroups, see dw_tail.h.
 struct DwTail;
-daq_status conv_bwd_filter_lds(const daq_conv_desc& d, const int8_t* qx, const float* s_x, const int8_t* vq,
+daq_status conv_bwd_filter_lds(const daq_conv_desc& d, const Plan32& pl, const int8_t* qx, const float* s_x, const int8_t* vq,
                                const float* s_chan, float* dW, int32_t* acc, void* ws, hipStream_t st,
                                DwTail* defer = nullptr, bool bf16 = false, const DwDepth* dp = nullptr);
 
@@ -199,7 +220,7 @@ daq_status conv_bwd_data_halo(const daq_conv_desc& d, const int8_t* qg, const fl
                               bool bf16 = false);
 // Both gradients of a small layer in one launch (and a reduction, if the filter gradient is split); false: the layer has no
 // such form, and nothing was launched.
-bool conv_bwd_both_small(const daq_conv_desc& d, const int8_t* qx, const float* s_x, const int8_t* vq, const float* s_chan, float* dW,
+bool conv_bwd_both_small(const daq_conv_desc& d, const Plan32& plan_w, const int8_t* qx, const float* s_x, const int8_t* vq, const float* s_chan, float* dW,
                          int32_t* dW_acc, const int8_t* qg, const float* s_g, const int8_t* qw, const float* s_w, float* dX, int32_t* dX_acc,
                          void* ws, hipStream_t st, daq_status& rc);
 bool fwd_halo_supported(const daq_conv_desc& d);
@@ -222,6 +243,9 @@ daq_status conv_fwd_depthwise(const daq_conv_desc& d, const int8_t* qx_cnhw, con
                               const float* s_w, float* Y, int32_t* acc, hipStream_t st);
 bool depthwise_dw_supported(const daq_conv_desc& d);
 size_t depthwise_dw_ws_bytes(const daq_conv_desc& d);
+
+// layout.hip: workspace of a filter gradient (a multiple of 256), `pl` being its make_plan32
+size_t bwd_filter_ws_bytes(const daq_conv_desc& d, const Plan32& pl);
 daq_status conv_bwd_filter_depthwise(const daq_conv_desc& d, const int8_t* qx, const float* s_x, const int8_t* vq,
                                      const float* s_chan, float* dW, int32_t* acc, void* ws, hipStream_t st, bool bf16 = false);
 

@@ -45,8 +45,8 @@ struct DwBeside {
     size_t lds_bytes;
     DwTail tail;
 };
-bool bwd_filter_beside(const daq_conv_desc& d, const int8_t* qx, const float* s_x, const int8_t* vq, const float* s_chan, float* dW, int32_t* acc,
-                       void* ws, int max_blocks, double other_us, DwBeside& out);
+bool bwd_filter_beside(const daq_conv_desc& d, Plan32 pl, const int8_t* qx, const float* s_x, const int8_t* vq, const float* s_chan, float* dW,
+                       int32_t* acc, void* ws, int max_blocks, double other_us, DwBeside& out);
 
 namespace {
 

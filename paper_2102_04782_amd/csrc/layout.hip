@@ -1,6 +1,7 @@
 // Host-side logic: descriptor validation, int8 buffer layouts, workspace sizes.
 // No GPU call is made from this file.
 #include <algorithm>
+#include <cmath>
 
 #include "daq_internal.h"
 
@@ -110,6 +111,53 @@ static void fill_nhwc(daq_layout* L, int C, int N, int H, int W) {
     L->bytes = round_up((int64_t)N * H * W * L->c_pitch, 256);
 }
 
+// Planning is host time of every call (trying every count up to 1024 took 3 us, several times a call).  Inside a round the cost
+// follows a convex curve but for the rounding up of the longest part: it is searched from the curve's minimum outwards, the
+// smallest count for each length of the longest part only, until the curve alone is above what has been found (by more than its rounding).
+int cheapest_split(const SplitModel& m, int* tried) {
+    constexpr int64_t kCus = 256;
+    int best_s = 1, count = 0;
+    double best = 0.0;
+    auto curve = [&](int64_t rounds, int64_t s) {
+        return (double)rounds * std::max((double)m.n / (double)s * m.t_step + m.t_fixed, m.t_floor) + m.t_reduce + m.t_part * (double)s;
+    };
+    auto look = [&](int64_t rounds, int64_t s) {
+        double c = (double)rounds * std::max((double)ceil_div(m.n, s) * m.t_step + m.t_fixed, m.t_floor);
+        if (s > 1) c += m.t_reduce + m.t_part * (double)s;
+        if (!count++ || c < best || (c == best && s < best_s)) { best = c; best_s = (int)s; }
+    };
+    look(ceil_div(m.tiles, kCus), 1);
+    const int64_t top = std::min(m.limit, m.n);
+    for (int64_t r = 1;; ++r) {
+        const int64_t lo = std::max<int64_t>(2, kCus * (r - 1) / m.tiles + 1), hi = std::min(top, kCus * r / m.tiles);
+        if (lo > top) break;
+        if (hi < lo) continue;
+        double at = (double)hi;
+        if (m.t_part > 0.0) at = std::min(at, std::sqrt((double)r * (double)m.n * m.t_step / m.t_part));
+        if (m.t_floor > m.t_fixed) at = std::min(at, (double)m.n * m.t_step / (m.t_floor - m.t_fixed));
+        const int64_t mid = std::max(lo, (int64_t)at), longest = ceil_div(m.n, mid);
+        for (int64_t s = mid;; --s) {
+            s = std::max(lo, ceil_div(m.n, ceil_div(m.n, s)));
+            look(r, s);
+            if (s == lo || curve(r, s - 1) > best * (1.0 + 1e-9)) break;
+        }
+        for (int64_t q = longest - 1; q >= 1; --q) {
+            const int64_t s = ceil_div(m.n, q);
+            if (s > hi || curve(r, s) > best * (1.0 + 1e-9)) break;
+            look(r, s);
+            q = ceil_div(m.n, s);
+        }
+    }
+    if (tried) *tried = count;
+    return best_s;
+}
+
+bool plannable(const daq_conv_desc* d) { return desc_valid(d) && sizes_ok(*d); }
+
+size_t bwd_filter_ws_bytes(const daq_conv_desc& d, const Plan32& pl) {
+    return 256 + (pl.ok ? bwd_filter_lds_ws_bytes(pl) : std::max(bwd_filter_mfma_ws_bytes(d), depthwise_dw_ws_bytes(d)));
+}
+
 }  // namespace daq
 
 using namespace daq;
@@ -174,12 +222,12 @@ daq_status daq_layout_qw(const daq_conv_desc* d, daq_wpack_layout* out) {
 }
 
 size_t daq_workspace_bytes(daq_op op, const daq_conv_desc* d) {
-    if (!desc_valid(d) || !sizes_ok(*d)) return 0;
+    if (!plannable(d)) return 0;
     switch (op) {
         case DAQ_OP_QUANTIZE_GRAD: return quantize_grad_ws_bytes(*d);
         case DAQ_OP_CONV_FWD: return fwd_quant_ws_bytes(*d);
         case DAQ_OP_CONV_BWD_DATA: return 256;
-        case DAQ_OP_CONV_BWD_FILTER: return 256 + std::max({bwd_filter_mfma_ws_bytes(*d), bwd_filter_lds_ws_bytes(*d), depthwise_dw_ws_bytes(*d)});
+        case DAQ_OP_CONV_BWD_FILTER: return bwd_filter_ws_bytes(*d, make_plan32(*d));
         case DAQ_OP_CONV_BWD: return daq_workspace_bytes(DAQ_OP_CONV_BWD_FILTER, d) + daq_workspace_bytes(DAQ_OP_CONV_BWD_DATA, d);
         case DAQ_OP_CLIP_SEARCH: return clip_search_ws_bytes(*d);
         default: return 0;

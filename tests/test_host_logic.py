@@ -191,17 +191,25 @@ def test_workspace_and_validation_without_a_gpu():
     assert daq.status_string(daq.ERR_WORKSPACE).startswith("workspace")
 
 
-@pytest.mark.skipif(shutil.which("hipcc") is None, reason="no hipcc")
-def test_frame_copies_of_3d_layers_stay_inside_the_workspace(tmp_path):
-    exe = str(tmp_path / "frame_copies")
-    pkg = os.path.join(ROOT, "paper_2102_04782_amd")
-    cmd = ["hipcc", "--offload-arch=gfx950", "-O1", "-std=c++17", "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops", "-Wno-unused-function",
-           "-Wno-pass-failed", "-I", os.path.join(ROOT, "include"), "-I", os.path.join(pkg, "csrc"), os.path.join(ROOT, "tests", "host", "frame_copies.hip"),
-           "-o", exe, "-L" + pkg, "-ldaq", "-Wl,-rpath," + pkg]
-    res = subprocess.run(cmd, capture_output=True, text=True, timeout=600)
+def _run_host_program(name, tmp_path, *extra):
+    """Compiles tests/host/<name> against the library's sources and runs it (no GPU call)."""
+    exe, pkg = str(tmp_path / "prog"), os.path.join(ROOT, "paper_2102_04782_amd")
+    res = subprocess.run(["hipcc", "-O1", "-std=c++17", *extra, "-Wno-unused-function", "-Wno-pass-failed", "-I", os.path.join(ROOT, "include"), "-I",
+                          os.path.join(pkg, "csrc"), os.path.join(ROOT, "tests", "host", name), "-o", exe, "-L" + pkg, "-ldaq", "-Wl,-rpath," + pkg],
+                         capture_output=True, text=True, timeout=600)
     assert res.returncode == 0, res.stderr[-4000:]
     run = subprocess.run([exe], capture_output=True, text=True, timeout=600)
     assert run.returncode == 0, run.stdout + run.stderr
+
+
+@pytest.mark.skipif(shutil.which("hipcc") is None, reason="no hipcc")
+def test_frame_copies_of_3d_layers_stay_inside_the_workspace(tmp_path):
+    _run_host_program("frame_copies.hip", tmp_path, "--offload-arch=gfx950", "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops")
+
+
+@pytest.mark.skipif(shutil.which("hipcc") is None, reason="no hipcc")
+def test_split_search_finds_the_cheapest_count_among_few(tmp_path):
+    _run_host_program("split_search.hip", tmp_path, "--offload-arch=gfx950")
 
 
 def test_workload_tables():
