@@ -4,7 +4,7 @@ import pytest
 
 from paper_2102_04782_amd import binding as daq
 from paper_2102_04782_amd import workloads as wl
-from test_gpu_parity import check_forward, run_convs_on_codes
+from test_gpu_parity import check_forward, check_quantize_grad, check_quantize_grad_bf16, run_convs_on_codes
 
 pytestmark = pytest.mark.gpu
 
@@ -40,8 +40,8 @@ def test_filter_gradient_splits(layer):
     wl.Layer("tile_less1", 2, 31, 9, 9, 33, 3, 3, 1, 1),    # one short of a 32-channel tile, one past it
     wl.Layer("tile_past", 2, 65, 6, 6, 32, 1, 1, 1, 0),     # a second 64-channel block of the contraction axis
     wl.Layer("two_taps", 3, 40, 7, 7, 70, 1, 2, 1, 0),
-    wl.Layer("ten_taps", 2, 33, 8, 12, 34, 2, 5, 1, 2),     # a chunk of nine taps and one of one
-    wl.Layer("stem", 2, 3, 15, 15, 33, 7, 7, 2, 3),         # 49 taps: five chunks of nine, one of four
+    wl.Layer("ten_taps", 2, 33, 8, 12, 34, 2, 5, 1, 2),     # three chunks of three taps and one of one
+    wl.Layer("stem", 2, 3, 15, 15, 33, 7, 7, 2, 3),         # 49 taps: sixteen chunks of three, one of one
     wl.Layer("grouped", 2, 36, 6, 8, 54, 3, 3, 1, 1, groups=2),
     wl.Layer("depthwise", 2, 33, 5, 6, 33, 3, 3, 2, 1, groups=33),
 ], ids=lambda l: l.name)
@@ -72,3 +72,27 @@ def test_both_gradients_of_a_small_layer(layer):
 def test_filter_gradient_of_any_extent(kH, kW, pad, stride, batch):
     """Tap counts at both sides of the kernel's forms; K steps from fewer than the load ring holds to several rounds of it."""
     on_random_codes(wl.Layer("taps", batch, 3 if kH == 7 and kW == 7 else 20, 12, 11, 70, kH, kW, stride, pad), 60 + batch)
+
+
+# (images, rows, columns) by the load units - four elements, the last of a plane fewer - that the resident quantizer gives a
+# thread: planes of 1, 2 and 3 mod 4 elements, and of fewer than four
+RESIDENT_PLANES = {
+    2: [(5, 13, 13), (7, 10, 13), (6, 7, 13), (9, 1, 2), (11, 1, 3), (3, 1, 5)],
+    4: [(50, 13, 13), (70, 10, 13), (95, 7, 13)],
+    8: [(100, 13, 13), (130, 10, 13), (190, 7, 13)],
+    16: [(200, 13, 13), (260, 10, 13), (370, 7, 13)],
+}
+
+
+@pytest.mark.parametrize("per_thread,n,h,w", [(u, *p) for u, planes in RESIDENT_PLANES.items() for p in planes])
+@pytest.mark.parametrize("k", [1, 3])
+def test_resident_quantizer_on_planes_of_any_size(per_thread, n, h, w, k):
+    """Codes straight from registers (1 x 1: no padding in the plane) and through the image in LDS (3 x 3)."""
+    units = n * -(-h * w // 4)
+    assert units <= per_thread * 1024 and (per_thread == 2 or units > per_thread * 512)
+    layer = wl.Layer("resident", n, 1, h, w, 3, k, k, 1, k // 2)
+    dY = wl.make_dY(layer, wl.seed_for(21, n))
+    st = wl.make_state(dY, wl.seed_for(21, n))
+    for mode, seed in ((daq.ROUND_NEAREST, 0), (daq.ROUND_STOCHASTIC, 31 + n)):
+        check_quantize_grad(layer, dY, st, mode=mode, seed=seed)
+        check_quantize_grad_bf16(layer, dY, st, mode=mode, seed=seed)
