@@ -161,6 +161,12 @@ constexpr int kFwdWsFree = 1000;
 daq_status quantize_forward(const daq_conv_desc& d, const float* X, int8_t* qx_nhwc, int8_t* qx_cnhw, float* s_x, const float* W,
                             int8_t* qw_packed, float* s_w, void* ws, hipStream_t st, daq_schedule schedule);
 
+// Channel-resident quantizer: `units` load units of a channel (four elements of a plane each, fewer at its end) on a workgroup of
+// `waves` waves, `nu` units to a thread.
+struct ResidentForm { int nu, waves; };
+ResidentForm resident_form(int C, int64_t units);
+bool resident_pays(int C, int64_t units);   // against the sweeps
+
 // clip_search.hip
 size_t clip_search_ws_bytes(const daq_conv_desc& d);
 

@@ -1653,6 +1653,40 @@ size_t quantize_grad_ws_bytes(const daq_conv_desc& d) {
 size_t fwd_quant_ws_bytes(const daq_conv_desc&) { return 4096; }
 static_assert(kAbsmaxBlocksX + kAbsmaxBlocksW + 8 <= kFwdWsFree && kFwdWsFree + 8 <= 4096 / 4, "forward workspace");
 
+// A wave's work is serial, some 100 instructions a unit.  While the chip holds a wave of every workgroup at once, fewer units to a
+// thread are faster (16 channels of 832 units: 7.2, 7.4, 8.2, 11.0 us with 2, 4, 8, 16); from there on the form that keeps the most
+// waves on a CU, which takes 24 of 2 to 8 units and 16 of 16 (1024 channels of 5289 units, whole call: 54.9 us as 12 waves of 8
+// units, two workgroups a CU; 60.8 as 8 of 16, 75.3 as 6 of 16), of equals the one with fewer dead units.  From five waves on they
+// come in fours, one to a SIMD: a SIMD with a wave more than the others sets the time (546 channels of 14256 units: 67.5 us with 14
+// waves, 59.3 with 16).  Over 528 sizes the choice is 0.7 % from the fastest form, at most 10 %.
+ResidentForm resident_form(int C, int64_t units) {
+    constexpr int kUnits[4] = {2, 4, 8, 16}, kHeld[4] = {24, 24, 24, 16};
+    ResidentForm best{16, 16};
+    int best_held = 0;
+    for (int i = 0; i < 4; ++i) {
+        int64_t w = ceil_div(units, kUnits[i] * kWave);
+        if (w > 16) continue;
+        if (w > 4) w = round_up(w, 4);
+        const int per_cu = kHeld[i] / (int)w, held = per_cu * (int)w;
+        if (i < 3 && C <= 256 * per_cu) return ResidentForm{kUnits[i], (int)w};
+        if (held > best_held || (held == best_held && kUnits[i] * w <= best.nu * best.waves)) {
+            best = ResidentForm{kUnits[i], (int)w};
+            best_held = held;
+        }
+    }
+    return best;
+}
+
+// A workgroup per channel leaves CUs idle where channels are few, and a large one takes 20 us and more: three sweeps of a tensor
+// of a few channels take 15 (16 channels of 15466 units 27.5 us, the sweeps 15.8; 64 of 8000: 19.5 and 18.4; 128 of 9460: 27.9 and 29.3).
+// Channels of more than 8 Ki units run one to a CU, and a second round for a few of them does not pay either (268 of 11952 units in
+// bfloat16: 46 and 43 us).  (512 channels of 12544 units in two rounds are level with the sweeps, 59 + 27 us against 31 + 50 + 8, but
+// save a launch.)
+bool resident_pays(int C, int64_t units) {
+    if (units > 8 * 1024 && C > 256 && C < 288) return false;
+    return units <= 6 * 1024 || C >= 96;
+}
+
 // ---------------------------------------------------------------------------------------------
 // forward-side quantization of X (two layouts) and W (packed)
 // ---------------------------------------------------------------------------------------------
@@ -1822,22 +1856,13 @@ daq_status quantize_grad_impl(const daq_conv_desc* desc, const T* dY, float* s_s
 
     // Channels that fit in LDS: one read of dY serves statistics, count, decision and the per-channel copy
     // (k_chan_resident); the global copy follows in the counting kernel's copy-only form.
-    // A workgroup holds the channel, 2, 4, 8 or 16 units to a thread, as many waves as that takes.  A wave's work is serial, some
-    // 100 instructions a unit, so while the chip has room for the waves fewer units are faster (16 channels of 832 units: 7.2, 7.4,
-    // 8.2, 11.0 us with 2, 4, 8, 16); once it is full, waves with more loads in flight are (2048 channels of 1664 units: 31.5, 24.5,
-    // 22.4, 24.6 us; 512 channels of 1664: 10.5, 10.2, 10.6, 14.0; 1024 of 832: 10.8, 10.3, 10.2, 11.9).
     const bool res_v4 = HW >= 4;   // dword-aligned 16-byte loads run at full rate, as in the statistics sweep
     const int res_upp = res_v4 ? (HW + 3) / 4 : HW;
     const int64_t res_units = (int64_t)N * res_upp;
-    auto res_fits = [&](int nu) { return res_units <= nu * 1024 && C * ceil_div(res_units, nu * kWave) <= 6144; };   // 24 waves a CU
-    const int res_nu = res_fits(2) ? 2 : res_fits(4) ? 4 : res_fits(8) || res_units <= 8 * 512 ? 8 : 16;
-    const int res_th = (int)round_up(ceil_div(res_units, res_nu), kWave);
+    const ResidentForm res = resident_form(C, res_units);
     const bool resident_ok = scheme == DAQ_SCHEME_DAQ && res_units <= 16 * 1024 && Lv.plane_pitch <= kResidentMaxLds &&
                              (Lv.plane_pitch & 15) == 0 && (Lv.chan_pitch & 15) == 0;
-    // (The 1024-thread form runs one workgroup per CU, whose load, count and packing phases follow each other with nothing
-    // to overlap them: on 128 -> 512 at 28 x 28, batch 64, it takes 59 + 27 us against 31 + 50 + 8 us for the sweeps - level -
-    // but it saves a launch, and ResNet-50's backward pass as a whole measured 1 % faster with it than without.)
-    if (!given && resident_ok && (schedule == DAQ_SCHEDULE_CHANNEL_RESIDENT || schedule == DAQ_SCHEDULE_AUTO)) {
+    if (!given && resident_ok && (schedule == DAQ_SCHEDULE_CHANNEL_RESIDENT || (schedule == DAQ_SCHEDULE_AUTO && resident_pays(C, res_units)))) {
         ws.slabs = 1;   // one |g|max partial per channel
         ws.part_n = C;
         const ResArgs ra{make_fastdiv((uint32_t)res_upp), make_fastdiv((uint32_t)Wo), N, C, HW, k, A, lambda, keys};
@@ -1852,7 +1877,7 @@ daq_status quantize_grad_impl(const daq_conv_desc* desc, const T* dY, float* s_s
         auto kern = k_chan_resident<T, S, V, NUV, FL, TL>;                                                           \
         if (!FL && !allow_lds((const void*)kern, lds)) \
             return DAQ_ERR_HIP;                                                                                      \
-        DAQ_LAUNCH("chan_resident", st, hipLaunchKernelGGL(kern, rgrid, dim3((unsigned)res_th), lds, st, dY, cnhw_view(Lv), vq, ra, ws, ca)); \
+        DAQ_LAUNCH("chan_resident", st, hipLaunchKernelGGL(kern, rgrid, dim3((unsigned)(res.waves * kWave)), lds, st, dY, cnhw_view(Lv), vq, ra, ws, ca)); \
     }
 #define DAQ_RES_FORM(S, NUV)                                                                                         \
     {                                                                                                                \
@@ -1864,9 +1889,9 @@ daq_status quantize_grad_impl(const daq_conv_desc* desc, const T* dY, float* s_s
     }
 #define DAQ_RES_SIZE(S)                                                                                              \
     {                                                                                                                \
-        if (res_nu == 2) DAQ_RES_FORM(S, 2)                                                                          \
-        else if (res_nu == 4) DAQ_RES_FORM(S, 4)                                                                     \
-        else if (res_nu == 8) DAQ_RES_FORM(S, 8)                                                                     \
+        if (res.nu == 2) DAQ_RES_FORM(S, 2)                                                                          \
+        else if (res.nu == 4) DAQ_RES_FORM(S, 4)                                                                     \
+        else if (res.nu == 8) DAQ_RES_FORM(S, 8)                                                                     \
         else DAQ_RES_FORM(S, 16)                                                                                     \
     }
         if (stoch) DAQ_RES_SIZE(true) else DAQ_RES_SIZE(false)

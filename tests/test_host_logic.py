@@ -212,6 +212,11 @@ def test_split_search_finds_the_cheapest_count_among_few(tmp_path):
     _run_host_program("split_search.hip", tmp_path, "--offload-arch=gfx950")
 
 
+@pytest.mark.skipif(shutil.which("hipcc") is None, reason="no hipcc")
+def test_dispatch_rules(tmp_path):
+    _run_host_program("dispatch.hip", tmp_path, "--offload-arch=gfx950")
+
+
 def test_workload_tables():
     r50 = wl.config4()
     assert len(r50) == 53 and len({(l.Cin, l.Hin, l.Cout, l.kH, l.stride) for l in r50}) == 23
