@@ -1682,13 +1682,13 @@ ResidentForm resident_form(int C, int64_t units) {
 }
 
 // A workgroup per channel leaves CUs idle where channels are few, and a large one takes 20 us and more: three sweeps of a tensor
-// of a few channels take 15 (16 channels of 15466 units 27.5 us, the sweeps 15.8; 64 of 8000: 19.5 and 18.4; 128 of 9460: 27.9 and 29.3).
+// of a few channels take 15 (16 channels of 15466 units 27.5 us, the sweeps 15.8; 64 of 8000: 19.5 and 18.4; 96 of 13200: 31 and 28; 128 of 9460: 27.9 and 29.3).
 // Channels of more than 8 Ki units run one to a CU, and a second round for a few of them does not pay either (268 of 11952 units in
 // bfloat16: 46 and 43 us).  (512 channels of 12544 units in two rounds are level with the sweeps, 59 + 27 us against 31 + 50 + 8, but
 // save a launch.)
 bool resident_pays(int C, int64_t units) {
     if (units > 8 * 1024 && C > 256 && C < 288) return false;
-    return units <= 6 * 1024 || C >= 96;
+    return units <= 6 * 1024 || C >= (units <= 8 * 1024 ? 96 : 128);
 }
 
 // ---------------------------------------------------------------------------------------------

@@ -14,6 +14,7 @@ using namespace daq;
 static void resident_quantizer() {
     EXPECT(!resident_pays(16, 22 * 703));                                   // 22 images of 53 x 53, 16 channels
     EXPECT(!resident_pays(4, 8 * 1561) && !resident_pays(30, 60 * 160));
+    EXPECT(!resident_pays(96, 66 * 200));                                   // 66 images of 114 x 7
     EXPECT(!resident_pays(268, 83 * 144));                                  // a second round of twelve workgroups
     EXPECT(resident_pays(16, 5000) && resident_pays(128, 9460) && resident_pays(512, 12544) && resident_pays(300, 14000));
     auto is = [](int C, int64_t units, int nu, int waves) {

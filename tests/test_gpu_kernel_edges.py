@@ -90,7 +90,7 @@ def test_resident_quantizer_on_planes_of_any_size(per_thread, n, h, w, k):
     """Codes straight from registers (1 x 1: no padding in the plane) and through the image in LDS (3 x 3)."""
     units = n * -(-h * w // 4)
     assert units <= per_thread * 1024 and (per_thread == 2 or units > per_thread * 512)
-    layer = wl.Layer("resident", n, 1, h, w, 100, k, k, 1, k // 2)   # (so many that the largest are not left to the sweeps)
+    layer = wl.Layer("resident", n, 1, h, w, 128, k, k, 1, k // 2)   # (so many that the largest are not left to the sweeps)
     dY = wl.make_dY(layer, wl.seed_for(21, n))
     st = wl.make_state(dY, wl.seed_for(21, n))
     for mode, seed in ((daq.ROUND_NEAREST, 0), (daq.ROUND_STOCHASTIC, 31 + n)):
