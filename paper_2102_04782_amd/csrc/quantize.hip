@@ -796,6 +796,12 @@ __device__ __forceinline__ float given_scale(const float* __restrict__ scale, in
     return s;
 }
 
+// The same by one workgroup, for packing launches whose own many would spend longer on it (fold_in_packing).
+__global__ __launch_bounds__(kBlock) void k_fold_scale(const float* __restrict__ part, int n, float* publish, float* publish_raw) {
+    __shared__ float l_m[kBlock / kWave];
+    given_scale(part, n, publish, publish_raw, true, l_m);
+}
+
 struct PackArgs {
     FastDiv div_slot, div_pitch;
     int per_chan;          // workgroups per (channel, phase) plane
@@ -1598,6 +1604,14 @@ RowsArgs rows_args(const daq_layout& Ld, int v, bool early, int part_n, uint32_t
 }
 int64_t rows_blocks(const daq_layout& Ld, const RowsArgs& ra) { return round_up(Ld.C, kXcd) * (ra.grid_per_chan + 1); }
 
+// Workgroups of the launch below for one copy.
+int64_t pack_blocks(const daq_layout& Ld, const void* src, int elem_bytes) {
+    const int v = rows_vector(Ld, src, elem_bytes);
+    if (v) return rows_blocks(Ld, rows_args(Ld, v, false, 0, 0u, 0));
+    const dim3 g = pack_grid(Ld);
+    return (int64_t)g.x * g.z;
+}
+
 // Launches the channel-major packing of one fp32 NCHW tensor: the source-driven row kernel when the
 // layout allows it, the output-driven kernel otherwise.
 // With dst2 the same pass also writes a second copy quantized with the per-tensor scale scale2 (random stream
@@ -1680,6 +1694,11 @@ ResidentForm resident_form(int C, int64_t units) {
     }
     return best;
 }
+
+// The fold is a load, a reduction and a barrier in front of each workgroup's codes, a launch of its own some 3.5 us: level at two to
+// three rounds of eight workgroups a CU (depthwise, packing alone: 492 channels of 24 x 24, batch 92, 6888 workgroups, 27.5 us without the
+// fold and 30.8 with it; 672 of 38 x 38, batch 34, 16800: 38 and 48).
+bool fold_in_packing(int64_t workgroups) { return workgroups <= 4096; }
 
 // A workgroup per channel leaves CUs idle where channels are few, and a large one takes 20 us and more: three sweeps of a tensor
 // of a few channels take 15 (16 channels of 15466 units 27.5 us, the sweeps 15.8; 64 of 8000: 19.5 and 18.4; 96 of 13200: 31 and 28; 128 of 9460: 27.9 and 29.3).
@@ -1905,7 +1924,11 @@ daq_status quantize_grad_impl(const daq_conv_desc* desc, const T* dY, float* s_s
         // the per-channel copy, its scales, classes and clip state are complete here; the global copy follows on `st`
         if (side && stream_follows(side, st) != DAQ_OK) return DAQ_ERR_HIP;
         if (!qg_nhwc) {
-            // depthwise layers: the per-tensor copy is channel-major too; its workgroups fold the channel maxima themselves
+            // depthwise layers: the per-tensor copy is channel-major too
+            if (!fold_in_packing(pack_blocks(Lv, dY, (int)sizeof(T)))) {
+                DAQ_LAUNCH("fold_scale", st, hipLaunchKernelGGL(k_fold_scale, dim3(1), dim3(kBlock), 0, st, ws.part_max, ws.part_n, s_global, ws.layer));
+                return launch_pack("pack_qg", stoch, false, dY, Lv, s_global, qg, 1u, keys, ws, ClipArgs{}, st);
+            }
             return launch_pack("pack_qg", stoch, false, dY, Lv, ws.part_max, qg, 1u, keys, ws, ClipArgs{}, st, nullptr, nullptr, 0, nullptr, false,
                                ws.part_n, s_global);
         }

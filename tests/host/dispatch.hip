@@ -17,6 +17,7 @@ static void resident_quantizer() {
     EXPECT(!resident_pays(96, 66 * 200));                                   // 66 images of 114 x 7
     EXPECT(!resident_pays(268, 83 * 144));                                  // a second round of twelve workgroups
     EXPECT(resident_pays(16, 5000) && resident_pays(128, 9460) && resident_pays(512, 12544) && resident_pays(300, 14000));
+    EXPECT(!fold_in_packing(672 * 25) && fold_in_packing(192 * 4));         // depthwise: 672 channels of 38 x 38, batch 34
     auto is = [](int C, int64_t units, int nu, int waves) {
         const ResidentForm f = resident_form(C, units);
         return f.nu == nu && f.waves == waves;
