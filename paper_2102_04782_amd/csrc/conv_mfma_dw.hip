@@ -471,7 +471,7 @@ __global__ __launch_bounds__(256) void k_dw_direct(DwArgs p) {
 // Rows past Cout / Cin and unused tap slots compute on valid memory and are never stored.
 // ---------------------------------------------------------------------------------------------
 constexpr int kMaxTapSlots = 56;
-constexpr double kTapLoad = 0.4;   // us a K step of a workgroup takes for each of a wave's byte-aligned operand loads, which bound it
+constexpr double kTapLoad = 1.0;   // us a K step of a workgroup takes for each of a wave's byte-aligned operand loads, which bound it
 struct TapTable {
     int64_t off[kMaxTapSlots];   // byte offset of the tap's window start inside an activation channel
     int id[kMaxTapSlots];        // kh*kW + kw, or -1 for an unused slot
@@ -774,12 +774,13 @@ Plan make_general_plan(const daq_conv_desc& d) {
     const int64_t Tp = pl.row_kw ? d.kH : T;   // tap slots of the partial layout
     // K splits: the number that minimises
     //     rounds over the CUs * (steps of a wave * t_step + t_fixed) + (reduction and its launch, if any)
-    // with partial tiles on their way at 3 TB/s.  A CU is as fast with one workgroup as with two (its byte-aligned loads bound it:
+    // with a reduction of 3.3 us and partial tiles on their way at 2 TB/s (ranked on 149 layers as in conv_mfma_dw32.hip: 1.6 % from the
+    // fastest count on average; with 0.4 us a load, 5 us and 3 TB/s 4.1 %).  A CU is as fast with one workgroup as with two (its byte-aligned loads bound it:
     // 3 -> 64 7 x 7 stride 2 at 112 x 112, batch 64, 16 steps in 32 us).  (Bounded by the bytes of the operands instead, as
     // before, a tiny stem ran in two workgroups.)
     const double tile_bytes = (double)(kBM * 16 * pl.nb * Tp * 4);
     pl.splits = cheapest_split(SplitModel{ceil_div(nsteps, pl.wtaps ? 1 : 4), tiles, std::min<int64_t>(nsteps / (pl.wtaps ? 2 : 8), 1024 / tiles),   // two steps a wave
-                                          kTapLoad * pl.tw * pl.nb, 4.0, 0.0, 5.0, 2.0 * (double)tiles * tile_bytes / 3e6});
+                                          kTapLoad * pl.tw * pl.nb, 4.0, 0.0, 3.3, (double)tiles * tile_bytes / 1e6});
     pl.lds_bytes = pl.wtaps ? 256 : (size_t)12 * pl.nb * pl.tw * 4 * kWave * 4;
     if (pl.lds_bytes > 160 * 1024) return pl;
     pl.part_slots = tiles * 16 * pl.nb * Tp * kWave;

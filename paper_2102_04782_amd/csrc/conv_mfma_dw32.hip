@@ -77,16 +77,38 @@ __global__ __launch_bounds__(64 * WM * WN * WK) void k_dw11(Dw32Args p) {
 // 130 KB of LDS), so a launch of more than 256 runs in rounds, and 264 take as long as 512; a split launch is followed by
 // the reduction, which costs a launch and the partial tiles' way to memory and back.  The split that minimises
 //     rounds * (chunks of a workgroup * t_chunk + t_fixed) + (reduction, if any)
-// with the measured times: 0.75 us per chunk for nine taps and 0.45 us for one, 4 us of prologue, combine and stores, 5 us for
-// a reduction and its launch, partial tiles at 3 TB/s.  (64 -> 64, 3 x 3 x 3 on 8 x 56 x 56: 22 splits were 264 workgroups,
-// 57 us; 21 are 252.  16 -> 16, 3 x 3 on 16 x 16, batch 4: five chunks, one split, no reduction.)
-int choose_splits(int64_t tiles, int nchunks, double t_chunk, double tile_bytes) {
-    return cheapest_split(SplitModel{nchunks, tiles, 4 * 256 / tiles, t_chunk, 4.0, 0.0, 5.0, 2.0 * (double)tiles * tile_bytes / 3e6});
+// with times of 1.1 us per chunk for nine taps, 2 us for nine at stride 2 and 0.5 us for one, 4 us of prologue, combine and stores,
+// 3.3 us for a reduction and its launch, partial tiles at 2 TB/s: what ranks the counts measured on 450 layers best, 1.5 to 2 % from
+// the fastest on average (with 0.75, 0.75, 0.45, 5 and 3: 2.6, 6.5 and 3.2 %; 54 -> 56, stride 2 on 7 x 59, batch 11: one split
+// 15.4 us, four 11.2).  (64 -> 64, 3 x 3 x 3 on 8 x 56 x 56: 22 splits were 264 workgroups, 57 us; 21 are 252.)
+SplitModel split_model(int64_t tiles, int nchunks, double t_chunk, double tile_bytes) {
+    return SplitModel{nchunks, tiles, 4 * 256 / tiles, t_chunk, 4.0, 0.0, 3.3, (double)tiles * tile_bytes / 1e6};
+}
+
+SplitModel split_model(const Plan32& pl, int depth) {
+    const int64_t tiles = (int64_t)pl.tiles_m * pl.tiles_n * depth;
+    return pl.k11 ? split_model(tiles, pl.nchunks, 0.5, 64 * 64 * 4) : split_model(tiles, pl.nchunks, pl.s2 ? 2.0 : 1.1, 32 * 32 * kT * 4);
+}
+
+// 1 x 1 filters hardly reuse an operand inside a workgroup, and with 3, 5, 6 or 7 splits every XCD reads nearly all of both (dw_block_map):
+// a chunk takes half as long again (434 -> 689 at 8 x 46, batch 43: 26.9 us with three splits, 20.2 with two).
+int choose_splits(const Plan32& pl, int depth) {
+    const SplitModel m = split_model(pl, depth);
+    int s = cheapest_split(m);
+    if (!pl.k11 || s < 3 || s == 4 || s > 7) return s;
+    SplitModel scattered = m;
+    scattered.t_step *= 1.5;
+    double best = scattered.cost(s);
+    for (int64_t near : {1, 2, 4, 8})
+        if (near <= std::min(m.limit, m.n) && m.cost(near) < best) { best = m.cost(near); s = (int)near; }
+    return s;
 }
 
 // Rectangles per split for 1, 2 or 4 splits (8, 4 or 2 XCDs share a split): the cut of the tile grid that makes an
-// XCD touch the fewest operand rows, rows of the two operands weighted by their tile heights.
-void choose_bands(Plan32& pl, int bm, int bn) {
+// XCD touch the fewest operand rows, rows of the two operands weighted by their tile heights - unless its largest rectangle takes
+// a round over the XCD's 32 CUs more than the tiles dealt out evenly (513 -> 193, 3 x 3 on 77 x 6, batch 90: 238 workgroups in
+// rectangles of up to 35, 113 us; dealt out 66).
+void choose_bands(Plan32& pl, int bm, int bn, int depth = 1) {
     pl.bands_m = pl.bands_n = pl.band_m = pl.band_n = 0;
     pl.blocks = (int64_t)pl.tiles_m * pl.tiles_n * pl.splits;
     if (pl.splits != 1 && pl.splits != 2 && pl.splits != 4) return;
@@ -97,6 +119,7 @@ void choose_bands(Plan32& pl, int bm, int bn) {
         if (rm > pl.tiles_m || rn > pl.tiles_n) continue;
         const int64_t hm = ceil_div(pl.tiles_m, rm), hn = ceil_div(pl.tiles_n, rn);
         const int64_t rows = hm * bm + hn * bn;
+        if (ceil_div(hm * hn * depth, 32) > ceil_div(pl.blocks * depth, 256)) continue;
         if (best < 0 || rows < best) { best = rows; pl.bands_m = rm; pl.bands_n = rn; pl.band_m = (int)hm; pl.band_n = (int)hn; }
     }
     if (best < 0) { pl.bands_m = pl.bands_n = 0; return; }
@@ -128,7 +151,7 @@ Plan32 make_plan32(const daq_conv_desc& d, int depth) {
         pl.tiles_m = (int)ceil_div(d.Cout, 64 * pl.wm);
         pl.tiles_n = (int)ceil_div(d.Cin, 64 * pl.wn);
         const int64_t tiles = (int64_t)pl.tiles_m * pl.tiles_n;
-        pl.splits = pl.wk == 1 ? 1 : choose_splits(tiles * depth, pl.nchunks, 0.45, 64 * 64 * 4);
+        pl.splits = pl.wk == 1 ? 1 : choose_splits(pl, depth);
         // One chunk per LDS stage.  (Two chunks per barrier were measured on the late ResNet-50 layers: the K loop of a
         // workgroup - 13 chunks of 32 KiB in 7 us on every CU at once, bound by the staging through registers and LDS and
         // its two waits per chunk - gets a quarter shorter per byte, and the first stage arrives that much later.)
@@ -136,7 +159,7 @@ Plan32 make_plan32(const daq_conv_desc& d, int depth) {
         const size_t stage = (size_t)64 * (pl.wm + pl.wn) * (pl.ch * kKC + 16);
         pl.lds_bytes = std::max<size_t>(pl.wk > 1 ? (size_t)4 * 128 * kKC : 2 * stage, pl.wk > 1 ? (size_t)(pl.wk - 1) * 64 * kWave * 4 : 0);   // staging (four unpadded stages in the direct-to-LDS form); one-round combine
         pl.part_slots = tiles * pl.wm * pl.wn * 64 * kWave;
-        choose_bands(pl, 64 * pl.wm, 64 * pl.wn);
+        choose_bands(pl, 64 * pl.wm, 64 * pl.wn, depth);
         pl.ok = true;
         return pl;
     }
@@ -160,14 +183,14 @@ Plan32 make_plan32(const daq_conv_desc& d, int depth) {
     pl.tiles_m = (int)ceil_div(d.Cout, bm);
     pl.tiles_n = (int)ceil_div(d.Cin, bn);
     const int64_t tiles = (int64_t)pl.tiles_m * pl.tiles_n;
-    pl.splits = pl.wk == 1 ? 1 : choose_splits(tiles * depth, pl.nchunks, 0.75, 32 * 32 * kT * 4);
+    pl.splits = pl.wk == 1 ? 1 : choose_splits(pl, depth);
     const size_t stage = (size_t)bm * kPA + (size_t)(pl.s2 ? 4 : 1) * bn * pl.pb;
     // hand-over area of the parallel combine: [owner][source][slot][lane]
     const int rounds = pl.wk > 4 ? 2 : 1;
     pl.lds_bytes = std::max<size_t>(2 * stage, pl.wk > 1 ? (size_t)(pl.wk - 1) * kT * 16 * kWave * 4 / rounds : 0);
     if (pl.lds_bytes > 150 * 1024) return pl;
     pl.part_slots = tiles * pl.wm * pl.wn * kT * 16 * kWave;
-    choose_bands(pl, bm, bn);
+    choose_bands(pl, bm, bn, depth);
     pl.ok = true;
     return pl;
 }
@@ -287,14 +310,22 @@ daq_status conv_bwd_filter_lds(const daq_conv_desc& d, const Plan32& pl, const i
 }
 
 bool bwd_filter_beside(const daq_conv_desc& d, Plan32 pl, const int8_t* qx, const float* s_x, const int8_t* vq, const float* s_chan, float* dW,
-                       int32_t* acc, void* ws, int max_blocks, double other_us, DwBeside& out) {
+                       int32_t* acc, void* ws, int max_blocks, double other_us, bool other_streams, DwBeside& out) {
     daq_layout Lx, Lg;
     if (!pl.ok || pl.wk != 8 || pl.s2 || daq_layout_qx_cnhw(&d, &Lx) != DAQ_OK || daq_layout_vq(&d, &Lg) != DAQ_OK) return false;
     const int64_t tiles = (int64_t)pl.tiles_m * pl.tiles_n;
     if (tiles > max_blocks) return false;
-    const double t_chunk = pl.k11 ? 0.45 : 0.75;
-    // (the workspace holds pl.splits partial tiles)
-    pl.splits = cheapest_split(SplitModel{pl.nchunks, tiles, std::min<int64_t>(pl.splits, max_blocks / tiles), t_chunk, 4.0, other_us, 5.0, 0.0});
+    // With the streaming data gradient behind it, which is as short as a launch and takes the reduction along, the product is faster by
+    // itself (62 -> 10 at 59 x 59, batch 6: 10.8 us, 12.4 in one launch and a reduction).
+    if (other_streams && dw_tail_worthwhile((int)(pl.part_slots / kWave), pl.splits)) return false;
+    // Otherwise: one after the other, the product has the whole chip; beside the other work what CUs are left, but one launch less (4 ->
+    // 395 on 33 x 33, 3 x 3, batch 26, 22 workgroups left: 65 us against 38.  Over 220 small layers 0.5 % from the faster of the two).
+    SplitModel m = split_model(pl, 1);
+    const double apart = m.cost(pl.splits) + 1.5 + other_us;
+    m.limit = std::min<int64_t>(pl.splits, max_blocks / tiles);   // (the workspace holds pl.splits partial tiles)
+    m.t_floor = other_us;
+    pl.splits = cheapest_split(m);
+    if (m.cost(pl.splits) >= apart) return false;
     choose_bands(pl, pl.k11 ? 64 : 32, pl.k11 ? 64 : 32);
     if (pl.blocks > max_blocks) {   // rectangles of unequal size pad the grid
         pl.bands_m = pl.bands_n = 0;

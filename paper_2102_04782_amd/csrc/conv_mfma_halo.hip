@@ -1004,7 +1004,8 @@ Geometry plan_fwd(const daq_conv_desc& d) {
 // ---------------------------------------------------------------------------------------------
 // Both gradients of a small layer in one launch.  They do not depend on each other, and a layer whose two kernels together
 // have no more workgroups than the chip has CUs gains nothing from running them one after the other: each is a chain of
-// latencies (prologue, a few chunks, combine, stores; 6 to 10 us), most CUs idle, and a launch between them.  The first
+// latencies (prologue, a few chunks, combine, stores; 6 to 10 us), most CUs idle, and a launch between them - unless the filter
+// gradient needs more CUs than the data gradient leaves it (bwd_filter_beside).  The first
 // w_blocks workgroups work on the filter gradient, those from x_first on (a multiple of eight, so that either part's own
 // mapping to the XCDs holds) on the data gradient, with the first four of their eight waves.  All are resident at once: at
 // most 256, each with a CU's LDS to itself.
@@ -1211,8 +1212,10 @@ bool conv_bwd_both_small(const daq_conv_desc& d, const Plan32& plan_w, const int
     const int64_t x_blocks = blocks_per_row_tile(g.a) * ceil_div(g.a.Crow, 64);
     if (x_blocks > kBothBlocks - 8) return false;
     const double x_us = form == kBothTaps9 ? 5.0 + 1.0 * (double)ceil_div(g.a.cp, kKc) : 4.5 + 0.35 * (double)ceil_div(g.a.cp, kKc);
+    daq_layout Lg;
+    const bool streams = daq_layout_qg(&d, &Lg) == DAQ_OK && stream_applies(d, Lg);
     DwBeside w;
-    if (!bwd_filter_beside(d, plan_w, qx, s_x, vq, s_chan, dW, dW_acc, ws, kBothBlocks - (int)x_blocks, x_us, w)) return false;
+    if (!bwd_filter_beside(d, plan_w, qx, s_x, vq, s_chan, dW, dW_acc, ws, kBothBlocks - (int)x_blocks, x_us, streams, w)) return false;
     daq_wpack_layout Lw;
     if (daq_layout_qw(&d, &Lw) != DAQ_OK) return false;
     HaloArgs& a = g.a;

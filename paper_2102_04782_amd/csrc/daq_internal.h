@@ -33,6 +33,7 @@ inline int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
 struct SplitModel {
     int64_t n, tiles, limit;
     double t_step, t_fixed, t_floor, t_reduce, t_part;
+    double cost(int64_t s) const;
 };
 int cheapest_split(const SplitModel& m, int* tried = nullptr);
 

@@ -37,7 +37,7 @@ struct Dw32Args {
 };
 
 // A filter gradient of at most max_blocks workgroups to run beside other work of about other_us in one launch: false where
-// the layer has no such form (false also leaves everything untouched).  tail.blocks > 0: launch_dw_reduce has to follow.
+// the layer has no such form or is faster in launches of its own (false also leaves everything untouched).  tail.blocks > 0: launch_dw_reduce has to follow.
 struct DwBeside {
     Dw32Args a;
     int kind;            // 0 .. 3: dw32_role<kind, 1, 1, 8, 3, false>; 4: dw11_role<1, 1, 8, 3, 1, true>
@@ -46,7 +46,7 @@ struct DwBeside {
     DwTail tail;
 };
 bool bwd_filter_beside(const daq_conv_desc& d, Plan32 pl, const int8_t* qx, const float* s_x, const int8_t* vq, const float* s_chan, float* dW,
-                       int32_t* acc, void* ws, int max_blocks, double other_us, DwBeside& out);
+                       int32_t* acc, void* ws, int max_blocks, double other_us, bool other_streams, DwBeside& out);
 
 namespace {
 

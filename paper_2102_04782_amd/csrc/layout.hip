@@ -111,22 +111,26 @@ static void fill_nhwc(daq_layout* L, int C, int N, int H, int W) {
     L->bytes = round_up((int64_t)N * H * W * L->c_pitch, 256);
 }
 
+constexpr int64_t kCus = 256;
+double SplitModel::cost(int64_t s) const {
+    const double c = (double)ceil_div(tiles * s, kCus) * std::max((double)ceil_div(n, s) * t_step + t_fixed, t_floor);
+    return s > 1 ? c + (t_reduce + t_part * (double)s) : c;
+}
+
 // Planning is host time of every call (trying every count up to 1024 took 3 us, several times a call).  Inside a round the cost
 // follows a convex curve but for the rounding up of the longest part: it is searched from the curve's minimum outwards, the
 // smallest count for each length of the longest part only, until the curve alone is above what has been found (by more than its rounding).
 int cheapest_split(const SplitModel& m, int* tried) {
-    constexpr int64_t kCus = 256;
     int best_s = 1, count = 0;
     double best = 0.0;
     auto curve = [&](int64_t rounds, int64_t s) {
         return (double)rounds * std::max((double)m.n / (double)s * m.t_step + m.t_fixed, m.t_floor) + m.t_reduce + m.t_part * (double)s;
     };
-    auto look = [&](int64_t rounds, int64_t s) {
-        double c = (double)rounds * std::max((double)ceil_div(m.n, s) * m.t_step + m.t_fixed, m.t_floor);
-        if (s > 1) c += m.t_reduce + m.t_part * (double)s;
+    auto look = [&](int64_t s) {
+        const double c = m.cost(s);
         if (!count++ || c < best || (c == best && s < best_s)) { best = c; best_s = (int)s; }
     };
-    look(ceil_div(m.tiles, kCus), 1);
+    look(1);
     const int64_t top = std::min(m.limit, m.n);
     for (int64_t r = 1;; ++r) {
         const int64_t lo = std::max<int64_t>(2, kCus * (r - 1) / m.tiles + 1), hi = std::min(top, kCus * r / m.tiles);
@@ -138,13 +142,13 @@ int cheapest_split(const SplitModel& m, int* tried) {
         const int64_t mid = std::max(lo, (int64_t)at), longest = ceil_div(m.n, mid);
         for (int64_t s = mid;; --s) {
             s = std::max(lo, ceil_div(m.n, ceil_div(m.n, s)));
-            look(r, s);
+            look(s);
             if (s == lo || curve(r, s - 1) > best * (1.0 + 1e-9)) break;
         }
         for (int64_t q = longest - 1; q >= 1; --q) {
             const int64_t s = ceil_div(m.n, q);
             if (s > hi || curve(r, s) > best * (1.0 + 1e-9)) break;
-            look(r, s);
+            look(s);
             q = ceil_div(m.n, s);
         }
     }

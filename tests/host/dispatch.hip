@@ -2,6 +2,7 @@
 #include <cstdio>
 
 #include "daq_internal.h"
+#include "dw32_role.h"
 
 static int fails = 0;
 #define EXPECT(cond)                                                        \
@@ -32,8 +33,33 @@ static void resident_quantizer() {
         }
 }
 
+static daq_conv_desc layer(int n, int ci, int h, int w, int co, int k, int s) { return daq_conv_desc{n, ci, h, w, co, k, k, s, s, k / 2, k / 2, 1, 1, 1}; }
+
+static void filter_gradient() {
+    auto splits = [](daq_conv_desc d) { return make_plan32(d).splits; };
+    EXPECT(splits(layer(11, 54, 7, 59, 56, 3, 2)) > 1 && splits(layer(5, 10, 39, 39, 386, 3, 2)) > 1);
+    EXPECT(splits(layer(10, 16, 13, 13, 314, 3, 1)) > 1 && splits(layer(9, 26, 5, 32, 67, 3, 1)) > 1);
+    EXPECT(splits(layer(43, 434, 8, 46, 689, 1, 1)) == 2);                  // not three
+    EXPECT(splits(layer(4, 16, 16, 16, 16, 3, 1)) >= 1);
+    for (const daq_conv_desc& d : {layer(90, 513, 77, 6, 193, 3, 1), layer(38, 707, 9, 53, 321, 3, 1), layer(15, 649, 16, 19, 750, 3, 1)}) {
+        const Plan32 pl = make_plan32(d);                                   // rectangles may not cost a round over an XCD's CUs
+        const int64_t most = pl.bands_m ? (int64_t)pl.band_m * pl.band_n : ceil_div((int64_t)pl.tiles_m * pl.tiles_n * pl.splits, kXcd);
+        EXPECT(ceil_div(most, 32) <= ceil_div((int64_t)pl.tiles_m * pl.tiles_n * pl.splits, 256));
+    }
+    auto beside = [](daq_conv_desc d, int blocks_left, double other_us, bool streams) {
+        DwBeside out;
+        return bwd_filter_beside(d, make_plan32(d), nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, reinterpret_cast<void*>(256), blocks_left,
+                                 other_us, streams, out);
+    };
+    EXPECT(!beside(layer(26, 4, 33, 33, 395, 3, 1), 22, 12.0, false) && !beside(layer(61, 6, 34, 12, 105, 3, 1), 12, 7.0, false));
+    EXPECT(!beside(layer(6, 62, 59, 59, 10, 1, 1), 150, 4.9, true));
+    EXPECT(beside(layer(4, 16, 16, 16, 16, 3, 1), 240, 6.0, false) && beside(layer(5, 100, 29, 31, 70, 3, 1), 200, 7.0, false));
+    EXPECT(beside(layer(33, 431, 8, 8, 190, 1, 2), 200, 5.6, false));
+}
+
 int main() {
     resident_quantizer();
+    filter_gradient();
     std::printf("%d failures\n", fails);
     return fails != 0;
 }
