@@ -578,10 +578,12 @@ __global__ __launch_bounds__(64 * WAVES) void k_dw_taps(DwArgs p, TapTable tt) {
         }
     };
 
-    // Whole rounds of the ring, then what has been loaded by then.  Every step of a round issues the same loads (past the end the last
-    // step's again, which the caches absorb): with a condition around them the compiler cannot count what is in flight
-    // and waits for everything in every step, the latency of memory.  (With the split count below: 3 -> 96 7 x 7 stride 2 at 15 x 15,
-    // batch 7, 48.8 -> 11.2 us; 32 -> 384 5 x 5 at 29 x 32 97 -> 25; 176 -> 128 5 x 5 at 27 x 31, batch 28, 386 -> 118.)
+    // Whole rounds of the ring, every step of which issues the same loads: with a condition around them the compiler cannot count what
+    // is in flight and waits for everything in every step, the latency of memory.  (With the split count below: 3 -> 96 7 x 7
+    // stride 2 at 15 x 15, batch 7, 48.8 -> 11.2 us; 32 -> 384 5 x 5 at 29 x 32 97 -> 25; 176 -> 128 5 x 5 at 27 x 31, batch 28, 386
+    // -> 118.)  What is left, fewer than two rounds - in a small layer all there is - loads just what it needs: repeating the last
+    // step's byte-aligned loads instead costs more than the waits (76 -> 22 1 x 7 stride 2 at 9 x 9, batch 2: 18.4 -> 13.7 us; 925 ->
+    // 424 1 x 7 at 13 x 13, batch 7, 73 -> 66).
     auto multiply = [&](int u) {
 #pragma unroll
         for (int t = 0; t < NT; ++t)
@@ -589,25 +591,54 @@ __global__ __launch_bounds__(64 * WAVES) void k_dw_taps(DwArgs p, TapTable tt) {
             for (int m = 0; m < 4; ++m)
                 acc[m][t] = __builtin_amdgcn_mfma_i32_16x16x64_i8(ra[u][m], rb[u][t], acc[m][t], 0, 0, 0);
     };
-    if (s_begin < s_end) {
+    int base = s_begin;
+    if constexpr (WAVES == 4) {
+        if (s_end - s_begin >= 2 * PFD) {   // uniform per wave, as all conditions below
+#pragma unroll
+            for (int i = 0; i < PFD; ++i) {
+                load_step(s_begin + i, i);
+                __builtin_amdgcn_sched_barrier(0);   // keep the steps in program order
+            }
+            for (; base + 2 * PFD <= s_end; base += PFD) {
+#pragma unroll
+                for (int u = 0; u < PFD; ++u) {
+                    multiply(u);
+                    load_step(base + u + PFD, u);
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+            }
+        } else {
+#pragma unroll
+            for (int i = 0; i < PFD; ++i)
+                if (s_begin + i < s_end) load_step(s_begin + i, i);
+        }
+#pragma unroll
+        for (int u = 0; u < PFD; ++u)
+            if (base + u < s_end) {
+                multiply(u);
+                if (base + PFD + u < s_end) load_step(base + PFD + u, u);
+            }
+#pragma unroll
+        for (int u = 0; u < PFD; ++u)
+            if (base + PFD + u < s_end) multiply(u);
+    } else if (s_begin < s_end) {   // eight waves have no registers left for that; past the end they load the last step again, once at most
 #pragma unroll
         for (int i = 0; i < PFD; ++i) {
             load_step(min(s_begin + i, s_end - 1), i);
-            __builtin_amdgcn_sched_barrier(0);   // keep the steps in program order
-        }
-    }
-    int base = s_begin;
-    for (; base + PFD < s_end; base += PFD) {
-#pragma unroll
-        for (int u = 0; u < PFD; ++u) {
-            multiply(u);
-            load_step(min(base + u + PFD, s_end - 1), u);
             __builtin_amdgcn_sched_barrier(0);
         }
-    }
+        for (; base + PFD < s_end; base += PFD) {
 #pragma unroll
-    for (int u = 0; u < PFD; ++u)
-        if (base + u < s_end) multiply(u);   // uniform per wave
+            for (int u = 0; u < PFD; ++u) {
+                multiply(u);
+                load_step(min(base + u + PFD, s_end - 1), u);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < PFD; ++u)
+            if (base + u < s_end) multiply(u);
+    }
 
     const float sx = *p.s_x / 127.0f;
     const int T = tt.T;
