@@ -1674,22 +1674,24 @@ static_assert(kAbsmaxBlocksX + kAbsmaxBlocksW + 8 <= kFwdWsFree && kFwdWsFree + 
 // A wave's work is serial, some 100 instructions a unit.  While the chip holds a wave of every workgroup at once, fewer units to a
 // thread are faster (16 channels of 832 units: 7.2, 7.4, 8.2, 11.0 us with 2, 4, 8, 16); from there on the form that keeps the most
 // waves on a CU, which takes 24 of 2 to 8 units and 16 of 16 (1024 channels of 5289 units, whole call: 54.9 us as 12 waves of 8
-// units, two workgroups a CU; 60.8 as 8 of 16, 75.3 as 6 of 16), of equals the one with fewer dead units.  From five waves on they
+// units, two workgroups a CU; 60.8 as 8 of 16, 75.3 as 6 of 16), of equals the one whose waves have less to do, then the one with fewer
+// slots (1240 channels of 2401 units: 8 waves of 8, five of them in use, 33 us; 12 of 4 35).  From five waves on they
 // come in fours, one to a SIMD: a SIMD with a wave more than the others sets the time (546 channels of 14256 units: 67.5 us with 14
 // waves, 59.3 with 16).  Over 528 sizes the choice is 0.7 % from the fastest form, at most 10 %.
 ResidentForm resident_form(int C, int64_t units) {
     constexpr int kUnits[4] = {2, 4, 8, 16}, kHeld[4] = {24, 24, 24, 16};
     ResidentForm best{16, 16};
-    int best_held = 0;
+    int64_t best_held = 0, best_work = 0;
     for (int i = 0; i < 4; ++i) {
         int64_t w = ceil_div(units, kUnits[i] * kWave);
         if (w > 16) continue;
         if (w > 4) w = round_up(w, 4);
-        const int per_cu = kHeld[i] / (int)w, held = per_cu * (int)w;
+        const int64_t per_cu = kHeld[i] / w, held = per_cu * w, work = w * ceil_div(units, w * kWave);
         if (i < 3 && C <= 256 * per_cu) return ResidentForm{kUnits[i], (int)w};
-        if (held > best_held || (held == best_held && kUnits[i] * w <= best.nu * best.waves)) {
+        if (held > best_held || (held == best_held && (work < best_work || (work == best_work && kUnits[i] * w <= best.nu * best.waves)))) {
             best = ResidentForm{kUnits[i], (int)w};
             best_held = held;
+            best_work = work;
         }
     }
     return best;
@@ -1701,13 +1703,15 @@ ResidentForm resident_form(int C, int64_t units) {
 bool fold_in_packing(int64_t workgroups) { return workgroups <= 4096; }
 
 // A workgroup per channel leaves CUs idle where channels are few, and a large one takes 20 us and more: three sweeps of a tensor
-// of a few channels take 15 (16 channels of 15466 units 27.5 us, the sweeps 15.8; 64 of 8000: 19.5 and 18.4; 96 of 13200: 31 and 28; 128 of 9460: 27.9 and 29.3).
+// of a few channels take 15 (16 channels of 15466 units 27.5 us, the sweeps 15.8; 64 of 8000: 19.5 and 18.4; 96 of 13200: 31 and 28; 128
+// of 9460: 27.9 and 29.3; these of padded planes that are not whole units, other planes are quicker: 64 of 8000 17.8 and 17.2, 85 of 6528
+// without padding 15.1 and 18.1, 97 of 14196 25.6 and 29).
 // Channels of more than 8 Ki units run one to a CU, and a second round for a few of them does not pay either (268 of 11952 units in
 // bfloat16: 46 and 43 us).  (512 channels of 12544 units in two rounds are level with the sweeps, 59 + 27 us against 31 + 50 + 8, but
 // save a launch.)
-bool resident_pays(int C, int64_t units) {
+bool resident_pays(int C, int64_t units, bool ragged) {
     if (units > 8 * 1024 && C > 256 && C < 288) return false;
-    return units <= 6 * 1024 || C >= (units <= 8 * 1024 ? 96 : 128);
+    return units <= 6 * 1024 || C >= (ragged ? units <= 8 * 1024 ? 96 : 128 : units <= 8 * 1024 ? 64 : 80);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -1883,16 +1887,16 @@ daq_status quantize_grad_impl(const daq_conv_desc* desc, const T* dY, float* s_s
     const int res_upp = res_v4 ? (HW + 3) / 4 : HW;
     const int64_t res_units = (int64_t)N * res_upp;
     const ResidentForm res = resident_form(C, res_units);
+    // planes without padding between rows and images hold element m at byte lead + m
+    const bool res_flat = res_v4 && Lv.row_pitch == Lv.W && Lv.img_rows == Lv.H && (Lv.lead & 3) == 0 && (Lv.plane_pitch & 3) == 0 &&
+                          Lv.lead + (int64_t)N * HW <= Lv.plane_pitch;
     const bool resident_ok = scheme == DAQ_SCHEME_DAQ && res_units <= 16 * 1024 && Lv.plane_pitch <= kResidentMaxLds &&
                              (Lv.plane_pitch & 15) == 0 && (Lv.chan_pitch & 15) == 0;
-    if (!given && resident_ok && (schedule == DAQ_SCHEDULE_CHANNEL_RESIDENT || (schedule == DAQ_SCHEDULE_AUTO && resident_pays(C, res_units)))) {
+    if (!given && resident_ok && (schedule == DAQ_SCHEDULE_CHANNEL_RESIDENT || (schedule == DAQ_SCHEDULE_AUTO && resident_pays(C, res_units, HW % 4 != 0 && !res_flat)))) {
         ws.slabs = 1;   // one |g|max partial per channel
         ws.part_n = C;
         const ResArgs ra{make_fastdiv((uint32_t)res_upp), make_fastdiv((uint32_t)Wo), N, C, HW, k, A, lambda, keys};
         const ClipArgs ca{k, A, lambda, s_state, s_chan, cls, stats};
-        // planes without padding between rows and images hold element m at byte lead + m
-        const bool res_flat = res_v4 && Lv.row_pitch == Lv.W && Lv.img_rows == Lv.H && (Lv.lead & 3) == 0 && (Lv.plane_pitch & 3) == 0 &&
-                              Lv.lead + (int64_t)N * HW <= Lv.plane_pitch;
         const size_t lds = res_flat ? 0 : (size_t)Lv.plane_pitch;
         const dim3 rgrid((unsigned)round_up(C, kXcd));
 #define DAQ_RES_LAUNCH(S, V, NUV, FL, TL)                                                                            \

@@ -13,11 +13,12 @@ static int fails = 0;
 using namespace daq;
 
 static void resident_quantizer() {
-    EXPECT(!resident_pays(16, 22 * 703));                                   // 22 images of 53 x 53, 16 channels
-    EXPECT(!resident_pays(4, 8 * 1561) && !resident_pays(30, 60 * 160));
-    EXPECT(!resident_pays(96, 66 * 200));                                   // 66 images of 114 x 7
-    EXPECT(!resident_pays(268, 83 * 144));                                  // a second round of twelve workgroups
-    EXPECT(resident_pays(16, 5000) && resident_pays(128, 9460) && resident_pays(512, 12544) && resident_pays(300, 14000));
+    EXPECT(!resident_pays(16, 22 * 703, true));                             // 22 images of 53 x 53, 16 channels
+    EXPECT(!resident_pays(4, 8 * 1561, true) && !resident_pays(30, 60 * 160, false));
+    EXPECT(!resident_pays(96, 66 * 200, true));                             // 66 images of 114 x 7
+    EXPECT(resident_pays(85, 102 * 64, false) && resident_pays(97, 84 * 169, false));
+    EXPECT(!resident_pays(268, 83 * 144, false));                           // a second round of twelve workgroups
+    EXPECT(resident_pays(16, 5000, true) && resident_pays(128, 9460, true) && resident_pays(512, 12544, false) && resident_pays(300, 14000, true));
     EXPECT(!fold_in_packing(672 * 25) && fold_in_packing(192 * 4));         // depthwise: 672 channels of 38 x 38, batch 34
     auto is = [](int C, int64_t units, int nu, int waves) {
         const ResidentForm f = resident_form(C, units);
@@ -25,6 +26,7 @@ static void resident_quantizer() {
     };
     EXPECT(is(546, 44 * 324, 16, 16) && is(328, 38 * 361, 16, 16));         // not 14 waves
     EXPECT(is(678, 108 * 49, 8, 12) && is(1024, 5289, 8, 12));              // not 6 waves of 16 units
+    EXPECT(is(1240, 2401, 8, 8));                                           // five of eight units in use, not four of four on 12 waves
     EXPECT(is(2048, 2795, 4, 12) && is(2048, 7998, 16, 8) && is(256, 7998, 8, 16) && is(700, 9460, 16, 12));
     for (int C : {1, 3, 200, 257, 700, 3000})
         for (int64_t units = 1; units <= 16 * 1024; ++units) {
