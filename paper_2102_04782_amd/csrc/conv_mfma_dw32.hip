@@ -104,6 +104,24 @@ int choose_splits(const Plan32& pl, int depth) {
     return s;
 }
 
+// The split where a later kernel takes the reduction along, from 33 splits on (dw_tail_worthwhile): its launch, 2.8 of its 3.3 us, is
+// saved.  (7 -> 106, 3 x 3 on 99 x 12, batch 30, both gradients: 23 us with 25 splits and a reduction, 21 with 64.)
+int choose_splits_tail(const Plan32& pl) {
+    const SplitModel m = split_model(pl, 1);
+    const int64_t top = std::min(m.limit, m.n);
+    if (pl.wk == 1 || pl.splits > 32 || top <= 32 || !dw_tail_worthwhile((int)(pl.part_slots / kWave), 33)) return pl.splits;
+    int best_s = pl.splits;
+    double best = m.cost(pl.splits) + 2.8;
+    int64_t s = 33;
+    for (int i = 0; i < 3 && s <= top; ++i) {   // the next lengths of the longest part: from there on partial tiles cost more than they save
+        const int64_t longest = ceil_div(m.n, s);
+        if (m.cost(s) < best) { best = m.cost(s); best_s = (int)s; }
+        if (longest <= 1) break;
+        s = ceil_div(m.n, longest - 1);
+    }
+    return best_s;
+}
+
 // Rectangles per split for 1, 2 or 4 splits (8, 4 or 2 XCDs share a split): the cut of the tile grid that makes an
 // XCD touch the fewest operand rows, rows of the two operands weighted by their tile heights - unless its largest rectangle takes
 // a round over the XCD's 32 CUs more than the tiles dealt out evenly (513 -> 193, 3 x 3 on 77 x 6, batch 90: 238 workgroups in
@@ -159,6 +177,7 @@ Plan32 make_plan32(const daq_conv_desc& d, int depth) {
         const size_t stage = (size_t)64 * (pl.wm + pl.wn) * (pl.ch * kKC + 16);
         pl.lds_bytes = std::max<size_t>(pl.wk > 1 ? (size_t)4 * 128 * kKC : 2 * stage, pl.wk > 1 ? (size_t)(pl.wk - 1) * 64 * kWave * 4 : 0);   // staging (four unpadded stages in the direct-to-LDS form); one-round combine
         pl.part_slots = tiles * pl.wm * pl.wn * 64 * kWave;
+        pl.splits_tail = choose_splits_tail(pl);
         choose_bands(pl, 64 * pl.wm, 64 * pl.wn, depth);
         pl.ok = true;
         return pl;
@@ -190,6 +209,7 @@ Plan32 make_plan32(const daq_conv_desc& d, int depth) {
     pl.lds_bytes = std::max<size_t>(2 * stage, pl.wk > 1 ? (size_t)(pl.wk - 1) * kT * 16 * kWave * 4 / rounds : 0);
     if (pl.lds_bytes > 150 * 1024) return pl;
     pl.part_slots = tiles * pl.wm * pl.wn * kT * 16 * kWave;
+    pl.splits_tail = choose_splits_tail(pl);
     choose_bands(pl, bm, bn, depth);
     pl.ok = true;
     return pl;
@@ -273,16 +293,22 @@ daq_status launch32(const Plan32& pl, const Dw32Args& a, int wq4, hipStream_t st
 }  // namespace
 
 size_t bwd_filter_lds_ws_bytes(const Plan32& pl, int depth) {
-    if (!pl.ok || pl.splits == 1) return 0;
-    return (size_t)round_up(pl.part_slots * pl.splits * depth * 4, 256);
+    const int splits = depth == 1 ? std::max(pl.splits, pl.splits_tail) : pl.splits;
+    if (!pl.ok || splits == 1) return 0;
+    return (size_t)round_up(pl.part_slots * splits * depth * 4, 256);
 }
 
 int64_t bwd_filter_lds_row_bytes(const Plan32& pl) { return (int64_t)(pl.nchunks - 1) * kKC + (pl.k11 ? kKC : 16 * pl.b_units); }
 
-daq_status conv_bwd_filter_lds(const daq_conv_desc& d, const Plan32& pl, const int8_t* qx, const float* s_x, const int8_t* vq,
+daq_status conv_bwd_filter_lds(const daq_conv_desc& d, const Plan32& plan, const int8_t* qx, const float* s_x, const int8_t* vq,
                                const float* s_chan, float* dW, int32_t* acc, void* ws, hipStream_t st, DwTail* defer, bool bf16, const DwDepth* dp) {
     if (defer) defer->blocks = 0;
     const int depth = dp ? dp->kD : 1;
+    Plan32 pl = plan;
+    if (defer && pl.splits_tail != pl.splits) {
+        pl.splits = pl.splits_tail;
+        choose_bands(pl, pl.k11 ? 64 : 32, pl.k11 ? 64 : 32);
+    }
     if (!pl.ok) return DAQ_ERR_UNSUPPORTED;
     daq_layout Lx, Lg;
     if (daq_layout_qx_cnhw(&d, &Lx) != DAQ_OK || daq_layout_vq(&d, &Lg) != DAQ_OK) return DAQ_ERR_INVALID_ARG;
@@ -318,10 +344,11 @@ bool bwd_filter_beside(const daq_conv_desc& d, Plan32 pl, const int8_t* qx, cons
     // With the streaming data gradient behind it, which is as short as a launch and takes the reduction along, the product is faster by
     // itself (62 -> 10 at 59 x 59, batch 6: 10.8 us, 12.4 in one launch and a reduction).
     if (other_streams && dw_tail_worthwhile((int)(pl.part_slots / kWave), pl.splits)) return false;
+    const bool rides = dw_tail_worthwhile((int)(pl.part_slots / kWave), pl.splits_tail);
     // Otherwise: one after the other, the product has the whole chip; beside the other work what CUs are left, but one launch less (4 ->
     // 395 on 33 x 33, 3 x 3, batch 26, 22 workgroups left: 65 us against 38.  Over 220 small layers 0.5 % from the faster of the two).
     SplitModel m = split_model(pl, 1);
-    const double apart = m.cost(pl.splits) + 1.5 + other_us;
+    const double apart = m.cost(pl.splits_tail) - (rides ? 2.8 : 0.0) + 1.5 + other_us;
     m.limit = std::min<int64_t>(pl.splits, max_blocks / tiles);   // (the workspace holds pl.splits partial tiles)
     m.t_floor = other_us;
     pl.splits = cheapest_split(m);

@@ -206,6 +206,7 @@ struct Plan32 {
     bool k11;             // 1 x 1 filter: the plain GEMM kernel
     bool s2;              // 3 x 3 filter at stride 2: four stride-phase planes per input channel
     int wm, wn, wk, splits, tiles_m, tiles_n, nchunks, pb, b_units, ch;
+    int splits_tail;      // K splits where the reduction can ride along in the next kernel (with `defer`)
     int bands_m, bands_n, band_m, band_n;   // rectangles of the tile grid per K split when there are 1, 2 or 4 splits (else 0)
     int64_t blocks;       // workgroups of the launch
     size_t lds_bytes;
@@ -218,7 +219,7 @@ int64_t bwd_filter_lds_row_bytes(const Plan32& pl);   // read of an activation r
 // With `defer`, a K-split launch leaves its last stage (sum of the partial tiles, de-quantization) undone and
 // describes it in *defer (blocks == 0: nothing is left) for a later kernel's extra workgroups, see dw_tail.h.
 struct DwTail;
-daq_status conv_bwd_filter_lds(const daq_conv_desc& d, const Plan32& pl, const int8_t* qx, const float* s_x, const int8_t* vq,
+daq_status conv_bwd_filter_lds(const daq_conv_desc& d, const Plan32& plan, const int8_t* qx, const float* s_x, const int8_t* vq,
                                const float* s_chan, float* dW, int32_t* acc, void* ws, hipStream_t st,
                                DwTail* defer = nullptr, bool bf16 = false, const DwDepth* dp = nullptr);
 

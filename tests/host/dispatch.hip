@@ -48,6 +48,8 @@ static void filter_gradient() {
         const int64_t most = pl.bands_m ? (int64_t)pl.band_m * pl.band_n : ceil_div((int64_t)pl.tiles_m * pl.tiles_n * pl.splits, kXcd);
         EXPECT(ceil_div(most, 32) <= ceil_div((int64_t)pl.tiles_m * pl.tiles_n * pl.splits, 256));
     }
+    EXPECT(make_plan32(layer(30, 7, 99, 12, 106, 3, 1)).splits_tail > 32 && make_plan32(layer(79, 53, 18, 18, 303, 1, 1)).splits_tail > 32);
+    EXPECT(make_plan32(layer(4, 16, 16, 16, 16, 3, 1)).splits_tail <= 6);   // six chunks
     auto beside = [](daq_conv_desc d, int blocks_left, double other_us, bool streams) {
         DwBeside out;
         return bwd_filter_beside(d, make_plan32(d), nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, reinterpret_cast<void*>(256), blocks_left,
