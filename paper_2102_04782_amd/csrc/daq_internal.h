@@ -166,7 +166,7 @@ daq_status quantize_forward(const daq_conv_desc& d, const float* X, int8_t* qx_n
 // `waves` waves, `nu` units to a thread.
 struct ResidentForm { int nu, waves; };
 ResidentForm resident_form(int C, int64_t units);
-bool resident_pays(int C, int64_t units, bool ragged);   // against the sweeps; ragged: padded planes that are not whole units
+bool resident_pays(int C, int64_t units, bool padded, bool tails, bool stochastic);   // tails: planes that are not whole units
 bool fold_in_packing(int64_t workgroups);   // whether those of a channel-major packing launch fold its scale themselves
 
 // clip_search.hip

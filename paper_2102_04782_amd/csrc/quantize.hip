@@ -1702,16 +1702,25 @@ ResidentForm resident_form(int C, int64_t units) {
 // fold and 30.8 with it; 672 of 38 x 38, batch 34, 16800: 38 and 48).
 bool fold_in_packing(int64_t workgroups) { return workgroups <= 4096; }
 
-// A workgroup per channel leaves CUs idle where channels are few, and a large one takes 20 us and more: three sweeps of a tensor
-// of a few channels take 15 (16 channels of 15466 units 27.5 us, the sweeps 15.8; 64 of 8000: 19.5 and 18.4; 96 of 13200: 31 and 28; 128
-// of 9460: 27.9 and 29.3; these of padded planes that are not whole units, other planes are quicker: 64 of 8000 17.8 and 17.2, 85 of 6528
-// without padding 15.1 and 18.1, 97 of 14196 25.6 and 29).
-// Channels of more than 8 Ki units run one to a CU, and a second round for a few of them does not pay either (268 of 11952 units in
-// bfloat16: 46 and 43 us).  (512 channels of 12544 units in two rounds are level with the sweeps, 59 + 27 us against 31 + 50 + 8, but
-// save a launch.)
-bool resident_pays(int C, int64_t units, bool ragged) {
+// A workgroup per channel leaves CUs idle where channels are few, and a large one takes 10 to 30 us; three sweeps of a tensor of a few
+// channels take 13 to 15.  What a unit costs the workgroup: finding its row where planes are padded, elements one by one where they are
+// not whole units, and twice that the random word of a stochastic code.  Level with the sweeps, by these and by thousands of units, at
+// (resident and sweeps in us)
+//   units         6.5 Ki                    9.5 Ki                    14 Ki
+//   plain         4: 10.8 and 12.7          4: 12.0 and 13.2          16 (1.04 of the sweeps)
+//   padded        4: 0.97 of them           32: 14.9 and 15.0         64 (1.00)
+//   both          32: 14.7 and 14.9         64 (1.04)                 96 (1.02)
+//   stochastic    16: 13.9 and 14.1         64: 17.6 and 18.6         80 (1.02)
+//   and padded    48: 15.5 and 16.2         80 (0.98)                 96 (1.01)
+//   and both      80 (0.95)                 96 (1.04)                 128 (1.01)
+// channels.  Channels of more than 8 Ki units run one to a CU, and a second round for a few of them does not pay either (268 of 11952
+// units in bfloat16: 46 and 43 us).  (512 channels of 12544 units in two rounds are level with the sweeps, 59 + 27 us against 31 + 50 + 8,
+// but save a launch.)
+bool resident_pays(int C, int64_t units, bool padded, bool tails, bool stochastic) {
     if (units > 8 * 1024 && C > 256 && C < 288) return false;
-    return units <= 6 * 1024 || C >= (ragged ? units <= 8 * 1024 ? 96 : 128 : units <= 8 * 1024 ? 64 : 80);
+    constexpr int kChannels[] = {1, 1, 32, 64, 88, 112, 128};
+    const int size = units <= 8 * 1024 ? 0 : units <= 12 * 1024 ? 1 : 2;
+    return units <= 6 * 1024 || C >= kChannels[size + padded + tails + 2 * stochastic];
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -1892,7 +1901,7 @@ daq_status quantize_grad_impl(const daq_conv_desc* desc, const T* dY, float* s_s
                           Lv.lead + (int64_t)N * HW <= Lv.plane_pitch;
     const bool resident_ok = scheme == DAQ_SCHEME_DAQ && res_units <= 16 * 1024 && Lv.plane_pitch <= kResidentMaxLds &&
                              (Lv.plane_pitch & 15) == 0 && (Lv.chan_pitch & 15) == 0;
-    if (!given && resident_ok && (schedule == DAQ_SCHEDULE_CHANNEL_RESIDENT || (schedule == DAQ_SCHEDULE_AUTO && resident_pays(C, res_units, HW % 4 != 0 && !res_flat)))) {
+    if (!given && resident_ok && (schedule == DAQ_SCHEDULE_CHANNEL_RESIDENT || (schedule == DAQ_SCHEDULE_AUTO && resident_pays(C, res_units, !res_flat, HW % 4 != 0, stoch)))) {
         ws.slabs = 1;   // one |g|max partial per channel
         ws.part_n = C;
         const ResArgs ra{make_fastdiv((uint32_t)res_upp), make_fastdiv((uint32_t)Wo), N, C, HW, k, A, lambda, keys};

@@ -1,5 +1,6 @@
 // Rules of the dispatch at sizes where an earlier one cost time: each line a call that was measured slower than another form of it.
 #include <cstdio>
+#include <cstring>
 
 #include "daq_internal.h"
 #include "dw32_role.h"
@@ -13,12 +14,17 @@ static int fails = 0;
 using namespace daq;
 
 static void resident_quantizer() {
-    EXPECT(!resident_pays(16, 22 * 703, true));                             // 22 images of 53 x 53, 16 channels
-    EXPECT(!resident_pays(4, 8 * 1561, true) && !resident_pays(30, 60 * 160, false));
-    EXPECT(!resident_pays(96, 66 * 200, true));                             // 66 images of 114 x 7
-    EXPECT(resident_pays(85, 102 * 64, false) && resident_pays(97, 84 * 169, false));
-    EXPECT(!resident_pays(268, 83 * 144, false));                           // a second round of twelve workgroups
-    EXPECT(resident_pays(16, 5000, true) && resident_pays(128, 9460, true) && resident_pays(512, 12544, false) && resident_pays(300, 14000, true));
+    auto pays = [](int C, int64_t units, const char* kind) {                // p: padded planes, t: not whole units, s: stochastic codes
+        return resident_pays(C, units, std::strchr(kind, 'p'), std::strchr(kind, 't'), std::strchr(kind, 's'));
+    };
+    EXPECT(!pays(16, 22 * 703, "pts"));                                     // 22 images of 53 x 53, 16 channels
+    EXPECT(!pays(4, 8 * 1561, "pts") && !pays(30, 60 * 160, "s"));
+    EXPECT(!pays(96, 66 * 200, "pts"));                                     // 66 images of 114 x 7
+    EXPECT(pays(85, 102 * 64, "s") && pays(97, 84 * 169, "s"));
+    EXPECT(!pays(268, 83 * 144, "s"));                                      // a second round of twelve workgroups
+    EXPECT(pays(16, 5000, "pts") && pays(128, 9460, "pts") && pays(512, 12544, "s") && pays(300, 14000, "pts"));
+    EXPECT(pays(16, 9 * 729, "") && pays(25, 3 * 2475, "") && pays(12, 14 * 578, ""));   // frames of 27 x 27, 30 x 30 and 34 x 34
+    EXPECT(pays(4, 8000, "p") && pays(4, 8000, "t") && pays(32, 8000, "pt") && !pays(16, 9460, "pt") && !pays(4, 14272, ""));
     EXPECT(!fold_in_packing(672 * 25) && fold_in_packing(192 * 4));         // depthwise: 672 channels of 38 x 38, batch 34
     auto is = [](int C, int64_t units, int nu, int waves) {
         const ResidentForm f = resident_form(C, units);
