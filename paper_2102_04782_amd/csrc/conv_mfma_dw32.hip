@@ -346,9 +346,13 @@ bool bwd_filter_beside(const daq_conv_desc& d, Plan32 pl, const int8_t* qx, cons
     if (other_streams && dw_tail_worthwhile((int)(pl.part_slots / kWave), pl.splits)) return false;
     const bool rides = dw_tail_worthwhile((int)(pl.part_slots / kWave), pl.splits_tail);
     // Otherwise: one after the other, the product has the whole chip; beside the other work what CUs are left, but one launch less (4 ->
-    // 395 on 33 x 33, 3 x 3, batch 26, 22 workgroups left: 65 us against 38.  Over 220 small layers 0.5 % from the faster of the two).
+    // 395 on 33 x 33, 3 x 3, batch 26, 22 workgroups left: 65 us against 38).  Half the CUs and more are idle in such a launch, a chunk takes
+    // 0.6 us whatever the filter, and beginning and end are the longer ones of the two parts, 6.5 us (16 -> 16, 3 x 3 on 16 x 16, batch 4,
+    // six chunks: 10.3 us in one part, 12.7 in two and a reduction).  Over 220 small layers 0.6 % from the fastest split.
     SplitModel m = split_model(pl, 1);
     const double apart = m.cost(pl.splits_tail) - (rides ? 2.8 : 0.0) + 1.5 + other_us;
+    m.t_step = 0.6;
+    m.t_fixed = 6.5;
     m.limit = std::min<int64_t>(pl.splits, max_blocks / tiles);   // (the workspace holds pl.splits partial tiles)
     m.t_floor = other_us;
     pl.splits = cheapest_split(m);

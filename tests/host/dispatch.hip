@@ -65,6 +65,14 @@ static void filter_gradient() {
     EXPECT(!beside(layer(6, 62, 59, 59, 10, 1, 1), 150, 4.9, true));
     EXPECT(beside(layer(4, 16, 16, 16, 16, 3, 1), 240, 6.0, false) && beside(layer(5, 100, 29, 31, 70, 3, 1), 200, 7.0, false));
     EXPECT(beside(layer(33, 431, 8, 8, 190, 1, 2), 200, 5.6, false));
+    auto beside_splits = [](daq_conv_desc d, int blocks_left, double other_us) {
+        DwBeside out;
+        const bool ok = bwd_filter_beside(d, make_plan32(d), nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, reinterpret_cast<void*>(256),
+                                          blocks_left, other_us, false, out);
+        return ok ? out.a.splits : 0;
+    };
+    EXPECT(beside_splits(layer(4, 16, 16, 16, 16, 3, 1), 252, 4.9) == 1);   // six chunks: no reduction's launch for them
+    EXPECT(beside_splits(layer(4, 12, 25, 20, 20, 3, 1), 240, 4.9) > 1);    // 32 and more: shared out
 }
 
 int main() {
