@@ -91,10 +91,13 @@ SplitModel split_model(const Plan32& pl, int depth) {
 }
 
 // 1 x 1 filters hardly reuse an operand inside a workgroup, and with 3, 5, 6 or 7 splits every XCD reads nearly all of both (dw_block_map):
-// a chunk takes half as long again (434 -> 689 at 8 x 46, batch 43: 26.9 us with three splits, 20.2 with two).
+// a chunk takes half as long again (434 -> 689 at 8 x 46, batch 43: 26.9 us with three splits, 20.2 with two).  And a split has to save
+// what the reduction's launch takes the host, 2.5 us: networks of such small layers are enqueued more slowly than they run (384 -> 64 at
+// 14 x 14, batch 16: 10.1 us in one part, 8.8 in two launches, 5.7 and 7.4 on the host; 24 of 157 layers, 0.3 us each on the GPU).
 int choose_splits(const Plan32& pl, int depth) {
     const SplitModel m = split_model(pl, depth);
     int s = cheapest_split(m);
+    if (pl.k11 && m.cost(1) < m.cost(s) + 2.5) return 1;
     if (!pl.k11 || s < 3 || s == 4 || s > 7) return s;
     SplitModel scattered = m;
     scattered.t_step *= 1.5;

@@ -49,6 +49,8 @@ static void filter_gradient() {
     EXPECT(splits(layer(10, 16, 13, 13, 314, 3, 1)) > 1 && splits(layer(9, 26, 5, 32, 67, 3, 1)) > 1);
     EXPECT(splits(layer(43, 434, 8, 46, 689, 1, 1)) == 2);                  // not three
     EXPECT(splits(layer(4, 16, 16, 16, 16, 3, 1)) >= 1);
+    EXPECT(splits(layer(16, 384, 14, 14, 64, 1, 1)) == 1 && splits(layer(16, 64, 14, 14, 384, 1, 1)) == 1);   // a launch more for 1.3 us
+    EXPECT(splits(layer(16, 96, 56, 56, 24, 1, 1)) > 1);
     for (const daq_conv_desc& d : {layer(90, 513, 77, 6, 193, 3, 1), layer(38, 707, 9, 53, 321, 3, 1), layer(15, 649, 16, 19, 750, 3, 1)}) {
         const Plan32 pl = make_plan32(d);                                   // rectangles may not cost a round over an XCD's CUs
         const int64_t most = pl.bands_m ? (int64_t)pl.band_m * pl.band_n : ceil_div((int64_t)pl.tiles_m * pl.tiles_n * pl.splits, kXcd);
