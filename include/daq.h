@@ -221,11 +221,12 @@ daq_status daq_quantize_grad_scheme(const daq_conv_desc* desc, const float* dY, 
  *                     DAQ_SCHEDULE_EARLY_COPY    the counting sweep also writes vq under a guessed class
  *                     DAQ_SCHEDULE_CHANNEL_RESIDENT  one workgroup per channel keeps the channel in registers,
  *                                                so that statistics, count, decision and vq take ONE read of dY;
- *                                                a second launch writes qg.  For channels of at most 65536
- *                                                elements (N*Hout*Wout; 16384 where Hout*Wout is not a multiple
- *                                                of four or dY is not a 16-byte aligned fp32 tensor) whose int8
- *                                                plane is at most 96 KiB, under Algorithm 1's rule with an NHWC
- *                                                global copy; taken by default where it applies.
+ *                                                a second launch writes qg.  For channels of at most 16384
+ *                                                units of up to four elements of one plane (N*ceil(Hout*Wout/4);
+ *                                                planes of fewer than four elements count each) whose int8 plane
+ *                                                is at most 96 KiB, under Algorithm 1's rule, dY fp32 or bfloat16,
+ *                                                for NHWC and channel-major (depthwise) global copies.  AUTO takes
+ *                                                it up to 6144 units, and beyond for layers of enough channels.
  *                   A schedule the layer cannot take (the early copy needs Algorithm 1's rule, an NHWC
  *                   global copy and an unsplit channel-major layout with rows of even length) falls
  *                   back to three sweeps.
