@@ -177,7 +177,7 @@ size_t daq_workspace_bytes(daq_op op, const daq_conv_desc* desc);
  * Hyper-parameters of the paper: k = 1, A = 0.8, lambda = 0.3.
  *
  * Schedule (results do not depend on it, see daq_schedule): three sweeps over dY - statistics;
- * count + qg; vq.  For gradients of 8 Mi elements and more the second sweep also writes vq under a
+ * count + qg; vq.  For gradients of 4 Mi elements and more the second sweep also writes vq under a
  * class guessed from |g|max / sigma, and the third only redoes the channels whose guess was wrong.
  * ------------------------------------------------------------------------------------------- */
 daq_status daq_quantize_grad(const daq_conv_desc* desc, const float* dY, float* s_state, float k, float A,
@@ -357,7 +357,7 @@ daq_status daq_conv_fwd_int8(const daq_conv_desc* desc, const float* X, const fl
                              void* workspace, size_t workspace_bytes, void* stream);
 
 /* daq_conv_fwd_int8 with the schedule of its activation quantizer explicit: DAQ_SCHEDULE_EARLY_COPY
- * writes both layouts of q(X) in one sweep over X (taken by default from 8 Mi elements on, where
+ * writes both layouts of q(X) in one sweep over X (taken by default from 4 Mi elements on, where
  * the channel-major layout is unsplit), DAQ_SCHEDULE_THREE_SWEEPS (and DAQ_SCHEDULE_CHANNEL_RESIDENT, which has no
  * forward form) one sweep per layout.  Same bits. */
 daq_status daq_conv_fwd_int8_ex(const daq_conv_desc* desc, const float* X, const float* W, int8_t* qx_nhwc,

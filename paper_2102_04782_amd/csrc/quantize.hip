@@ -22,12 +22,43 @@ typedef uint32_t v2u __attribute__((ext_vector_type(2)));
 constexpr int kBlock = 256;
 constexpr int kStatsElems = 4096;  // elements one statistics workgroup sweeps per iteration (16 per thread, all in flight)
 constexpr int kMaxSlabs = 16;      // statistics partials per channel (every consumer re-folds them)
-constexpr int kCountGrid = 1024;   // workgroups the counting pass aims for; one count partial per channel each
-constexpr int64_t kEarlyVqMinElems = (int64_t)8 << 20;   // gradients from this size on take the early per-channel copy
+constexpr int kCountWaves = 16;      // waves of the counting pass that a CU holds
+constexpr int kCountMaxWaves = 12;   // of one workgroup
+constexpr int kCountGroups = 1024;  // count partials of a channel, at most
+// What the memory-side cache holds.  A tensor that does not fit is read with the streaming hint, and what else there is stays in the caches
+// until whole lines of it are written back (128 x 96 x 112 x 112, 617 MB, both copies 243 -> 224 us; tensors of 50 to 230 MB, that the
+// statistics sweep has just read, 2 to 10 % slower with the hint).
+constexpr int64_t kCacheBytes = (int64_t)256 << 20;
+// Gradients from this size on take the early per-channel copy (three sweeps and early copy, us: 64 channels of 56 x 56, batch 16 and 32, 19.6 and
+// 19.6, 28.9 and 27.2; 96 of 56 x 56, batch 16, 25.0 and 23.2).
+constexpr int64_t kEarlyVqMinElems = (int64_t)4 << 20;
+
+int64_t channel_units(int N, int HW);
 
 // ---------------------------------------------------------------------------------------------
 // workspace carving
 // ---------------------------------------------------------------------------------------------
+struct CountPlan {
+    int tiles;         // tiles of 16 units (64 pixels) of the flattened (n, h*w) axis
+    int waves;         // of a workgroup
+    int width;         // groups of 16 channels of a block, a wave each
+    int blocks;        // blocks of channels
+    int cgroups;       // workgroups of a block, and entries of part_cnt a channel has room for
+    int cgroups_last;  // of the last block
+    FastDiv div_cgroups;
+    uint32_t by_groups[2];   // 2^16 over the groups of a full block, of the last one, rounded up: exact quotients below 768
+    __host__ __device__ int workgroups() const { return (blocks - 1) * cgroups + cgroups_last; }
+    // groups of 16 channels in block b of C channels; a workgroup with more waves than that takes several tiles at a time
+    __host__ __device__ int groups(int C, int b) const { return b + 1 < blocks ? width : (C + 15) / 16 - (blocks - 1) * width; }
+    // LDS of one of the two tiles a workgroup keeps: by pixel of a unit, unit and 16-byte share of the record, units an odd number of
+    // 16 bytes apart and pixels 64 bytes more than 16 units: no bank conflicts either way
+    __host__ __device__ static int pitch_dwords(int gb) { return 4 * (gb | 1); }
+    __host__ __device__ static int step_dwords(int gb) { return 16 * pitch_dwords(gb) + 16; }
+    int tile_dwords(int C) const {
+        auto of = [&](int gb) { return gb == 1 ? 0 : waves / gb * 4 * step_dwords(gb); };
+        return std::max(of(groups(C, 0)), of(groups(C, blocks - 1)));
+    }
+};
 struct QuantWs {
     float* gmax;          // [C]  |g|max, mean, sigma: written by the counting pass for the packing pass
     float* mean;          // [C]
@@ -44,13 +75,54 @@ struct QuantWs {
     int chunks;           // 4096-element chunks of one channel
     int slabs;            // statistics workgroups (partials) per channel
     int part_n;           // entries of part_max whose maximum is the scale of the per-tensor copy (C * slabs)
-    int tiles;            // 64-pixel tiles of the flattened (n, h*w) axis
-    int cgroups;          // counting workgroups per block of 64 channels
+    CountPlan cp;         // how the counting pass is dealt out
     int scheme;           // daq_scheme the launches of this call follow
     int64_t total_bytes;
 };
 
-QuantWs carve_quant_ws(void* base, int C, int N, int HW) {
+// A block is the channels whose shares of an NHWC record a workgroup writes as one run, up to 192 of them, a wave to 16; the width from 4 to
+// 12 waves that leaves the fewest idle in the last block, the largest of equals.  A record that several workgroups write reaches memory
+// in pieces of lines, each at its own time, and what counts is that there are few of them, not the waves a CU holds (statistics sweep, both
+// copies, padding; start of the work, then blocks of up to 64, 128, 192 channels, us: 128 x 144 x 56 x 56 130, 130, 130, 106; 37 x 792 x 59 x 63 358, 308,
+// 308, 264; 64 x 256 x 56 x 56 113, 106, 99, 99; up to 256: no further change).  Where blocks of 64 channels do not fill the chip once they
+// spread the work over more CUs (16 x 320 x 7 x 7, whole call: 15.1 and, blocks of 160, 16.6 us; 128 x 512 x 7 x 7 15.3 and 16.0).  `given`: the waves of a launch that has other roles too.
+CountPlan plan_count(int C, int N, int HW, int given) {
+    CountPlan p{};
+    const int G = (int)ceil_div(C, 16);
+    p.tiles = (int)ceil_div(channel_units(N, HW), 16);
+    const bool wide = !given && (int64_t)p.tiles * ceil_div(G, 4) > 4 * 256;
+    p.width = std::min(G, given ? given : wide ? 12 : 4);
+    if (wide)
+        for (int w = std::min(G, 11); w >= 4; --w)
+            if (ceil_div(G, w) * w < ceil_div(G, p.width) * p.width) p.width = w;
+    p.waves = given ? given : p.width == 1 ? 4 : p.width <= 3 ? 2 * p.width : p.width;
+    p.blocks = (int)ceil_div(G, p.width);
+    const int side = p.waves / p.groups(C, p.blocks - 1);   // tiles at a time of a workgroup of the last block
+    const int64_t last = ceil_div(p.tiles, side), most = p.blocks > 1 ? p.tiles : last;
+    // the last block gets as many workgroups fewer as they are quicker
+    const int64_t held = 256 * (kCountWaves / p.waves);   // workgroups the chip holds at once
+    int64_t want = std::max<int64_t>(1, std::min<int64_t>(kCountGroups, p.blocks > 1 ? held * side / ((int64_t)(p.blocks - 1) * side + 1) : held));
+    if (want >= 2 * kXcd) want -= want % kXcd;
+    const int64_t turns = ceil_div(most, want);
+    auto groups = [&](int64_t n) {
+        const int64_t q = ceil_div(n, turns);
+        return (int)(q >= 2 * kXcd ? round_up(q, kXcd) : q);   // whole rounds over the XCDs (see k_count_qg)
+    };
+    p.cgroups = groups(most);
+    if (C > 1024) {   // many channels: no more partial counts than the scratch of daq_quantize_grad_noalloc was laid out for
+        const int64_t tiles = ceil_div((int64_t)N * HW, kWave), n = std::max<int64_t>(1, 1024 / ceil_div(C, 64)), q = ceil_div(tiles, ceil_div(tiles, n));
+        p.cgroups = std::min(p.cgroups, (int)(q >= 2 * kXcd ? round_up(q, kXcd) : q));
+    }
+    p.cgroups_last = std::min(p.cgroups, groups(last));
+    p.div_cgroups = make_fastdiv((uint32_t)p.cgroups);
+    for (int b = 0; b < 2; ++b) {
+        const int gb = p.groups(C, b ? p.blocks - 1 : 0);
+        p.by_groups[b] = (uint32_t)((65536 + gb - 1) / gb);
+    }
+    return p;
+}
+
+QuantWs carve_quant_ws(void* base, int C, int N, int HW, int given_waves = 0) {
     QuantWs w{};
     const int64_t M = (int64_t)N * HW;
     // statistics sweep groups of four elements per plane (k_stats): the axis is padded to whole groups
@@ -59,12 +131,7 @@ QuantWs carve_quant_ws(void* base, int C, int N, int HW) {
     const int iters = (int)ceil_div(w.chunks, kMaxSlabs);
     w.slabs = (int)ceil_div(w.chunks, iters);
     w.part_n = C * w.slabs;
-    w.tiles = (int)ceil_div(M, kWave);
-    const int cb = (int)ceil_div(C, 64);
-    const int want = std::max(1, kCountGrid / cb);
-    const int titers = (int)ceil_div(w.tiles, want);
-    w.cgroups = (int)ceil_div(w.tiles, titers);
-    if (w.cgroups >= 2 * kXcd) w.cgroups = (int)round_up(w.cgroups, kXcd);   // whole rounds over the XCDs (see k_count_qg)
+    w.cp = plan_count(C, N, HW, given_waves);
     // byte offsets first; pointers only when there is a buffer (a size query passes none)
     int64_t off = 0;
     const int64_t o_head = off;
@@ -74,9 +141,9 @@ QuantWs carve_quant_ws(void* base, int C, int N, int HW) {
     const int64_t o_max = off;
     off += round_up((int64_t)C * w.slabs * 4, 256);
     const int64_t o_cnt = off;
-    off += round_up((int64_t)C * w.cgroups * 4, 256);
+    off += round_up((int64_t)C * w.cp.cgroups * 4, 256);
     const int64_t o_lcnt = off;
-    off += round_up((int64_t)cb * w.cgroups * (kBlock / kWave) * 4, 256);
+    off += round_up((int64_t)w.cp.workgroups() * w.cp.waves * 4, 256);
     w.total_bytes = off;
     if (base) {
         char* p = (char*)base;
@@ -105,21 +172,30 @@ QuantWs carve_quant_ws(void* base, int C, int N, int HW) {
 // and the two int8 copies take disjoint halves of the word as 16-bit uniforms: the per-channel copy (t = 0) U = h >> 16,
 // the per-tensor copy (t = 1) U = h & 0xFFFF, u = U * 2^-16.  A kernel that writes both copies of an element pays for
 // one hash (the calls below are pure, the compiler merges them); nothing is carried from one element to the next.
-__host__ __device__ __forceinline__ uint32_t fmix32(uint32_t h) {
-    h ^= h >> 16;
+__host__ __device__ __forceinline__ uint32_t fmix32_rest(uint32_t h) {   // fmix32 behind its first step
     h *= 0x85EBCA6Bu;
     h ^= h >> 13;
     h *= 0xC2B2AE35u;
     h ^= h >> 16;
     return h;
 }
+__host__ __device__ __forceinline__ uint32_t fmix32(uint32_t h) { return fmix32_rest(h ^ (h >> 16)); }
 // key = fmix32(seed_lo ^ fmix32(seed_hi ^ 0x9E3779B9)); it travels in the kernels' 64-bit seed argument
 inline uint64_t round_keys(uint64_t seed) {
     const uint32_t lo = (uint32_t)seed, hi = (uint32_t)(seed >> 32);
     return (uint64_t)fmix32(lo ^ fmix32(hi ^ 0x9E3779B9u));
 }
-__device__ __forceinline__ uint32_t draw_half(uint32_t h, uint32_t tensor) { return tensor == 0u ? h >> 16 : h & 0xFFFFu; }
-__device__ __forceinline__ uint32_t rng_u(uint64_t keys, uint32_t tensor, uint32_t idx) { return draw_half(fmix32(idx ^ (uint32_t)keys), tensor); }
+// What the kernels carry is the complement of the word: each half of it is then 65535 - U, the form the rounding below adds.
+__device__ __forceinline__ uint32_t draw_word(uint64_t keys, uint32_t idx) { return ~fmix32(idx ^ (uint32_t)keys); }
+// The words of elements idx .. idx + 3, idx a multiple of four: (idx + e) ^ key is (idx ^ key) ^ e, and as e < 4 touches no bit that
+// the mixer's first shift brings down, its first step is shared too (6.5 instead of 9 instructions an element).
+__device__ __forceinline__ void draw_words4(uint64_t keys, uint32_t idx, uint32_t (&w)[4]) {
+    uint32_t h = idx ^ (uint32_t)keys;
+    h ^= h >> 16;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) w[e] = ~fmix32_rest(h ^ (uint32_t)e);
+}
+__device__ __forceinline__ uint32_t draw_half(uint32_t w, uint32_t tensor) { return tensor == 0u ? w >> 16 : w & 0xFFFFu; }
 
 // 127/s, or 0 when the scale is treated as zero (then every code is 0).
 __device__ __forceinline__ float inv_scale(float s) { return (s >= kTinyScale) ? 127.0f / s : 0.0f; }
@@ -127,35 +203,29 @@ __device__ __forceinline__ float inv_scale(float s) { return (s >= kTinyScale) ?
 // Eq. "suq" in code space: round(clamp(x*inv, -127, 127)).  Stochastic rounding: floor(t) + [frac(t) > U * 2^-16] with
 // the element's 16-bit draw U, evaluated in integers: with c = ceil(t * 2^16) (exact: |t| <= 127) the bracket is
 // [c mod 2^16 > U] - a fraction of exactly 0 never rounds up, one above U * 2^-16 always - so the code is
-// (c + 65535 - U) >> 16 with an arithmetic shift.
+// (c + V) >> 16, V = 65535 - U, with an arithmetic shift.
+// The code is left in byte kCodeByte of a 32-bit word, the other bytes are don't-care: the shift is the packing's choice of byte.
+// Nearest: adding 1.5 * 2^23 to a value of magnitude <= 127 rounds it to an integer, ties to even, and leaves that integer
+// in two's complement in the low mantissa bits - one instruction instead of round + convert + mask.
+template <bool STOCH> constexpr int kCodeByte = STOCH ? 2 : 0;
 template <bool STOCH>
-__device__ __forceinline__ int quant_code(float x, float inv, uint32_t U) {
-    float t = x * inv;
-    t = fminf(fmaxf(t, -127.0f), 127.0f);
-    if (STOCH) {
+__device__ __forceinline__ uint32_t quant_bits(float x, float inv, uint32_t V) {
+    const float t = __builtin_amdgcn_fmed3f(x * inv, -127.0f, 127.0f);   // (a NaN gives -127)
+    if constexpr (STOCH) {
         // -ceil(t * 2^16) = floor(-t * 2^16), floor and conversion in one instruction (|t * 2^16| < 2^23: exact)
         int nc;
         asm("v_cvt_flr_i32_f32 %0, %1" : "=v"(nc) : "v"(t * -65536.0f));
-        return (65535 - (int)U - nc) >> 16;
+        return V - (uint32_t)nc;
     }
-    return (int)rintf(t);
-}
-
-// The same code as quant_code, left in the low byte of a 32-bit word (upper bytes are don't-care).
-// Nearest: adding 1.5 * 2^23 to a value of magnitude <= 127 rounds it to an integer, ties to even,
-// and leaves that integer in two's complement in the low mantissa bits - one instruction instead of
-// round + convert + mask.
-template <bool STOCH>
-__device__ __forceinline__ uint32_t quant_bits(float x, float inv, uint32_t U) {
-    if (STOCH) return (uint32_t)quant_code<true>(x, inv, U);
-    const float t = __builtin_amdgcn_fmed3f(x * inv, -127.0f, 127.0f);
     return __float_as_uint(t + 12582912.0f);
 }
-// Low bytes of four words -> one dword (a in byte 0).
+template <bool STOCH>
+__device__ __forceinline__ int8_t code_byte(uint32_t w) { return (int8_t)(w >> (8 * kCodeByte<STOCH>)); }
+// Byte B of four words -> one dword (a in byte 0).
+template <int B>
 __device__ __forceinline__ uint32_t pack4(uint32_t a, uint32_t b, uint32_t c, uint32_t d) {
-    const uint32_t lo = __builtin_amdgcn_perm(b, a, 0x0c0c0400u);
-    const uint32_t hi = __builtin_amdgcn_perm(d, c, 0x0c0c0400u);
-    return __builtin_amdgcn_perm(hi, lo, 0x05040100u);
+    constexpr uint32_t sel = 0x0c0c0400u + 0x0101u * B;
+    return __builtin_amdgcn_perm(__builtin_amdgcn_perm(d, c, sel), __builtin_amdgcn_perm(b, a, sel), 0x05040100u);
 }
 
 // fp32 tensors are read through a buffer descriptor with 32-bit byte offsets: an offset of kOobOff (or
@@ -310,16 +380,32 @@ __global__ __launch_bounds__(kBlock) void k_stats(const T* __restrict__ g, int N
     }
 }
 
-// Partials of channel c -> |g|max, mean, sigma (population std about the mean, fp64, rounded once).
-// Sequential in slab order, so every workgroup that calls it gets the same bits.
-__device__ __forceinline__ void fold_stats(const QuantWs& ws, int c, double Md, float& gmax, float& mean, float& sigma) {
-    // all partials are requested before the first one is used; slots past `slabs` read zeros, which change nothing
-    float pm[kMaxSlabs];
-    double p1[kMaxSlabs], p2[kMaxSlabs];
+// The value of the lane before, within rows of 16 lanes (of the first of a row: its own).
+__device__ __forceinline__ float lane_before(float v) {
+    const int b = __builtin_bit_cast(int, v);
+    return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(b, b, 0x111, 0xF, 0xF, false));
+}
+__device__ __forceinline__ double lane_before(double v) {
+    v2u b = __builtin_bit_cast(v2u, v);
 #pragma unroll
-    for (int j = 0; j < kMaxSlabs; ++j) {
-        const bool ok = j < ws.slabs;
-        const int64_t slot = (int64_t)c * ws.slabs + j;
+    for (int i = 0; i < 2; ++i) b[i] = (uint32_t)__builtin_amdgcn_update_dpp((int)b[i], (int)b[i], 0x111, 0xF, 0xF, false);
+    return __builtin_bit_cast(double, b);
+}
+
+// Partials of channel c (of C) -> |g|max, mean, sigma (population std about the mean, fp64, rounded once), by four adjacent lanes, a
+// quarter of the slots each; valid in the last of the four.  The sum runs through the slots in their order, from lane to lane, so
+// every workgroup that calls it gets the same bits.  All partials are requested before the first one is used; slots past
+// `slabs` read zeros, which change nothing.
+__device__ __forceinline__ void fold_stats(const QuantWs& ws, int c, int C, double Md, float& gmax, float& mean, float& sigma) {
+    constexpr int kEach = kMaxSlabs / 4;
+    const int part = (int)threadIdx.x % 4;
+    float pm[kEach];
+    double p1[kEach], p2[kEach];
+#pragma unroll
+    for (int j = 0; j < kEach; ++j) {
+        const int at = kEach * part + j;
+        const bool ok = at < ws.slabs && c < C;
+        const int64_t slot = (int64_t)c * ws.slabs + at;
         pm[j] = ldf_or_zero(ws.part_max + slot, ok);
         p1[j] = *(ok ? ws.part_s1 + slot : reinterpret_cast<const double*>(g_zero64));
         p2[j] = *(ok ? ws.part_s2 + slot : reinterpret_cast<const double*>(g_zero64));
@@ -327,10 +413,18 @@ __device__ __forceinline__ void fold_stats(const QuantWs& ws, int c, double Md, 
     float mx = 0.0f;
     double s1 = 0.0, s2 = 0.0;
 #pragma unroll
-    for (int j = 0; j < kMaxSlabs; ++j) {
-        mx = fmaxf(mx, pm[j]);
-        s1 += p1[j];
-        s2 += p2[j];
+    for (int k = 0; k < 4; ++k) {
+        if (k) {   // what the lane before has: after step k lane k of the four is complete
+            mx = lane_before(mx);
+            s1 = lane_before(s1);
+            s2 = lane_before(s2);
+        }
+#pragma unroll
+        for (int j = 0; j < kEach; ++j) {
+            mx = fmaxf(mx, pm[j]);
+            s1 += p1[j];
+            s2 += p2[j];
+        }
     }
     const double mu = s1 / Md;
     double var = s2 / Md - mu * mu;
@@ -360,22 +454,45 @@ struct EarlyVq {
     FastDiv div_w;
     float k, A;
     float ratio;           // a channel with |g|max > ratio * sigma is taken for long-tailed
-    int quad;              // rows are a multiple of four pixels long: four adjacent lanes hold four pixels of one row
+    int flat;              // no padding between rows and images: element m of a channel is byte lead + m
+    int once;              // larger than the caches hold to the end: read past them
+    int whole;             // four pixels of a unit are four consecutive bytes (flat, or rows of whole units)
 };
 
-// Value of `v` in the lane whose number differs in bit 0 (XOR1) or bit 1 (otherwise), by DPP quad permutation.
-template <bool XOR1>
-__device__ __forceinline__ uint32_t quad_swap(uint32_t v) {
-    return (uint32_t)__builtin_amdgcn_mov_dpp((int)v, XOR1 ? 0xB1 : 0x4E, 0xF, 0xF, false);
+// How the counting pass reads a channel plane: in units of four consecutive pixels (kWhole: planes are whole units; kTail: the
+// last unit of a plane is moved back to end with it, what it shares with the unit before is written twice, the same both
+// times, and counted once), or, planes of less than four pixels, four consecutive pixels of the flattened axis one by one.
+enum : int { kWhole, kTail, kElems };
+inline int unit_kind(int HW) { return HW < 4 ? kElems : HW % 4 ? kTail : kWhole; }
+__host__ __device__ inline int plane_units(int HW) { return (HW + 3) / 4; }
+int64_t channel_units(int N, int HW) { return HW < 4 ? ceil_div((int64_t)N * HW, 4) : (int64_t)N * plane_units(HW); }
+inline uint32_t unit_divisor(int HW) { return (uint32_t)(HW < 4 ? HW : plane_units(HW)); }   // what div_u of the pass divides by
+
+// Four registers of four rows of 16 lanes, transposed: register k of row r receives register r of row k.
+__device__ __forceinline__ void transpose_rows(uint32_t (&w)[4]) {
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+        const auto t = __builtin_amdgcn_permlane32_swap(w[k], w[k + 2], false, false);
+        w[k] = t[0];
+        w[k + 2] = t[1];
+    }
+#pragma unroll
+    for (int k = 0; k < 4; k += 2) {
+        const auto t = __builtin_amdgcn_permlane16_swap(w[k], w[k + 1], false, false);
+        w[k] = t[0];
+        w[k + 1] = t[1];
+    }
 }
 
 // ---------------------------------------------------------------------------------------------
 // S2 (+ the global copy of S5): tail-mass count per channel, fused with the globally quantized
-// NHWC copy.  A workgroup owns 64 channels and walks 64-pixel tiles p, p + cgroups, ... of the
-// flattened (n, h*w) axis; wave w handles channels 16w..16w+15 with lane = pixel, so every load is
-// a 256-byte run of one channel and the lane's 16 codes are 16 contiguous bytes of the NHWC output.
+// NHWC copy.  A workgroup owns 64 channels and walks tiles of 16 units (64 pixels) p, p + cgroups, ... of the
+// flattened (n, h*w) axis; wave w handles channels 16w..16w+15.  Lane 16 r + q holds unit q of channels 4r .. 4r+3 of
+// the wave's: four 16-byte loads, each 256 consecutive bytes of four channels a wave, the random words of a unit from one
+// first step, a per-channel unit is one dword, and four instructions between the lanes (transpose_rows) turn the codes of
+// four channels x one unit into 16 channels x one pixel for the NHWC copy.
 // The workgroup first folds the statistics partials of its 64 channels (sigma) and of all channels
-// (the global scale max_c |g|max), then counts with wave ballots into registers and stores one
+// (the global scale max_c |g|max), then counts into registers and stores one
 // count partial per channel: no atomics, no reduction launch.
 // ---------------------------------------------------------------------------------------------
 //
@@ -386,247 +503,308 @@ __device__ __forceinline__ uint32_t quad_swap(uint32_t v) {
 // decision, then only rewrites the channels whose guess was wrong (and writes the padding).  A correct guess saves
 // the third sweep over dY for that channel; a wrong one costs nothing but the bytes written here.
 // `bid`: the workgroup's number among those of this role (the forward pass launches it with other roles, k_fwd_quant).
-template <typename T, bool STOCH, bool WRITE_QG, bool COUNT, bool EARLY>
-__device__ __forceinline__ void count_qg_role(const int bid, const T* __restrict__ g, int N, int C, int HW, int c_pitch, FastDiv div_hw,
+template <typename T, bool STOCH, bool WRITE_QG, bool COUNT, bool EARLY, int UNIT>
+__device__ __forceinline__ void count_qg_role(const int bid, const T* __restrict__ g, int N, int C, int HW, int c_pitch, FastDiv div_u,
                                               const QuantWs& ws, int8_t* __restrict__ qg, uint64_t seed, const float* __restrict__ s_state,
-                                              float* __restrict__ s_global, const EarlyVq& ev, int qg_tail) {
-    __shared__ float l_sigma[64];
-    __shared__ float l_inv[64];
-    __shared__ float l_max[kBlock / kWave];
-    __shared__ __align__(16) int8_t l_tile[64 * 80];
-    const int tid = threadIdx.x, wave = tid / kWave, lane = tid % kWave;
-    const int p = bid % ws.cgroups;
-    const int cb = bid / ws.cgroups;
-    // A last block of at most 32 channels (thin tensors; channel counts like 96 or 144) has one or two groups of 16 channels,
-    // and two or three of the four waves would idle.  Its waves take four (or two) different pixel tiles instead, and
-    // since the block's share of an NHWC record is then 16 (or 32) bytes, a lane's codes are that share (or half of it):
-    // stored directly, no transposition through LDS, no barrier in the loop.
-    const int left = C - cb * 64;
-    const int narrow = left <= 16 ? 1 : left <= 32 ? 2 : 0;   // uniform: groups of 16 channels
-    const int sub = narrow ? wave / narrow : 0, nsub = narrow ? 4 / narrow : 1;   // the wave's pixel tile among the workgroup's
-    const int c0 = cb * 64 + 16 * (narrow ? wave % narrow : wave);
-    const int wg_tiles = (ws.tiles + nsub - 1) / nsub;
+                                              float* __restrict__ s_global, const EarlyVq& ev, int qg_tail, uint32_t* l_tile, int tile_dw) {
+    __shared__ __align__(16) float l_max[kCountMaxWaves];
+    const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid / kWave), lane = tid % kWave;
+    const int uq = lane % 16, row = lane / 16;
+    const CountPlan& cp = ws.cp;
+    const int cb = min((int)fdiv((uint32_t)bid, cp.div_cgroups), cp.blocks - 1);
+    const int p = bid - cb * cp.cgroups;
+    const int cgroups = cb + 1 == cp.blocks ? cp.cgroups_last : cp.cgroups;
+    // A wave to 16 channels of the block; where that leaves waves over (thin tensors, a last block), the workgroup has several
+    // sides, each with a tile of its own.
+    const int gb = cp.groups(C, cb);   // uniform, as are the next two
+    const uint32_t by_gb = cp.by_groups[cb + 1 == cp.blocks ? 1 : 0];
+    const int sides = (int)(((uint32_t)cp.waves * by_gb) >> 16);
+    const int side = (int)(((uint32_t)wave * by_gb) >> 16), kg = wave - side * gb;
+    const int c0 = 16 * (cb * cp.width + kg);
+    const int cl = c0 + 4 * row;                              // the lane's first channel
+    const int wg_tiles = (cp.tiles + sides - 1) / sides;
+    const int pitch = CountPlan::pitch_dwords(gb), step = CountPlan::step_dwords(gb);
     const uint32_t M = (uint32_t)N * (uint32_t)HW;
     constexpr uint32_t EB = sizeof(T);   // bytes of a source element
     const __amdgpu_buffer_rsrc_t rs = f32_rsrc(g, (uint32_t)M * (uint32_t)C * EB);
-    const uint32_t chan_bytes = (uint32_t)HW * EB;
-    // (measured: a gain where the kernel only counts or writes one copy, a loss in the form that writes both copies)
-    const bool dword16 = EB == 2 && !EARLY && (HW & 1) == 0 && ((uintptr_t)g & 3u) == 0;
+    const uint32_t upp = (uint32_t)plane_units(HW), units = UNIT == kElems ? (M + 3) / 4 : (uint32_t)N * upp;
 
     // Which tiles the workgroup walks.  A tile's 256-byte pieces of its channel planes start wherever the plane starts, so
     // neighbouring tiles share cache lines; with the workgroups of a channel block dealt round-robin over the tiles,
     // neighbours ran on different XCDs and both L2s fetched the shared lines (1.4 x the tensor on 14 x 14 planes).  With
     // a multiple of eight workgroups per block, workgroup p runs on XCD p % 8: each XCD takes one contiguous eighth of
     // the tiles, and its workgroups p / 8 walk that range side by side.
-    int t_first = p, t_step = ws.cgroups, t_end = wg_tiles;
-    if ((ws.cgroups & (kXcd - 1)) == 0) {   // uniform
+    int t_first = p, t_step = cgroups, t_end = wg_tiles;
+    if (((cp.cgroups | cgroups) & (kXcd - 1)) == 0) {   // uniform
         const int per_xcd = (wg_tiles + kXcd - 1) / kXcd, xcd = p % kXcd;
         t_first = xcd * per_xcd + p / kXcd;
-        t_step = ws.cgroups / kXcd;
+        t_step = cgroups / kXcd;
         t_end = min(wg_tiles, (xcd + 1) * per_xcd);
     }
 
-    float x[16];
-    uint32_t n_cur = 0, px_cur = 0;
-    bool v_cur = false;
-    auto fetch = [&](int tile, float (&dst)[16], uint32_t& n, uint32_t& px, bool& valid) {
-        const uint32_t P = (uint32_t)(nsub * tile + sub) * kWave + lane;
-        valid = tile < t_end && P < M;
-        const uint32_t Pc = valid ? P : 0u;
-        n = fdiv(Pc, div_hw);
-        px = Pc - n * (uint32_t)HW;
-        const uint32_t off = valid ? ((n * (uint32_t)C + (uint32_t)c0) * (uint32_t)HW + px) * EB : kOobOff;
-        if (EB == 2 && dword16) {   // uniform
-            // bfloat16 through dword loads (two-byte loads run at a fraction of the rate): the lane fetches the aligned
-            // dword that holds its element - its neighbour fetches the same one - and keeps one half.  Planes start on
-            // dword boundaries here (even plane size, aligned tensor), so the half is the same for all 16 channels.
-            const uint32_t offa = valid ? (off & ~3u) : kOobOff;
-            const bool upper = (off & 2u) != 0;
+    // image and first pixel of unit u of the channel, and how many of its pixels belong to the unit before (kWhole, kTail)
+    auto place = [&](uint32_t u, uint32_t& n, uint32_t& px, uint32_t& dup) {
+        n = fdiv(u, div_u);
+        const uint32_t at = (u - n * upp) * 4u;
+        px = UNIT == kTail ? min(at, (uint32_t)HW - 4u) : at;
+        dup = at - px;
+    };
+    // pixel e of a unit of kElems
+    auto pixel = [&](uint32_t u, uint32_t e, uint32_t& n, uint32_t& px) {
+        const uint32_t P = min(4u * u + e, M - 1u);
+        n = fdiv(P, div_u);
+        px = P - n * (uint32_t)HW;
+    };
+    struct Unit {
+        float x[4][4];     // channel, pixel
+        uint32_t u;
+        bool ok;
+    };
+    auto fetch = [&](int tile, Unit& t) {
+        const uint32_t u = (uint32_t)(sides * tile + side) * 16u + (uint32_t)uq;
+        t.ok = tile < t_end && side < sides && u < units;
+        t.u = t.ok ? u : 0u;
+        if constexpr (UNIT == kElems) {
 #pragma unroll
-            for (int i = 0; i < 16; ++i) {
-                const uint32_t raw = (uint32_t)__builtin_amdgcn_raw_buffer_load_b32(rs, (int)((c0 + i < C) ? offa : kOobOff), (int)((uint32_t)i * chan_bytes), 0);
-                dst[i] = __uint_as_float(upper ? (raw & 0xffff0000u) : (raw << 16));
+            for (int e = 0; e < 4; ++e) {
+                uint32_t n, px;
+                pixel(t.u, e, n, px);
+                const uint32_t off = ((n * (uint32_t)C + (uint32_t)cl) * (uint32_t)HW + px) * EB;
+#pragma unroll
+                for (int j = 0; j < 4; ++j) t.x[j][e] = buf_ld<T>(rs, t.ok && 4u * t.u + e < M && cl + j < C ? off : kOobOff, (uint32_t)(j * HW) * EB);
             }
-        } else if (c0 + 16 <= C) {   // uniform per wave
-#pragma unroll
-            for (int i = 0; i < 16; ++i) dst[i] = buf_ld<T>(rs, off, (uint32_t)i * chan_bytes);
         } else {
+            uint32_t n, px, dup;
+            place(t.u, n, px, dup);
+            const uint32_t at = (n * (uint32_t)C + (uint32_t)cl) * (uint32_t)HW + px;
 #pragma unroll
-            for (int i = 0; i < 16; ++i) dst[i] = buf_ld<T>(rs, c0 + i < C ? off : kOobOff, (uint32_t)i * chan_bytes);
+            for (int j = 0; j < 4; ++j) {
+                const bool ok = t.ok && cl + j < C;
+                if constexpr (EB == 4) {
+                    const int voff = (int)(ok ? at * EB : kOobOff), soff = (int)((uint32_t)(j * HW) * EB);
+                    v4u raw;
+                    if (EARLY && ev.once) raw = __builtin_amdgcn_raw_buffer_load_b128(rs, voff, soff, 2);   // uniform; nt
+                    else raw = __builtin_amdgcn_raw_buffer_load_b128(rs, voff, soff, 0);
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) t.x[j][e] = __uint_as_float(raw[e]);
+                } else {
+                    const uint4 raw = ld4_or_zero<T>(g + at + (uint32_t)(j * HW), ok);
+                    t.x[j][0] = __uint_as_float(raw.x);
+                    t.x[j][1] = __uint_as_float(raw.y);
+                    t.x[j][2] = __uint_as_float(raw.z);
+                    t.x[j][3] = __uint_as_float(raw.w);
+                }
+            }
         }
     };
-    fetch(t_first, x, n_cur, px_cur, v_cur);
+    Unit a, b;
+    fetch(t_first, a);
 
     // scale of the global copy: the maximum over the partials of the launch before
+    const int threads = cp.waves * kWave;
     {
         float m = 0.0f;
         const int total = ws.part_n;
-        for (int base = 0; base < total; base += 8 * kBlock) {
+        for (int base = 0; base < total; base += 8 * threads) {
             float v[8];
 #pragma unroll
-            for (int u = 0; u < 8; ++u) v[u] = ldf_or_zero(ws.part_max + base + u * kBlock + tid, base + u * kBlock + tid < total);
+            for (int u = 0; u < 8; ++u) v[u] = ldf_or_zero(ws.part_max + base + u * threads + tid, base + u * threads + tid < total);
 #pragma unroll
             for (int u = 0; u < 8; ++u) m = fmaxf(m, v[u]);
         }
         m = wave_max(m);
         if (lane == 0) l_max[wave] = m;
+        if (tid < kCountMaxWaves && tid >= cp.waves) l_max[tid] = 0.0f;
     }
-    if (COUNT && tid < 64) {
-        const int c = cb * 64 + tid;
-        float gm = 0.0f, mu = 0.0f, sig = 0.0f;
-        if (c < C) {
-            fold_stats(ws, c, (double)N * (double)HW, gm, mu, sig);
-            if (p == 0) { ws.gmax[c] = gm; ws.mean[c] = mu; ws.sigma[c] = sig; }
-            if (EARLY) {
-                const int guess = gm > ev.ratio * sig ? DAQ_CLASS_INVT : DAQ_CLASS_GAUSS;
-                l_inv[tid] = inv_scale(clip_rule(guess, gm, s_state[c], ev.k, ev.A));
-                if (p == 0) ws.pred[c] = (uint32_t)guess;
-            }
+    // sigma and 127/s of the lane's four channels, from the wave's own fold.  Lanes without a unit and channels past C hold x = 0, and
+    // 0 > sigma is false for every sigma >= 0, so the comparison needs no validity mask.
+    float sig[4] = {}, inv_c[4] = {};
+    if constexpr (COUNT) {
+        const int c = c0 + lane / 4;   // four lanes to a channel; the last of them ends up with the fold
+        float gm, mu, sg_c, inv_e = 0.0f;
+        fold_stats(ws, c, C, (double)N * (double)HW, gm, mu, sg_c);
+        const bool mine = lane % 4 == 3 && c < C;
+        if (mine && side == 0 && p == 0) { ws.gmax[c] = gm; ws.mean[c] = mu; ws.sigma[c] = sg_c; }
+        if constexpr (EARLY) {
+            const int guess = gm > ev.ratio * sg_c ? DAQ_CLASS_INVT : DAQ_CLASS_GAUSS;
+            inv_e = inv_scale(clip_rule(guess, gm, c < C ? s_state[c] : 0.0f, ev.k, ev.A));
+            if (mine && side == 0 && p == 0) ws.pred[c] = (uint32_t)guess;
         }
         // layer-wise clipping compares every element with the standard deviation of the whole tensor
-        l_sigma[tid] = ws.scheme == DAQ_SCHEME_MCS ? ws.layer[2] : sig;
+        if (ws.scheme == DAQ_SCHEME_MCS) sg_c = ws.layer[2];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            sig[j] = __shfl(sg_c, 16 * row + 4 * j + 3);
+            if (EARLY) inv_c[j] = __shfl(inv_e, 16 * row + 4 * j + 3);
+        }
     }
     __syncthreads();
-    float sg = fmaxf(fmaxf(l_max[0], l_max[1]), fmaxf(l_max[2], l_max[3]));
+    float sg = 0.0f;
+#pragma unroll
+    for (int w = 0; w < kCountMaxWaves; ++w) sg = fmaxf(sg, l_max[w]);
     const float sg_raw = sg;
     if (!(sg >= kTinyScale)) sg = 0.0f;
     if (COUNT && bid == 0) {
         // the clip state is overwritten by the packing pass: keep what this iteration started from
-        for (int i = tid; i < C; i += kBlock) ws.s_prev[i] = s_state[i];
+        for (int i = tid; i < C; i += threads) ws.s_prev[i] = s_state[i];
     }
     if (bid == 0 && tid == 0) {
         *s_global = sg;
         ws.layer[0] = sg_raw;
     }
     // the NHWC buffer is a multiple of 256 bytes long: the bytes behind the last pixel hold no element and are zero
-    if (WRITE_QG && bid == 0 && tid < qg_tail) qg[(int64_t)M * c_pitch + tid] = 0;
+    if (WRITE_QG && bid == 0)
+        for (int i = tid; i < qg_tail; i += threads) qg[(int64_t)M * c_pitch + i] = 0;
     const float inv = inv_scale(sg);
-    // sigma of the wave's 16 channels.  Lanes without a pixel and channels past C hold x = 0, and
-    // 0 > sigma is false for every sigma >= 0, so the comparison needs no validity mask.
-    // (both arrays are the same in every lane of the wave: moved to scalar registers, they cost no vector ones)
-    auto uniform = [](float v) { return __uint_as_float((uint32_t)__builtin_amdgcn_readfirstlane((int)__float_as_uint(v))); };
-    float sig[16];
+    if constexpr (EARLY && !COUNT) {   // forward: one scale
 #pragma unroll
-    for (int i = 0; i < 16; ++i) sig[i] = COUNT ? uniform(l_sigma[c0 - cb * 64 + i]) : 0.0f;
+        for (int j = 0; j < 4; ++j) inv_c[j] = inv;
+    }
+    // what the lane stores of a tile: a 16-byte unit of one of its side's pixels
+    const int at_px = (int)(((uint32_t)(kg * kWave + lane) * by_gb) >> 16), at_ch = (kg * kWave + lane) - at_px * gb;
+    int8_t* const qg_lane = WRITE_QG ? qg + 16 * (cb * cp.width + (gb == 1 ? 0 : at_ch)) : nullptr;
+    int8_t* const vq_lane = EARLY ? ev.vq + (int64_t)cl * ev.chan_pitch + (uint32_t)ev.lead : nullptr;
 
-    float inv_c[16];
-#pragma unroll
-    for (int i = 0; i < 16; ++i) inv_c[i] = EARLY ? (COUNT ? uniform(l_inv[c0 - cb * 64 + i]) : inv) : 0.0f;   // forward: one scale
-
-    uint32_t cnt[16];   // wave-uniform counters
-#pragma unroll
-    for (int i = 0; i < 16; ++i) cnt[i] = 0;
-    for (int tile = t_first; tile < t_end; tile += t_step) {
-        float nx[16];
-        uint32_t n_nxt, px_nxt;
-        bool v_nxt;
-        fetch(tile + t_step, nx, n_nxt, px_nxt, v_nxt);
-        uint32_t b[16], vb[16];
-        const uint32_t idx0 = (n_cur * (uint32_t)C + (uint32_t)c0) * (uint32_t)HW + px_cur;   // the lane's 16 elements are one plane apart
-#pragma unroll
-        for (int i = 0; i < 16; ++i) {
-            if (COUNT) cnt[i] += (uint32_t)__popcll(__ballot(fabsf(x[i]) > sig[i]));
-            const uint32_t idx = idx0 + (uint32_t)i * (uint32_t)HW;
-            if (WRITE_QG) b[i] = quant_bits<STOCH>(x[i], inv, STOCH ? rng_u(seed, 1u, idx) : 0u);
-            if (EARLY) vb[i] = quant_bits<STOCH>(x[i], inv_c[i], STOCH ? rng_u(seed, 0u, idx) : 0u);
+    uint32_t cnt[4] = {0u, 0u, 0u, 0u};
+    auto work = [&](int tile, const Unit& t, uint32_t* tile_buf) {
+        uint32_t n = 0, px = 0, dup = 0;
+        if constexpr (UNIT != kElems) place(t.u, n, px, dup);
+        const uint32_t idx0 = (n * (uint32_t)C + (uint32_t)cl) * (uint32_t)HW + px;   // NCHW index; the lane's channels are one plane apart
+        // channel-major copy: the unit sits at the same offset of each of the lane's four channel planes
+        uint32_t at_vq = 0;
+        bool whole = true;   // the unit does not run on into the next row
+        if constexpr (EARLY && UNIT != kElems) {
+            const uint32_t h = ev.flat ? 0u : fdiv(px, ev.div_w);
+            const uint32_t col = px - h * (uint32_t)ev.W;
+            whole = ev.whole || col + 4u <= (uint32_t)ev.W;
+            at_vq = ev.flat ? n * (uint32_t)HW + px : (n * (uint32_t)ev.img_rows + h) * (uint32_t)ev.row_pitch + col;
         }
-        if (EARLY) {
-            // channel-major copy: the lane's pixel sits at the same offset of each of its 16 channel planes
-            const uint32_t h = fdiv(px_cur, ev.div_w);
-            int8_t* dst = ev.vq + (int64_t)c0 * ev.chan_pitch + (uint32_t)ev.lead +
-                          (n_cur * (uint32_t)ev.img_rows + h) * (uint32_t)ev.row_pitch + (px_cur - h * (uint32_t)ev.W);
-            if (ev.quad) {   // uniform
-                // Four adjacent lanes hold four consecutive pixels of one row.  Their 4 x 16 codes are transposed inside
-                // the quad - dwords between lanes, then bytes between dwords - so that lane r of the quad ends up with
-                // the four pixels of channels 4r .. 4r+3 as one dword each: four stores per lane instead of sixteen.
-                uint32_t wd[4];
+        uint32_t d[4];   // global codes: pixel k of the unit, the lane's four channels
+        uint32_t half[4];
+        constexpr uint32_t kB = 0x0101u * kCodeByte<STOCH>;
 #pragma unroll
-                for (int k4 = 0; k4 < 4; ++k4) wd[k4] = pack4(vb[4 * k4], vb[4 * k4 + 1], vb[4 * k4 + 2], vb[4 * k4 + 3]);
-                const bool o1 = lane & 1, o2 = lane & 2;
+        for (int j = 0; j < 4; ++j) {
+            uint32_t draw[4] = {0u, 0u, 0u, 0u};
+            if constexpr (STOCH && (WRITE_QG || EARLY)) {
+                const uint32_t idx = idx0 + (uint32_t)(j * HW);
+                if constexpr (UNIT == kWhole) {
+                    draw_words4(seed, idx, draw);
+                } else {
 #pragma unroll
-                for (int k4 = 0; k4 < 4; k4 += 2) {
-                    const uint32_t got = quad_swap<true>(o1 ? wd[k4] : wd[k4 + 1]);
-                    wd[k4] = o1 ? got : wd[k4];
-                    wd[k4 + 1] = o1 ? wd[k4 + 1] : got;
+                    for (int e = 0; e < 4; ++e) {
+                        uint32_t at = idx + (uint32_t)e;
+                        if constexpr (UNIT == kElems) {
+                            uint32_t ne, pe;
+                            pixel(t.u, e, ne, pe);
+                            at = (ne * (uint32_t)C + (uint32_t)(cl + j)) * (uint32_t)HW + pe;
+                        }
+                        draw[e] = draw_word(seed, at);
+                    }
                 }
+            }
+            uint32_t vb[4];
 #pragma unroll
-                for (int k4 = 0; k4 < 2; ++k4) {
-                    const uint32_t got = quad_swap<false>(o2 ? wd[k4] : wd[k4 + 2]);
-                    wd[k4] = o2 ? got : wd[k4];
-                    wd[k4 + 2] = o2 ? wd[k4 + 2] : got;
+            for (int e = 0; e < 4; ++e) {
+                const float v = t.x[j][e];
+                if (COUNT) cnt[j] += (fabsf(v) > sig[j] && (UNIT != kTail || e == 3 || (uint32_t)e >= dup)) ? 1u : 0u;
+                if (WRITE_QG) {
+                    const uint32_t w = quant_bits<STOCH>(v, inv, draw_half(draw[e], 1u));
+                    if (j % 2 == 0) half[e] = w;
+                    else half[e] = __builtin_amdgcn_perm(w, half[e], 0x0c0c0400u + kB);
+                    if (j == 1) d[e] = half[e];
+                    if (j == 3) d[e] = __builtin_amdgcn_perm(half[e], d[e], 0x05040100u);
                 }
-                // wd[q] = channels 4r .. 4r+3 of the quad's pixel q; now bytes: out[j] = pixels 0 .. 3 of channel 4r + j
-                const uint32_t t0 = __builtin_amdgcn_perm(wd[1], wd[0], 0x05010400u), t1 = __builtin_amdgcn_perm(wd[1], wd[0], 0x07030602u);
-                const uint32_t t2 = __builtin_amdgcn_perm(wd[3], wd[2], 0x05010400u), t3 = __builtin_amdgcn_perm(wd[3], wd[2], 0x07030602u);
-                const uint32_t out[4] = {__builtin_amdgcn_perm(t2, t0, 0x05040100u), __builtin_amdgcn_perm(t2, t0, 0x07060302u),
-                                         __builtin_amdgcn_perm(t3, t1, 0x05040100u), __builtin_amdgcn_perm(t3, t1, 0x07060302u)};
-                const int r = lane & 3;
-                int8_t* dq = dst - r + (int64_t)(4 * r) * ev.chan_pitch;   // first pixel of the quad, plane of channel c0 + 4r
-                if (v_cur) {
+                if (EARLY) vb[e] = quant_bits<STOCH>(v, inv_c[j], draw_half(draw[e], 0u));
+            }
+            if (EARLY && t.ok && cl + j < C) {
+                const uint32_t wv = pack4<kCodeByte<STOCH>>(vb[0], vb[1], vb[2], vb[3]);
+                int8_t* plane = vq_lane + (int64_t)j * ev.chan_pitch;
+                if (UNIT != kElems && whole) {
+                    __builtin_memcpy(plane + at_vq, &wv, 4);   // byte aligned only
+                } else {
 #pragma unroll
-                    for (int j = 0; j < 4; ++j)
-                        if (c0 + 4 * r + j < C) __builtin_memcpy(dq + (int64_t)j * ev.chan_pitch, &out[j], 4);   // byte aligned only
+                    for (int e = 0; e < 4; ++e) {
+                        uint32_t ne = n, pe = px + (uint32_t)e;
+                        if constexpr (UNIT == kElems) pixel(t.u, e, ne, pe);
+                        const uint32_t he = fdiv(pe, ev.div_w);
+                        const uint32_t at = (ne * (uint32_t)ev.img_rows + he) * (uint32_t)ev.row_pitch + (pe - he * (uint32_t)ev.W);
+                        if (UNIT != kElems || 4u * t.u + e < M) plane[at] = (int8_t)(wv >> (8 * e));
+                    }
                 }
-            } else if (v_cur) {
-#pragma unroll
-                for (int i = 0; i < 16; ++i)
-                    if (c0 + i < C) dst[(int64_t)i * ev.chan_pitch] = (int8_t)vb[i];
+            }
+            if (EARLY && j < 3) __builtin_amdgcn_sched_barrier(0);   // a channel at a time: four at once do not fit the registers
+        }
+        if (WRITE_QG) {
+            // then pixel `row` of the unit, channels 4k .. 4k+3 of the wave's
+            transpose_rows(d);
+            const uint4 rec = make_uint4(d[0], d[1], d[2], d[3]);
+            if (gb == 1) {   // uniform
+                const uint32_t P = (UNIT == kElems ? 4u * t.u : n * (uint32_t)HW + px) + (uint32_t)row;
+                if (t.ok && (UNIT != kElems || P < M)) *reinterpret_cast<uint4*>(qg_lane + (int64_t)P * c_pitch) = rec;   // bytes of channels past C are codes of 0.0f: zeros
+            } else {
+                // A lane holds 16 channel bytes of ONE pixel, so a direct store would put 16 bytes into each of 64 different
+                // places.  The tile goes through LDS instead and leaves as whole runs: gb adjacent lanes write what the block
+                // has of a pixel's record.
+                uint32_t* l = tile_buf + side * 4 * step;
+                if (side < sides) *reinterpret_cast<uint4*>(l + row * step + uq * pitch + 4 * kg) = rec;
+                __syncthreads();   // (a wave that is here again for the next tile but one has seen all others read this one)
+                const uint32_t u = (uint32_t)(sides * tile + side) * 16u + (uint32_t)(at_px >> 2);
+                uint32_t P = 4u * u;
+                if constexpr (UNIT == kTail) {
+                    uint32_t on, opix, odup;
+                    place(u, on, opix, odup);
+                    P = on * (uint32_t)HW + opix;
+                }
+                P += (uint32_t)(at_px & 3);
+                if (side < sides && u < units && (UNIT != kElems || P < M))
+                    *reinterpret_cast<uint4*>(qg_lane + (int64_t)P * c_pitch) =
+                        *reinterpret_cast<const uint4*>(l + (at_px & 3) * step + (at_px >> 2) * pitch + 4 * at_ch);
             }
         }
-        if (WRITE_QG && narrow) {
-            const uint4 w = make_uint4(pack4(b[0], b[1], b[2], b[3]), pack4(b[4], b[5], b[6], b[7]),
-                                       pack4(b[8], b[9], b[10], b[11]), pack4(b[12], b[13], b[14], b[15]));
-            const uint32_t P = (uint32_t)(nsub * tile + sub) * kWave + lane;
-            if (v_cur) *reinterpret_cast<uint4*>(qg + (int64_t)P * c_pitch + c0) = w;   // bytes of channels past C are codes of 0.0f: zeros
-        } else if (WRITE_QG) {
-            // A lane holds 16 channel bytes of ONE pixel, so a direct store would put 16 bytes into each of 64 different
-            // lines.  The 64-pixel x 64-channel tile goes through LDS instead (80-byte pitch: conflict free both ways)
-            // and leaves as whole 64-byte runs: four adjacent lanes write the 64 channel bytes of one pixel.
-            const uint4 w = make_uint4(pack4(b[0], b[1], b[2], b[3]), pack4(b[4], b[5], b[6], b[7]),
-                                       pack4(b[8], b[9], b[10], b[11]), pack4(b[12], b[13], b[14], b[15]));
-            __syncthreads();   // the previous tile has been read out
-            *reinterpret_cast<uint4*>(l_tile + lane * 80 + 16 * wave) = w;
-            __syncthreads();
-            const int opx = tid >> 2, och = 16 * (tid & 3);
-            const uint32_t P = (uint32_t)tile * kWave + opx;   // pixels of a tile are consecutive in NHWC
-            if (P < M && cb * 64 + och < c_pitch)
-                *reinterpret_cast<uint4*>(qg + (int64_t)P * c_pitch + cb * 64 + och) =
-                    *reinterpret_cast<const uint4*>(l_tile + opx * 80 + och);
-        }
-#pragma unroll
-        for (int i = 0; i < 16; ++i) x[i] = nx[i];
-        n_cur = n_nxt; px_cur = px_nxt; v_cur = v_nxt;
+    };
+    // the next tile's loads are in flight while a tile is worked on; two buffers that take turns
+    for (int tile = t_first; tile < t_end; tile += 2 * t_step) {
+        fetch(tile + t_step, b);
+        work(tile, a, l_tile);
+        if (tile + t_step >= t_end) break;
+        fetch(tile + 2 * t_step, a);
+        work(tile + t_step, b, l_tile + tile_dw);
     }
     if (COUNT) {
-        uint32_t mine = 0;
 #pragma unroll
-        for (int i = 0; i < 16; ++i) mine = (lane == i) ? cnt[i] : mine;
-        const bool mine_ok = lane < 16 && c0 + lane < C;
-        if (narrow) {   // uniform: waves counted the same channels on different tiles
-            uint32_t* l_c = reinterpret_cast<uint32_t*>(l_tile);
-            if (lane < 16) l_c[16 * wave + lane] = mine;
+        for (int j = 0; j < 4; ++j)
+#pragma unroll
+            for (int o = 8; o > 0; o >>= 1) cnt[j] += __shfl_xor(cnt[j], o);   // over the row's 16 units
+        uint32_t mine = 0;   // lane 16 r + j, j < 4: channel 4 r + j of the wave's
+#pragma unroll
+        for (int j = 0; j < 4; ++j) mine = uq == j ? cnt[j] : mine;
+        const bool mine_ok = uq < 4 && cl + uq < C && side < sides;
+        if (sides > 1) {   // uniform: waves counted the same channels on different tiles
+            __shared__ uint32_t l_cnt[kCountMaxWaves * 16];
+            if (uq < 4) l_cnt[16 * wave + 4 * row + uq] = mine;
             __syncthreads();
-            if (sub == 0 && mine_ok) {
+            if (side == 0 && mine_ok) {
                 uint32_t all = 0;
-                for (int w = wave; w < 4; w += narrow) all += l_c[16 * w + lane];
-                ws.part_cnt[(int64_t)(c0 + lane) * ws.cgroups + p] = all;
+                for (int w = kg; w < sides * gb; w += gb) all += l_cnt[16 * w + 4 * row + uq];
+                ws.part_cnt[(int64_t)(cl + uq) * cp.cgroups + p] = all;
             }
         } else if (mine_ok) {
-            ws.part_cnt[(int64_t)(c0 + lane) * ws.cgroups + p] = mine;
+            ws.part_cnt[(int64_t)(cl + uq) * cp.cgroups + p] = mine;
         }
         if (ws.scheme == DAQ_SCHEME_MCS) {   // uniform: one population; its count is the sum over all counting waves
             const uint32_t all = wave_sum_u32(mine_ok ? mine : 0u);
-            if (lane == 0) ws.layer_cnt[bid * (kBlock / kWave) + wave] = all;
+            if (lane == 0) ws.layer_cnt[bid * cp.waves + wave] = all;
         }
     }
 }
 
-template <typename T, bool STOCH, bool WRITE_QG, bool COUNT, bool EARLY = false>
-__global__ __launch_bounds__(kBlock, 4) void k_count_qg(const T* __restrict__ g, int N, int C, int HW, int c_pitch, FastDiv div_hw,
+template <typename T, bool STOCH, bool WRITE_QG, bool COUNT, bool EARLY, int UNIT>
+__global__ __launch_bounds__(kCountMaxWaves * kWave, 4) void k_count_qg(const T* __restrict__ g, int N, int C, int HW, int c_pitch, FastDiv div_u,
                                                         QuantWs ws, int8_t* __restrict__ qg, uint64_t seed,
                                                         const float* __restrict__ s_state, float* __restrict__ s_global, EarlyVq ev,
-                                                        int qg_tail) {
-    count_qg_role<T, STOCH, WRITE_QG, COUNT, EARLY>((int)blockIdx.x, g, N, C, HW, c_pitch, div_hw, ws, qg, seed, s_state, s_global, ev, qg_tail);
+                                                        int qg_tail, int tile_dw) {
+    extern __shared__ __align__(16) uint32_t l_records[];   // two tiles (CountPlan::tile_dwords)
+    count_qg_role<T, STOCH, WRITE_QG, COUNT, EARLY, UNIT>((int)blockIdx.x, g, N, C, HW, c_pitch, div_u, ws, qg, seed, s_state, s_global, ev, qg_tail, l_records, tile_dw);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -738,13 +916,14 @@ __device__ __forceinline__ float clip_value(const QuantWs& ws, const ClipArgs& c
         return s;
     }
     uint32_t cnt = 0;
-    static_assert(kCountGrid <= 4 * kBlock, "a thread sums at most four count partials");
+    static_assert(kCountGroups <= 4 * kBlock, "a thread sums at most four count partials");
     {
+        const int have = c / (16 * ws.cp.width) + 1 == ws.cp.blocks ? ws.cp.cgroups_last : ws.cp.cgroups;
         uint32_t v[4];
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
             const int i = tid + u * kBlock;
-            v[u] = __float_as_uint(ldf_or_zero(reinterpret_cast<const float*>(ws.part_cnt + (int64_t)c * ws.cgroups + i), i < ws.cgroups));
+            v[u] = __float_as_uint(ldf_or_zero(reinterpret_cast<const float*>(ws.part_cnt + (int64_t)c * ws.cp.cgroups + i), i < have));
         }
         cnt = v[0] + v[1] + v[2] + v[3];
     }
@@ -889,8 +1068,8 @@ __device__ __forceinline__ void pack_cnhw_role(const int b, const int phase, con
         uint32_t bits[4];
 #pragma unroll
         for (int i = 0; i < 4; ++i)
-            bits[i] = quant_bits<STOCH>(x[u][i], inv, STOCH ? rng_u(pa.seed, pa.tensor, eoff[u][i] / EB) : 0u);
-        if (d < plane_dw) *reinterpret_cast<uint32_t*>(plane + 4 * (int64_t)d) = pack4(bits[0], bits[1], bits[2], bits[3]);
+            bits[i] = quant_bits<STOCH>(x[u][i], inv, STOCH ? draw_half(draw_word(pa.seed, eoff[u][i] / EB), pa.tensor) : 0u);
+        if (d < plane_dw) *reinterpret_cast<uint32_t*>(plane + 4 * (int64_t)d) = pack4<kCodeByte<STOCH>>(bits[0], bits[1], bits[2], bits[3]);
     }
 }
 
@@ -932,6 +1111,8 @@ __device__ __forceinline__ void store_codes(int8_t* p, uint32_t w) {
     // the destination has no alignment beyond one byte; the compiler picks the widest legal store
     if (V == 4) {
         __builtin_memcpy(p, &w, 4);
+    } else if (V == 1) {
+        *p = (int8_t)w;
     } else {
         const uint16_t h = (uint16_t)w;
         __builtin_memcpy(p, &h, 2);
@@ -1018,6 +1199,8 @@ __device__ __forceinline__ void pack_rows_role(const int b, const T* __restrict_
             const v4u raw = __builtin_amdgcn_raw_buffer_load_b128(rs, (int)eoff[u], 0, 0);
 #pragma unroll
             for (int i = 0; i < V; ++i) x[u][i] = __uint_as_float(raw[i]);
+        } else if constexpr (V == 1) {
+            x[u][0] = buf_ld<T>(rs, eoff[u], 0u);
         } else if constexpr (EB == 4) {
             const v2u raw = __builtin_amdgcn_raw_buffer_load_b64(rs, (int)eoff[u], 0, 0);
 #pragma unroll
@@ -1035,15 +1218,17 @@ __device__ __forceinline__ void pack_rows_role(const int b, const T* __restrict_
         }
     }
 
-    uint32_t hash[4][V];   // of the elements: the two copies draw from its two halves
+    uint32_t draw[4][V];   // of the elements: the two copies draw from the two halves
     if constexpr (STOCH) {
 #pragma unroll
-        for (int u = 0; u < 4; ++u)
+        for (int u = 0; u < 4; ++u) {
+            if constexpr (V == 4) draw_words4(pa.seed, eoff[u] / EB, draw[u]);   // rows and planes are whole groups
 #pragma unroll
             for (int i = 0; i < V; ++i) {
-                hash[u][i] = fmix32((eoff[u] / EB + i) ^ (uint32_t)pa.seed);
-                asm volatile("" : "+v"(hash[u][i]));   // computed once, not once a copy
+                if constexpr (V != 4) draw[u][i] = draw_word(pa.seed, eoff[u] / EB + i);
+                asm volatile("" : "+v"(draw[u][i]));   // computed once, not once a copy
             }
+        }
     }
     // a given scale is folded while the loads are in flight (without `early` there is one pass)
     if constexpr (!CLIP)
@@ -1052,8 +1237,8 @@ __device__ __forceinline__ void pack_rows_role(const int b, const T* __restrict_
     for (int u = 0; u < 4; ++u) {
         uint32_t bits[4] = {0u, 0u, 0u, 0u};
 #pragma unroll
-        for (int i = 0; i < V; ++i) bits[i] = quant_bits<STOCH>(x[u][i], inv, STOCH ? draw_half(hash[u][i], pa.tensor) : 0u);
-        if (live[u]) store_codes<V>(plane + doff[u], pack4(bits[0], bits[1], bits[2], bits[3]));
+        for (int i = 0; i < V; ++i) bits[i] = quant_bits<STOCH>(x[u][i], inv, STOCH ? draw_half(draw[u][i], pa.tensor) : 0u);
+        if (live[u]) store_codes<V>(plane + doff[u], pack4<kCodeByte<STOCH>>(bits[0], bits[1], bits[2], bits[3]));
         if (row_end[u])
             for (int k = 0; k < padw; ++k) plane[doff[u] + V + k] = 0;
     }
@@ -1063,8 +1248,8 @@ __device__ __forceinline__ void pack_rows_role(const int b, const T* __restrict_
         for (int u = 0; u < 4; ++u) {
             uint32_t bits[4] = {0u, 0u, 0u, 0u};
 #pragma unroll
-            for (int i = 0; i < V; ++i) bits[i] = quant_bits<STOCH>(x[u][i], inv2, STOCH ? draw_half(hash[u][i], pa.tensor2) : 0u);
-            if (live[u]) store_codes<V>(plane2 + doff[u], pack4(bits[0], bits[1], bits[2], bits[3]));
+            for (int i = 0; i < V; ++i) bits[i] = quant_bits<STOCH>(x[u][i], inv2, STOCH ? draw_half(draw[u][i], pa.tensor2) : 0u);
+            if (live[u]) store_codes<V>(plane2 + doff[u], pack4<kCodeByte<STOCH>>(bits[0], bits[1], bits[2], bits[3]));
             if (row_end[u])
                 for (int k = 0; k < padw; ++k) plane2[doff[u] + V + k] = 0;
         }
@@ -1177,15 +1362,18 @@ __global__ __launch_bounds__(1024, NU <= 2 ? 8 : NU <= 8 ? 6 : 4) void k_chan_re
     uint32_t draw[STOCH ? (NU * PER + 1) / 2 : 1];
     if constexpr (STOCH) {
         const uint32_t tid2 = again();
+        uint32_t h[PER == 4 ? 4 : 2] = {};   // (units past the channel hash a number nobody uses)
 #pragma unroll
-        for (int k = 0; k < NU * PER; k += 2) {
-            uint32_t h[2] = {0u, 0u};
-#pragma unroll
-            for (int t = 0; t < 2 && k + t < NU * PER; ++t) {
-                const int u = (k + t) / PER, e = (k + t) % PER;
-                h[t] = fmix32((index((uint32_t)(u * TH) + tid2) + (uint32_t)e) ^ (uint32_t)ra.seed);   // (units past the channel hash a number nobody uses)
+        for (int k = 0; k < NU * PER; ++k) {
+            const int u = k / PER, e = k % PER;
+            if constexpr (PER == 4 && !TAIL) {
+                if (e == 0) draw_words4(ra.seed, index((uint32_t)(u * TH) + tid2), h);
+            } else {
+                h[k % (PER == 4 ? 4 : 2)] = draw_word(ra.seed, index((uint32_t)(u * TH) + tid2) + (uint32_t)e);
             }
-            draw[k / 2] = (h[0] >> 16) | (h[1] & 0xffff0000u);   // the per-channel copy draws from the upper half of the hash
+            // the per-channel copy draws from the upper half of the word
+            if (k % 2 == 1) draw[k / 2] = (h[k % (PER == 4 ? 4 : 2) - 1] >> 16) | (h[k % (PER == 4 ? 4 : 2)] & 0xffff0000u);
+            else if (k + 1 == NU * PER) draw[k / 2] = h[0] >> 16;
         }
         // (without this the compiler moves the hashes down to where they are used, behind the barriers; as many of
         // them as the registers of the form allow)
@@ -1289,7 +1477,7 @@ __global__ __launch_bounds__(1024, NU <= 2 ? 8 : NU <= 8 ? 6 : 4) void k_chan_re
                 uint32_t b[4];
 #pragma unroll
                 for (int e = 0; e < 4; ++e) b[e] = quant_bits<STOCH>(x[u][e], inv, draw_of(u, e));
-                const uint32_t w = pack4(b[0], b[1], b[2], b[3]);
+                const uint32_t w = pack4<kCodeByte<STOCH>>(b[0], b[1], b[2], b[3]);
                 if constexpr (TAIL) {
                     uint32_t n, i, dup;
                     place(q, n, i, dup);
@@ -1320,7 +1508,7 @@ __global__ __launch_bounds__(1024, NU <= 2 ? 8 : NU <= 8 ? 6 : 4) void k_chan_re
             uint32_t pos = (uint32_t)L.lead + n * slot + r * (uint32_t)L.row_pitch + col;
 #pragma unroll
             for (int e = 0; e < PER; ++e) {
-                if (!TAIL || e == 3 || (uint32_t)e >= dup) l_img[pos] = (int8_t)quant_bits<STOCH>(x[u][e], inv, draw_of(u, e));
+                if (!TAIL || e == 3 || (uint32_t)e >= dup) l_img[pos] = code_byte<STOCH>(quant_bits<STOCH>(x[u][e], inv, draw_of(u, e)));
                 const bool wrap = ++col == (uint32_t)L.W;   // a unit stays inside its image, but may run on into the next row
                 col = wrap ? 0u : col;
                 pos += wrap ? (uint32_t)(L.row_pitch - L.W) + 1u : 1u;
@@ -1428,7 +1616,7 @@ __device__ __forceinline__ void pack_w_tile(const int b, const PackWArgs& a, flo
 #pragma unroll
     for (int k = 0; k < 4 * NT; ++k) {
         place(e0 + kBlock * k, at, pl);
-        const int8_t code = at != ~0u ? (int8_t)quant_code<false>(x[k], inv, 0u) : (int8_t)0;
+        const int8_t code = at != ~0u ? code_byte<false>(quant_bits<false>(x[k], inv, 0u)) : (int8_t)0;
         if (at != ~0u) a.out[a.L.off_plain + at] = code;
         if (pl != ~0u) {
             const uint32_t t = pl >> 10, co = pl >> 5 & 31u, ci = pl & 31u;
@@ -1493,10 +1681,10 @@ __device__ __forceinline__ void pack_w_units(const int b, const PackWArgs& a, fl
     const float inv = inv_scale(s);
     uint32_t c[16];
 #pragma unroll
-    for (int i = 0; i < 16; ++i) c[i] = i < count ? (uint32_t)quant_code<false>(x[i], inv, 0u) : 0u;
+    for (int i = 0; i < 16; ++i) c[i] = i < count ? quant_bits<false>(x[i], inv, 0u) : 0u;
     if (o < a.L.bytes)
-        *reinterpret_cast<uint4*>(a.out + o) = make_uint4(pack4(c[0], c[1], c[2], c[3]), pack4(c[4], c[5], c[6], c[7]),
-                                                          pack4(c[8], c[9], c[10], c[11]), pack4(c[12], c[13], c[14], c[15]));
+        *reinterpret_cast<uint4*>(a.out + o) = make_uint4(pack4<0>(c[0], c[1], c[2], c[3]), pack4<0>(c[4], c[5], c[6], c[7]),
+                                                          pack4<0>(c[8], c[9], c[10], c[11]), pack4<0>(c[12], c[13], c[14], c[15]));
 }
 
 // Everything the forward pass quantizes, in one launch behind k_absmax: q(W), the two copies of q(X).  The three are
@@ -1505,7 +1693,7 @@ __device__ __forceinline__ void pack_w_units(const int b, const PackWArgs& a, fl
 // batch 8, whole pass: 39.8 -> 26.7 us; 1 x 1, 64 -> 256 at 56 x 56, batch 64: 91 -> 66; 416 -> 320 3 x 3 at 21 x 21: 59 -> 36).
 // Each role starts at a multiple of eight workgroups, so that its own mapping to the XCDs holds.
 // EARLY: the NHWC role writes both copies from one read of X, the channel-major role only the zeros round about the rows.
-// V: elements per thread of the source-driven channel-major role, 0: the output-driven one.
+// V: elements per thread of the source-driven channel-major role, 0: the output-driven one; 1 only with EARLY.  UNIT: see the NHWC role.
 struct FwdQuantArgs {
     const float* x;
     int8_t *nhwc, *cnhw;
@@ -1513,7 +1701,7 @@ struct FwdQuantArgs {
     int N, C, HW, c_pitch, tail;
     int w_blocks, x_blocks;   // of the first two roles, rounded up to a multiple of eight
     int phase_blocks;         // output-driven channel-major role: workgroups per stride phase
-    FastDiv div_hw;
+    FastDiv div_u;
     CnhwView Lc;
     PackArgs pa;
     RowsArgs ra;
@@ -1521,10 +1709,12 @@ struct FwdQuantArgs {
     QuantWs ws;
     PackWArgs w;
 };
-template <bool EARLY, int V>
+constexpr int kFwdTileDw = 1664;   // CountPlan::tile_dwords of four waves, at most
+template <bool EARLY, int V, int UNIT>
 __global__ __launch_bounds__(kBlock, 4) void k_fwd_quant(FwdQuantArgs a) {
     __shared__ float l_red[kBlock / kWave];
     __shared__ __align__(16) int8_t l_w[2 * kWTaps * kWPlane];
+    __shared__ __align__(16) uint32_t l_records[2 * kFwdTileDw];
     int b = (int)blockIdx.x;
     if (b < a.w_blocks) {   // uniform, as all branches below
         if (b >= a.w.blocks) return;
@@ -1535,8 +1725,8 @@ __global__ __launch_bounds__(kBlock, 4) void k_fwd_quant(FwdQuantArgs a) {
     }
     b -= a.w_blocks;
     if (b < a.x_blocks) {
-        if (b >= (a.C + 63) / 64 * a.ws.cgroups) return;
-        count_qg_role<float, false, true, false, EARLY>(b, a.x, a.N, a.C, a.HW, a.c_pitch, a.div_hw, a.ws, a.nhwc, 0, nullptr, a.s_x, a.ev, a.tail);
+        if (b >= a.ws.cp.workgroups()) return;
+        count_qg_role<float, false, true, false, EARLY, UNIT>(b, a.x, a.N, a.C, a.HW, a.c_pitch, a.div_u, a.ws, a.nhwc, 0, nullptr, a.s_x, a.ev, a.tail, l_records, kFwdTileDw);
         return;
     }
     b -= a.x_blocks;
@@ -1577,7 +1767,9 @@ bool f32_tensor_supported(int64_t elems) { return elems * 4 < ((int64_t)1 << 31)
 int nhwc_tail(const daq_layout& L) { return (int)(L.bytes - (int64_t)L.N * L.H * L.W * L.c_pitch); }
 
 // Elements per thread of the source-driven row kernel (4 or 2), or 0 when the layout needs the output-driven one.
-int rows_vector(const daq_layout& Ld, const void* src, int elem_bytes = 4) {
+// `any`: a row length or an alignment that fits neither is served element by element (1), which pays where the kernel only writes
+// the padding and the channels whose class was guessed wrong.
+int rows_vector(const daq_layout& Ld, const void* src, int elem_bytes = 4, bool any = false) {
     const int64_t lim24 = (int64_t)1 << 24;
     const bool unsplit = Ld.phases_h == 1 && Ld.phases_w == 1 && Ld.org_h == 0 && Ld.org_w == 0 &&
                          (int64_t)Ld.N * Ld.img_rows < lim24 && (int64_t)Ld.H * Ld.W < lim24 &&
@@ -1585,7 +1777,25 @@ int rows_vector(const daq_layout& Ld, const void* src, int elem_bytes = 4) {
     // the vector of 4 or 2 source elements a thread loads must be aligned as a whole
     if (unsplit && Ld.W % 4 == 0 && ((uintptr_t)src & (uintptr_t)(4 * elem_bytes - 1)) == 0) return 4;
     if (unsplit && Ld.W % 2 == 0 && ((uintptr_t)src & (uintptr_t)(2 * elem_bytes - 1)) == 0) return 2;
-    return 0;
+    return unsplit && any ? 1 : 0;
+}
+
+// Whether the NHWC pass over a tensor can write the channel-major copy of this layout too, and what it needs for that.
+bool early_copy_supported(const daq_layout& Ld, const void* src, int elem_bytes) {
+    return rows_vector(Ld, src, elem_bytes, true) != 0 && Ld.lead + (int64_t)Ld.N * Ld.img_rows * Ld.row_pitch < ((int64_t)1 << 31);
+}
+EarlyVq early_vq(const daq_layout& Ld, int8_t* dst) {
+    EarlyVq ev{};
+    ev.vq = dst;
+    ev.chan_pitch = Ld.chan_pitch;
+    ev.lead = (int32_t)Ld.lead;
+    ev.img_rows = Ld.img_rows;
+    ev.row_pitch = Ld.row_pitch;
+    ev.W = Ld.W;
+    ev.div_w = make_fastdiv((uint32_t)Ld.W);
+    ev.flat = Ld.row_pitch == Ld.W && Ld.img_rows == Ld.H;
+    ev.whole = ev.flat || Ld.W % 4 == 0;
+    return ev;
 }
 
 RowsArgs rows_args(const daq_layout& Ld, int v, bool early, int part_n, uint32_t tensor, uint64_t seed) {
@@ -1624,7 +1834,7 @@ daq_status launch_pack(const char* name, bool stoch, bool clip, const T* src, co
                        float* publish = nullptr) {
     if (fused) *fused = false;
     const CnhwView V = cnhw_view(Ld);
-    const int v = rows_vector(Ld, src, (int)sizeof(T));
+    const int v = rows_vector(Ld, src, (int)sizeof(T), early);
     if (early && !v) return DAQ_ERR_INVALID_ARG;   // the caller checks rows_vector before it asks for the early copy
     if (v) {
         RowsArgs ra = rows_args(Ld, v, early, part_n, tensor, seed);
@@ -1640,6 +1850,9 @@ daq_status launch_pack(const char* name, bool stoch, bool clip, const T* src, co
         if (v == 4) {
             if (stoch) { if (clip) DAQ_ROWS(true, true, 4); else DAQ_ROWS(true, false, 4); }
             else { if (clip) DAQ_ROWS(false, true, 4); else DAQ_ROWS(false, false, 4); }
+        } else if (v == 1) {
+            if (!clip) return DAQ_ERR_INVALID_ARG;
+            if (stoch) DAQ_ROWS(true, true, 1); else DAQ_ROWS(false, true, 1);
         } else {
             if (stoch) { if (clip) DAQ_ROWS(true, true, 2); else DAQ_ROWS(true, false, 2); }
             else { if (clip) DAQ_ROWS(false, true, 2); else DAQ_ROWS(false, false, 2); }
@@ -1756,19 +1969,20 @@ daq_status quantize_forward(const daq_conv_desc& d, const float* X, int8_t* qx_n
     FwdQuantArgs a{};
     a.x = X; a.nhwc = qx_nhwc; a.cnhw = qx_cnhw; a.s_x = s_x;
     a.N = d.N; a.C = d.Cin; a.HW = HW; a.c_pitch = Ln.c_pitch; a.tail = nhwc_tail(Ln);
-    a.div_hw = make_fastdiv((uint32_t)HW);
+    a.div_u = make_fastdiv(unit_divisor(HW));
     a.Lc = cnhw_view(Lc);
-    a.ws = carve_quant_ws(nullptr, d.Cin, d.N, HW);  // only the tile geometry is used: nothing is counted here
+    a.ws = carve_quant_ws(nullptr, d.Cin, d.N, HW, kBlock / kWave);
+    if (a.ws.cp.tile_dwords(d.Cin) > kFwdTileDw) return DAQ_ERR_UNSUPPORTED;   // (four waves: never)  // only the tile geometry is used: nothing is counted here
     a.ws.part_max = part;
     a.ws.part_n = m.blocks[0];
     a.ws.layer = part + kAbsmaxBlocksX + kAbsmaxBlocksW;
-    a.x_blocks = (int)round_up(ceil_div(d.Cin, 64) * a.ws.cgroups, kXcd);
+    a.x_blocks = (int)round_up(a.ws.cp.workgroups(), kXcd);
     // Unit-stride layers whose channel-major layout the row kernel serves: one sweep over X writes both copies (the
     // mechanism of the early per-channel copy of dY, with the per-tensor scale), and only the padding bytes are left.
-    // (by default from 8 Mi elements on: below that the two lean passes are faster, as for dY)
-    const int v = rows_vector(Lc, X);
-    const bool early = (schedule == DAQ_SCHEDULE_EARLY_COPY || (schedule == DAQ_SCHEDULE_AUTO && n >= ((int64_t)8 << 20))) && v != 0 &&
-                       Lc.lead + (int64_t)d.N * Lc.img_rows * Lc.row_pitch < ((int64_t)1 << 32);
+    // (by default from 4 Mi elements on: below that the two lean passes are as fast, as for dY)
+    const bool early = (schedule == DAQ_SCHEDULE_EARLY_COPY || (schedule == DAQ_SCHEDULE_AUTO && n >= kEarlyVqMinElems)) &&
+                       early_copy_supported(Lc, X, 4);
+    const int v = rows_vector(Lc, X, 4, early);
     int64_t c_blocks;
     if (v) {
         a.ra = rows_args(Lc, v, early, a.ws.part_n, 0u, 0);
@@ -1779,9 +1993,10 @@ daq_status quantize_forward(const daq_conv_desc& d, const float* X, int8_t* qx_n
         a.phase_blocks = (int)g.x;
         c_blocks = (int64_t)g.x * g.z;
     }
-    if (early)
-        a.ev = EarlyVq{qx_cnhw, Lc.chan_pitch, (int32_t)Lc.lead, Lc.img_rows, Lc.row_pitch, Lc.W, make_fastdiv((uint32_t)Lc.W),
-                       0.0f, 0.0f, 0.0f, Lc.W % 4 == 0 ? 1 : 0};
+    if (early) {
+        a.ev = early_vq(Lc, qx_cnhw);
+        a.ev.once = n * 4 > kCacheBytes;
+    }
     if (W) {
         PackWArgs& w = a.w;
         if (daq_layout_qw(&d, &w.L) != DAQ_OK) return DAQ_ERR_INVALID_ARG;
@@ -1802,11 +2017,22 @@ daq_status quantize_forward(const daq_conv_desc& d, const float* X, int8_t* qx_n
     }
     const int64_t blocks = a.w_blocks + a.x_blocks + c_blocks;
     if (blocks >= ((int64_t)1 << 31)) return DAQ_ERR_UNSUPPORTED;
-#define DAQ_FWD_QUANT(E, VV) DAQ_LAUNCH("quant_fwd", st, hipLaunchKernelGGL((k_fwd_quant<E, VV>), dim3((unsigned)blocks), dim3(kBlock), 0, st, a))
-    if (early) { if (v == 4) DAQ_FWD_QUANT(true, 4); else DAQ_FWD_QUANT(true, 2); }
-    else if (v == 4) DAQ_FWD_QUANT(false, 4);
-    else if (v == 2) DAQ_FWD_QUANT(false, 2);
-    else DAQ_FWD_QUANT(false, 0);
+#define DAQ_FWD_QUANT(E, VV, UN) DAQ_LAUNCH("quant_fwd", st, hipLaunchKernelGGL((k_fwd_quant<E, VV, UN>), dim3((unsigned)blocks), dim3(kBlock), 0, st, a))
+    const int unit = unit_kind(HW);
+    if (v == 4) { if (early) DAQ_FWD_QUANT(true, 4, kWhole); else DAQ_FWD_QUANT(false, 4, kWhole); }   // rows of whole units
+    else if (unit == kWhole) {
+        if (v == 2) { if (early) DAQ_FWD_QUANT(true, 2, kWhole); else DAQ_FWD_QUANT(false, 2, kWhole); }
+        else if (early) DAQ_FWD_QUANT(true, 1, kWhole);
+        else DAQ_FWD_QUANT(false, 0, kWhole);
+    } else if (unit == kTail) {
+        if (v == 2) { if (early) DAQ_FWD_QUANT(true, 2, kTail); else DAQ_FWD_QUANT(false, 2, kTail); }
+        else if (early) DAQ_FWD_QUANT(true, 1, kTail);
+        else DAQ_FWD_QUANT(false, 0, kTail);
+    } else {
+        if (v == 2) { if (early) DAQ_FWD_QUANT(true, 2, kElems); else DAQ_FWD_QUANT(false, 2, kElems); }
+        else if (early) DAQ_FWD_QUANT(true, 1, kElems);
+        else DAQ_FWD_QUANT(false, 0, kElems);
+    }
 #undef DAQ_FWD_QUANT
     return DAQ_OK;
 }
@@ -1887,8 +2113,8 @@ daq_status quantize_grad_impl(const daq_conv_desc* desc, const T* dY, float* s_s
     ws.scheme = (int)scheme;
     const double Mtot = (double)N * (double)C * (double)HW;
 
-    const FastDiv div_hw = make_fastdiv((uint32_t)HW);
-    const int CB = (int)ceil_div(C, 64);
+    const int unit = unit_kind(HW);
+    const FastDiv div_hw = make_fastdiv((uint32_t)HW), div_u = make_fastdiv(unit_divisor(HW));
 
     // Channels that fit in LDS: one read of dY serves statistics, count, decision and the per-channel copy
     // (k_chan_resident); the global copy follows in the counting kernel's copy-only form.
@@ -1945,13 +2171,17 @@ daq_status quantize_grad_impl(const daq_conv_desc* desc, const T* dY, float* s_s
             return launch_pack("pack_qg", stoch, false, dY, Lv, ws.part_max, qg, 1u, keys, ws, ClipArgs{}, st, nullptr, nullptr, 0, nullptr, false,
                                ws.part_n, s_global);
         }
-        const dim3 cgrid((unsigned)(CB * ws.cgroups));
-#define DAQ_COPY_LAUNCH(S)                                                                                           \
+        const dim3 cgrid((unsigned)ws.cp.workgroups()), cblock((unsigned)(ws.cp.waves * kWave));
+        const int tile_dw = ws.cp.tile_dwords(C);
+        const size_t clds = (size_t)tile_dw * 8;
+#define DAQ_COPY_LAUNCH(S, UN)                                                                                        \
     DAQ_LAUNCH("global_copy", st,                                                                                    \
-               hipLaunchKernelGGL((k_count_qg<T, S, true, false, false>), cgrid, dim3(kBlock), 0, st, dY, N, C, HW, Lg.c_pitch, \
-                                  div_hw, ws, qg, keys, (const float*)s_state, s_global, EarlyVq{}, nhwc_tail(Lg)))
-        if (stoch) DAQ_COPY_LAUNCH(true);
-        else DAQ_COPY_LAUNCH(false);
+               hipLaunchKernelGGL((k_count_qg<T, S, true, false, false, UN>), cgrid, cblock, clds, st, dY, N, C, HW, Lg.c_pitch, \
+                                  div_u, ws, qg, keys, (const float*)s_state, s_global, EarlyVq{}, nhwc_tail(Lg), tile_dw))
+        if (unit == kWhole) { if (stoch) DAQ_COPY_LAUNCH(true, kWhole); else DAQ_COPY_LAUNCH(false, kWhole); }
+        else if (unit == kTail) { if (stoch) DAQ_COPY_LAUNCH(true, kTail); else DAQ_COPY_LAUNCH(false, kTail); }
+        else if (stoch) DAQ_COPY_LAUNCH(true, kElems);
+        else DAQ_COPY_LAUNCH(false, kElems);
 #undef DAQ_COPY_LAUNCH
         return DAQ_OK;
     }
@@ -1977,40 +2207,49 @@ daq_status quantize_grad_impl(const daq_conv_desc* desc, const T* dY, float* s_s
         DAQ_LAUNCH("layer_stats", st, hipLaunchKernelGGL(k_layer_stats, dim3(1), dim3(kBlock), 0, st, ws, C, Mtot));
 
     // S2 (+ the NHWC global copy); folds the statistics itself
-    const dim3 cgrid((unsigned)(CB * ws.cgroups));
+    const dim3 cgrid((unsigned)ws.cp.workgroups()), cblock((unsigned)(ws.cp.waves * kWave));
+    const int tile_dw = qg_nhwc ? ws.cp.tile_dwords(C) : 0;
+    const size_t clds = (size_t)tile_dw * 8;
     // Large gradients: the counting pass also writes the per-channel copy under a guessed class (see k_count_qg), so
     // that the third sweep over dY only touches the channels whose guess was wrong.  Small ones are bound by launch
     // latency, not by bytes, and keep the leaner counting kernel.
     // (With the producer's statistics the counting sweep is the only full read of dY: it always writes both copies.)
     const bool want_early = schedule == DAQ_SCHEDULE_EARLY_COPY || (schedule == DAQ_SCHEDULE_AUTO && (int64_t)N * C * HW >= kEarlyVqMinElems) ||
                             (given && schedule != DAQ_SCHEDULE_THREE_SWEEPS);
-    const bool early = want_early && scheme == DAQ_SCHEME_DAQ && qg_nhwc && rows_vector(Lv, dY, (int)sizeof(T)) != 0 &&
-                       Lv.lead + (int64_t)N * Lv.img_rows * Lv.row_pitch < ((int64_t)1 << 32);
+    const bool early = want_early && scheme == DAQ_SCHEME_DAQ && qg_nhwc && early_copy_supported(Lv, dY, (int)sizeof(T));
     EarlyVq ev{};
     if (early) {
         // |g|max / sigma of M Gaussian samples is about sqrt(2 ln M), of M Laplace samples ln M / sqrt 2: halfway
         const double lnM = std::log((double)N * HW);
-        ev = EarlyVq{vq, Lv.chan_pitch, (int32_t)Lv.lead, Lv.img_rows, Lv.row_pitch, Lv.W, make_fastdiv((uint32_t)Lv.W), k, A,
-                     (float)(0.5 * (std::sqrt(2.0 * lnM) + lnM / std::sqrt(2.0))), Lv.W % 4 == 0 ? 1 : 0};
+        ev = early_vq(Lv, vq);
+        ev.once = (int64_t)N * C * HW * (int64_t)sizeof(T) > kCacheBytes;
+        ev.k = k;
+        ev.A = A;
+        ev.ratio = (float)(0.5 * (std::sqrt(2.0 * lnM) + lnM / std::sqrt(2.0)));
     }
-#define DAQ_COUNT_LAUNCH(S, Q, E)                                                                                    \
+#define DAQ_COUNT_LAUNCH(S, Q, E, UN)                                                                                \
     DAQ_LAUNCH("count_qg", st,                                                                                       \
-               hipLaunchKernelGGL((k_count_qg<T, S, Q, true, E>), cgrid, dim3(kBlock), 0, st, dY, N, C, HW,             \
-                                  qg_nhwc ? Lg.c_pitch : 0, div_hw, ws, qg, keys, (const float*)s_state,   \
-                                  s_global, ev, qg_nhwc ? nhwc_tail(Lg) : 0))
-    if (early) {
-        if (stoch) DAQ_COUNT_LAUNCH(true, true, true);
-        else DAQ_COUNT_LAUNCH(false, true, true);
-    } else if (qg_nhwc) {
-        if (stoch) DAQ_COUNT_LAUNCH(true, true, false);
-        else DAQ_COUNT_LAUNCH(false, true, false);
-    } else {
-        DAQ_COUNT_LAUNCH(false, false, false);
+               hipLaunchKernelGGL((k_count_qg<T, S, Q, true, E, UN>), cgrid, cblock, clds, st, dY, N, C, HW,         \
+                                  qg_nhwc ? Lg.c_pitch : 0, div_u, ws, qg, keys, (const float*)s_state,    \
+                                  s_global, ev, qg_nhwc ? nhwc_tail(Lg) : 0, tile_dw))
+#define DAQ_COUNT_UNIT(S, Q, E)                                                                                      \
+    {                                                                                                                \
+        if (unit == kWhole) DAQ_COUNT_LAUNCH(S, Q, E, kWhole);                                                       \
+        else if (unit == kTail) DAQ_COUNT_LAUNCH(S, Q, E, kTail);                                                    \
+        else DAQ_COUNT_LAUNCH(S, Q, E, kElems);                                                                      \
     }
+    if (early) {
+        if (stoch) DAQ_COUNT_UNIT(true, true, true) else DAQ_COUNT_UNIT(false, true, true)
+    } else if (qg_nhwc) {
+        if (stoch) DAQ_COUNT_UNIT(true, true, false) else DAQ_COUNT_UNIT(false, true, false)
+    } else {
+        DAQ_COUNT_UNIT(false, false, false)
+    }
+#undef DAQ_COUNT_UNIT
 #undef DAQ_COUNT_LAUNCH
     if (scheme == DAQ_SCHEME_MCS)
         DAQ_LAUNCH("layer_decide", st,
-                   hipLaunchKernelGGL(k_layer_decide, dim3(1), dim3(kBlock), 0, st, ws, (int)cgrid.x * (kBlock / kWave), Mtot, k, A,
+                   hipLaunchKernelGGL(k_layer_decide, dim3(1), dim3(kBlock), 0, st, ws, (int)cgrid.x * ws.cp.waves, Mtot, k, A,
                                       lambda));
 
     // S3 + S4 + S5: discriminator, clip rule and the per-channel copy in CNHW (and the global copy for

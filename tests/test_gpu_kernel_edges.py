@@ -96,3 +96,19 @@ def test_resident_quantizer_on_planes_of_any_size(per_thread, n, h, w, k):
     for mode, seed in ((daq.ROUND_NEAREST, 0), (daq.ROUND_STOCHASTIC, 31 + n)):
         check_quantize_grad(layer, dY, st, mode=mode, seed=seed)
         check_quantize_grad_bf16(layer, dY, st, mode=mode, seed=seed)
+
+
+# Channel counts by the groups of 16 that the counting pass gives a workgroup's waves: one to three groups (several tiles at a
+# time), a whole record, blocks of equal width, a last block of two groups beside one of seven, of one beside five
+@pytest.mark.parametrize("channels", [9, 24, 48, 90, 144, 190, 208, 330])
+@pytest.mark.parametrize("n,h,w", [(5, 8, 8), (3, 7, 7), (4, 6, 9), (9, 1, 3)], ids=lambda v: str(v))
+@pytest.mark.parametrize("schedule", [daq.SCHEDULE_THREE_SWEEPS, daq.SCHEDULE_EARLY_COPY])
+def test_counting_pass_units_and_blocks(channels, n, h, w, schedule):
+    """Planes of whole units of four, with a shorter last unit, and of less than one; both copies byte for byte, with guessed classes
+    that hold and (lambda 0 and 1) that do not."""
+    for k in (1, 3):
+        layer = wl.Layer("units", n, 1, h, w, channels, k, k, 1, k // 2)
+        dY = wl.make_dY(layer, wl.seed_for(22, channels))
+        st = wl.make_state(dY, wl.seed_for(22, channels))
+        for mode, seed, lam in ((daq.ROUND_NEAREST, 0, 0.3), (daq.ROUND_STOCHASTIC, 7 + n, 0.0), (daq.ROUND_STOCHASTIC, 8 + n, 1.0)):
+            check_quantize_grad(layer, dY, st, lam=lam, mode=mode, seed=seed, schedule=schedule)
