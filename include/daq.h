@@ -357,7 +357,7 @@ daq_status daq_conv_fwd_int8(const daq_conv_desc* desc, const float* X, const fl
                              void* workspace, size_t workspace_bytes, void* stream);
 
 /* daq_conv_fwd_int8 with the schedule of its activation quantizer explicit: DAQ_SCHEDULE_EARLY_COPY
- * writes both layouts of q(X) in one sweep over X (taken by default from 4 Mi elements on, where
+ * writes both layouts of q(X) in one sweep over X (taken by default from 8 Mi elements on, where
  * the channel-major layout is unsplit), DAQ_SCHEDULE_THREE_SWEEPS (and DAQ_SCHEDULE_CHANNEL_RESIDENT, which has no
  * forward form) one sweep per layout.  Same bits. */
 daq_status daq_conv_fwd_int8_ex(const daq_conv_desc* desc, const float* X, const float* W, int8_t* qx_nhwc,

@@ -1188,6 +1188,15 @@ daq_status launch_stream(const char* name, const daq_conv_desc& d, const daq_lay
 
 }  // namespace
 
+static OtherKernel as_other(const Geometry& g) {
+    const HaloArgs& a = g.a;
+    int taps = a.ph_taps[0];
+    for (int c = 1; c < a.stride * a.stride; ++c) taps = std::max(taps, a.ph_taps[c]);
+    const TileForm form = ring1_applies(g) ? TileForm::kRing1 : taps9_applies(g) ? TileForm::kTaps9 : g.rows == 128 ? TileForm::kRows128
+                          : a.Crow <= 32   ? TileForm::kNarrow : TileForm::kTaps;
+    return OtherKernel{form, a.stride > 1, blocks_per_row_tile(a) * ceil_div(a.Crow, g.rows), taps * (int)ceil_div(a.cp, kKc)};
+}
+
 bool bwd_data_halo_supported(const daq_conv_desc& d) { return plan_bwd(d).ok; }
 
 daq_status conv_bwd_data_halo(const daq_conv_desc& d, const int8_t* qg, const float* s_g, const int8_t* qw,
@@ -1201,6 +1210,8 @@ daq_status conv_bwd_data_halo(const daq_conv_desc& d, const int8_t* qg, const fl
     if (daq_layout_qg(&d, &Lg) == DAQ_OK && stream_applies(d, Lg))
         return launch_stream("conv_bwd_data_stream", d, Lg, qg, qw + Lw.off_bwd_frag, Lw.bytes - Lw.off_bwd_frag, d.Cin, s_w, s_g, dX, acc,
                              st, tail, bf16);
+    daq_status rc;
+    if (conv_direct(true, d, as_other(g), qg, qw, s_w, s_g, dX, acc, st, tail, bf16, rc)) return rc;
     g.a.src = qg;
     g.a.wfrag = qw + Lw.off_bwd_frag;
     g.a.s_a = s_w; g.a.s_b = s_g;
@@ -1265,6 +1276,8 @@ daq_status conv_fwd_halo(const daq_conv_desc& d, const int8_t* qx, const int8_t*
     if (daq_layout_qx_nhwc(&d, &Lx) == DAQ_OK && stream_applies(d, Lx))   // thin 1 x 1 layers: the streaming kernel, rows = Cout
         return launch_stream("conv_fwd_stream", d, Lx, qx, qw + Lw.off_fwd_frag, Lw.off_bwd_frag - Lw.off_fwd_frag, d.Cout, s_x, s_w, Y,
                              acc, st, nullptr);
+    daq_status rc;
+    if (conv_direct(false, d, as_other(g), qx, qw, s_x, s_w, Y, acc, st, nullptr, false, rc)) return rc;
     g.a.src = qx;
     g.a.wfrag = qw + Lw.off_fwd_frag;
     g.a.s_a = s_x; g.a.s_b = s_w;

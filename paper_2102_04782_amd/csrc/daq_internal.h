@@ -245,6 +245,20 @@ daq_status conv3d_bwd_data_halo(const daq_conv3d_desc& d, const int8_t* qg, cons
 daq_status conv3d_fwd_halo(const daq_conv3d_desc& d, const int8_t* qx, const int8_t* w_fwd, const float* s_x, const float* s_w, float* Y,
                            int32_t* acc, void* frag, hipStream_t st);
 
+// conv_mfma_direct.hip: the same products for layers of few tiles, operands straight from global memory.  `other` is what would serve
+// the layer otherwise, with its workgroups and the steps (tap x 64 channels) of each; false: that is the faster one by the two's cost
+// models, or these kernels do not serve the layer, and nothing was launched.
+struct DwTail;
+enum class TileForm { kTaps9, kRows128, kNarrow, kTaps, kRing1, kNhwc };
+struct OtherKernel {
+    TileForm form;
+    bool classes;      // a strided data gradient, by parity class
+    int64_t blocks;
+    int steps;
+};
+bool conv_direct(bool backward, const daq_conv_desc& d, const OtherKernel& other, const int8_t* src, const int8_t* qw, const float* s_a,
+                 const float* s_b, float* out, int32_t* acc, hipStream_t st, const DwTail* tail, bool bf16, daq_status& rc);
+
 // conv_depthwise.hip: groups == channels, both operands channel-major
 bool depthwise_dx_supported(const daq_conv_desc& d);
 daq_status conv_bwd_data_depthwise(const daq_conv_desc& d, const int8_t* qg, const float* s_g, const int8_t* qw,

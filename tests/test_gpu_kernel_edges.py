@@ -112,3 +112,40 @@ def test_counting_pass_units_and_blocks(channels, n, h, w, schedule):
         st = wl.make_state(dY, wl.seed_for(22, channels))
         for mode, seed, lam in ((daq.ROUND_NEAREST, 0, 0.3), (daq.ROUND_STOCHASTIC, 7 + n, 0.0), (daq.ROUND_STOCHASTIC, 8 + n, 1.0)):
             check_quantize_grad(layer, dY, st, lam=lam, mode=mode, seed=seed, schedule=schedule)
+
+
+FEW_TILES = [
+    wl.Layer("d_one", 1, 1, 1, 1, 1, 3, 3, 1, 1),                # one pixel, one record unit a tap, five steps
+    wl.Layer("d_units1", 2, 16, 9, 11, 33, 5, 5, 1, 2),          # one 16-byte unit a record: a step spans two taps
+    wl.Layer("d_units3", 3, 40, 7, 9, 65, 3, 3, 1, 1),           # three: a step may, or may not
+    wl.Layer("d_units5", 2, 70, 13, 5, 31, 1, 7, 1, 3),
+    wl.Layer("d_stem", 3, 3, 17, 15, 40, 7, 7, 2, 3),            # 49 taps: the forward's eighth wave has the odd step
+    wl.Layer("d_s2", 4, 50, 14, 13, 60, 3, 3, 2, 1),             # four parity classes of 1, 2, 2 and 4 taps
+    wl.Layer("d_s2_1x1", 3, 130, 9, 8, 20, 1, 1, 2, 0),          # three of them without a tap: zeros
+    wl.Layer("d_s2_dil", 2, 33, 15, 14, 40, 3, 3, 2, 2, dil=2),  # even dilation: all taps in one class
+    wl.Layer("d_s3", 2, 20, 14, 16, 40, 3, 3, 3, 1),             # forward only
+    wl.Layer("d_ks1", 40, 32, 32, 33, 48, 3, 3, 1, 1),           # tiles enough for a wave each
+    wl.Layer("d_ks2", 12, 96, 32, 33, 64, 3, 3, 2, 1),
+]
+
+
+@pytest.mark.parametrize("layer", FEW_TILES, ids=lambda l: l.name)
+def test_products_of_few_tiles(layer):
+    """Both products without staging, 1 to 8 waves to a tile, records of 1 to 17 units, every class of taps."""
+    on_random_codes(layer, 71)
+    check_forward(layer, 72)
+
+
+@pytest.mark.parametrize("layer", [
+    wl.Layer("t_narrow", 40, 70, 21, 23, 40, 3, 3, 1, 1),
+    wl.Layer("t_taps9", 16, 140, 21, 23, 100, 3, 3, 1, 1),
+    wl.Layer("t_ring", 30, 300, 25, 27, 300, 1, 1, 1, 0),
+    wl.Layer("t_ring_s2", 40, 90, 31, 33, 330, 1, 1, 2, 0),
+    wl.Layer("t_r128_s2", 40, 70, 41, 43, 70, 3, 3, 2, 1),
+    wl.Layer("t_s2", 60, 30, 41, 43, 40, 3, 3, 2, 1),
+    wl.Layer("t_s3", 8, 20, 9, 9, 20, 3, 3, 3, 1),
+], ids=lambda l: l.name)
+def test_products_of_many_ragged_tiles(layer):
+    """Tiles enough for the tile kernel's forms, odd images, channel counts off every block."""
+    on_random_codes(layer, 73)
+    check_forward(layer, 74)
