@@ -167,6 +167,7 @@ daq_status quantize_forward(const daq_conv_desc& d, const float* X, int8_t* qx_n
 struct ResidentForm { int nu, waves; };
 ResidentForm resident_form(int C, int64_t units);
 bool resident_pays(int C, int64_t units, bool padded, bool tails, bool stochastic);   // tails: planes that are not whole units
+bool resident_all_pays(int C, int64_t M, int64_t units);   // whether the launch also writes the global copy of C channels of M elements
 bool fold_in_packing(int64_t workgroups);   // whether those of a channel-major packing launch fold its scale themselves
 
 // clip_search.hip

@@ -1281,6 +1281,10 @@ struct ResArgs {
     int N, C, HW;
     float k, A, lambda;
     uint64_t seed;         // the keys of stochastic rounding (round_keys)
+    // the form that writes the NHWC global copy too
+    int8_t* qg;
+    float* s_global;
+    int c_pitch, qg_tail;
 };
 
 // A load unit is four consecutive elements of one plane (VEC4, planes of at least four elements) or one element; a thread
@@ -1290,7 +1294,10 @@ struct ResArgs {
 // instead of 49.  (512 -> 2048 1 x 1 at 7 x 7, batch 128, bfloat16: 27 us with a load an element, 22.5 here.)
 // FLAT (without TAIL): the plane has no padding between rows or images (1 x 1 layers), so element m of the channel sits at
 // byte lead + m and a unit's four codes are one aligned dword of the plane: they go straight to memory, no LDS image.
-template <typename T, bool STOCH, bool VEC4, int NU, bool FLAT, bool TAIL>
+// ALL: the global copy as well, in the same launch.  Its scale is the maximum over all channels, so every workgroup reads the whole tensor
+// for it, 16 bytes a thread and eight loads at a time, and its codes leave as single bytes of the NHWC records: a few microseconds
+// where tensors are small, less than the launch they replace (resident_all_pays).
+template <typename T, bool STOCH, bool VEC4, int NU, bool FLAT, bool TAIL, bool ALL>
 __global__ __launch_bounds__(1024, NU <= 2 ? 8 : NU <= 8 ? 6 : 4) void k_chan_resident(const T* __restrict__ g, CnhwView L, int8_t* __restrict__ vq,
                                                       ResArgs ra, QuantWs ws, ClipArgs ca) {
     extern __shared__ __align__(16) int8_t l_img[];   // the channel's plane as it will sit in memory
@@ -1298,8 +1305,9 @@ __global__ __launch_bounds__(1024, NU <= 2 ? 8 : NU <= 8 ? 6 : 4) void k_chan_re
     __shared__ float l_mx[kMaxWaves];
     __shared__ double l_s1[kMaxWaves], l_s2[kMaxWaves];
     __shared__ uint32_t l_cnt[kMaxWaves];
+    __shared__ float l_all[ALL ? kMaxWaves : 1];
     const int TH = (int)blockDim.x;
-    __shared__ float l_bc[4];   // |g|max, mean, sigma, clip value
+    __shared__ float l_bc[5];   // |g|max, mean, sigma, clip value, the tensor's |g|max
     // workgroup b runs on XCD b % 8: an XCD takes a contiguous eighth of the channels, whose planes are neighbours in
     // every image and share cache lines where a plane is not a whole number of them
     const int per_xcd = (ra.C + kXcd - 1) / kXcd;
@@ -1403,6 +1411,27 @@ __global__ __launch_bounds__(1024, NU <= 2 ? 8 : NU <= 8 ? 6 : 4) void k_chan_re
         if (!TAIL || e == 3) return x[u][e];
         return (dups >> (2 * u) & 3u) > (uint32_t)e ? 0.0f : x[u][e];
     };
+    float all = 0.0f;   // |g|max of the tensor
+    if constexpr (ALL) {
+        const uint32_t total = (uint32_t)M * (uint32_t)ra.C, quads = (total + 3u) / 4u;
+        if (total >= 4u) {   // uniform
+            for (uint32_t q0 = (uint32_t)tid; q0 < quads; q0 += 8u * (uint32_t)TH) {
+                uint4 v[8];
+#pragma unroll
+                for (int u = 0; u < 8; ++u) {   // (what lies past the end is the last one again; the last one ends with the tensor)
+                    const uint32_t at = min(4u * min(q0 + (uint32_t)(u * TH), quads - 1u), total - 4u);
+                    v[u] = ld4_or_zero<T>(g + at, true);
+                }
+#pragma unroll
+                for (int u = 0; u < 8; ++u)
+                    all = fmaxf(fmaxf(all, fmaxf(fabsf(__uint_as_float(v[u].x)), fabsf(__uint_as_float(v[u].y)))),
+                                fmaxf(fabsf(__uint_as_float(v[u].z)), fabsf(__uint_as_float(v[u].w))));
+            }
+        } else if ((uint32_t)tid < total) {
+            all = fabsf(ld1_or_zero<T>(g + tid, true));
+        }
+        all = wave_max(all);
+    }
     float mx = 0.0f;
     double s1 = 0.0, s2 = 0.0;
 #pragma unroll
@@ -1419,6 +1448,7 @@ __global__ __launch_bounds__(1024, NU <= 2 ? 8 : NU <= 8 ? 6 : 4) void k_chan_re
     s1 = wave_sum(s1);
     s2 = wave_sum(s2);
     if (lane == 0) { l_mx[wave] = mx; l_s1[wave] = s1; l_s2[wave] = s2; }
+    if (ALL && lane == 0) l_all[wave] = all;
     // the padding of the plane image, while the partials settle
     if constexpr (!FLAT)
         for (int i = tid; i < (int)(L.plane_pitch >> 4); i += TH) reinterpret_cast<uint4*>(l_img)[i] = make_uint4(0u, 0u, 0u, 0u);
@@ -1432,6 +1462,11 @@ __global__ __launch_bounds__(1024, NU <= 2 ? 8 : NU <= 8 ? 6 : 4) void k_chan_re
         l_bc[0] = mx;
         l_bc[1] = (float)mu;
         l_bc[2] = (float)sqrt(var);
+        if constexpr (ALL) {
+            for (int w = 1; w < TH / kWave; ++w) all = fmaxf(all, l_all[w]);
+            l_bc[4] = all >= kTinyScale ? all : 0.0f;
+            if (c == 0) *ra.s_global = l_bc[4];
+        }
     }
     __syncthreads();
     const float gm = l_bc[0], sigma = l_bc[2];
@@ -1460,7 +1495,35 @@ __global__ __launch_bounds__(1024, NU <= 2 ? 8 : NU <= 8 ? 6 : 4) void k_chan_re
             ca.stats[4 * c + 2] = sigma;
             ca.stats[4 * c + 3] = (float)((double)cnt / Md);
         }
-        ws.part_max[c] = gm;   // one partial per channel: the copy-only launch folds them into the global scale
+        if constexpr (!ALL) ws.part_max[c] = gm;   // one partial per channel: the copy-only launch folds them into the global scale
+    }
+    if constexpr (ALL) {
+        // ---- S5, the global copy: the channel's byte of every record (the upper halves of the words above are the per-channel copy's) ----
+        const float inv_g = inv_scale(l_bc[4]);
+#pragma unroll
+        for (int u = 0; u < NU; ++u) {
+            const uint32_t q = (uint32_t)(u * TH + tid);
+            if (q < units) {
+                uint32_t n, i, dup, w[4] = {0u, 0u, 0u, 0u};
+                place(q, n, i, dup);
+                const uint32_t at = n * image + first + i;
+                if constexpr (STOCH && PER == 4 && !TAIL) draw_words4(ra.seed, at, w);
+                int8_t* rec = ra.qg + (int64_t)(n * (uint32_t)HW + i) * ra.c_pitch + c;
+#pragma unroll
+                for (int e = 0; e < PER; ++e) {   // (what a unit shares with the one before it, both write the same)
+                    if constexpr (STOCH && (PER != 4 || TAIL)) w[e] = draw_word(ra.seed, at + (uint32_t)e);
+                    rec[(int64_t)e * ra.c_pitch] = code_byte<STOCH>(quant_bits<STOCH>(x[u][e], inv_g, draw_half(w[e], 1u)));
+                }
+            }
+        }
+        if (c == ra.C - 1) {   // the bytes of channels past the last one, and those behind the last record
+            const uint32_t pad = (uint32_t)(ra.c_pitch - ra.C), bytes = (uint32_t)M * pad;
+            for (uint32_t t = (uint32_t)tid; t < bytes; t += (uint32_t)TH) {
+                const uint32_t P = t / pad;
+                ra.qg[(int64_t)P * ra.c_pitch + ra.C + (t - P * pad)] = 0;
+            }
+            for (int t = tid; t < ra.qg_tail; t += TH) ra.qg[(int64_t)M * ra.c_pitch + t] = 0;
+        }
     }
     __syncthreads();
     const float inv = inv_scale(l_bc[3]);
@@ -1936,6 +1999,11 @@ bool resident_pays(int C, int64_t units, bool padded, bool tails, bool stochasti
     return units <= 6 * 1024 || C >= kChannels[size + padded + tails + 2 * stochastic];
 }
 
+// Whether the resident launch writes the NHWC copy as well: every workgroup of eight waves then reads the whole tensor and stores its
+// codes byte by byte.  Two launches and one, us a call: 16 channels of 1024 elements 9.5 and 7.1, 64 of 1024 9.6 and 8.0, 96 of 784
+// 9.9 and 8.0; 128 of 784 10.1 and 9.1 but 160 of 784 10.2 and 10.5, 256 of 512 9.9 and 10.7; 24 of 3280 10.4 and 13.0.
+bool resident_all_pays(int C, int64_t M, int64_t units) { return units <= 2 * 8 * kWave && M <= 1024 && (int64_t)C * M <= 80 * 1024; }
+
 // ---------------------------------------------------------------------------------------------
 // forward-side quantization of X (two layouts) and W (packed)
 // ---------------------------------------------------------------------------------------------
@@ -2130,31 +2198,34 @@ daq_status quantize_grad_impl(const daq_conv_desc* desc, const T* dY, float* s_s
     if (!given && resident_ok && (schedule == DAQ_SCHEDULE_CHANNEL_RESIDENT || (schedule == DAQ_SCHEDULE_AUTO && resident_pays(C, res_units, !res_flat, HW % 4 != 0, stoch)))) {
         ws.slabs = 1;   // one |g|max partial per channel
         ws.part_n = C;
-        const ResArgs ra{make_fastdiv((uint32_t)res_upp), make_fastdiv((uint32_t)Wo), N, C, HW, k, A, lambda, keys};
+        const bool all = qg_nhwc && resident_all_pays(C, (int64_t)N * HW, res_units);
+        const ResArgs ra{make_fastdiv((uint32_t)res_upp), make_fastdiv((uint32_t)Wo), N, C, HW, k, A, lambda, keys, qg, s_global, all ? Lg.c_pitch : 0, all ? nhwc_tail(Lg) : 0};
+        const int res_waves = all ? 8 : res.waves;
         const ClipArgs ca{k, A, lambda, s_state, s_chan, cls, stats};
         const size_t lds = res_flat ? 0 : (size_t)Lv.plane_pitch;
         const dim3 rgrid((unsigned)round_up(C, kXcd));
-#define DAQ_RES_LAUNCH(S, V, NUV, FL, TL)                                                                            \
+#define DAQ_RES_LAUNCH(S, V, NUV, FL, TL, AL)                                                                           \
     {                                                                                                                \
-        auto kern = k_chan_resident<T, S, V, NUV, FL, TL>;                                                           \
+        auto kern = k_chan_resident<T, S, V, NUV, FL, TL, AL>;                                                           \
         if (!FL && !allow_lds((const void*)kern, lds)) \
             return DAQ_ERR_HIP;                                                                                      \
-        DAQ_LAUNCH("chan_resident", st, hipLaunchKernelGGL(kern, rgrid, dim3((unsigned)(res.waves * kWave)), lds, st, dY, cnhw_view(Lv), vq, ra, ws, ca)); \
+        DAQ_LAUNCH("chan_resident", st, hipLaunchKernelGGL(kern, rgrid, dim3((unsigned)(res_waves * kWave)), lds, st, dY, cnhw_view(Lv), vq, ra, ws, ca)); \
     }
-#define DAQ_RES_FORM(S, NUV)                                                                                         \
+#define DAQ_RES_FORM(S, NUV, AL)                                                                                         \
     {                                                                                                                \
-        if (!res_v4) DAQ_RES_LAUNCH(S, false, NUV, false, false)                                                     \
-        else if (res_flat && HW % 4 == 0) DAQ_RES_LAUNCH(S, true, NUV, true, false)                                  \
-        else if (res_flat) DAQ_RES_LAUNCH(S, true, NUV, true, true)                                                  \
-        else if (HW % 4 == 0) DAQ_RES_LAUNCH(S, true, NUV, false, false)                                             \
-        else DAQ_RES_LAUNCH(S, true, NUV, false, true)                                                               \
+        if (!res_v4) DAQ_RES_LAUNCH(S, false, NUV, false, false, AL)                                                     \
+        else if (res_flat && HW % 4 == 0) DAQ_RES_LAUNCH(S, true, NUV, true, false, AL)                                  \
+        else if (res_flat) DAQ_RES_LAUNCH(S, true, NUV, true, true, AL)                                                  \
+        else if (HW % 4 == 0) DAQ_RES_LAUNCH(S, true, NUV, false, false, AL)                                             \
+        else DAQ_RES_LAUNCH(S, true, NUV, false, true, AL)                                                               \
     }
 #define DAQ_RES_SIZE(S)                                                                                              \
     {                                                                                                                \
-        if (res.nu == 2) DAQ_RES_FORM(S, 2)                                                                          \
-        else if (res.nu == 4) DAQ_RES_FORM(S, 4)                                                                     \
-        else if (res.nu == 8) DAQ_RES_FORM(S, 8)                                                                     \
-        else DAQ_RES_FORM(S, 16)                                                                                     \
+        if (all) DAQ_RES_FORM(S, 2, true)                                                                            \
+        else if (res.nu == 2) DAQ_RES_FORM(S, 2, false)                                                                          \
+        else if (res.nu == 4) DAQ_RES_FORM(S, 4, false)                                                                     \
+        else if (res.nu == 8) DAQ_RES_FORM(S, 8, false)                                                                     \
+        else DAQ_RES_FORM(S, 16, false)                                                                                     \
     }
         if (stoch) DAQ_RES_SIZE(true) else DAQ_RES_SIZE(false)
 #undef DAQ_RES_FORM
@@ -2162,6 +2233,7 @@ daq_status quantize_grad_impl(const daq_conv_desc* desc, const T* dY, float* s_s
 #undef DAQ_RES_LAUNCH
         // the per-channel copy, its scales, classes and clip state are complete here; the global copy follows on `st`
         if (side && stream_follows(side, st) != DAQ_OK) return DAQ_ERR_HIP;
+        if (all) return DAQ_OK;
         if (!qg_nhwc) {
             // depthwise layers: the per-tensor copy is channel-major too
             if (!fold_in_packing(pack_blocks(Lv, dY, (int)sizeof(T)))) {

@@ -1,6 +1,7 @@
 """Sizes at which a kernel's loop or a dispatch rule turns over, against the oracle (integers exactly, see test_gpu_parity)."""
 import numpy as np
 import pytest
+import torch
 
 from paper_2102_04782_amd import binding as daq
 from paper_2102_04782_amd import workloads as wl
@@ -149,3 +150,16 @@ def test_products_of_many_ragged_tiles(layer):
     """Tiles enough for the tile kernel's forms, odd images, channel counts off every block."""
     on_random_codes(layer, 73)
     check_forward(layer, 74)
+
+
+@pytest.mark.parametrize("channels,n,h,w", [(80, 4, 16, 16), (81, 4, 16, 16), (16, 25, 5, 8), (7, 205, 1, 5), (33, 3, 13, 13), (79, 147, 1, 1), (1, 1, 1, 3), (40, 300, 1, 3)])
+@pytest.mark.parametrize("k", [1, 3])
+def test_resident_quantizer_writes_both_copies(channels, n, h, w, k):
+    """Small tensors, both sides of the line to a launch of its own for the global copy, in every kind of load unit."""
+    layer = wl.Layer("all", n, 1, h, w, channels, k, k, 1, k // 2)
+    dY = wl.make_dY(layer, wl.seed_for(23, channels))
+    st = wl.make_state(dY, wl.seed_for(23, channels))
+    for mode, seed in ((daq.ROUND_NEAREST, 0), (daq.ROUND_STOCHASTIC, 41 + n)):
+        check_quantize_grad(layer, dY, st, mode=mode, seed=seed, degenerate=n * h * w == 1)
+        check_quantize_grad(layer, dY, st, mode=mode, seed=seed, degenerate=n * h * w == 1, side=torch.cuda.Stream())
+        check_quantize_grad_bf16(layer, dY, st, mode=mode, seed=seed)
