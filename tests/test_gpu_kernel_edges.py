@@ -163,3 +163,21 @@ def test_resident_quantizer_writes_both_copies(channels, n, h, w, k):
         check_quantize_grad(layer, dY, st, mode=mode, seed=seed, degenerate=n * h * w == 1)
         check_quantize_grad(layer, dY, st, mode=mode, seed=seed, degenerate=n * h * w == 1, side=torch.cuda.Stream())
         check_quantize_grad_bf16(layer, dY, st, mode=mode, seed=seed)
+
+
+@pytest.mark.parametrize("channels,n,h,w", [(20, 5, 9, 7), (65, 3, 8, 5), (70, 4, 7, 9), (33, 6, 1, 3)])
+def test_depthwise_copies_from_one_sweep(channels, n, h, w):
+    """Both channel-major copies of a gradient of odd rows from the counting pass, with guessed classes that hold and that do not."""
+    layer = wl.Layer("dwise", n, channels, h, w, channels, 3, 3, 1, 1, groups=channels)
+    dY = wl.make_dY(layer, wl.seed_for(24, channels))
+    st = wl.make_state(dY, wl.seed_for(24, channels))
+    for mode, seed, lam in ((daq.ROUND_NEAREST, 0, 0.3), (daq.ROUND_STOCHASTIC, 3, 0.0), (daq.ROUND_STOCHASTIC, 4, 1.0)):
+        check_quantize_grad(layer, dY, st, lam=lam, mode=mode, seed=seed, schedule=daq.SCHEDULE_EARLY_COPY)
+        check_quantize_grad(layer, dY, st, lam=lam, mode=mode, seed=seed, schedule=daq.SCHEDULE_EARLY_COPY, side=torch.cuda.Stream())
+
+
+@pytest.mark.parametrize("batch,size,channels", [(1, 8, 3), (2, 9, 20), (3, 13, 33), (40, 30, 9), (5, 31, 64)])
+def test_depthwise_filter_gradient_at_stride_2(batch, size, channels):
+    """Row pitches of every residue, one slab and several."""
+    for w in range(size, size + 4):
+        on_random_codes(wl.Layer("dws2", batch, channels, size, 2 * w, channels, 3, 3, 2, 1, groups=channels), 80 + w)
