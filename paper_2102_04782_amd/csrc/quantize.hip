@@ -449,6 +449,7 @@ __device__ __forceinline__ float clip_rule(int klass, float gm, float prev, floa
 // What the counting pass needs to write the per-channel copy of channels whose class it can guess.
 struct EarlyVq {
     int8_t* vq;            // nullptr: the counting pass does not write the per-channel copy
+    int8_t* qg;            // a global copy in the same layout (depthwise layers), or nullptr
     int64_t chan_pitch;
     int32_t lead, img_rows, row_pitch, W;
     FastDiv div_w;
@@ -664,6 +665,8 @@ __device__ __forceinline__ void count_qg_role(const int bid, const T* __restrict
     const int at_px = (int)(((uint32_t)(kg * kWave + lane) * by_gb) >> 16), at_ch = (kg * kWave + lane) - at_px * gb;
     int8_t* const qg_lane = WRITE_QG ? qg + 16 * (cb * cp.width + (gb == 1 ? 0 : at_ch)) : nullptr;
     int8_t* const vq_lane = EARLY ? ev.vq + (int64_t)cl * ev.chan_pitch + (uint32_t)ev.lead : nullptr;
+    constexpr bool BOTH = EARLY && COUNT && !WRITE_QG;   // both copies channel-major
+    const int64_t to_qg = BOTH ? ev.qg - ev.vq : 0;
 
     uint32_t cnt[4] = {0u, 0u, 0u, 0u};
     auto work = [&](int tile, const Unit& t, uint32_t* tile_buf) {
@@ -702,7 +705,7 @@ __device__ __forceinline__ void count_qg_role(const int bid, const T* __restrict
                     }
                 }
             }
-            uint32_t vb[4];
+            uint32_t vb[4], gb4[4];
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
                 const float v = t.x[j][e];
@@ -715,12 +718,15 @@ __device__ __forceinline__ void count_qg_role(const int bid, const T* __restrict
                     if (j == 3) d[e] = __builtin_amdgcn_perm(half[e], d[e], 0x05040100u);
                 }
                 if (EARLY) vb[e] = quant_bits<STOCH>(v, inv_c[j], draw_half(draw[e], 0u));
+                if (BOTH) gb4[e] = quant_bits<STOCH>(v, inv, draw_half(draw[e], 1u));
             }
             if (EARLY && t.ok && cl + j < C) {
                 const uint32_t wv = pack4<kCodeByte<STOCH>>(vb[0], vb[1], vb[2], vb[3]);
+                const uint32_t wg = BOTH ? pack4<kCodeByte<STOCH>>(gb4[0], gb4[1], gb4[2], gb4[3]) : 0u;
                 int8_t* plane = vq_lane + (int64_t)j * ev.chan_pitch;
                 if (UNIT != kElems && whole) {
                     __builtin_memcpy(plane + at_vq, &wv, 4);   // byte aligned only
+                    if (BOTH) __builtin_memcpy(plane + to_qg + at_vq, &wg, 4);
                 } else {
 #pragma unroll
                     for (int e = 0; e < 4; ++e) {
@@ -728,7 +734,10 @@ __device__ __forceinline__ void count_qg_role(const int bid, const T* __restrict
                         if constexpr (UNIT == kElems) pixel(t.u, e, ne, pe);
                         const uint32_t he = fdiv(pe, ev.div_w);
                         const uint32_t at = (ne * (uint32_t)ev.img_rows + he) * (uint32_t)ev.row_pitch + (pe - he * (uint32_t)ev.W);
-                        if (UNIT != kElems || 4u * t.u + e < M) plane[at] = (int8_t)(wv >> (8 * e));
+                        if (UNIT != kElems || 4u * t.u + e < M) {
+                            plane[at] = (int8_t)(wv >> (8 * e));
+                            if (BOTH) plane[to_qg + at] = (int8_t)(wg >> (8 * e));
+                        }
                     }
                 }
             }
@@ -2288,13 +2297,18 @@ daq_status quantize_grad_impl(const daq_conv_desc* desc, const T* dY, float* s_s
     // (With the producer's statistics the counting sweep is the only full read of dY: it always writes both copies.)
     const bool want_early = schedule == DAQ_SCHEDULE_EARLY_COPY || (schedule == DAQ_SCHEDULE_AUTO && (int64_t)N * C * HW >= kEarlyVqMinElems) ||
                             (given && schedule != DAQ_SCHEDULE_THREE_SWEEPS);
-    const bool early = want_early && scheme == DAQ_SCHEME_DAQ && qg_nhwc && early_copy_supported(Lv, dY, (int)sizeof(T));
+    // Two channel-major copies: where the packing kernel takes rows in whole vectors, one read of dY for both copies behind the counting
+    // sweep is as fast (128 x 144 x 56 x 56, depthwise: 138 and 157 us); where rows are odd it would take two launches, an element at a time
+    // (40 x 200 x 59 x 63: 116 and 90; 20 x 100 x 61 x 63: 44 and 37).
+    const bool early = want_early && scheme == DAQ_SCHEME_DAQ && early_copy_supported(Lv, dY, (int)sizeof(T)) &&
+                       (qg_nhwc || rows_vector(Lv, dY, (int)sizeof(T)) == 0);
     EarlyVq ev{};
     if (early) {
         // |g|max / sigma of M Gaussian samples is about sqrt(2 ln M), of M Laplace samples ln M / sqrt 2: halfway
         const double lnM = std::log((double)N * HW);
         ev = early_vq(Lv, vq);
         ev.once = (int64_t)N * C * HW * (int64_t)sizeof(T) > kCacheBytes;
+        ev.qg = qg_nhwc ? nullptr : qg;
         ev.k = k;
         ev.A = A;
         ev.ratio = (float)(0.5 * (std::sqrt(2.0 * lnM) + lnM / std::sqrt(2.0)));
@@ -2311,7 +2325,8 @@ daq_status quantize_grad_impl(const daq_conv_desc* desc, const T* dY, float* s_s
         else DAQ_COUNT_LAUNCH(S, Q, E, kElems);                                                                      \
     }
     if (early) {
-        if (stoch) DAQ_COUNT_UNIT(true, true, true) else DAQ_COUNT_UNIT(false, true, true)
+        if (qg_nhwc) { if (stoch) DAQ_COUNT_UNIT(true, true, true) else DAQ_COUNT_UNIT(false, true, true) }
+        else { if (stoch) DAQ_COUNT_UNIT(true, false, true) else DAQ_COUNT_UNIT(false, false, true) }
     } else if (qg_nhwc) {
         if (stoch) DAQ_COUNT_UNIT(true, true, false) else DAQ_COUNT_UNIT(false, true, false)
     } else {
