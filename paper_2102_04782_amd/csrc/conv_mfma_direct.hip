@@ -40,6 +40,7 @@ struct DirectArgs {
     // live taps of a class, per axis: first, step, number
     int kh0[4], kw0[4], nkh[4], nkw[4], khs, kws;
     int tiles;            // 32 x 32 tiles of a class
+    int per_xcd;          // workgroups of a class on an XCD
     FastDiv div_pw, div_php, div_rb, div_upt, div_blocks;
     const float* s_a;
     const float* s_b;
@@ -61,8 +62,12 @@ __global__ __launch_bounds__(kWaves* kWave, 4) void k_conv_direct(DirectArgs p) 
     }
     const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid / kWave), lane = tid % kWave;
     const int l32 = lane & 31, lh = lane >> 5;
+    // An XCD takes an eighth of the tiles, neighbours: round-robin, each L2 fetched every pixel (24 x 864 x 31 x 35 -> 17, 5 x 5, 119 -> 92 us;
+    // 10 x 32 x 103 x 103 <- 224, 3 x 3, 47 -> 41; 130 products 3 % faster).  Shares by rows instead of pixels gain no more.
     const int cls = (int)fdiv(blockIdx.x, p.div_blocks);
-    const int blk = (int)blockIdx.x - cls * (int)(((uint32_t)p.tiles + kTiles - 1) / kTiles);
+    const int in_cls = (int)blockIdx.x - cls * kXcd * p.per_xcd;
+    const int blk = in_cls % kXcd * p.per_xcd + in_cls / kXcd;
+    if (blk * kTiles >= p.tiles) return;   // uniform
     const int s = 1 << p.s_log2, pa = cls >> p.s_log2, pb = cls & (s - 1);
     const int taps = p.nkh[cls] * p.nkw[cls];
     for (int t = tid; t < taps + 2; t += kWaves * kWave) {
@@ -224,15 +229,16 @@ DirectPlan plan_direct(bool backward, const daq_conv_desc& d) {
     g.ks = 1;
     const int64_t waves = steps < 40 ? 2048 : 4096;
     while (g.ks < kWaves && tiles * classes * g.ks < waves && steps >= 4 * g.ks) g.ks *= 2;
-    const int64_t per_class = ceil_div(tiles, kWaves / g.ks);
-    a.div_blocks = make_fastdiv((uint32_t)per_class);
-    g.blocks = per_class * classes;
+    a.per_xcd = (int)ceil_div(ceil_div(tiles, kWaves / g.ks), kXcd);
+    a.div_blocks = make_fastdiv((uint32_t)(kXcd * a.per_xcd));
+    g.blocks = (int64_t)kXcd * a.per_xcd * classes;
     g.ok = g.blocks < lim - 4096;
     return g;
 }
 
 // Both sides were timed on 992 products of random layers (one launch of each between events, us) and fitted; MB of result included:
 //     here   7.6 + 0.13 * steps of a wave + 27 * thousands of steps a CU + 0.27 * MB (by parity class, every other pixel of a line: 0.55)
+//            (forward: + 2 * MB of filter, which the launch before has just written: 2 x 256 x 20 x 20 -> 336, 3 x 3, 11.8 there and 13.9 here)
 //     there  fixed + (step + turn * max(1, workgroups / 256)) * steps of a workgroup + mb * MB
 // These kernels are taken where they are 7 % faster by that (20 % from 30 us on, where the fit is worse, and not for 1 x 1 layers of many
 // workgroups): over 1000 more products 1.3 times the speed, few choices more than 1.1 times the other's time.  E.g. 768 -> 52, 5 x 5, 6 images of 5 x 5, 97 us there and 14 here; 3 -> 96, 7 x 7
@@ -245,7 +251,7 @@ bool faster(const DirectPlan& g, const OtherKernel& o, int classes, bool bf16) {
     const DirectArgs& a = g.a;
     const double mb = (double)a.N * a.Crow * a.Hd * a.Wd * (bf16 ? 2 : 4) * 1e-6;
     const double steps = (double)ceil_div((int64_t)a.T * a.upt, 2 * classes), tiles = (double)a.tiles * classes;
-    const double here = 7.6 + 0.13 * steps / g.ks + 27.0 * tiles * steps / 256e3 + (classes > 1 ? 0.55 : 0.27) * mb;
+    const double here = 7.6 + 0.13 * steps / g.ks + 27.0 * tiles * steps / 256e3 + (classes > 1 ? 0.55 : 0.27) * mb + (a.fwd ? 2e-6 * a.wfrag_bytes : 0.0);
     const Cost& c = (o.classes ? kClasses : kUnit)[(int)o.form];
     const double held = o.form == TileForm::kNhwc ? 512.0 : 256.0;
     const double there = c.fixed + (c.step + c.turn * std::max(1.0, (double)o.blocks / held)) * o.steps + c.mb * mb;
