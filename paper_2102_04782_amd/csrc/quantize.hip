@@ -86,7 +86,7 @@ struct QuantWs {
 // copies, padding; start of the work, then blocks of up to 64, 128, 192 channels, us: 128 x 144 x 56 x 56 130, 130, 130, 106; 37 x 792 x 59 x 63 358, 308,
 // 308, 264; 64 x 256 x 56 x 56 113, 106, 99, 99; up to 256: no further change).  Where blocks of 64 channels do not fill the chip once they
 // spread the work over more CUs (16 x 320 x 7 x 7, whole call: 15.1 and, blocks of 160, 16.6 us; 128 x 512 x 7 x 7 15.3 and 16.0).  `given`: the waves of a launch that has other roles too.
-CountPlan plan_count(int C, int N, int HW, int given) {
+CountPlan plan_count(int C, int N, int HW, int given, int held_given) {
     CountPlan p{};
     const int G = (int)ceil_div(C, 16);
     p.tiles = (int)ceil_div(channel_units(N, HW), 16);
@@ -100,7 +100,7 @@ CountPlan plan_count(int C, int N, int HW, int given) {
     const int side = p.waves / p.groups(C, p.blocks - 1);   // tiles at a time of a workgroup of the last block
     const int64_t last = ceil_div(p.tiles, side), most = p.blocks > 1 ? p.tiles : last;
     // the last block gets as many workgroups fewer as they are quicker
-    const int64_t held = 256 * (kCountWaves / p.waves);   // workgroups the chip holds at once
+    const int64_t held = held_given ? held_given : 256 * (kCountWaves / p.waves);   // workgroups at once
     int64_t want = std::max<int64_t>(1, std::min<int64_t>(kCountGroups, p.blocks > 1 ? held * side / ((int64_t)(p.blocks - 1) * side + 1) : held));
     if (want >= 2 * kXcd) want -= want % kXcd;
     const int64_t turns = ceil_div(most, want);
@@ -122,7 +122,7 @@ CountPlan plan_count(int C, int N, int HW, int given) {
     return p;
 }
 
-QuantWs carve_quant_ws(void* base, int C, int N, int HW, int given_waves = 0) {
+QuantWs carve_quant_ws(void* base, int C, int N, int HW, int given_waves = 0, int given_held = 0) {
     QuantWs w{};
     const int64_t M = (int64_t)N * HW;
     // statistics sweep groups of four elements per plane (k_stats): the axis is padded to whole groups
@@ -131,7 +131,7 @@ QuantWs carve_quant_ws(void* base, int C, int N, int HW, int given_waves = 0) {
     const int iters = (int)ceil_div(w.chunks, kMaxSlabs);
     w.slabs = (int)ceil_div(w.chunks, iters);
     w.part_n = C * w.slabs;
-    w.cp = plan_count(C, N, HW, given_waves);
+    w.cp = plan_count(C, N, HW, given_waves, given_held);
     // byte offsets first; pointers only when there is a buffer (a size query passes none)
     int64_t off = 0;
     const int64_t o_head = off;
@@ -2048,17 +2048,21 @@ daq_status quantize_forward(const daq_conv_desc& d, const float* X, int8_t* qx_n
     a.N = d.N; a.C = d.Cin; a.HW = HW; a.c_pitch = Ln.c_pitch; a.tail = nhwc_tail(Ln);
     a.div_u = make_fastdiv(unit_divisor(HW));
     a.Lc = cnhw_view(Lc);
-    a.ws = carve_quant_ws(nullptr, d.Cin, d.N, HW, kBlock / kWave);
-    if (a.ws.cp.tile_dwords(d.Cin) > kFwdTileDw) return DAQ_ERR_UNSUPPORTED;   // (four waves: never)  // only the tile geometry is used: nothing is counted here
-    a.ws.part_max = part;
-    a.ws.part_n = m.blocks[0];
-    a.ws.layer = part + kAbsmaxBlocksX + kAbsmaxBlocksW;
-    a.x_blocks = (int)round_up(a.ws.cp.workgroups(), kXcd);
     // Unit-stride layers whose channel-major layout the row kernel serves: one sweep over X writes both copies (the
     // mechanism of the early per-channel copy of dY, with the per-tensor scale), and only the padding bytes are left.
     // (by default from 8 Mi elements on: below that the two lean passes are as fast or faster; 28 x 176 x 27 x 31, 4.1 Mi: 49.6 and 50.5 us a call)
     const bool early = (schedule == DAQ_SCHEDULE_EARLY_COPY || (schedule == DAQ_SCHEDULE_AUTO && n >= ((int64_t)8 << 20))) &&
                        early_copy_supported(Lc, X, 4);
+    // Where the channel-major copy has workgroups of its own, both kinds read X side by side, and the sweep over NHWC records is
+    // one workgroup a CU: more of them take from the other kind more than they gain (quantizing launch, us, 4, 1 a CU: 12 x 224 x 37 x 37
+    // 14.9 and 12.0, 9 x 640 x 25 x 25 17.8 and 14.4, 7 x 464 x 83 x 83 at stride 2 67.6 and 64.8).  Alone it takes all the chip
+    // holds (29 x 224 x 48 x 47 18.7, one a CU 21.2; 72 x 49 x 99 x 99 47.6 and 57.0).
+    a.ws = carve_quant_ws(nullptr, d.Cin, d.N, HW, kBlock / kWave, early ? 0 : 256);
+    if (a.ws.cp.tile_dwords(d.Cin) > kFwdTileDw) return DAQ_ERR_UNSUPPORTED;   // (four waves: never)  // only the tile geometry is used: nothing is counted here
+    a.ws.part_max = part;
+    a.ws.part_n = m.blocks[0];
+    a.ws.layer = part + kAbsmaxBlocksX + kAbsmaxBlocksW;
+    a.x_blocks = (int)round_up(a.ws.cp.workgroups(), kXcd);
     const int v = rows_vector(Lc, X, 4, early);
     int64_t c_blocks;
     if (v) {
