@@ -1856,6 +1856,11 @@ int rows_vector(const daq_layout& Ld, const void* src, int elem_bytes = 4, bool 
 bool early_copy_supported(const daq_layout& Ld, const void* src, int elem_bytes) {
     return rows_vector(Ld, src, elem_bytes, true) != 0 && Ld.lead + (int64_t)Ld.N * Ld.img_rows * Ld.row_pitch < ((int64_t)1 << 31);
 }
+// A tensor larger than the caches hold to the end is read with the streaming hint, on planes of whole units only: elsewhere units are not
+// aligned, neighbouring tiles share lines that the hint gives up between the two (quantizing launch, us, with and without: 128 x 96 x 112 x 112
+// 167 and 230; call of 128 x 144 x 70 x 70 172 and 189; 55 x 384 x 71 x 70 153 and 133, call of 64 x 128 x 101 x 101 305 and 294).
+bool read_once(int64_t bytes, int HW) { return bytes > kCacheBytes && unit_kind(HW) == kWhole; }
+
 EarlyVq early_vq(const daq_layout& Ld, int8_t* dst) {
     EarlyVq ev{};
     ev.vq = dst;
@@ -2076,7 +2081,7 @@ daq_status quantize_forward(const daq_conv_desc& d, const float* X, int8_t* qx_n
     }
     if (early) {
         a.ev = early_vq(Lc, qx_cnhw);
-        a.ev.once = n * 4 > kCacheBytes;
+        a.ev.once = read_once(n * 4, HW);
     }
     if (W) {
         PackWArgs& w = a.w;
@@ -2311,7 +2316,7 @@ daq_status quantize_grad_impl(const daq_conv_desc* desc, const T* dY, float* s_s
         // |g|max / sigma of M Gaussian samples is about sqrt(2 ln M), of M Laplace samples ln M / sqrt 2: halfway
         const double lnM = std::log((double)N * HW);
         ev = early_vq(Lv, vq);
-        ev.once = (int64_t)N * C * HW * (int64_t)sizeof(T) > kCacheBytes;
+        ev.once = read_once((int64_t)N * C * HW * (int64_t)sizeof(T), HW);
         ev.qg = qg_nhwc ? nullptr : qg;
         ev.k = k;
         ev.A = A;
