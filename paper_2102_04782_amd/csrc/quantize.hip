@@ -675,10 +675,13 @@ __device__ __forceinline__ void count_qg_role(const int bid, const T* __restrict
         const uint32_t idx0 = (n * (uint32_t)C + (uint32_t)cl) * (uint32_t)HW + px;   // NCHW index; the lane's channels are one plane apart
         // channel-major copy: the unit sits at the same offset of each of the lane's four channel planes
         uint32_t at_vq = 0;
+        uint32_t in_row = 4u, gap = 0u;   // pixels of the unit in its first row, bytes between the rows
         bool whole = true;   // the unit does not run on into the next row
         if constexpr (EARLY && UNIT != kElems) {
             const uint32_t h = ev.flat ? 0u : fdiv(px, ev.div_w);
             const uint32_t col = px - h * (uint32_t)ev.W;
+            in_row = (uint32_t)ev.W - col;
+            gap = (uint32_t)ev.row_pitch - (uint32_t)ev.W;
             whole = ev.whole || col + 4u <= (uint32_t)ev.W;
             at_vq = ev.flat ? n * (uint32_t)HW + px : (n * (uint32_t)ev.img_rows + h) * (uint32_t)ev.row_pitch + col;
         }
@@ -727,6 +730,13 @@ __device__ __forceinline__ void count_qg_role(const int bid, const T* __restrict
                 if (UNIT != kElems && whole) {
                     __builtin_memcpy(plane + at_vq, &wv, 4);   // byte aligned only
                     if (BOTH) __builtin_memcpy(plane + to_qg + at_vq, &wg, 4);
+                } else if (UNIT != kElems && ev.W >= 4) {   // into the next row at most
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        const uint32_t at = at_vq + (uint32_t)e + ((uint32_t)e >= in_row ? gap : 0u);
+                        plane[at] = (int8_t)(wv >> (8 * e));
+                        if (BOTH) plane[to_qg + at] = (int8_t)(wg >> (8 * e));
+                    }
                 } else {
 #pragma unroll
                     for (int e = 0; e < 4; ++e) {
