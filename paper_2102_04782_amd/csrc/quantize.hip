@@ -32,6 +32,9 @@ constexpr int64_t kCacheBytes = (int64_t)256 << 20;
 // Gradients from this size on take the early per-channel copy (three sweeps and early copy, us: 64 channels of 56 x 56, batch 16 and 32, 19.6 and
 // 19.6, 28.9 and 27.2; 96 of 56 x 56, batch 16, 25.0 and 23.2).
 constexpr int64_t kEarlyVqMinElems = (int64_t)4 << 20;
+// With the producer's statistics and rows that are no whole vectors: the counting sweep and the packing behind it, us, both copies early and not:
+// 3 x 168 x 71 x 71, whole call, 31.1 and 30.0, 2 x 256 x 71 x 71 10.4 and 7.9, 28 x 880 x 13 x 11 11.7 and 14.5, 118 x 32 x 31 x 31 9.0 and 10.6.
+constexpr int64_t kEarlyGivenOddMinElems = (int64_t)3 << 20;
 
 int64_t channel_units(int N, int HW);
 
@@ -2313,14 +2316,15 @@ daq_status quantize_grad_impl(const daq_conv_desc* desc, const T* dY, float* s_s
     // Large gradients: the counting pass also writes the per-channel copy under a guessed class (see k_count_qg), so
     // that the third sweep over dY only touches the channels whose guess was wrong.  Small ones are bound by launch
     // latency, not by bytes, and keep the leaner counting kernel.
-    // (With the producer's statistics the counting sweep is the only full read of dY: it always writes both copies.)
+    // (With the producer's statistics the counting sweep is the only full read of dY: it writes both copies, small gradients of odd rows aside.)
+    const bool odd_rows = rows_vector(Lv, dY, (int)sizeof(T)) == 0;
     const bool want_early = schedule == DAQ_SCHEDULE_EARLY_COPY || (schedule == DAQ_SCHEDULE_AUTO && (int64_t)N * C * HW >= kEarlyVqMinElems) ||
-                            (given && schedule != DAQ_SCHEDULE_THREE_SWEEPS);
+                            (given && schedule != DAQ_SCHEDULE_THREE_SWEEPS && (!odd_rows || (int64_t)N * C * HW >= kEarlyGivenOddMinElems));
     // Two channel-major copies: where the packing kernel takes rows in whole vectors, one read of dY for both copies behind the counting
     // sweep is as fast (128 x 144 x 56 x 56, depthwise: 138 and 157 us); where rows are odd it would take two launches, an element at a time
     // (40 x 200 x 59 x 63: 116 and 90; 20 x 100 x 61 x 63: 44 and 37).
     const bool early = want_early && scheme == DAQ_SCHEME_DAQ && early_copy_supported(Lv, dY, (int)sizeof(T)) &&
-                       (qg_nhwc || rows_vector(Lv, dY, (int)sizeof(T)) == 0);
+                       (qg_nhwc || odd_rows);
     EarlyVq ev{};
     if (early) {
         // |g|max / sigma of M Gaussian samples is about sqrt(2 ln M), of M Laplace samples ln M / sqrt 2: halfway
