@@ -285,8 +285,8 @@ daq_status daq_quantize_grad_split(const daq_conv_desc* desc, const void* dY, fl
  * is the same code.  One sweep over dY remains: it counts and writes both copies (the per-channel
  * one under a guessed class, redone for the channels whose guess was wrong), 6 bytes per element
  * instead of 10; layers whose copies that sweep does not write (two channel-major copies of even
- * rows, ablation rules) and opts->schedule = DAQ_SCHEDULE_THREE_SWEEPS keep a
- * counting and a packing sweep.  Results: those of daq_quantize_grad_ex bit for bit when the
+ * rows, gradients of less than 3 Mi elements whose rows are no whole vectors, ablation rules) and
+ * opts->schedule = DAQ_SCHEDULE_THREE_SWEEPS keep a counting and a packing sweep.  Results: those of daq_quantize_grad_ex bit for bit when the
  * statistics are the channel's (fp64 sums taken in another order can differ in their last bits;
  * sigma is rounded to fp32, so that shows only where an element's magnitude or a channel's count
  * sits exactly on the threshold); for other values, the algorithm's result for those statistics.
