@@ -88,7 +88,7 @@ def kernel_work(layer, d, name: str, dy_bytes: float, dx_bytes: float, qg_nhwc: 
     if name == "stats":
         return dy_bytes * E_Y, 0.0
     if name == "count_qg":
-        return (dy_bytes + (1.0 if qg_nhwc else 0.0) + (1.0 if early else 0.0)) * E_Y, 0.0
+        return (dy_bytes + (2.0 if early else 1.0 if qg_nhwc else 0.0)) * E_Y, 0.0
     if name == "pack_vq" and early:
         return 0.0, 0.0
     if name in ("pack_vq", "pack_qg", "chan_resident", "global_copy"):
@@ -353,10 +353,10 @@ def run_network(args, dev) -> int:
         row = {"layer": L.name, "shape": f"N{L.N} {L.Cin}->{L.Cout} {L.Hin}x{L.Win} k{L.kH} s{L.stride} g{L.groups}"}
         for k, (us, n) in per[li].items():
             dx_b = 2.0 if (net[li].bf16_ok and k.startswith("conv_bwd_data")) else 4.0
-            # the library's rule for the early per-channel copy (gradients of 8 Mi elements and more, NHWC global copy,
-            # rows of an even number of pixels); a layer without a channel-resident launch took the sweeps
-            early = (args.scheme == "daq" and qg_nhwc and "chan_resident" not in per[li] and L.Wo % 2 == 0 and
-                     (args.schedule == "early_copy" or (args.schedule == "auto" and float(np.prod(d.y_shape)) >= 8 * 2 ** 20)))
+            # the library's rule for the early per-channel copy (gradients of 4 Mi elements and more, NHWC global copy or odd rows,
+            # no channel-resident kernel)
+            early = (args.scheme == "daq" and (qg_nhwc or L.Wo % 2 == 1) and "chan_resident" not in per[li] and
+                     (args.schedule == "early_copy" or (args.schedule == "auto" and float(np.prod(d.y_shape)) >= 4 * 2 ** 20)))
             b, o = kernel_work(L, d, k, dy_b, dx_b, qg_nhwc, early)
             e = kernels.setdefault(k, {"us": 0.0, "launches": 0.0, "bytes": 0.0, "ops": 0.0})
             e["us"] += us * n
