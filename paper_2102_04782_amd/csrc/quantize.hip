@@ -2027,9 +2027,18 @@ bool resident_pays(int C, int64_t units, bool padded, bool tails, bool stochasti
 }
 
 // Whether the resident launch writes the NHWC copy as well: every workgroup of eight waves then reads the whole tensor and stores its
-// codes byte by byte.  Two launches and one, us a call: 16 channels of 1024 elements 9.5 and 7.1, 64 of 1024 9.6 and 8.0, 96 of 784
-// 9.9 and 8.0; 128 of 784 10.1 and 9.1 but 160 of 784 10.2 and 10.5, 256 of 512 9.9 and 10.7; 24 of 3280 10.4 and 13.0.
-bool resident_all_pays(int C, int64_t M, int64_t units) { return units <= 2 * 8 * kWave && M <= 1024 && (int64_t)C * M <= 80 * 1024; }
+// codes byte by byte.  What a CU reads is C * M elements for each of its workgroups, one to 256 channels, and that sets the time: two launches
+// are 9.9 to 10.2 us a call at any of these sizes, one launch 7.0 to 7.3 up to 32 Ki elements a CU and (channels of elements; elements a CU)
+//   one workgroup a CU     64 of 1024 (64 Ki) 7.5, 256 of 256 (64 Ki) 8.0, 96 of 784 (74 Ki) 8.3; 160 of 784 (123 Ki) 10.5, 256 of 512 (128 Ki) 10.7
+//   two                    512 of 64 (64 Ki) 8.3, 264 of 160 (83 Ki) 8.4, 384 of 160 (120 Ki) 9.4; 512 of 128 (128 Ki) 10.4, 448 of 160 10.9
+//   three                  768 of 16 (36 Ki) 8.2, 576 of 49 (83 Ki) 10.0, 520 of 64 (98 Ki) 9.3; 576 of 64 (108 Ki) 10.4, 640 of 64 (120 Ki) 10.9
+//   four                   1024 of 16 (64 Ki) 9.3; 1024 of 49 (196 Ki) 14.2
+//   six and more           1536 of 1 11.0, 2048 of 16 17, 5120 of 16 57, 8192 of 8 72
+bool resident_all_pays(int C, int64_t M, int64_t units) {
+    constexpr int kMost[4] = {80, 120, 98, 80};   // Ki elements a CU, by its workgroups
+    const int64_t each = ceil_div(C, 256);
+    return units <= 2 * 8 * kWave && M <= 1024 && each <= 4 && each * C * M <= kMost[each - 1] * 1024;
+}
 
 // ---------------------------------------------------------------------------------------------
 // forward-side quantization of X (two layouts) and W (packed)

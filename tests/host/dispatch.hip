@@ -41,6 +41,17 @@ static void resident_quantizer() {
         }
 }
 
+// The resident launch that writes the global copy too: every workgroup reads the whole tensor.
+static void resident_both_copies() {
+    auto pays = [](int C, int64_t M) { return resident_all_pays(C, M, ceil_div(M, 4)); };
+    EXPECT(!pays(8192, 8) && !pays(5120, 16) && !pays(2048, 40) && !pays(1536, 1));   // up to six times the two launches
+    EXPECT(!pays(1024, 49) && !pays(640, 128) && !pays(512, 160) && !pays(264, 256));
+    EXPECT(pays(16, 1024) && pays(80, 1024) && pays(256, 256) && pays(384, 160) && pays(520, 64) && pays(768, 16) && pays(1024, 16));
+    for (int C = 1; C <= 12000; ++C)
+        for (int64_t M : {1, 2, 3, 5, 16, 49, 100, 300, 1000, 1024, 1025, 5000})
+            if (pays(C, M)) EXPECT(ceil_div(M, 4) <= 2 * 8 * kWave && ceil_div(C, 256) * C * M <= 120 * 1024);   // units of the launch's threads
+}
+
 static daq_conv_desc layer(int n, int ci, int h, int w, int co, int k, int s) { return daq_conv_desc{n, ci, h, w, co, k, k, s, s, k / 2, k / 2, 1, 1, 1}; }
 
 static void filter_gradient() {
@@ -79,6 +90,7 @@ static void filter_gradient() {
 
 int main() {
     resident_quantizer();
+    resident_both_copies();
     filter_gradient();
     std::printf("%d failures\n", fails);
     return fails != 0;

@@ -152,7 +152,8 @@ def test_products_of_many_ragged_tiles(layer):
     check_forward(layer, 74)
 
 
-@pytest.mark.parametrize("channels,n,h,w", [(80, 4, 16, 16), (81, 4, 16, 16), (16, 25, 5, 8), (7, 205, 1, 5), (33, 3, 13, 13), (79, 147, 1, 1), (1, 1, 1, 3), (40, 300, 1, 3)])
+@pytest.mark.parametrize("channels,n,h,w", [(80, 4, 16, 16), (81, 4, 16, 16), (16, 25, 5, 8), (7, 205, 1, 5), (33, 3, 13, 13), (79, 147, 1, 1), (1, 1, 1, 3), (40, 300, 1, 3),
+                                            (300, 5, 4, 4), (400, 7, 5, 3), (1024, 16, 1, 1), (1024, 5, 2, 2), (1025, 16, 1, 1)])
 @pytest.mark.parametrize("k", [1, 3])
 def test_resident_quantizer_writes_both_copies(channels, n, h, w, k):
     """Small tensors, both sides of the line to a launch of its own for the global copy, in every kind of load unit."""
