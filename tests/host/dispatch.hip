@@ -52,6 +52,12 @@ static void resident_both_copies() {
             if (pays(C, M)) EXPECT(ceil_div(M, 4) <= 2 * 8 * kWave && ceil_div(C, 256) * C * M <= 120 * 1024);   // units of the launch's threads
 }
 
+// The packing launch behind an early copy: its workgroups mostly return at once, and their number does not follow the row length.
+static void early_packing() {
+    EXPECT(early_pack_blocks(72 * 143) == 3 && early_pack_blocks(131 * 49) == 2 && early_pack_blocks(49) == 1);
+    EXPECT(early_pack_blocks(32 * 3136) == 16 && early_pack_blocks(4096) == 1 && early_pack_blocks(4097) == 2);
+}
+
 static daq_conv_desc layer(int n, int ci, int h, int w, int co, int k, int s) { return daq_conv_desc{n, ci, h, w, co, k, k, s, s, k / 2, k / 2, 1, 1, 1}; }
 
 static void filter_gradient() {
@@ -91,6 +97,7 @@ static void filter_gradient() {
 int main() {
     resident_quantizer();
     resident_both_copies();
+    early_packing();
     filter_gradient();
     std::printf("%d failures\n", fails);
     return fails != 0;
