@@ -5,6 +5,8 @@
 #include <stddef.h>
 #include <stdint.h>
 
+#include <algorithm>
+
 #include "daq.h"
 
 namespace daq {
@@ -161,6 +163,33 @@ daq_status quantize_activation_check(const daq_conv_desc& d, const float* X);   
 constexpr int kFwdWsFree = 1000;
 daq_status quantize_forward(const daq_conv_desc& d, const float* X, int8_t* qx_nhwc, int8_t* qx_cnhw, float* s_x, const float* W,
                             int8_t* qw_packed, float* s_w, void* ws, hipStream_t st, daq_schedule schedule);
+
+// How the counting pass is dealt out.
+constexpr int kCountWaves = 16;      // waves of the counting pass that a CU holds
+constexpr int kCountMaxWaves = 12;   // of one workgroup
+constexpr int kCountGroups = 1024;   // count partials of a channel, at most
+struct CountPlan {
+    int tiles;         // tiles of 16 units (64 pixels) of the flattened (n, h*w) axis
+    int waves;         // of a workgroup
+    int width;         // groups of 16 channels of a block, a wave each
+    int blocks;        // blocks of channels
+    int cgroups;       // workgroups of a block, and entries of part_cnt a channel has room for
+    int cgroups_last;  // of the last block
+    FastDiv div_cgroups;
+    uint32_t by_groups[2];   // 2^16 over the groups of a full block, of the last one, rounded up: exact quotients below 768
+    __host__ __device__ int workgroups() const { return (blocks - 1) * cgroups + cgroups_last; }
+    // groups of 16 channels in block b of C channels; a workgroup with more waves than that takes several tiles at a time
+    __host__ __device__ int groups(int C, int b) const { return b + 1 < blocks ? width : (C + 15) / 16 - (blocks - 1) * width; }
+    // LDS of one of the two tiles a workgroup keeps: by pixel of a unit, unit and 16-byte share of the record, units an odd number of
+    // 16 bytes apart and pixels 64 bytes more than 16 units: no bank conflicts either way
+    __host__ __device__ static int pitch_dwords(int gb) { return 4 * (gb | 1); }
+    __host__ __device__ static int step_dwords(int gb) { return 16 * pitch_dwords(gb) + 16; }
+    int tile_dwords(int C) const {
+        auto of = [&](int gb) { return gb == 1 ? 0 : waves / gb * 4 * step_dwords(gb); };
+        return std::max(of(groups(C, 0)), of(groups(C, blocks - 1)));
+    }
+};
+CountPlan plan_count(int C, int N, int HW, int given = 0, int held_given = 0);
 
 // Channel-resident quantizer: `units` load units of a channel (four elements of a plane each, fewer at its end) on a workgroup of
 // `waves` waves, `nu` units to a thread.

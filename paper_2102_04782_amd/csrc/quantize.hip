@@ -22,9 +22,6 @@ typedef uint32_t v2u __attribute__((ext_vector_type(2)));
 constexpr int kBlock = 256;
 constexpr int kStatsElems = 4096;  // elements one statistics workgroup sweeps per iteration (16 per thread, all in flight)
 constexpr int kMaxSlabs = 16;      // statistics partials per channel (every consumer re-folds them)
-constexpr int kCountWaves = 16;      // waves of the counting pass that a CU holds
-constexpr int kCountMaxWaves = 12;   // of one workgroup
-constexpr int kCountGroups = 1024;  // count partials of a channel, at most
 // What the memory-side cache holds.  A tensor that does not fit is read with the streaming hint, and what else there is stays in the caches
 // until whole lines of it are written back (128 x 96 x 112 x 112, 617 MB, both copies 243 -> 224 us; tensors of 50 to 230 MB, that the
 // statistics sweep has just read, 2 to 10 % slower with the hint).
@@ -41,27 +38,6 @@ int64_t channel_units(int N, int HW);
 // ---------------------------------------------------------------------------------------------
 // workspace carving
 // ---------------------------------------------------------------------------------------------
-struct CountPlan {
-    int tiles;         // tiles of 16 units (64 pixels) of the flattened (n, h*w) axis
-    int waves;         // of a workgroup
-    int width;         // groups of 16 channels of a block, a wave each
-    int blocks;        // blocks of channels
-    int cgroups;       // workgroups of a block, and entries of part_cnt a channel has room for
-    int cgroups_last;  // of the last block
-    FastDiv div_cgroups;
-    uint32_t by_groups[2];   // 2^16 over the groups of a full block, of the last one, rounded up: exact quotients below 768
-    __host__ __device__ int workgroups() const { return (blocks - 1) * cgroups + cgroups_last; }
-    // groups of 16 channels in block b of C channels; a workgroup with more waves than that takes several tiles at a time
-    __host__ __device__ int groups(int C, int b) const { return b + 1 < blocks ? width : (C + 15) / 16 - (blocks - 1) * width; }
-    // LDS of one of the two tiles a workgroup keeps: by pixel of a unit, unit and 16-byte share of the record, units an odd number of
-    // 16 bytes apart and pixels 64 bytes more than 16 units: no bank conflicts either way
-    __host__ __device__ static int pitch_dwords(int gb) { return 4 * (gb | 1); }
-    __host__ __device__ static int step_dwords(int gb) { return 16 * pitch_dwords(gb) + 16; }
-    int tile_dwords(int C) const {
-        auto of = [&](int gb) { return gb == 1 ? 0 : waves / gb * 4 * step_dwords(gb); };
-        return std::max(of(groups(C, 0)), of(groups(C, blocks - 1)));
-    }
-};
 struct QuantWs {
     float* gmax;          // [C]  |g|max, mean, sigma: written by the counting pass for the packing pass
     float* mean;          // [C]
@@ -83,21 +59,36 @@ struct QuantWs {
     int64_t total_bytes;
 };
 
-// A block is the channels whose shares of an NHWC record a workgroup writes as one run, up to 192 of them, a wave to 16; the width from 4 to
-// 12 waves that leaves the fewest idle in the last block, the largest of equals.  A record that several workgroups write reaches memory
-// in pieces of lines, each at its own time, and what counts is that there are few of them, not the waves a CU holds (statistics sweep, both
-// copies, padding; start of the work, then blocks of up to 64, 128, 192 channels, us: 128 x 144 x 56 x 56 130, 130, 130, 106; 37 x 792 x 59 x 63 358, 308,
-// 308, 264; 64 x 256 x 56 x 56 113, 106, 99, 99; up to 256: no further change).  Where blocks of 64 channels do not fill the chip once they
-// spread the work over more CUs (16 x 320 x 7 x 7, whole call: 15.1 and, blocks of 160, 16.6 us; 128 x 512 x 7 x 7 15.3 and 16.0).  `given`: the waves of a launch that has other roles too.
+}  // namespace
+
+// A block is the channels whose shares of an NHWC record a workgroup writes as one run, a wave to 16 of them.  Its width goes by the size of
+// the tensor, in steps of 64 pixels x 64 channels, of which the chip holds 1024 at once.  Quantizing calls (both copies in one sweep) of 16 G channels, 6 to
+// 100 M elements, both roundings, planes of whole units and not: the speed with blocks of 128 and of 192 channels (G up to 12: whole records) over that of 64
+//   1 to 2 Ki steps    G 8 0.97, 0.97    G 9 to 12 0.97, 0.97    G from 13 on 0.98, 0.98    more and smaller workgroups are the faster
+//   2 to 4 Ki               1.01, 1.01              1.01, 0.99                1.03, 1.00    a CU holds 16 waves in blocks of 128, but 12 in blocks of 192
+//   4 to 10 Ki              1.00, 1.00              1.01, 0.99                1.01, 1.00
+//   10 to 18 Ki             1.08, 1.08              1.04, 1.06                1.05, 1.05    the pieces of a record no longer meet in the caches: the fewer
+//   from 18 Ki on           1.06, 1.06              1.05, 1.10                1.05, 1.05    the better, and whole records best
+// Workgroups of five waves are the slowest at any size (80 channels whole over 64 + 16: 0.84 and 0.87 up to 10 Ki steps, beyond 0.96, in bfloat16 1.15;
+// 240 channels as 3 x 80 over 128 + 112: 0.84 to 0.87): only whole records of a large tensor take them.  Six are no faster than 64 + 32 up to 10 Ki steps (0.97
+// to 0.99), seven are faster than 64 + 48 from 1 Ki on (1.02 to 1.04).
+static int block_width(int G, int64_t steps) {
+    if (steps > 10 * 1024) {   // the width up to 12, from six on, that leaves the fewest waves of the last block idle, the largest of equals
+        int width = std::min(G, 12);
+        for (int w = std::min(G, 11); w >= 6; --w)
+            if (ceil_div(G, w) * w < ceil_div(G, width) * width) width = w;
+        return width;
+    }
+    if (G == 7 ? steps > 1024 : G > 7 && steps > 2 * 1024) return std::min(G, 8);
+    return std::min(G, 4);
+}
+
+// `given`: the waves of a launch that has other roles too; `held_given`: how many workgroups of it the chip is to hold.
 CountPlan plan_count(int C, int N, int HW, int given, int held_given) {
     CountPlan p{};
     const int G = (int)ceil_div(C, 16);
     p.tiles = (int)ceil_div(channel_units(N, HW), 16);
-    const bool wide = !given && (int64_t)p.tiles * ceil_div(G, 4) > 4 * 256;
-    p.width = std::min(G, given ? given : wide ? 12 : 4);
-    if (wide)
-        for (int w = std::min(G, 11); w >= 4; --w)
-            if (ceil_div(G, w) * w < ceil_div(G, p.width) * p.width) p.width = w;
+    p.width = given ? std::min(G, given) : block_width(G, (int64_t)p.tiles * ceil_div(G, 4));
     p.waves = given ? given : p.width == 1 ? 4 : p.width <= 3 ? 2 * p.width : p.width;
     p.blocks = (int)ceil_div(G, p.width);
     const int side = p.waves / p.groups(C, p.blocks - 1);   // tiles at a time of a workgroup of the last block
@@ -124,6 +115,8 @@ CountPlan plan_count(int C, int N, int HW, int given, int held_given) {
     }
     return p;
 }
+
+namespace {
 
 QuantWs carve_quant_ws(void* base, int C, int N, int HW, int given_waves = 0, int given_held = 0) {
     QuantWs w{};
@@ -2292,6 +2285,10 @@ daq_status quantize_grad_impl(const daq_conv_desc* desc, const T* dY, float* s_s
             return launch_pack("pack_qg", stoch, false, dY, Lv, ws.part_max, qg, 1u, keys, ws, ClipArgs{}, st, nullptr, nullptr, 0, nullptr, false,
                                ws.part_n, s_global);
         }
+        // The copy-only form has half the registers and is held to as many waves a CU as the counting one, which is the faster up to some 2000 channels;
+        // beyond, blocks are many, workgroups of each few, and what is lost by whole rounds over the XCDs is more than that (sixteen and
+        // twenty-four waves a CU, nearest, us: 27 x 2051 x 43 x 9 27 and 23, 3 x 3655 x 54 x 54 38 and 30, 47 x 3819 x 12 x 11 in bfloat16 24 and 16).
+        if (C > 2000) ws.cp = plan_count(C, N, HW, 0, 256 * (24 / ws.cp.waves));
         const dim3 cgrid((unsigned)ws.cp.workgroups()), cblock((unsigned)(ws.cp.waves * kWave));
         const int tile_dw = ws.cp.tile_dwords(C);
         const size_t clds = (size_t)tile_dw * 8;

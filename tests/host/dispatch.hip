@@ -58,6 +58,38 @@ static void early_packing() {
     EXPECT(early_pack_blocks(32 * 3136) == 16 && early_pack_blocks(4096) == 1 && early_pack_blocks(4097) == 2);
 }
 
+// The counting pass: blocks of channels by the size of the tensor, and what its kernel and its buffers take for granted.
+static void counting_pass() {
+    auto width = [](int C, int N, int HW) { return plan_count(C, N, HW).width; };
+    EXPECT(width(80, 40, 3136) == 4 && width(74, 99, 26 * 26) == 4);        // not workgroups of five waves
+    EXPECT(width(240, 14, 3136) == 8 && width(400, 16, 3136) == 8 && width(400, 80, 3136) != 5);
+    EXPECT(width(144, 20, 3136) == 8 && width(3000, 37, 143) == 8 && width(1216, 107, 81) == 8);   // not 9 or 12 waves a CU
+    EXPECT(width(880, 9, 27 * 29) == 4 && width(128, 12, 3136) == 4);       // under two rounds
+    EXPECT(width(112, 14, 3136) == 7 && width(144, 128, 3136) == 9 && width(96, 128, 12544) == 6 && width(792, 37, 59 * 63) == 10);
+    // the sizes of test_counting_pass_wide_blocks: width, and channel groups of the last block
+    auto is = [](int C, int N, int HW, int width, int last) {
+        const CountPlan p = plan_count(C, N, HW);
+        return p.width == width && p.groups(C, p.blocks - 1) == last && p.tiles > 2 * p.cgroups * (p.waves / p.groups(C, 0));   // and several turns
+    };
+    EXPECT(is(112, 4, 140 * 139, 7, 7) && is(240, 3, 112 * 112, 8, 7) && is(200, 20, 45 * 49, 8, 5) && is(272, 11, 55 * 57, 8, 1));
+    EXPECT(is(208, 20, 101 * 103, 7, 6) && is(270, 16, 99 * 101, 9, 8) && is(400, 35, 56 * 56, 9, 7) && is(186, 73, 56 * 56, 12, 12));
+    for (int C = 1; C <= 9000; C += C < 420 ? 1 : 37)
+        for (int N : {1, 3, 16, 128, 700})
+            for (int HW : {1, 2, 3, 4, 49, 143, 784, 3136, 12544, 50176}) {
+                if ((int64_t)C * N * HW >= (int64_t)1 << 29) continue;
+                for (int given : {0, 4}) {
+                    const CountPlan p = plan_count(C, N, HW, given);
+                    const int G = (C + 15) / 16;
+                    EXPECT(p.width <= p.waves && p.waves <= kCountMaxWaves && (p.blocks - 1) * p.width < G && p.blocks * p.width >= G);
+                    EXPECT(1 <= p.cgroups_last && p.cgroups_last <= p.cgroups && p.cgroups <= kCountGroups);
+                    EXPECT(p.tile_dwords(C) * 8 <= 48 << 10);               // two tiles of LDS, no more than a launch has without asking
+                    for (int b = 0; b < 2; ++b)
+                        for (uint32_t i = 0, gb = (uint32_t)p.groups(C, b ? p.blocks - 1 : 0); i < 64 * kCountMaxWaves; ++i)
+                            EXPECT(i * p.by_groups[b] >> 16 == i / gb);
+                }
+            }
+}
+
 static daq_conv_desc layer(int n, int ci, int h, int w, int co, int k, int s) { return daq_conv_desc{n, ci, h, w, co, k, k, s, s, k / 2, k / 2, 1, 1, 1}; }
 
 static void filter_gradient() {
@@ -98,6 +130,7 @@ int main() {
     resident_quantizer();
     resident_both_copies();
     early_packing();
+    counting_pass();
     filter_gradient();
     std::printf("%d failures\n", fails);
     return fails != 0;

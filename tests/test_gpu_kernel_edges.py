@@ -99,8 +99,8 @@ def test_resident_quantizer_on_planes_of_any_size(per_thread, n, h, w, k):
         check_quantize_grad_bf16(layer, dY, st, mode=mode, seed=seed)
 
 
-# Channel counts by the groups of 16 that the counting pass gives a workgroup's waves: one to three groups (several tiles at a
-# time), a whole record, blocks of equal width, a last block of two groups beside one of seven, of one beside five
+# Channel counts by the groups of 16 that the counting pass gives a workgroup's waves, in blocks of up to four: one to three groups
+# (several tiles at a time), whole blocks, last blocks of one and of two groups
 @pytest.mark.parametrize("channels", [9, 24, 48, 90, 144, 190, 208, 330])
 @pytest.mark.parametrize("n,h,w", [(5, 8, 8), (3, 7, 7), (4, 6, 9), (9, 1, 3)], ids=lambda v: str(v))
 @pytest.mark.parametrize("schedule", [daq.SCHEDULE_THREE_SWEEPS, daq.SCHEDULE_EARLY_COPY])
@@ -113,6 +113,26 @@ def test_counting_pass_units_and_blocks(channels, n, h, w, schedule):
         st = wl.make_state(dY, wl.seed_for(22, channels))
         for mode, seed, lam in ((daq.ROUND_NEAREST, 0, 0.3), (daq.ROUND_STOCHASTIC, 7 + n, 0.0), (daq.ROUND_STOCHASTIC, 8 + n, 1.0)):
             check_quantize_grad(layer, dY, st, lam=lam, mode=mode, seed=seed, schedule=schedule)
+
+
+# Blocks of more than four groups, which tensors of that size take (widths and last blocks: counting_pass() of tests/host/dispatch.hip): a
+# whole record, 8 + 7, 8 + 5 and 8 + 8 + 1 groups, and of the large ones 7 + 6, 9 + 8, 9 + 9 + 7 and a whole record of twelve
+@pytest.mark.parametrize("channels,n,h,w,k", [
+    (112, 4, 140, 139, 3), (240, 3, 112, 112, 1), (200, 20, 45, 49, 1), (272, 11, 55, 57, 3),
+    (208, 20, 101, 103, 1), (270, 16, 99, 101, 3), (400, 35, 56, 56, 3), (186, 73, 56, 56, 1),
+])
+def test_counting_pass_wide_blocks(channels, n, h, w, k):
+    """Every workgroup walks several tiles, so both LDS tiles take their turns; both copies byte for byte, codes of both roundings, with
+    guessed classes that hold and that do not, and one population for the whole layer."""
+    layer = wl.Layer("wide", n, 1, h, w, channels, k, k, 1, k // 2)
+    dY = wl.make_dY(layer, wl.seed_for(25, channels))
+    st = wl.make_state(dY, wl.seed_for(25, channels))
+    check_quantize_grad(layer, dY, st, mode=daq.ROUND_STOCHASTIC, seed=9 + n, schedule=daq.SCHEDULE_EARLY_COPY)
+    check_quantize_grad(layer, dY, st, lam=0.0, schedule=daq.SCHEDULE_EARLY_COPY, check_padding=False)
+    check_quantize_grad(layer, dY, st, lam=1.0, mode=daq.ROUND_STOCHASTIC, seed=n, schedule=daq.SCHEDULE_THREE_SWEEPS, check_padding=False)
+    if n * h * w * channels < 2 ** 24:
+        check_quantize_grad(layer, dY, st, scheme=daq.SCHEME_MCS, mode=daq.ROUND_STOCHASTIC, seed=n, check_padding=False)
+        check_quantize_grad_bf16(layer, dY, st, mode=daq.ROUND_STOCHASTIC, seed=5)
 
 
 FEW_TILES = [
