@@ -72,6 +72,17 @@ def traced_avg_us(config: int):
     return out
 
 
+def early_copy_from(args, d, qg_nhwc: bool) -> float:
+    """The library's rule: from how many elements on a gradient that takes the sweeps takes the early per-channel copy."""
+    Mi, nearest, vector4 = 2.0 ** 20, args.rounding == "nearest", d.Wo % 4 == 0
+    lv = daq.layout_vq(d)
+    if not nearest or not qg_nhwc:
+        return float("inf") if nearest and d.Wo < 16 else 4 * Mi
+    if lv.row_pitch != lv.W or lv.img_rows != lv.H:
+        return (6 if args.dy_bf16 and not vector4 else 8) * Mi
+    return (6 if vector4 else 4) * Mi
+
+
 def kernel_work(layer, d, name: str, dy_bytes: float, dx_bytes: float, qg_nhwc: bool, early: bool = False):
     """(algorithmic HBM bytes, int8 operations) of one launch of kernel `name` on `layer`.
 
@@ -353,10 +364,8 @@ def run_network(args, dev) -> int:
         row = {"layer": L.name, "shape": f"N{L.N} {L.Cin}->{L.Cout} {L.Hin}x{L.Win} k{L.kH} s{L.stride} g{L.groups}"}
         for k, (us, n) in per[li].items():
             dx_b = 2.0 if (net[li].bf16_ok and k.startswith("conv_bwd_data")) else 4.0
-            # the library's rule for the early per-channel copy (gradients of 4 Mi elements and more, NHWC global copy or odd rows,
-            # no channel-resident kernel)
             early = (args.scheme == "daq" and (qg_nhwc or L.Wo % 2 == 1) and "chan_resident" not in per[li] and
-                     (args.schedule == "early_copy" or (args.schedule == "auto" and float(np.prod(d.y_shape)) >= 4 * 2 ** 20)))
+                     (args.schedule == "early_copy" or (args.schedule == "auto" and float(np.prod(d.y_shape)) >= early_copy_from(args, d, qg_nhwc))))
             b, o = kernel_work(L, d, k, dy_b, dx_b, qg_nhwc, early)
             e = kernels.setdefault(k, {"us": 0.0, "launches": 0.0, "bytes": 0.0, "ops": 0.0})
             e["us"] += us * n

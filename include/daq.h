@@ -177,8 +177,9 @@ size_t daq_workspace_bytes(daq_op op, const daq_conv_desc* desc);
  * Hyper-parameters of the paper: k = 1, A = 0.8, lambda = 0.3.
  *
  * Schedule (results do not depend on it, see daq_schedule): three sweeps over dY - statistics;
- * count + qg; vq.  For gradients of 4 Mi elements and more the second sweep also writes vq under a
- * class guessed from |g|max / sigma, and the third only redoes the channels whose guess was wrong.
+ * count + qg; vq.  For large gradients (from 4 to 8 Mi elements on, by rounding, padding and element
+ * type) the second sweep also writes vq under a class guessed from |g|max / sigma, and the third only
+ * redoes the channels whose guess was wrong.
  * ------------------------------------------------------------------------------------------- */
 daq_status daq_quantize_grad(const daq_conv_desc* desc, const float* dY, float* s_state, float k, float A,
                              float lambda, daq_round mode, uint64_t seed, int8_t* vq, int8_t* qg, float* s_chan,
@@ -285,8 +286,9 @@ daq_status daq_quantize_grad_split(const daq_conv_desc* desc, const void* dY, fl
  * is the same code.  One sweep over dY remains: it counts and writes both copies (the per-channel
  * one under a guessed class, redone for the channels whose guess was wrong), 6 bytes per element
  * instead of 10; layers whose copies that sweep does not write (two channel-major copies of even
- * rows, gradients of less than 3 Mi elements whose rows are no whole vectors, ablation rules) and
- * opts->schedule = DAQ_SCHEDULE_THREE_SWEEPS keep a counting and a packing sweep.  Results: those of daq_quantize_grad_ex bit for bit when the
+ * rows; rows that are no whole vectors in gradients of less than 3 Mi elements, of less than 16 Mi if
+ * padded and rounded to nearest; ablation rules) and opts->schedule = DAQ_SCHEDULE_THREE_SWEEPS keep a
+ * counting and a packing sweep.  Results: those of daq_quantize_grad_ex bit for bit when the
  * statistics are the channel's (fp64 sums taken in another order can differ in their last bits;
  * sigma is rounded to fp32, so that shows only where an element's magnitude or a channel's count
  * sits exactly on the threshold); for other values, the algorithm's result for those statistics.

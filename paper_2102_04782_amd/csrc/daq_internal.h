@@ -197,6 +197,10 @@ struct ResidentForm { int nu, waves; };
 ResidentForm resident_form(int C, int64_t units);
 bool resident_pays(int C, int64_t units, bool padded, bool tails, bool stochastic);   // tails: planes that are not whole units
 bool resident_all_pays(int C, int64_t M, int64_t units);   // whether the launch also writes the global copy of C channels of M elements
+// From how many elements on the counting sweep writes the per-channel copy too.  vector: elements of a row a thread of the packing launch
+// loads at once, 0: rows of no whole vectors; channel_major: the global copy is (depthwise layers).
+struct EarlyCase { bool given, nearest, padded, bf16, channel_major; int vector, W; };
+int64_t early_copy_from(const EarlyCase& e);
 int early_pack_blocks(int64_t channel_elems);   // workgroups a channel of the packing launch behind an early copy
 bool fold_in_packing(int64_t workgroups);   // whether those of a channel-major packing launch fold its scale themselves
 

@@ -26,12 +26,6 @@ constexpr int kMaxSlabs = 16;      // statistics partials per channel (every con
 // until whole lines of it are written back (128 x 96 x 112 x 112, 617 MB, both copies 243 -> 224 us; tensors of 50 to 230 MB, that the
 // statistics sweep has just read, 2 to 10 % slower with the hint).
 constexpr int64_t kCacheBytes = (int64_t)256 << 20;
-// Gradients from this size on take the early per-channel copy (three sweeps and early copy, us: 64 channels of 56 x 56, batch 16 and 32, 19.6 and
-// 19.6, 28.9 and 27.2; 96 of 56 x 56, batch 16, 25.0 and 23.2).
-constexpr int64_t kEarlyVqMinElems = (int64_t)4 << 20;
-// With the producer's statistics and rows that are no whole vectors: the counting sweep and the packing behind it, us, both copies early and not:
-// 3 x 168 x 71 x 71, whole call, 31.1 and 30.0, 2 x 256 x 71 x 71 10.4 and 7.9, 28 x 880 x 13 x 11 11.7 and 14.5, 118 x 32 x 31 x 31 9.0 and 10.6.
-constexpr int64_t kEarlyGivenOddMinElems = (int64_t)3 << 20;
 
 int64_t channel_units(int N, int HW);
 
@@ -2028,6 +2022,26 @@ bool resident_pays(int C, int64_t units, bool padded, bool tails, bool stochasti
     return units <= 6 * 1024 || C >= kChannels[size + padded + tails + 2 * stochastic];
 }
 
+// Both copies in the counting sweep save a read of dY and cost it instructions and stores of four bytes; the packing launch behind it is left with
+// the padding between the rows, its own line where an image has any.  Speed of the early copy over three sweeps, by millions of elements (16 to 200
+// channels, fp32; bfloat16 the same but where it is given):
+//                                         4      5      6      8      10
+//   stochastic, rows of whole vectors     1.02   1.04   1.04   1.07   1.11       odd rows 1.06 to 1.18
+//   nearest, no padding, 4 to a vector    0.95   0.99   1.02   1.06   1.08       2 to a vector and odd 1.06 and more
+//   nearest, padded                       0.95   0.96   0.97   0.99   1.02       bfloat16, 2 to a vector and odd 0.99, 0.99, 1.02, 1.03, 1.05
+// With the producer's statistics the sweep is the only read of dY left and writes both copies at any size, but for odd rows, where the
+// packing launch is slow: without padding 1.06 at 3 to 4 M, 1.15 from 4 on, padded and nearest 0.93 to 1.0 up to 16 M (48 to 3000 channels), stochastic 1.03.
+// Depthwise gradients of odd rows, whose two copies are both channel-major: 1.08 to 1.4, but nearest on rows of 7 0.95 (of 29: 1.10; with the producer's
+// statistics 1.00).
+int64_t early_copy_from(const EarlyCase& e) {
+    constexpr int64_t kMi = (int64_t)1 << 20;
+    if (e.channel_major) return e.given ? 3 * kMi : e.nearest && e.W < 16 ? INT64_MAX : 4 * kMi;
+    if (e.given) return e.vector ? 0 : (e.nearest && e.padded ? 16 : 3) * kMi;
+    if (!e.nearest) return 4 * kMi;
+    if (e.padded) return (e.bf16 && e.vector != 4 ? 6 : 8) * kMi;
+    return (e.vector == 4 ? 6 : 4) * kMi;
+}
+
 // Whether the resident launch writes the NHWC copy as well: every workgroup of eight waves then reads the whole tensor and stores its
 // codes byte by byte.  What a CU reads is C * M elements for each of its workgroups, one to 256 channels, and that sets the time: two launches
 // are 9.9 to 10.2 us a call at any of these sizes, one launch 7.0 to 7.3 up to 32 Ki elements a CU and (channels of elements; elements a CU)
@@ -2331,15 +2345,16 @@ daq_status quantize_grad_impl(const daq_conv_desc* desc, const T* dY, float* s_s
     // Large gradients: the counting pass also writes the per-channel copy under a guessed class (see k_count_qg), so
     // that the third sweep over dY only touches the channels whose guess was wrong.  Small ones are bound by launch
     // latency, not by bytes, and keep the leaner counting kernel.
-    // (With the producer's statistics the counting sweep is the only full read of dY: it writes both copies, small gradients of odd rows aside.)
-    const bool odd_rows = rows_vector(Lv, dY, (int)sizeof(T)) == 0;
-    const bool want_early = schedule == DAQ_SCHEDULE_EARLY_COPY || (schedule == DAQ_SCHEDULE_AUTO && (int64_t)N * C * HW >= kEarlyVqMinElems) ||
-                            (given && schedule != DAQ_SCHEDULE_THREE_SWEEPS && (!odd_rows || (int64_t)N * C * HW >= kEarlyGivenOddMinElems));
+    const int rows_v = rows_vector(Lv, dY, (int)sizeof(T));
+    const bool padded = Lv.row_pitch != Lv.W || Lv.img_rows != Lv.H;
+    const bool want_early = schedule == DAQ_SCHEDULE_EARLY_COPY ||
+                            ((schedule == DAQ_SCHEDULE_AUTO || (given && schedule != DAQ_SCHEDULE_THREE_SWEEPS)) &&
+                             (int64_t)N * C * HW >= early_copy_from({given != nullptr, !stoch, padded, sizeof(T) == 2, !qg_nhwc, rows_v, Wo}));
     // Two channel-major copies: where the packing kernel takes rows in whole vectors, one read of dY for both copies behind the counting
     // sweep is as fast (128 x 144 x 56 x 56, depthwise: 138 and 157 us); where rows are odd it would take two launches, an element at a time
     // (40 x 200 x 59 x 63: 116 and 90; 20 x 100 x 61 x 63: 44 and 37).
     const bool early = want_early && scheme == DAQ_SCHEME_DAQ && early_copy_supported(Lv, dY, (int)sizeof(T)) &&
-                       (qg_nhwc || odd_rows);
+                       (qg_nhwc || rows_v == 0);
     EarlyVq ev{};
     if (early) {
         // |g|max / sigma of M Gaussian samples is about sqrt(2 ln M), of M Laplace samples ln M / sqrt 2: halfway

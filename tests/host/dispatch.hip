@@ -58,6 +58,23 @@ static void early_packing() {
     EXPECT(early_pack_blocks(32 * 3136) == 16 && early_pack_blocks(4096) == 1 && early_pack_blocks(4097) == 2);
 }
 
+// From which size on the counting sweep writes both copies: calls that got slower with them.
+static void early_copy() {
+    const int64_t mi = 1 << 20;
+    enum { kNearest = 1, kPadded = 2, kBf16 = 4, kGiven = 8, kChannelMajor = 16 };
+    auto from = [](int flags, int vector, int W) {
+        return early_copy_from({bool(flags & kGiven), bool(flags & kNearest), bool(flags & kPadded), bool(flags & kBf16), bool(flags & kChannelMajor), vector, W});
+    };
+    EXPECT(from(kNearest, 4, 56) > 5 * mi && from(kNearest | kPadded, 4, 56) > 7 * mi && from(kNearest | kPadded, 0, 49) > 7 * mi);
+    EXPECT(from(kNearest | kPadded | kBf16, 4, 56) > 7 * mi && from(kNearest | kPadded | kBf16, 0, 49) > 5 * mi);
+    EXPECT(from(kNearest | kPadded | kGiven, 0, 31) > 12 * mi && from(kNearest | kChannelMajor | kPadded, 0, 7) > 100 * mi);
+    for (int vector : {0, 2, 4}) EXPECT(from(0, vector, 56) == 4 * mi && from(kPadded | kBf16, vector, 56) == 4 * mi);
+    EXPECT(from(kNearest, 2, 26) == 4 * mi && from(kNearest, 0, 49) == 4 * mi && from(kNearest | kPadded, 2, 26) == 8 * mi);
+    EXPECT(from(kGiven, 0, 49) == 3 * mi && from(kGiven | kNearest, 0, 49) == 3 * mi && from(kGiven | kPadded, 0, 49) == 3 * mi);
+    for (int flags : {0, (int)kNearest, (int)kPadded, kNearest | kPadded}) EXPECT(from(flags | kGiven, 2, 26) == 0 && from(flags | kGiven, 4, 56) == 0);
+    EXPECT(from(kChannelMajor | kPadded, 0, 7) == 4 * mi && from(kChannelMajor | kPadded | kNearest, 0, 49) == 4 * mi && from(kChannelMajor | kNearest | kGiven, 0, 7) == 3 * mi);
+}
+
 // The counting pass: blocks of channels by the size of the tensor, and what its kernel and its buffers take for granted.
 static void counting_pass() {
     auto width = [](int C, int N, int HW) { return plan_count(C, N, HW).width; };
@@ -130,6 +147,7 @@ int main() {
     resident_quantizer();
     resident_both_copies();
     early_packing();
+    early_copy();
     counting_pass();
     filter_gradient();
     std::printf("%d failures\n", fails);
