@@ -1199,6 +1199,14 @@ static OtherKernel as_other(const Geometry& g) {
 
 bool bwd_data_halo_supported(const daq_conv_desc& d) { return plan_bwd(d).ok; }
 
+int product_direct_waves(bool backward, const daq_conv_desc& d, bool bf16) {
+    daq_layout L;
+    if ((backward ? daq_layout_qg(&d, &L) : daq_layout_qx_nhwc(&d, &L)) != DAQ_OK) return 0;
+    const Geometry g = backward ? plan_bwd(d) : plan_fwd(d);
+    if (g.ok) return stream_applies(d, L) ? 0 : direct_waves(backward, d, as_other(g), bf16);
+    return !backward && fwd_mfma_supported(d) ? direct_waves(false, d, fwd_nhwc_as_other(d), bf16) : 0;
+}
+
 daq_status conv_bwd_data_halo(const daq_conv_desc& d, const int8_t* qg, const float* s_g, const int8_t* qw,
                               const float* s_w, float* dX, int32_t* acc, hipStream_t st, const DwTail* tail, bool bf16) {
     Geometry g = plan_bwd(d);

@@ -338,15 +338,18 @@ daq_status conv_bwd_data_mfma(const daq_conv_desc& d, const int8_t* qg, const fl
 
 bool fwd_mfma_supported(const daq_conv_desc& d) { return nhwc_supported(d); }
 
+OtherKernel fwd_nhwc_as_other(const daq_conv_desc& d) {
+    const int64_t px_tiles = ceil_div((int64_t)d.N * daq_out_h(&d) * daq_out_w(&d), kPxWg);
+    return OtherKernel{TileForm::kNhwc, false, d.Cout > 64 ? px_tiles * ceil_div(d.Cout, 128) : px_tiles, d.kH * d.kW * (int)ceil_div(round_up(d.Cin, 16), 64)};
+}
+
 daq_status conv_fwd_mfma(const daq_conv_desc& d, const int8_t* qx, const int8_t* qw, const float* s_x,
                          const float* s_w, float* Y, int32_t* acc, hipStream_t st) {
     daq_layout Lx;
     daq_wpack_layout Lw;
     if (daq_layout_qx_nhwc(&d, &Lx) != DAQ_OK || daq_layout_qw(&d, &Lw) != DAQ_OK) return DAQ_ERR_INVALID_ARG;
-    const int64_t px_tiles = ceil_div((int64_t)d.N * daq_out_h(&d) * daq_out_w(&d), kPxWg);
-    const OtherKernel other{TileForm::kNhwc, false, d.Cout > 64 ? px_tiles * ceil_div(d.Cout, 128) : px_tiles, d.kH * d.kW * (int)ceil_div(Lx.c_pitch, 64)};
     daq_status rc;
-    if (conv_direct(false, d, other, qx, qw, s_x, s_w, Y, acc, st, nullptr, false, rc)) return rc;
+    if (conv_direct(false, d, fwd_nhwc_as_other(d), qx, qw, s_x, s_w, Y, acc, st, nullptr, false, rc)) return rc;
     NhwcArgs a{};
     a.src = qx;
     a.wpk = qw + Lw.off_fwd;

@@ -291,6 +291,9 @@ struct OtherKernel {
     int64_t blocks;
     int steps;
 };
+OtherKernel fwd_nhwc_as_other(const daq_conv_desc& d);   // conv_mfma_nhwc.hip
+int direct_waves(bool backward, const daq_conv_desc& d, const OtherKernel& other, bool bf16);   // waves to a tile, 0: `other` is the faster
+int product_direct_waves(bool backward, const daq_conv_desc& d, bool bf16);   // conv_mfma_halo.hip: the same with what would serve the product
 bool conv_direct(bool backward, const daq_conv_desc& d, const OtherKernel& other, const int8_t* src, const int8_t* qw, const float* s_a,
                  const float* s_b, float* out, int32_t* acc, hipStream_t st, const DwTail* tail, bool bf16, daq_status& rc);
 

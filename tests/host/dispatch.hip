@@ -143,6 +143,31 @@ static void filter_gradient() {
     EXPECT(beside_splits(layer(4, 12, 25, 20, 20, 3, 1), 240, 4.9) > 1);    // 32 and more: shared out
 }
 
+// Products without staging: what goes back to the tile kernel, and the waves to a tile of the layers of test_products_of_few_tiles.
+static void products() {
+    auto fwd = [](daq_conv_desc d) { return product_direct_waves(false, d, false); };
+    auto bwd = [](daq_conv_desc d) { return product_direct_waves(true, d, false); };
+    EXPECT(!fwd(layer(37, 871, 34, 34, 16, 1, 1)) && !fwd(layer(16, 1219, 63, 50, 16, 1, 1)) && !fwd(layer(10, 1397, 51, 51, 6, 1, 1)));   // a source beyond the L2s
+    EXPECT(!fwd(layer(71, 7, 135, 135, 4, 3, 1)) && !bwd(layer(101, 5, 123, 123, 10, 5, 2)));                                            // hundreds of tiles a CU
+    EXPECT(fwd(layer(6, 768, 5, 5, 52, 5, 1)) && fwd(layer(23, 3, 16, 16, 96, 7, 2)) && fwd(layer(39, 3, 133, 133, 96, 3, 2)));
+    EXPECT(fwd(layer(26, 1173, 14, 14, 37, 1, 1)) && bwd(layer(20, 649, 5, 5, 985, 1, 1)));
+    auto both = [&](daq_conv_desc d, int f, int b) {
+        if (fwd(d) != f || bwd(d) != b) { std::printf("FAILED: %d and %d waves, not %d and %d\n", fwd(d), bwd(d), f, b); ++fails; }
+    };
+    both(layer(1, 1, 1, 1, 1, 3, 1), 2, 2);
+    both(layer(2, 16, 9, 11, 33, 5, 1), 4, 8);
+    both(layer(3, 40, 7, 9, 65, 3, 1), 4, 8);
+    both(daq_conv_desc{2, 70, 13, 5, 31, 1, 7, 1, 1, 3, 3, 1, 1, 1}, 8, 2);
+    both(layer(3, 3, 17, 15, 40, 7, 2), 8, 8);
+    both(layer(4, 50, 14, 13, 60, 3, 2), 8, 2);
+    both(layer(3, 130, 9, 8, 20, 1, 2), 2, 1);
+    both(daq_conv_desc{2, 33, 15, 14, 40, 3, 3, 2, 2, 2, 2, 2, 2, 1}, 4, 2);
+    both(layer(2, 20, 14, 16, 40, 3, 3), 4, 0);
+    both(layer(41, 20, 64, 65, 40, 5, 2), 1, 0);
+    both(layer(19, 80, 35, 41, 5, 5, 1), 8, 1);
+    both(layer(12, 96, 32, 33, 64, 3, 2), 8, 0);
+}
+
 int main() {
     resident_quantizer();
     resident_both_copies();
@@ -150,6 +175,7 @@ int main() {
     early_copy();
     counting_pass();
     filter_gradient();
+    products();
     std::printf("%d failures\n", fails);
     return fails != 0;
 }

@@ -145,14 +145,16 @@ FEW_TILES = [
     wl.Layer("d_s2_1x1", 3, 130, 9, 8, 20, 1, 1, 2, 0),          # three of them without a tap: zeros
     wl.Layer("d_s2_dil", 2, 33, 15, 14, 40, 3, 3, 2, 2, dil=2),  # even dilation: all taps in one class
     wl.Layer("d_s3", 2, 20, 14, 16, 40, 3, 3, 3, 1),             # forward only
-    wl.Layer("d_ks1", 40, 32, 32, 33, 48, 3, 3, 1, 1),           # tiles enough for a wave each
-    wl.Layer("d_ks2", 12, 96, 32, 33, 64, 3, 3, 2, 1),
+    wl.Layer("d_ks1", 41, 20, 64, 65, 40, 5, 5, 2, 2),           # forward, tiles enough for a wave each: 25 steps, ragged last workgroup
+    wl.Layer("d_ks1_x", 19, 80, 35, 41, 5, 5, 5, 1, 2),          # data gradient, a wave each: 13 steps
+    wl.Layer("d_ks8", 12, 96, 32, 33, 64, 3, 3, 2, 1),           # forward only
 ]
 
 
 @pytest.mark.parametrize("layer", FEW_TILES, ids=lambda l: l.name)
 def test_products_of_few_tiles(layer):
-    """Both products without staging, 1 to 8 waves to a tile, records of 1 to 17 units, every class of taps."""
+    """Both products without staging, 1 to 8 waves to a tile, records of 1 to 17 units, every class of taps (which of the two takes the
+    kernel, and the waves: products() of tests/host/dispatch.hip)."""
     on_random_codes(layer, 71)
     check_forward(layer, 72)
 
