@@ -102,10 +102,10 @@ def test_resident_quantizer_on_planes_of_any_size(per_thread, n, h, w, k):
 # Channel counts by the groups of 16 that the counting pass gives a workgroup's waves, in blocks of up to four: one to three groups
 # (several tiles at a time), whole blocks, last blocks of one and of two groups
 @pytest.mark.parametrize("channels", [9, 24, 48, 90, 144, 190, 208, 330])
-@pytest.mark.parametrize("n,h,w", [(5, 8, 8), (3, 7, 7), (4, 6, 9), (9, 1, 3)], ids=lambda v: str(v))
+@pytest.mark.parametrize("n,h,w", [(5, 8, 8), (3, 7, 7), (4, 6, 9), (9, 1, 3), (3, 7, 6), (5, 4, 10), (4, 6, 2)], ids=lambda v: str(v))
 @pytest.mark.parametrize("schedule", [daq.SCHEDULE_THREE_SWEEPS, daq.SCHEDULE_EARLY_COPY])
 def test_counting_pass_units_and_blocks(channels, n, h, w, schedule):
-    """Planes of whole units of four, with a shorter last unit, and of less than one; both copies byte for byte, with guessed classes
+    """Planes of whole units of four, with a shorter last unit, and of less than one; rows of whole units, even and odd ones; both copies byte for byte, with guessed classes
     that hold and (lambda 0 and 1) that do not."""
     for k in (1, 3):
         layer = wl.Layer("units", n, 1, h, w, channels, k, k, 1, k // 2)
@@ -113,6 +113,14 @@ def test_counting_pass_units_and_blocks(channels, n, h, w, schedule):
         st = wl.make_state(dY, wl.seed_for(22, channels))
         for mode, seed, lam in ((daq.ROUND_NEAREST, 0, 0.3), (daq.ROUND_STOCHASTIC, 7 + n, 0.0), (daq.ROUND_STOCHASTIC, 8 + n, 1.0)):
             check_quantize_grad(layer, dY, st, lam=lam, mode=mode, seed=seed, schedule=schedule)
+
+
+@pytest.mark.parametrize("n,h,w", [(3, 7, 6), (5, 4, 10), (4, 6, 2), (2, 9, 14), (3, 5, 7), (3, 6, 3)], ids=lambda v: str(v))
+@pytest.mark.parametrize("channels", [3, 40, 90])
+def test_forward_early_copy_of_rows_off_the_units(channels, n, h, w):
+    """Units that run on into the next row: after two pixels, after any number, over several rows."""
+    for k in (1, 3):
+        check_forward(wl.Layer("rows", n, channels, h, w, 20, k, k, 1, k // 2), 26, schedule=daq.SCHEDULE_EARLY_COPY)
 
 
 # Blocks of more than four groups, which tensors of that size take (widths and last blocks: counting_pass() of tests/host/dispatch.hip): a
