@@ -182,12 +182,15 @@ struct CountPlan {
     __host__ __device__ int groups(int C, int b) const { return b + 1 < blocks ? width : (C + 15) / 16 - (blocks - 1) * width; }
     // LDS of one of the two tiles a workgroup keeps: by pixel of a unit, unit and 16-byte share of the record, units an odd number of
     // 16 bytes apart and pixels 64 bytes more than 16 units: no bank conflicts either way
-    __host__ __device__ static int pitch_dwords(int gb) { return 4 * (gb | 1); }
-    __host__ __device__ static int step_dwords(int gb) { return 16 * pitch_dwords(gb) + 16; }
-    int tile_dwords(int C) const {
-        auto of = [&](int gb) { return gb == 1 ? 0 : waves / gb * 4 * step_dwords(gb); };
-        return std::max(of(groups(C, 0)), of(groups(C, blocks - 1)));
+    __host__ __device__ static constexpr int pitch_dwords(int gb) { return 4 * (gb | 1); }
+    __host__ __device__ static constexpr int step_dwords(int gb) { return 16 * pitch_dwords(gb) + 16; }
+    static constexpr int block_dwords(int waves, int gb) { return gb == 1 ? 0 : waves / gb * 4 * step_dwords(gb); }
+    static constexpr int most_tile_dwords(int waves) {
+        int most = 0;
+        for (int gb = 1; gb <= waves; ++gb) most = std::max(most, block_dwords(waves, gb));
+        return most;
     }
+    int tile_dwords(int C) const { return std::max(block_dwords(waves, groups(C, 0)), block_dwords(waves, groups(C, blocks - 1))); }
 };
 CountPlan plan_count(int C, int N, int HW, int given = 0, int held_given = 0);
 

@@ -1787,7 +1787,7 @@ struct FwdQuantArgs {
     QuantWs ws;
     PackWArgs w;
 };
-constexpr int kFwdTileDw = 1664;   // CountPlan::tile_dwords of four waves, at most
+constexpr int kFwdTileDw = CountPlan::most_tile_dwords(kBlock / kWave);
 template <bool EARLY, int V, int UNIT>
 __global__ __launch_bounds__(kBlock, 4) void k_fwd_quant(FwdQuantArgs a) {
     __shared__ float l_red[kBlock / kWave];
@@ -2089,7 +2089,6 @@ daq_status quantize_forward(const daq_conv_desc& d, const float* X, int8_t* qx_n
     m.x[1] = W; m.n[1] = nw; m.part[1] = part + kAbsmaxBlocksX;
     m.blocks[0] = (int)std::min<int64_t>(ceil_div(n, kBlock * 32), kAbsmaxBlocksX);
     m.blocks[1] = (int)std::min<int64_t>(ceil_div(nw, kBlock * 32), kAbsmaxBlocksW);
-    DAQ_LAUNCH("absmax", st, hipLaunchKernelGGL(k_absmax, dim3((unsigned)(m.blocks[0] + m.blocks[1])), dim3(kBlock), 0, st, m));
 
     const int HW = d.Hin * d.Win;
     FwdQuantArgs a{};
@@ -2106,8 +2105,7 @@ daq_status quantize_forward(const daq_conv_desc& d, const float* X, int8_t* qx_n
     // one workgroup a CU: more of them take from the other kind more than they gain (quantizing launch, us, 4, 1 a CU: 12 x 224 x 37 x 37
     // 14.9 and 12.0, 9 x 640 x 25 x 25 17.8 and 14.4, 7 x 464 x 83 x 83 at stride 2 67.6 and 64.8).  Alone it takes all the chip
     // holds (29 x 224 x 48 x 47 18.7, one a CU 21.2; 72 x 49 x 99 x 99 47.6 and 57.0).
-    a.ws = carve_quant_ws(nullptr, d.Cin, d.N, HW, kBlock / kWave, early ? 0 : 256);
-    if (a.ws.cp.tile_dwords(d.Cin) > kFwdTileDw) return DAQ_ERR_UNSUPPORTED;   // (four waves: never)  // only the tile geometry is used: nothing is counted here
+    a.ws = carve_quant_ws(nullptr, d.Cin, d.N, HW, kBlock / kWave, early ? 0 : 256);   // only the tile geometry is used: nothing is counted here
     a.ws.part_max = part;
     a.ws.part_n = m.blocks[0];
     a.ws.layer = part + kAbsmaxBlocksX + kAbsmaxBlocksW;
@@ -2147,6 +2145,7 @@ daq_status quantize_forward(const daq_conv_desc& d, const float* X, int8_t* qx_n
     }
     const int64_t blocks = a.w_blocks + a.x_blocks + c_blocks;
     if (blocks >= ((int64_t)1 << 31)) return DAQ_ERR_UNSUPPORTED;
+    DAQ_LAUNCH("absmax", st, hipLaunchKernelGGL(k_absmax, dim3((unsigned)(m.blocks[0] + m.blocks[1])), dim3(kBlock), 0, st, m));   // the first launch: nothing behind it fails
 #define DAQ_FWD_QUANT(E, VV, UN) DAQ_LAUNCH("quant_fwd", st, hipLaunchKernelGGL((k_fwd_quant<E, VV, UN>), dim3((unsigned)blocks), dim3(kBlock), 0, st, a))
     const int unit = unit_kind(HW);
     if (v == 4) { if (early) DAQ_FWD_QUANT(true, 4, kWhole); else DAQ_FWD_QUANT(false, 4, kWhole); }   // rows of whole units

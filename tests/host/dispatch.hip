@@ -100,6 +100,7 @@ static void counting_pass() {
                     EXPECT(p.width <= p.waves && p.waves <= kCountMaxWaves && (p.blocks - 1) * p.width < G && p.blocks * p.width >= G);
                     EXPECT(1 <= p.cgroups_last && p.cgroups_last <= p.cgroups && p.cgroups <= kCountGroups);
                     EXPECT(p.tile_dwords(C) * 8 <= 48 << 10);               // two tiles of LDS, no more than a launch has without asking
+                    if (given) EXPECT(p.tile_dwords(C) <= CountPlan::most_tile_dwords(given));   // the forward's, whose LDS is of a fixed size
                     for (int b = 0; b < 2; ++b)
                         for (uint32_t i = 0, gb = (uint32_t)p.groups(C, b ? p.blocks - 1 : 0); i < 64 * kCountMaxWaves; ++i)
                             EXPECT(i * p.by_groups[b] >> 16 == i / gb);
