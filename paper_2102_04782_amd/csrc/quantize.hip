@@ -477,14 +477,18 @@ __device__ __forceinline__ void transpose_rows(uint32_t (&w)[4]) {
 
 // ---------------------------------------------------------------------------------------------
 // S2 (+ the global copy of S5): tail-mass count per channel, fused with the globally quantized
-// NHWC copy.  A workgroup owns 64 channels and walks tiles of 16 units (64 pixels) p, p + cgroups, ... of the
-// flattened (n, h*w) axis; wave w handles channels 16w..16w+15.  Lane 16 r + q holds unit q of channels 4r .. 4r+3 of
+// NHWC copy.  A workgroup owns a block of up to 192 channels (block_width) and walks tiles of 16 units (64 pixels) of the
+// flattened (n, h*w) axis; a wave handles 16 of the channels.  Where the block leaves waves over (thin tensors, the smaller
+// last block), the waves form several sides, each with a tile of its own.  Lane 16 r + q holds unit q of channels 4r .. 4r+3 of
 // the wave's: four 16-byte loads, each 256 consecutive bytes of four channels a wave, the random words of a unit from one
 // first step, a per-channel unit is one dword, and four instructions between the lanes (transpose_rows) turn the codes of
 // four channels x one unit into 16 channels x one pixel for the NHWC copy.
-// The workgroup first folds the statistics partials of its 64 channels (sigma) and of all channels
-// (the global scale max_c |g|max), then counts into registers and stores one
+// A wave first folds the statistics partials of its own 16 channels (sigma), the workgroup those of all channels
+// (the global scale max_c |g|max); then the pass counts into registers and stores one
 // count partial per channel: no atomics, no reduction launch.
+// Registers: 128, four waves a SIMD.  The copy alone needs 54 to 64 of them, the count with it 80 to 90, all of it with stochastic codes 127 on
+// planes of whole units, with 22 scalars kept in vector lanes; with a shorter last unit 3 vector registers are spilled, on planes of
+// less than a unit (kElems, which loads and places each element by itself) 32.
 // ---------------------------------------------------------------------------------------------
 //
 // EARLY: the pass also writes the per-channel copy vq.  The class of a channel is only known once the counts of all
