@@ -74,6 +74,8 @@ def traced_avg_us(config: int):
 
 def early_copy_from(args, d, qg_nhwc: bool) -> float:
     """The library's rule: from how many elements on a gradient that takes the sweeps takes the early per-channel copy."""
+    from paper_2102_04782_amd import binding as daq
+
     Mi, nearest, vector4 = 2.0 ** 20, args.rounding == "nearest", d.Wo % 4 == 0
     lv = daq.layout_vq(d)
     if not nearest or not qg_nhwc:

@@ -236,3 +236,17 @@ def test_workload_tables():
     assert all(kurt(dY[:, c].ravel()) < 4 for c in range(0, 16, 2))
     assert all(kurt(dY[:, c].ravel()) > 20 for c in range(1, 16, 2))
     assert np.all(st > 0)
+
+
+def test_bench_prices_every_layer_by_the_early_copy_it_takes():
+    import argparse
+    import bench
+
+    Mi = 2 ** 20
+    for net in (wl.config4(), wl.config5()):
+        for layer in net:
+            d = daq.ConvDesc.make(*layer.desc_fields())
+            qg_nhwc = daq.layout_qg(d).kind == daq.LAYOUT_NHWC
+            for rounding, bf16 in (("stochastic", False), ("nearest", False), ("nearest", True)):
+                at = bench.early_copy_from(argparse.Namespace(rounding=rounding, dy_bf16=bf16), d, qg_nhwc)
+                assert at == 4 * Mi if rounding == "stochastic" else at in (4 * Mi, 6 * Mi, 8 * Mi, float("inf"))
