@@ -193,6 +193,8 @@ struct CountPlan {
     int tile_dwords(int C) const { return std::max(block_dwords(waves, groups(C, 0)), block_dwords(waves, groups(C, blocks - 1))); }
 };
 CountPlan plan_count(int C, int N, int HW, int given = 0, int held_given = 0);
+// Waves of a workgroup of the forward quantizing launch, where its sweep writes both copies of X; w_blocks: its workgroups for the filter.
+int forward_waves(int C, int N, int HW, int w_blocks);
 
 // Channel-resident quantizer: `units` load units of a channel (four elements of a plane each, fewer at its end) on a workgroup of
 // `waves` waves, `nu` units to a thread.

@@ -110,6 +110,24 @@ CountPlan plan_count(int C, int N, int HW, int given, int held_given) {
     return p;
 }
 
+// Workgroups of the forward sweep over X that writes both copies: eight waves, so that a block is 128 channels and 128 bytes of a record leave as one run,
+// or four.  Speed of its launch with eight over four waves, 80 to 1024 channels, planes of 27 x 31 to 71 x 70, by millions of elements
+//                                    12 to 13         28 to 30         57 to 60         100 to 115
+//   up to 64 channels                never: four waves hold the whole record
+//   80, 112 channels                 0.97 to 1.05     1.10 to 1.14     1.13 to 1.33     1.12 to 1.28
+//   96 channels                      0.96 to 1.03     1.04 to 1.09     1.17 to 1.20     1.05 to 1.19
+//   a last block of one group        0.97 to 1.10     0.98 to 1.05     0.98 to 1.02     0.98 to 1.03
+//   others                           0.93 to 1.08     0.94 to 1.08     1.02 to 1.21     1.01 to 1.22
+// In four waves a record of several times 64 bytes leaves from as many workgroups, which do not keep step; up to some 20 M elements the caches
+// bring the pieces together all the same.  Whole pass, 384 channels: 55 of 71 x 70, 1 x 1,
+// 336 us with four waves, 319 with eight; 60 of 58 x 58, 3 x 3, 282 and 272; 96 channels, 128 of 105 x 105, 1 x 1, 431 and 365.
+// The filter's workgroups come first in the launch, and where they are many a CU that holds one is short of a workgroup of twice the size: over 400
+// drawn tensors of 24 to 112 Mi elements 1.04 to 1.12 times the speed up to a workgroup a CU, 0.98 up to 400, 0.95 beyond (768 channels and more, 5 x 5: 0.83 to
+// 0.95).  Beyond 2048 channels, where they are 130 and more for any filter, level or down to 0.90.
+int forward_waves(int C, int N, int HW, int w_blocks) {
+    return C > 64 && HW >= 4 && (int64_t)C * N * HW > (int64_t)24 << 20 && C <= 2048 && w_blocks <= 256 ? 8 : kBlock / kWave;
+}
+
 namespace {
 
 QuantWs carve_quant_ws(void* base, int C, int N, int HW, int given_waves = 0, int given_held = 0) {
@@ -1791,15 +1809,17 @@ struct FwdQuantArgs {
     QuantWs ws;
     PackWArgs w;
 };
-constexpr int kFwdTileDw = CountPlan::most_tile_dwords(kBlock / kWave);
-template <bool EARLY, int V, int UNIT>
-__global__ __launch_bounds__(kBlock, 4) void k_fwd_quant(FwdQuantArgs a) {
+// WAVES: of a workgroup, four or (EARLY) eight, see forward_waves; the other roles are written for four.
+template <bool EARLY, int V, int UNIT, int WAVES>
+__global__ __launch_bounds__(WAVES * kWave, 4) void k_fwd_quant(FwdQuantArgs a) {
+    constexpr int kTileDw = CountPlan::most_tile_dwords(WAVES);
     __shared__ float l_red[kBlock / kWave];
     __shared__ __align__(16) int8_t l_w[2 * kWTaps * kWPlane];
-    __shared__ __align__(16) uint32_t l_records[2 * kFwdTileDw];
+    __shared__ __align__(16) uint32_t l_records[2 * kTileDw];
     int b = (int)blockIdx.x;
-    if (b < a.w_blocks) {   // uniform, as all branches below
+    if (b < a.w_blocks) {   // uniform, as all branches on b
         if (b >= a.w.blocks) return;
+        if (WAVES * kWave > kBlock && threadIdx.x >= kBlock) return;   // (a barrier waits for the waves that are still there)
         if (a.w.groups > 1) pack_w_units(b, a.w, l_red);
         else if (a.w.taps == 1) pack_w_tile<1>(b, a.w, l_red, l_w, l_w + kWTaps * kWPlane);
         else pack_w_tile<kWTaps>(b, a.w, l_red, l_w, l_w + kWTaps * kWPlane);
@@ -1808,9 +1828,10 @@ __global__ __launch_bounds__(kBlock, 4) void k_fwd_quant(FwdQuantArgs a) {
     b -= a.w_blocks;
     if (b < a.x_blocks) {
         if (b >= a.ws.cp.workgroups()) return;
-        count_qg_role<float, false, true, false, EARLY, UNIT>(b, a.x, a.N, a.C, a.HW, a.c_pitch, a.div_u, a.ws, a.nhwc, 0, nullptr, a.s_x, a.ev, a.tail, l_records, kFwdTileDw);
+        count_qg_role<float, false, true, false, EARLY, UNIT>(b, a.x, a.N, a.C, a.HW, a.c_pitch, a.div_u, a.ws, a.nhwc, 0, nullptr, a.s_x, a.ev, a.tail, l_records, kTileDw);
         return;
     }
+    if (WAVES * kWave > kBlock && threadIdx.x >= kBlock) return;
     b -= a.x_blocks;
     if constexpr (V > 0) pack_rows_role<float, false, false, V>(b, a.x, a.Lc, a.ws.part_max, a.cnhw, a.ra, a.ws, ClipArgs{});
     else pack_cnhw_role<float, false, false>(b % a.phase_blocks, b / a.phase_blocks, a.x, a.Lc, a.ws.part_max, a.cnhw, a.pa, a.ws, ClipArgs{});
@@ -2105,11 +2126,30 @@ daq_status quantize_forward(const daq_conv_desc& d, const float* X, int8_t* qx_n
     // (by default from 8 Mi elements on: below that the two lean passes are as fast or faster; 28 x 176 x 27 x 31, 4.1 Mi: 49.6 and 50.5 us a call)
     const bool early = (schedule == DAQ_SCHEDULE_EARLY_COPY || (schedule == DAQ_SCHEDULE_AUTO && n >= ((int64_t)8 << 20))) &&
                        early_copy_supported(Lc, X, 4);
+    if (W) {
+        PackWArgs& w = a.w;
+        if (daq_layout_qw(&d, &w.L) != DAQ_OK) return DAQ_ERR_INVALID_ARG;
+        w.w = W; w.out = qw; w.s_w = s_w; w.part = m.part[1]; w.part_n = m.blocks[1];
+        w.Cout = d.Cout; w.Cin = d.Cin; w.groups = d.groups; w.taps = taps;
+        w.cig = d.Cin / d.groups; w.cog = d.Cout / d.groups;
+        if (d.groups == 1) {
+            w.chunks = (int)ceil_div(taps, kWTaps);
+            w.ci_tiles = 2 * (int)ceil_div(d.Cin, 64);
+            const int first = std::min(taps, kWTaps), last = taps - (w.chunks - 1) * kWTaps;
+            w.div_run = make_fastdiv((uint32_t)(32 * first)); w.div_tap = make_fastdiv((uint32_t)first);
+            w.div_runl = make_fastdiv((uint32_t)(32 * last)); w.div_tapl = make_fastdiv((uint32_t)last);
+            w.blocks = 2 * (int)ceil_div(d.Cout, 64) * w.ci_tiles * w.chunks;
+        } else {
+            w.blocks = (int)ceil_div(w.L.bytes, 16 * kBlock);
+        }
+        a.w_blocks = (int)round_up(w.blocks, kXcd);
+    }
     // Where the channel-major copy has workgroups of its own, both kinds read X side by side, and the sweep over NHWC records is
     // one workgroup a CU: more of them take from the other kind more than they gain (quantizing launch, us, 4, 1 a CU: 12 x 224 x 37 x 37
     // 14.9 and 12.0, 9 x 640 x 25 x 25 17.8 and 14.4, 7 x 464 x 83 x 83 at stride 2 67.6 and 64.8).  Alone it takes all the chip
     // holds (29 x 224 x 48 x 47 18.7, one a CU 21.2; 72 x 49 x 99 x 99 47.6 and 57.0).
-    a.ws = carve_quant_ws(nullptr, d.Cin, d.N, HW, kBlock / kWave, early ? 0 : 256);   // only the tile geometry is used: nothing is counted here
+    const int waves = early ? forward_waves(d.Cin, d.N, HW, a.w_blocks) : kBlock / kWave;
+    a.ws = carve_quant_ws(nullptr, d.Cin, d.N, HW, waves, early ? 0 : 256);   // only the tile geometry is used: nothing is counted here
     a.ws.part_max = part;
     a.ws.part_n = m.blocks[0];
     a.ws.layer = part + kAbsmaxBlocksX + kAbsmaxBlocksW;
@@ -2129,43 +2169,28 @@ daq_status quantize_forward(const daq_conv_desc& d, const float* X, int8_t* qx_n
         a.ev = early_vq(Lc, qx_cnhw);
         a.ev.once = read_once(n * 4, HW);
     }
-    if (W) {
-        PackWArgs& w = a.w;
-        if (daq_layout_qw(&d, &w.L) != DAQ_OK) return DAQ_ERR_INVALID_ARG;
-        w.w = W; w.out = qw; w.s_w = s_w; w.part = m.part[1]; w.part_n = m.blocks[1];
-        w.Cout = d.Cout; w.Cin = d.Cin; w.groups = d.groups; w.taps = taps;
-        w.cig = d.Cin / d.groups; w.cog = d.Cout / d.groups;
-        if (d.groups == 1) {
-            w.chunks = (int)ceil_div(taps, kWTaps);
-            w.ci_tiles = 2 * (int)ceil_div(d.Cin, 64);
-            const int first = std::min(taps, kWTaps), last = taps - (w.chunks - 1) * kWTaps;
-            w.div_run = make_fastdiv((uint32_t)(32 * first)); w.div_tap = make_fastdiv((uint32_t)first);
-            w.div_runl = make_fastdiv((uint32_t)(32 * last)); w.div_tapl = make_fastdiv((uint32_t)last);
-            w.blocks = 2 * (int)ceil_div(d.Cout, 64) * w.ci_tiles * w.chunks;
-        } else {
-            w.blocks = (int)ceil_div(w.L.bytes, 16 * kBlock);
-        }
-        a.w_blocks = (int)round_up(w.blocks, kXcd);
-    }
     const int64_t blocks = a.w_blocks + a.x_blocks + c_blocks;
     if (blocks >= ((int64_t)1 << 31)) return DAQ_ERR_UNSUPPORTED;
     DAQ_LAUNCH("absmax", st, hipLaunchKernelGGL(k_absmax, dim3((unsigned)(m.blocks[0] + m.blocks[1])), dim3(kBlock), 0, st, m));   // the first launch: nothing behind it fails
-#define DAQ_FWD_QUANT(E, VV, UN) DAQ_LAUNCH("quant_fwd", st, hipLaunchKernelGGL((k_fwd_quant<E, VV, UN>), dim3((unsigned)blocks), dim3(kBlock), 0, st, a))
+#define DAQ_FWD_QUANT(E, VV, UN, WV) \
+    DAQ_LAUNCH("quant_fwd", st, hipLaunchKernelGGL((k_fwd_quant<E, VV, UN, WV>), dim3((unsigned)blocks), dim3(WV * kWave), 0, st, a))
+#define DAQ_FWD_EARLY(VV, UN) do { if (waves == 8) DAQ_FWD_QUANT(true, VV, UN, 8); else DAQ_FWD_QUANT(true, VV, UN, 4); } while (0)
     const int unit = unit_kind(HW);
-    if (v == 4) { if (early) DAQ_FWD_QUANT(true, 4, kWhole); else DAQ_FWD_QUANT(false, 4, kWhole); }   // rows of whole units
+    if (v == 4) { if (early) DAQ_FWD_EARLY(4, kWhole); else DAQ_FWD_QUANT(false, 4, kWhole, 4); }   // rows of whole units
     else if (unit == kWhole) {
-        if (v == 2) { if (early) DAQ_FWD_QUANT(true, 2, kWhole); else DAQ_FWD_QUANT(false, 2, kWhole); }
-        else if (early) DAQ_FWD_QUANT(true, 1, kWhole);
-        else DAQ_FWD_QUANT(false, 0, kWhole);
+        if (v == 2) { if (early) DAQ_FWD_EARLY(2, kWhole); else DAQ_FWD_QUANT(false, 2, kWhole, 4); }
+        else if (early) DAQ_FWD_EARLY(1, kWhole);
+        else DAQ_FWD_QUANT(false, 0, kWhole, 4);
     } else if (unit == kTail) {
-        if (v == 2) { if (early) DAQ_FWD_QUANT(true, 2, kTail); else DAQ_FWD_QUANT(false, 2, kTail); }
-        else if (early) DAQ_FWD_QUANT(true, 1, kTail);
-        else DAQ_FWD_QUANT(false, 0, kTail);
+        if (v == 2) { if (early) DAQ_FWD_EARLY(2, kTail); else DAQ_FWD_QUANT(false, 2, kTail, 4); }
+        else if (early) DAQ_FWD_EARLY(1, kTail);
+        else DAQ_FWD_QUANT(false, 0, kTail, 4);
     } else {
-        if (v == 2) { if (early) DAQ_FWD_QUANT(true, 2, kElems); else DAQ_FWD_QUANT(false, 2, kElems); }
-        else if (early) DAQ_FWD_QUANT(true, 1, kElems);
-        else DAQ_FWD_QUANT(false, 0, kElems);
+        if (v == 2) { if (early) DAQ_FWD_QUANT(true, 2, kElems, 4); else DAQ_FWD_QUANT(false, 2, kElems, 4); }
+        else if (early) DAQ_FWD_QUANT(true, 1, kElems, 4);
+        else DAQ_FWD_QUANT(false, 0, kElems, 4);
     }
+#undef DAQ_FWD_EARLY
 #undef DAQ_FWD_QUANT
     return DAQ_OK;
 }

@@ -94,7 +94,7 @@ static void counting_pass() {
         for (int N : {1, 3, 16, 128, 700})
             for (int HW : {1, 2, 3, 4, 49, 143, 784, 3136, 12544, 50176}) {
                 if ((int64_t)C * N * HW >= (int64_t)1 << 29) continue;
-                for (int given : {0, 4}) {
+                for (int given : {0, 4, 8}) {
                     const CountPlan p = plan_count(C, N, HW, given);
                     const int G = (C + 15) / 16;
                     EXPECT(p.width <= p.waves && p.waves <= kCountMaxWaves && (p.blocks - 1) * p.width < G && p.blocks * p.width >= G);
@@ -106,6 +106,15 @@ static void counting_pass() {
                             EXPECT(i * p.by_groups[b] >> 16 == i / gb);
                 }
             }
+}
+
+// The forward sweep that writes both copies: records in blocks of 128 channels from 24 Mi elements on (the sizes of test_forward_wide_blocks).
+static void forward_blocks() {
+    EXPECT(forward_waves(384, 55, 71 * 70, 48) == 8 && forward_waves(384, 60, 58 * 58, 48) == 8);                       // slower in pieces of 64 bytes
+    EXPECT(forward_waves(64, 128, 112 * 112, 48) == 4 && forward_waves(256, 16, 3136, 48) == 4 && forward_waves(8192, 2048, 3, 48) == 4);
+    EXPECT(forward_waves(80, 101, 3136, 48) == 8 && forward_waves(100, 79, 57 * 57, 48) == 8 && forward_waves(129, 59, 58 * 58, 48) == 8);
+    EXPECT(forward_waves(208, 25, 71 * 70, 48) == 8 && forward_waves(400, 77, 27 * 31, 48) == 8 && forward_waves(72, 23400, 15, 48) == 8);
+    EXPECT(forward_waves(768, 37, 37 * 37, 256) == 8 && forward_waves(864, 60, 37 * 37, 512) == 4 && forward_waves(2677, 296, 36, 168) == 4);   // many workgroups for the filter
 }
 
 static daq_conv_desc layer(int n, int ci, int h, int w, int co, int k, int s) { return daq_conv_desc{n, ci, h, w, co, k, k, s, s, k / 2, k / 2, 1, 1, 1}; }
@@ -175,6 +184,7 @@ int main() {
     early_packing();
     early_copy();
     counting_pass();
+    forward_blocks();
     filter_gradient();
     products();
     std::printf("%d failures\n", fails);

@@ -123,6 +123,13 @@ def test_forward_early_copy_of_rows_off_the_units(channels, n, h, w):
         check_forward(wl.Layer("rows", n, channels, h, w, 20, k, k, 1, k // 2), 26, schedule=daq.SCHEDULE_EARLY_COPY)
 
 
+# Forward tensors that take blocks of eight groups: five and seven of them, 8 + 1, 8 + 5, 8 + 8 + 8 + 1; rows of whole units, odd and even ones
+@pytest.mark.parametrize("channels,n,h,w,k", [(80, 101, 56, 56, 1), (100, 79, 57, 57, 3), (129, 59, 58, 58, 3), (208, 25, 71, 70, 1), (400, 77, 27, 31, 3),
+                                              (72, 23400, 3, 5, 3)])
+def test_forward_wide_blocks(channels, n, h, w, k):
+    check_forward(wl.Layer("wide", n, channels, h, w, 4, k, k, 1, k // 2), wl.seed_for(27, channels))
+
+
 # Blocks of more than four groups, which tensors of that size take (widths and last blocks: counting_pass() of tests/host/dispatch.hip): a
 # whole record, 8 + 7, 8 + 5 and 8 + 8 + 1 groups, and of the large ones 7 + 6, 9 + 8, 9 + 9 + 7 and a whole record of twelve
 @pytest.mark.parametrize("channels,n,h,w,k", [
