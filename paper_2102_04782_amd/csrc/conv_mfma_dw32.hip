@@ -3,20 +3,13 @@
 //
 // Same shifted-correlation form as conv_mfma_dw.hip:
 //     acc[co][ci][kh][kw] = sum_f  G[co][f] * X[ci][f + kh*row_pitch + kw]
-// A workgroup stages, per 256-byte chunk of the flat axis, 32*WM gradient rows and 32*WN activation
-// rows (the latter 256 + 2*row_pitch + 2 bytes long: every tap's window of the chunk) with
-// coalesced loads, double buffered in LDS behind a register ring that keeps the loads of the next
-// chunks in flight.  A wave owns a 32 (co) x 32 (ci) x 9 (tap) accumulator tile (144 registers).
-// Its gradient fragment is one aligned 16-byte LDS read; for each filter row it reads the 24 bytes
-// from the dword at or below the row's first window (activation rows have a pitch of 4 * odd bytes,
-// so the 32 rows of a fragment fall into different banks, at the price of dword-aligned accesses)
-// and derives the three kw windows with v_alignbyte_b32 (shift (kh*row_pitch mod 4) + kw, a
-// compile-time constant per instantiation).  Waves either hold different tiles (WK = 1, four waves,
-// 64 x 64 per workgroup) or share one tile and take one of the eight K steps of every chunk each
-// (WK = 8: two waves per SIMD, so that one's LDS phase overlaps the other's multiplies), combined in
-// parallel through LDS at the end; the latter keeps all CUs busy on layers with few channels.  K
+// A workgroup stages, per 256-byte chunk of the flat axis, gradient rows and activation rows (the latter as
+// much longer as the last tap's window reaches), multiplies with four waves, each a 32 (co) x 32 (ci) x 9 (tap) accumulator tile (144
+// registers), and derives the windows of neighbouring columns with v_alignbyte_b32.  k_dw32_ring: the four waves share one tile and take two
+// of the eight K steps of every chunk each, combined through LDS at the end, four more waves ask for the operands (dw32_role.h); K
 // can also be split across workgroups: partial tiles are written with coalesced stores and summed
-// by k_dw_reduce.
+// by k_dw_reduce.  k_dw32, for layers with 256 and more tiles of 64 x 64: a tile for each wave, coalesced loads, double buffered in LDS behind
+// registers that keep the next chunk in flight.
 #include <algorithm>
 
 #include "daq_internal.h"
@@ -63,9 +56,14 @@ __global__ __launch_bounds__(256) void k_dw_reduce(DwTail t) {
     if (t.acc_out) t.acc_out[off] = a;
 }
 
-template <int WQ4, int WM, int WN, int WK, int PF, bool S2 = false>
-__global__ __launch_bounds__(64 * WM * WN * WK) void k_dw32(Dw32Args p) {
-    dw32_role<WQ4, WM, WN, WK, PF, S2>(p, (int)blockIdx.x);
+template <int WQ4>
+__global__ __launch_bounds__(256) void k_dw32(Dw32Args p) {
+    dw32_role<WQ4>(p, (int)blockIdx.x);
+}
+
+template <bool S2>
+__global__ __launch_bounds__(512) void k_dw32_ring(Dw32Args p) {
+    dw32_ring_role<S2>(p, (int)blockIdx.x);
 }
 
 template <int WM, int WN, int WK, int PF, int CH, bool DMA = false>
@@ -73,21 +71,21 @@ __global__ __launch_bounds__(64 * WM * WN * WK) void k_dw11(Dw32Args p) {
     dw11_role<WM, WN, WK, PF, CH, DMA>(p, (int)blockIdx.x);
 }
 
-// K splits across workgroups.  A workgroup fills a CU (its combine area, or the four stages of the direct-to-LDS form, is
-// 130 KB of LDS), so a launch of more than 256 runs in rounds, and 264 take as long as 512; a split launch is followed by
+// K splits across workgroups.  A workgroup fills a CU (its stage buffers are 100 to 150 KB of LDS), so a launch of more than 256 runs in
+// rounds, and 264 take as long as 512; a split launch is followed by
 // the reduction, which costs a launch and the partial tiles' way to memory and back.  The split that minimises
 //     rounds * (chunks of a workgroup * t_chunk + t_fixed) + (reduction, if any)
-// with times of 1.1 us per chunk for nine taps, 2 us for nine at stride 2 and 0.5 us for one, 4 us of prologue, combine and stores,
-// 3.3 us for a reduction and its launch, partial tiles at 2 TB/s: what ranks the counts measured on 450 layers best, 1.5 to 2 % from
-// the fastest on average (with 0.75, 0.75, 0.45, 5 and 3: 2.6, 6.5 and 3.2 %; 54 -> 56, stride 2 on 7 x 59, batch 11: one split
-// 15.4 us, four 11.2).  (64 -> 64, 3 x 3 x 3 on 8 x 56 x 56: 22 splits were 264 workgroups, 57 us; 21 are 252.)
-SplitModel split_model(int64_t tiles, int nchunks, double t_chunk, double tile_bytes) {
-    return SplitModel{nchunks, tiles, 4 * 256 / tiles, t_chunk, 4.0, 0.0, 3.3, (double)tiles * tile_bytes / 1e6};
-}
-
+// with 4 us of prologue, combine and stores and
+//     nine taps               0.65 us a chunk, 2.5 for a reduction and its launch, partial tiles at 0.83 TB/s there and back
+//     nine taps at stride 2   1.0, 4.5, 0.83
+//     one tap                 0.5, 3.3, 1
+// is 1.7 (2.9 with 1.1 us, 3.3 and 1 TB/s, as the kernel took before), 1.5 (4.5 with 2.0) and 2 % from the fastest of up to 20 counts on average, over 152, 65 and
+// 230 layers.  (64 -> 64, 3 x 3 x 3 on 8 x 56 x 56: 22 splits are 264 workgroups and take 1.7 times as long as 21, which are 252.)
 SplitModel split_model(const Plan32& pl, int depth) {
     const int64_t tiles = (int64_t)pl.tiles_m * pl.tiles_n * depth;
-    return pl.k11 ? split_model(tiles, pl.nchunks, 0.5, 64 * 64 * 4) : split_model(tiles, pl.nchunks, pl.s2 ? 2.0 : 1.1, 32 * 32 * kT * 4);
+    const double t_chunk = pl.k11 ? 0.5 : pl.s2 ? 1.0 : 0.65, t_reduce = pl.k11 ? 3.3 : pl.s2 ? 4.5 : 2.5;
+    const double part_us = pl.k11 ? 64 * 64 * 4 / 1e6 : 1.2 * 32 * 32 * kT * 4 / 1e6;   // of a partial tile
+    return SplitModel{pl.nchunks, tiles, 4 * 256 / tiles, t_chunk, 4.0, 0.0, t_reduce, (double)tiles * part_us};
 }
 
 // 1 x 1 filters hardly reuse an operand inside a workgroup, and with 3, 5, 6 or 7 splits every XCD reads nearly all of both (dw_block_map):
@@ -192,25 +190,26 @@ Plan32 make_plan32(const daq_conv_desc& d, int depth) {
             return pl;
         pl.s2 = true;
     }
-    // bytes of an activation row a chunk needs: its own 256 plus the largest tap offset, plus the bytes the
-    // six-dword reads of the last K step touch beyond that
-    const int need = kKC + (pl.s2 ? 1 : 2) * Lx.row_pitch + 2 + 8;
-    pl.b_units = (int)ceil_div(need, 16);
-    pl.pb = 16 * pl.b_units + 4;              // pitch/4 odd: the 32 rows of a fragment read fall into 32 different banks
+    if (Lx.row_pitch > (pl.s2 ? ring32_max_pitch<true>() : ring32_max_pitch<false>())) return pl;
     const int64_t t64 = ceil_div(d.Cout, 64) * ceil_div(d.Cin, 64);
     if (t64 >= 256 && !pl.s2) { pl.wm = 2; pl.wn = 2; pl.wk = 1; }
     else { pl.wm = 1; pl.wn = 1; pl.wk = 8; }   // eight waves: two per SIMD, so that one's LDS phase overlaps the other's MFMAs
     const int bm = 32 * pl.wm, bn = 32 * pl.wn;
-    if (pl.s2 ? 4 * bn * pl.b_units > 5 * 512 : (int64_t)bn * pl.b_units > 4 * pl.wn * 256) return pl;   // staging registers of the activation tile (B_MAX * threads)
     pl.tiles_m = (int)ceil_div(d.Cout, bm);
     pl.tiles_n = (int)ceil_div(d.Cin, bn);
     const int64_t tiles = (int64_t)pl.tiles_m * pl.tiles_n;
-    pl.splits = pl.wk == 1 ? 1 : choose_splits(pl, depth);
-    const size_t stage = (size_t)bm * kPA + (size_t)(pl.s2 ? 4 : 1) * bn * pl.pb;
-    // hand-over area of the parallel combine: [owner][source][slot][lane]
-    const int rounds = pl.wk > 4 ? 2 : 1;
-    pl.lds_bytes = std::max<size_t>(2 * stage, pl.wk > 1 ? (size_t)(pl.wk - 1) * kT * 16 * kWave * 4 / rounds : 0);
-    if (pl.lds_bytes > 150 * 1024) return pl;
+    if (pl.wk == 1) {
+        // bytes of an activation row a chunk needs: its own 256 plus the largest tap offset, plus the bytes the
+        // six-dword reads of the last K step touch beyond that
+        pl.b_units = (int)ceil_div(kKC + 2 * Lx.row_pitch + 2 + 8, 16);
+        pl.pb = 16 * pl.b_units + 4;          // pitch/4 odd: the 32 rows of a fragment read fall into 32 different banks
+        pl.splits = 1;
+        pl.lds_bytes = 2 * ((size_t)bm * kPA + (size_t)bn * pl.pb);
+    } else {
+        pl.b_units = ring32_units(pl.s2, Lx.row_pitch);
+        pl.splits = choose_splits(pl, depth);
+        pl.lds_bytes = pl.s2 ? Ring32<true>::LDS : Ring32<false>::LDS;
+    }
     pl.part_slots = tiles * pl.wm * pl.wn * kT * 16 * kWave;
     pl.splits_tail = choose_splits_tail(pl);
     choose_bands(pl, bm, bn, depth);
@@ -277,20 +276,19 @@ daq_status finish(const Plan32& pl, const DwTail& t, DwTail* defer, int depth, h
     return launch_dw_reduce(t, depth, st);
 }
 
-template <int WM, int WN, int WK, int PF, bool S2 = false>
-daq_status launch32(const Plan32& pl, const Dw32Args& a, int wq4, hipStream_t st, int depth) {
+daq_status launch32(const Plan32& pl, const Dw32Args& a, hipStream_t st, int depth) {
     const dim3 grid((unsigned)pl.blocks, (unsigned)depth);
-#define DAQ_DW32_CASE(Q)                                                                                          \
-    if (wq4 == Q) {                                                                                               \
-        auto kern = k_dw32<Q, WM, WN, WK, PF, S2>;                                                                    \
-        if (!allow_lds((const void*)kern, pl.lds_bytes))                                                 \
-            return DAQ_ERR_HIP;                                                                                   \
-        DAQ_LAUNCH("conv_bwd_filter_dw32", st, hipLaunchKernelGGL(kern, grid, dim3(64 * WM * WN * WK), pl.lds_bytes, st, a)); \
-        return DAQ_OK;                                                                                            \
+    if (pl.wk == 1) {
+        const int wq4 = a.row_pitch & 3;
+        auto kern = wq4 == 0 ? k_dw32<0> : wq4 == 1 ? k_dw32<1> : wq4 == 2 ? k_dw32<2> : k_dw32<3>;
+        if (!allow_lds((const void*)kern, pl.lds_bytes)) return DAQ_ERR_HIP;
+        DAQ_LAUNCH("conv_bwd_filter_dw32", st, hipLaunchKernelGGL(kern, grid, dim3(256), pl.lds_bytes, st, a));
+    } else {
+        auto kern = pl.s2 ? k_dw32_ring<true> : k_dw32_ring<false>;
+        if (!allow_lds((const void*)kern, pl.lds_bytes)) return DAQ_ERR_HIP;
+        DAQ_LAUNCH("conv_bwd_filter_dw32", st, hipLaunchKernelGGL(kern, grid, dim3(512), pl.lds_bytes, st, a));
     }
-    DAQ_DW32_CASE(0) DAQ_DW32_CASE(1) DAQ_DW32_CASE(2) DAQ_DW32_CASE(3)
-#undef DAQ_DW32_CASE
-    return DAQ_ERR_UNSUPPORTED;
+    return DAQ_OK;
 }
 
 }  // namespace
@@ -316,7 +314,6 @@ daq_status conv_bwd_filter_lds(const daq_conv_desc& d, const Plan32& plan, const
     daq_layout Lx, Lg;
     if (daq_layout_qx_cnhw(&d, &Lx) != DAQ_OK || daq_layout_vq(&d, &Lg) != DAQ_OK) return DAQ_ERR_INVALID_ARG;
     const Dw32Args a = fill_args(pl, d, Lx, Lg, qx, s_x, vq, s_chan, dW, acc, ws, bf16, dp);
-    const int wq4 = Lx.row_pitch & 3;
     if (pl.k11) {
         const dim3 grid((unsigned)pl.blocks, (unsigned)depth);
         if (pl.wk == 1) {
@@ -332,8 +329,7 @@ daq_status conv_bwd_filter_lds(const daq_conv_desc& d, const Plan32& plan, const
         }
         return finish(pl, tail_of(pl, a, d, depth), defer, depth, st);
     }
-    const daq_status rc = pl.s2 ? launch32<1, 1, 8, 2, true>(pl, a, wq4, st, depth)
-                          : pl.wk == 1 ? launch32<2, 2, 1, 1>(pl, a, wq4, st, depth) : launch32<1, 1, 8, 3>(pl, a, wq4, st, depth);
+    const daq_status rc = launch32(pl, a, st, depth);
     if (rc != DAQ_OK) return rc;
     return finish(pl, tail_of(pl, a, d, depth), defer, depth, st);
 }
@@ -350,12 +346,12 @@ bool bwd_filter_beside(const daq_conv_desc& d, Plan32 pl, const int8_t* qx, cons
     const bool rides = dw_tail_worthwhile((int)(pl.part_slots / kWave), pl.splits_tail);
     // Otherwise: one after the other, the product has the whole chip; beside the other work what CUs are left, but one launch less (4 ->
     // 395 on 33 x 33, 3 x 3, batch 26, 22 workgroups left: 65 us against 38).  Half the CUs and more are idle in such a launch, a chunk takes
-    // 0.6 us whatever the filter, and beginning and end are the longer ones of the two parts, 6.5 us (16 -> 16, 3 x 3 on 16 x 16, batch 4,
-    // six chunks: 10.3 us in one part, 12.7 in two and a reduction).  Over 220 small layers 0.6 % from the fastest split.
+    // 0.4 us (one tap 0.3), and beginning and end are the longer ones of the two parts, 4 us.  Over 630 small layers 0.6 % from the
+    // fastest split (with 0.6 and 6.5: 2.1 %, one tap 0.9); together 0.70 of the time apart.
     SplitModel m = split_model(pl, 1);
     const double apart = m.cost(pl.splits_tail) - (rides ? 2.8 : 0.0) + 1.5 + other_us;
-    m.t_step = 0.6;
-    m.t_fixed = 6.5;
+    m.t_step = pl.k11 ? 0.3 : 0.4;
+    m.t_fixed = 4.0;
     m.limit = std::min<int64_t>(pl.splits, max_blocks / tiles);   // (the workspace holds pl.splits partial tiles)
     m.t_floor = other_us;
     pl.splits = cheapest_split(m);
@@ -366,7 +362,7 @@ bool bwd_filter_beside(const daq_conv_desc& d, Plan32 pl, const int8_t* qx, cons
         pl.blocks = tiles * pl.splits;
     }
     out.a = fill_args(pl, d, Lx, Lg, qx, s_x, vq, s_chan, dW, acc, ws, false, nullptr);
-    out.kind = pl.k11 ? 4 : Lx.row_pitch & 3;
+    out.k11 = pl.k11;
     out.blocks = (int)pl.blocks;
     out.lds_bytes = pl.lds_bytes;
     out.tail = tail_of(pl, out.a, d, 1);

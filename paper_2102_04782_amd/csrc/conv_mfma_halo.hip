@@ -1021,13 +1021,13 @@ Geometry plan_fwd(const daq_conv_desc& d) {
 enum BothForm { kBothRing1, kBothTaps9, kBothOneChunk, kBothNarrow, kBothRing1S2, kBothNone };   // of the tile kernel
 constexpr int kBothBlocks = 256;
 
-template <int KIND, int FORM>
+template <bool K11, int FORM>
 __global__ __launch_bounds__(512, 1) void k_bwd_both(Dw32Args w, HaloArgs x, int w_blocks, int x_first) {
     const int b = (int)blockIdx.x;
     if (b < x_first) {   // uniform
         if (b >= w_blocks) return;
-        if constexpr (KIND < 4) dw32_role<KIND, 1, 1, 8, 3, false>(w, b);
-        else dw11_role<1, 1, 8, 3, 1, true>(w, b);
+        if constexpr (K11) dw11_role<1, 1, 8, 3, 1, true>(w, b);
+        else dw32_ring_role<false>(w, b);
         return;
     }
     if (threadIdx.x >= 256) return;   // (a barrier waits for the waves that are still there)
@@ -1259,16 +1259,14 @@ bool conv_bwd_both_small(const daq_conv_desc& d, const Plan32& plan_w, const int
     const size_t lds = std::max(w.lds_bytes, g.lds_bytes);
     auto run = [&]() -> daq_status {
 #define DAQ_BOTH(K, F)                                                                                                \
-    if (w.kind == K && form == F) {                                                                                  \
+    if (w.k11 == K && form == F) {                                                                                   \
         auto kern = k_bwd_both<K, F>;                                                                                \
         if (!allow_lds((const void*)kern, lds)) return DAQ_ERR_HIP;                                                  \
         DAQ_LAUNCH("conv_bwd_both", st, hipLaunchKernelGGL(kern, grid, dim3(512), lds, st, w.a, a, w.blocks, x_first)); \
         return w.tail.blocks > 0 ? launch_dw_reduce(w.tail, 1, st) : DAQ_OK;                                         \
     }
-#define DAQ_BOTH33(F) DAQ_BOTH(0, F) DAQ_BOTH(1, F) DAQ_BOTH(2, F) DAQ_BOTH(3, F)
-        DAQ_BOTH33(kBothTaps9) DAQ_BOTH33(kBothOneChunk) DAQ_BOTH33(kBothNarrow)
-        DAQ_BOTH(4, kBothRing1) DAQ_BOTH(4, kBothOneChunk) DAQ_BOTH(4, kBothNarrow) DAQ_BOTH(4, kBothRing1S2)
-#undef DAQ_BOTH33
+        DAQ_BOTH(false, kBothTaps9) DAQ_BOTH(false, kBothOneChunk) DAQ_BOTH(false, kBothNarrow)
+        DAQ_BOTH(true, kBothRing1) DAQ_BOTH(true, kBothOneChunk) DAQ_BOTH(true, kBothNarrow) DAQ_BOTH(true, kBothRing1S2)
 #undef DAQ_BOTH
         return DAQ_ERR_UNSUPPORTED;
     };

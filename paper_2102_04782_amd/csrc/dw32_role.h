@@ -17,7 +17,7 @@ struct Dw32Args {
     int64_t x_plane_pitch;   // stride 2: bytes of one stride-phase plane of an activation channel
     int Cout, Cin;
     int row_pitch;
-    int pb;               // LDS pitch of an activation row in bytes (a multiple of 4 with pb/4 odd)
+    int pb;               // LDS pitch of an activation row in bytes (a multiple of 4 with pb/4 odd; dw32_role)
     int b_units;          // 16-byte units of an activation row that are staged per chunk
     int nchunks, splits;
     int bands_m, bands_n;  // > 0: fewer than eight K splits, the tile grid is cut into bands_m x bands_n rectangles (dw_block_map)
@@ -40,7 +40,7 @@ struct Dw32Args {
 // the layer has no such form or is faster in launches of its own (false also leaves everything untouched).  tail.blocks > 0: launch_dw_reduce has to follow.
 struct DwBeside {
     Dw32Args a;
-    int kind;            // 0 .. 3: dw32_role<kind, 1, 1, 8, 3, false>; 4: dw11_role<1, 1, 8, 3, 1, true>
+    bool k11;            // dw11_role<1, 1, 8, 3, 1, true>; otherwise dw32_ring_role<false>
     int blocks;
     size_t lds_bytes;
     DwTail tail;
@@ -52,12 +52,29 @@ namespace {
 
 typedef int v4i __attribute__((ext_vector_type(4)));
 typedef int v16i __attribute__((ext_vector_type(16)));
+typedef int v2i __attribute__((ext_vector_type(2)));
 typedef int v4i_a4 __attribute__((ext_vector_type(4), aligned(4)));
 typedef int v2i_a4 __attribute__((ext_vector_type(2), aligned(4)));
 
 constexpr int kKC = 256;        // K bytes staged per chunk (8 MFMA K-steps of 32)
 constexpr int kPA = kKC + 16;   // LDS pitch of a gradient row: 16-byte aligned, rotates banks between rows
 constexpr int kT = 9;
+
+// 16 bytes of every lane, from its own address to 64 consecutive slots of LDS from `dst` on (lane l: slot l), without registers in between.
+__device__ __forceinline__ void load_to_lds(const int8_t* src, int8_t* dst) {
+    __builtin_amdgcn_global_load_lds(src, (__attribute__((address_space(3))) void*)dst, 16, 0, 0);
+}
+
+// The same with the address as a descriptor's base, a constant of the lane and a scalar: a request then takes no vector instruction, which
+// matters beside matrix instructions (a CU whose other waves multiply, 960 requests of 1 KiB: 12.9 us of the 19.2 that the multiplies take;
+// with an addition for each address none before the multiplies were through).  kNoByte: no address, the lane's slot is cleared.
+constexpr uint32_t kNoByte = 0xFFFFFFF0u;
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t tile_rsrc(const int8_t* base) {
+    return __builtin_amdgcn_make_buffer_rsrc((void*)base, 0, (int)0xFFFFFF00u, 0x00020000);
+}
+__device__ __forceinline__ void load_to_lds(__amdgpu_buffer_rsrc_t src, uint32_t lane_off, uint32_t off, int8_t* dst) {
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(src, (__attribute__((address_space(3))) void*)dst, 16, (int)lane_off, (int)off, 0, 0);
+}
 
 // The launch's share for depth tap blockIdx.y: where it reads the activation and where it leaves its results.
 __device__ __forceinline__ void dw_depth(Dw32Args& p, int taps) {
@@ -80,6 +97,16 @@ __device__ __forceinline__ void ring_round(F f) {
 
 __device__ __forceinline__ int alignbyte(int hi, int lo, int sh) {
     return (int)__builtin_amdgcn_alignbyte((unsigned)hi, (unsigned)lo, (unsigned)sh);
+}
+
+// The 16 bytes from byte S of a row of dwords on.
+template <int S, int N>
+__device__ __forceinline__ v4i window_at(const int (&d)[N]) {
+    constexpr int j = S >> 2, sh = S & 3;
+    if constexpr (sh == 0) return v4i{d[j], d[j + 1], d[j + 2], d[j + 3]};
+    else
+        return v4i{alignbyte(d[j + 1], d[j], sh), alignbyte(d[j + 2], d[j + 1], sh), alignbyte(d[j + 3], d[j + 2], sh),
+                   alignbyte(d[j + 4], d[j + 3], sh)};
 }
 
 // Workgroup b of the product -> (K split, output tile).  It runs on XCD b % 8, and what an XCD's workgroups read together is what
@@ -113,33 +140,23 @@ __device__ __forceinline__ bool dw_block_map(const Dw32Args& p, const int b, int
     return true;
 }
 
-// WQ4 = row_pitch mod 4.  WM x WN x WK = 4 or 8 waves: tiles along co, along ci, split of the K steps.
-// PF = chunks whose global loads are in flight beyond the one being written to LDS (register ring).
-//
-// S2: the same product for a 3 x 3 filter at stride 2.  The activation is stored as its four stride-phase planes
-// (row parity, column parity), each with the gradient's slot geometry, so tap (kh, kw) pairs gradient byte f with byte
-// f + (kh/2)*row_pitch + kw/2 of plane (kh%2, kw%2): still shifted correlations over the flat axis, now against four
-// staged rows per input channel (windows of 256 + row_pitch + 1 bytes).  Six 24-byte reads per K step - one per
-// (plane, row shift) - serve the nine taps.
-template <int WQ4, int WM, int WN, int WK, int PF, bool S2>
+// WQ4 = row_pitch mod 4.  Four waves, a tile each: 64 x 64 results per workgroup, for layers with enough of them to fill the chip.
+// The loads of the next chunk but one are in flight while a chunk is multiplied (register ring of one set).
+template <int WQ4>
 __device__ __forceinline__ void dw32_role(Dw32Args& p, const int bid) {
-    constexpr int WAVES = WM * WN * WK, NT = 64 * WAVES;
-    static_assert(WAVES == 4 || WAVES == 8, "four or eight waves");
-    static_assert(!S2 || (WM == 1 && WN == 1 && WK == 8), "the strided form shares one tile among eight waves");
-    constexpr int BM = 32 * WM, BN = 32 * WN;
-    constexpr int PL = S2 ? 4 : 1;                    // staged rows per input channel (stride-phase planes)
+    constexpr int WN = 2, NT = 256;
+    constexpr int BM = 64, BN = 64;
     constexpr int A_PER_T = BM * (kKC / 16) / NT;    // 16-byte units of the gradient tile per thread
     constexpr int A_BYTES = BM * kPA;
-    constexpr int B_MAX = S2 ? 5 : 4 * WN * 256 / NT;  // 16-byte units of the activation tile per thread, at most
+    constexpr int B_MAX = 4 * WN * 256 / NT;  // 16-byte units of the activation tile per thread, at most
     extern __shared__ __align__(16) int8_t lds[];
 
     dw_depth(p, kT);
     const int tid = threadIdx.x, lane = tid % kWave;
     const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
-    const int wk = wave % WK, wn = (wave / WK) % WN, wm = wave / (WK * WN);
+    const int wn = wave % WN, wm = wave / WN;
     const int l32 = lane & 31, lh = lane >> 5;
-    const int B_BYTES = PL * BN * p.pb;
-    const int STAGE = A_BYTES + B_BYTES;
+    const int STAGE = A_BYTES + BN * p.pb;
 
     int split, tile;
     if (!dw_block_map(p, bid, split, tile)) return;   // uniform
@@ -148,16 +165,7 @@ __device__ __forceinline__ void dw32_role(Dw32Args& p, const int bid) {
     const int per = p.nchunks / p.splits, rem = p.nchunks % p.splits;
     const int c_begin = split * per + min(split, rem);
     const int c_end = c_begin + per + (split < rem ? 1 : 0);
-
-    // a complete tile is de-quantized here: its scales are requested now, long before they are needed
-    float sx = 0.0f, sc_row[4] = {0.0f, 0.0f, 0.0f, 0.0f};
-    if (p.splits == 1) {   // uniform
-        sx = *p.s_x / 127.0f;
-        if constexpr (WK > 1) {
-#pragma unroll
-            for (int i = 0; i < 4; ++i) sc_row[i] = p.s_chan[min(co0 + wave + WAVES * i, p.Cout - 1)];   // the rows this wave stores
-        }
-    }
+    const float sx = *p.s_x / 127.0f;
 
     // ---- staging assignment ----
     // gradient: unit u = tid + 256*i -> row u / 16, 16-byte column u % 16
@@ -174,37 +182,37 @@ __device__ __forceinline__ void dw32_role(Dw32Args& p, const int bid) {
     // activation: unit u = tid + 256*i of the BN x b_units tile (row-major): consecutive lanes, consecutive 16 bytes
     uint32_t b_src[B_MAX];
     int b_dst[B_MAX];
-    const int b_total = PL * BN * p.b_units;
+    const int b_total = BN * p.b_units;
 #pragma unroll
     for (int i = 0; i < B_MAX; ++i) {
         const int u = tid + NT * i;
         const int uc = u < b_total ? u : 0;
-        const int row = uc / p.b_units, col = uc - row * p.b_units;   // staged row = plane * BN + channel of the tile
-        const int ci = ci0 + row % BN;
-        b_src[i] = (uint32_t)((int64_t)(ci < p.Cin ? ci : 0) * p.x_chan_pitch + (int64_t)(row / BN) * p.x_plane_pitch + 16 * col);
+        const int row = uc / p.b_units, col = uc - row * p.b_units;
+        const int ci = ci0 + row;
+        b_src[i] = (uint32_t)((int64_t)(ci < p.Cin ? ci : 0) * p.x_chan_pitch + 16 * col);
         b_dst[i] = u < b_total ? A_BYTES + row * p.pb + 16 * col : -1;
     }
     // Every call issues the same loads (past the end the last chunk is fetched again, which the caches absorb):
     // only then can the compiler count the loads in flight and wait for exactly the oldest set.
-    v4i ra[PF][A_PER_T], rb[PF][B_MAX];
+    v4i ra[A_PER_T], rb[B_MAX];
     const int c_last = max(c_end - 1, 0);
-    auto load_chunk = [&](int chunk, int set) {
+    auto load_chunk = [&](int chunk) {
         const int64_t k0 = (int64_t)min(chunk, c_last) * kKC;
         const int8_t* gk = p.g + k0;
         const int8_t* xk = p.x + k0;
 #pragma unroll
-        for (int i = 0; i < A_PER_T; ++i) ra[set][i] = *reinterpret_cast<const v4i*>(gk + a_src[i]);
+        for (int i = 0; i < A_PER_T; ++i) ra[i] = *reinterpret_cast<const v4i*>(gk + a_src[i]);
 #pragma unroll
-        for (int i = 0; i < B_MAX; ++i) rb[set][i] = *reinterpret_cast<const v4i*>(xk + b_src[i]);
+        for (int i = 0; i < B_MAX; ++i) rb[i] = *reinterpret_cast<const v4i*>(xk + b_src[i]);
         __builtin_amdgcn_sched_barrier(0);   // keep the sets in program order
     };
-    auto store_chunk = [&](int buf, int set) {
+    auto store_chunk = [&](int buf) {
         int8_t* base = lds + buf * STAGE;
 #pragma unroll
-        for (int i = 0; i < A_PER_T; ++i) *reinterpret_cast<v4i*>(base + a_dst[i]) = ra[set][i];
+        for (int i = 0; i < A_PER_T; ++i) *reinterpret_cast<v4i*>(base + a_dst[i]) = ra[i];
 #pragma unroll
         for (int i = 0; i < B_MAX; ++i)
-            if (b_dst[i] >= 0) *reinterpret_cast<v4i_a4*>(base + b_dst[i]) = rb[set][i];   // rows are only dword aligned
+            if (b_dst[i] >= 0) *reinterpret_cast<v4i_a4*>(base + b_dst[i]) = rb[i];   // rows are only dword aligned
     };
 
     v16i acc[kT];
@@ -213,190 +221,52 @@ __device__ __forceinline__ void dw32_role(Dw32Args& p, const int bid) {
 #pragma unroll
         for (int r = 0; r < 16; ++r) acc[t][r] = 0;
 
-    // chunk c_begin goes to LDS; chunks c_begin+1 .. c_begin+PF stay in flight in ring sets 1 .. PF-1, 0
-    load_chunk(c_begin, 0);
-    store_chunk(0, 0);
-#pragma unroll
-    for (int i = 1; i <= PF; ++i) load_chunk(c_begin + i, i % PF);
+    load_chunk(c_begin);
+    store_chunk(0);
+    load_chunk(c_begin + 1);
     __syncthreads();
 
     const int arow = (wm * 32 + l32) * kPA + 16 * lh;
     const int brow = A_BYTES + (wn * 32 + l32) * p.pb + 16 * lh;
-    auto step = [&](int chunk, auto ring_step) {
-        constexpr int u = ring_step;   // position in the ring: a constant, so that the sets stay in registers
+    for (int chunk = c_begin; chunk < c_end; ++chunk) {
         const int buf = (chunk - c_begin) & 1;
         const int8_t* A = lds + buf * STAGE + arow;
         const int8_t* B = lds + buf * STAGE + brow;
         // All LDS reads of this wave's K steps are issued before the first multiply: with one wave per SIMD nothing
         // else hides their latency.
-        constexpr int KS = (kKC / 32) / WK;
-        if constexpr (S2) {
-#pragma unroll
-            for (int i = 0; i < KS; ++i) {
-                const int ks = wk + i * WK;
-                const v4i fa = *reinterpret_cast<const v4i*>(A + 32 * ks);
-#pragma unroll
-                for (int pl = 0; pl < 4; ++pl) {
-                    const int ph_h = pl >> 1, ph_w = pl & 1;
-#pragma unroll
-                    for (int rs = 0; rs < 2; ++rs) {
-                        if (rs == 1 && ph_h == 1) continue;   // kh = 1 is the only tap row on the odd row planes
-                        const int kh = ph_h + 2 * rs;
-                        // 24 bytes from the dword at or below the first window of this (plane, row shift)
-                        const int8_t* src = B + pl * (BN * p.pb) + 32 * ks + ((rs * p.row_pitch) & ~3);
-                        const v4i_a4 lo = *reinterpret_cast<const v4i_a4*>(src);
-                        const v2i_a4 hi = *reinterpret_cast<const v2i_a4*>(src + 16);
-                        const int d[6] = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1]};
-#pragma unroll
-                        for (int cs = 0; cs < 2; ++cs) {
-                            if (cs == 1 && ph_w == 1) continue;
-                            const int kw = ph_w + 2 * cs;
-                            const int sft = (rs ? WQ4 : 0) + cs, j = sft >> 2, sh = sft & 3;
-                            v4i bf;
-                            if (sh == 0)
-                                bf = v4i{d[j], d[j + 1], d[j + 2], d[j + 3]};
-                            else
-                                bf = v4i{alignbyte(d[j + 1], d[j], sh), alignbyte(d[j + 2], d[j + 1], sh),
-                                         alignbyte(d[j + 3], d[j + 2], sh), alignbyte(d[j + 4], d[j + 3], sh)};
-                            acc[kh * 3 + kw] = __builtin_amdgcn_mfma_i32_32x32x32_i8(fa, bf, acc[kh * 3 + kw], 0, 0, 0);
-                        }
-                    }
-                }
-            }
-        } else {
+        constexpr int KS = kKC / 32;
         v4i fa[KS];
         int fd[KS][3][6];
 #pragma unroll
-        for (int i = 0; i < KS; ++i) {
-            const int ks = wk + i * WK;
-            fa[i] = *reinterpret_cast<const v4i*>(A + 32 * ks);
+        for (int ks = 0; ks < KS; ++ks) {
+            fa[ks] = *reinterpret_cast<const v4i*>(A + 32 * ks);
 #pragma unroll
             for (int kh = 0; kh < 3; ++kh) {
                 // 24 bytes from the dword at or below this filter row's first window
                 const int8_t* src = B + 32 * ks + ((kh * p.row_pitch) & ~3);
                 const v4i_a4 lo = *reinterpret_cast<const v4i_a4*>(src);
                 const v2i_a4 hi = *reinterpret_cast<const v2i_a4*>(src + 16);
-                fd[i][kh][0] = lo[0]; fd[i][kh][1] = lo[1]; fd[i][kh][2] = lo[2]; fd[i][kh][3] = lo[3];
-                fd[i][kh][4] = hi[0]; fd[i][kh][5] = hi[1];
+                fd[ks][kh][0] = lo[0]; fd[ks][kh][1] = lo[1]; fd[ks][kh][2] = lo[2]; fd[ks][kh][3] = lo[3];
+                fd[ks][kh][4] = hi[0]; fd[ks][kh][5] = hi[1];
             }
         }
         __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-        for (int i = 0; i < KS; ++i) {
-#pragma unroll
-            for (int kh = 0; kh < 3; ++kh) {
-                const int r0 = (kh * WQ4) & 3;
-                const int* d = fd[i][kh];
-#pragma unroll
-                for (int kw = 0; kw < 3; ++kw) {
-                    const int s = r0 + kw, j = s >> 2, sh = s & 3;
-                    v4i bf;
-                    if (sh == 0)
-                        bf = v4i{d[j], d[j + 1], d[j + 2], d[j + 3]};
-                    else
-                        bf = v4i{alignbyte(d[j + 1], d[j], sh), alignbyte(d[j + 2], d[j + 1], sh),
-                                 alignbyte(d[j + 3], d[j + 2], sh), alignbyte(d[j + 4], d[j + 3], sh)};
-                    acc[kh * 3 + kw] = __builtin_amdgcn_mfma_i32_32x32x32_i8(fa[i], bf, acc[kh * 3 + kw], 0, 0, 0);
-                }
-            }
-        }
-        }
-        // chunk+1 sits in ring set (u+1) % PF: it goes to the other LDS buffer and the set is refilled PF chunks ahead
-        store_chunk(buf ^ 1, (u + 1) % PF);
-        load_chunk(chunk + 1 + PF, (u + 1) % PF);
+        ring_round<KS>([&](auto ks) {
+            ring_round<3>([&](auto kh) {
+                ring_round<3>([&](auto kw) {
+                    constexpr int s = ((decltype(kh)::value * WQ4) & 3) + decltype(kw)::value;
+                    acc[kh * 3 + kw] =
+                        __builtin_amdgcn_mfma_i32_32x32x32_i8(fa[ks], window_at<s>(fd[ks][kh]), acc[kh * 3 + kw], 0, 0, 0);
+                });
+            });
+        });
+        // chunk+1 goes to the other LDS buffer, chunk+2 on its way
+        store_chunk(buf ^ 1);
+        load_chunk(chunk + 2);
         __syncthreads();
-    };
-    // Whole rounds of the ring first, without an exit in between: at the head of a loop that can be left and entered
-    // half-way round, the compiler no longer knows which loads are the oldest and waits for all of them (measured on this
-    // one: every third chunk waited for a load issued right before it).
-    int chunk = c_begin;
-    for (; chunk + PF <= c_end; chunk += PF) ring_round<PF>([&](auto u) { step(chunk + (int)u, u); });
-    ring_round<PF - 1>([&](auto u) { if (chunk + (int)u < c_end) step(chunk + (int)u, u); });
-
-    // register r of a 32 x 32 tile: row (co) 8*(r/4) + 4*lh + r%4, column (ci) l32; slot = tap*16 + r
-    constexpr int SLOTS = kT * 16;
-    if constexpr (WK > 1) {
-        // ---- combine the eight waves that share a tile, in parallel: every wave owns a share of the slots, hands the
-        // other owners theirs through LDS and keeps its own.  The unit of exchange is a quad of slots (the four
-        // consecutive registers 4g .. 4g+3 of a tap: one 16-byte LDS access per lane instead of four 4-byte ones);
-        // the hand-over area [quad][source wave][lane] for all 36 quads would not fit, so there are two rounds of 18
-        // quads, of which waves 0 and 1 own three each and waves 2 .. 7 two each. ----
-        static_assert(WK == 8, "the combine below is laid out for eight waves");
-        constexpr int QR = SLOTS / 4 / 2;       // quads per round
-        auto owner_of = [](int j) { return j < 3 ? 0 : j < 6 ? 1 : 2 + (j - 6) / 2; };   // j: quad inside its round
-        auto index_of = [](int j) { return j < 6 ? j % 3 : (j - 6) % 2; };               // position among its owner's quads
-        v4i* red4 = reinterpret_cast<v4i*>(lds);
-        int* red = reinterpret_cast<int*>(lds);
-        int32_t* dst = p.part + ((int64_t)tile * p.splits + split) * SLOTS * kWave + lane;
-        v4i own[2 * 3];
-#pragma unroll
-        for (int rd = 0; rd < 2; ++rd) {
-            __syncthreads();   // the staging buffers (or the previous round) are dead from here on
-#pragma unroll
-            for (int j = 0; j < QR; ++j) {
-                const int owner = owner_of(j);
-                if (owner != wk) {   // uniform
-                    const int Q = rd * QR + j, t = Q / 4, g4 = 4 * (Q % 4);
-                    const int srcw = wk < owner ? wk : wk - 1;
-                    red4[(j * (WK - 1) + srcw) * kWave + lane] = v4i{acc[t][g4], acc[t][g4 + 1], acc[t][g4 + 2], acc[t][g4 + 3]};
-                }
-            }
-            __syncthreads();
-#pragma unroll
-            for (int j = 0; j < QR; ++j) {
-                if (owner_of(j) != wk) continue;   // uniform
-                const int Q = rd * QR + j, t = Q / 4, g4 = 4 * (Q % 4);
-                v4i v = {acc[t][g4], acc[t][g4 + 1], acc[t][g4 + 2], acc[t][g4 + 3]};
-#pragma unroll
-                for (int w = 0; w < WK - 1; ++w) v += red4[(j * (WK - 1) + w) * kWave + lane];
-                own[rd * 3 + index_of(j)] = v;
-                if (p.splits > 1) {
-#pragma unroll
-                    for (int e = 0; e < 4; ++e)   // read next by other CUs, not by this one: streaming stores
-                        __builtin_nontemporal_store(v[e], &dst[(4 * Q + e) * kWave]);
-                }
-            }
-        }
-        if (p.splits > 1) return;
-        // Complete tile: dW[co][ci][t] has the 32 ci x 9 taps of one co contiguous (1152 bytes), but a lane holds one
-        // ci and a register one (co, t).  The tile is transposed through LDS so that the global stores are row runs.
-        __syncthreads();   // everyone is done reading the hand-over area
-        constexpr int ROWW = 32 * kT + 1;   // ints per co row in LDS (+1: lanes of a column hit different banks)
-#pragma unroll
-        for (int Q = 0; Q < SLOTS / 4; ++Q) {
-            if (owner_of(Q % QR) != wk) continue;   // uniform
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                const int t = Q / 4, r = 4 * (Q % 4) + e;
-                red[(8 * (r >> 2) + 4 * lh + (r & 3)) * ROWW + l32 * kT + t] = own[(Q / QR) * 3 + index_of(Q % QR)][e];
-            }
-        }
-        __syncthreads();
-        const int ncol = min(32, p.Cin - ci0) * kT;   // valid ints of a row
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const int row = wave + WAVES * i, co = co0 + row;
-            if (co >= p.Cout) break;
-            const float sc = sx * (sc_row[i] / 127.0f);
-            const int64_t off = ((int64_t)co * p.Cin + ci0) * p.taps_all;
-            for (int j = lane; j < ncol; j += kWave) {
-                const int v = red[row * ROWW + j];
-                const int64_t at = off + (p.taps_all == kT ? j : (j / kT) * p.taps_all + j % kT);   // (a depth tap's nine results, then the next ci's)
-                store_result(p.dW, at, (float)v * sc, p.bf16);
-                if (p.acc_out) p.acc_out[at] = v;
-            }
-        }
-        return;
     }
 
-    if (p.splits > 1) {
-        int32_t* dst = p.part + (((int64_t)tile * p.splits + split) * (WM * WN) + wm * WN + wn) * SLOTS * kWave + lane;
-#pragma unroll
-        for (int t = 0; t < kT; ++t)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) dst[(t * 16 + r) * kWave] = acc[t][r];
-        return;
-    }
+    // register r of a 32 x 32 tile: row (co) 8*(r/4) + 4*lh + r%4, column (ci) l32
     const int ci = ci0 + wn * 32 + l32;
     if (ci >= p.Cin) return;
 #pragma unroll
@@ -411,6 +281,336 @@ __device__ __forceinline__ void dw32_role(Dw32Args& p, const int bid) {
                 if (p.acc_out) p.acc_out[off + t] = acc[t][r];
             }
         }
+    }
+}
+
+// One 32 x 32 x 9 tile to a workgroup.  Waves 0 to 3, one to a SIMD, take two of the eight K steps of every chunk each (combined through LDS
+// at the end); waves 4 to 7 ask for the operands, which go from global memory straight into LDS: D stage buffers, one barrier per chunk.
+//
+// S2: the same product for a 3 x 3 filter at stride 2.  The activation is stored as its four stride-phase planes
+// (row parity, column parity), each with the gradient's slot geometry, so tap (kh, kw) pairs gradient byte f with byte
+// f + (kh/2)*row_pitch + kw/2 of plane (kh%2, kw%2): still shifted correlations over the flat axis, now against four
+// staged rows per input channel.  Six windows per K step - one per (plane, row shift) - serve the nine taps.
+//
+// What bounds it: 18 multiplies a wave and chunk, 576 cycles, of which a chunk takes about 790, the rest being what reads of LDS
+// (fourteen a wave) cost a wave that multiplies, the barrier and the loop.  128 x 512 -> 512 at 7 x 7, 33 chunks on 256 workgroups: 1.6 us to the first
+// operands, 15 for the chunks at the 1.75 GHz that the chip holds under this load, 2 to combine and 1 to store, 19.6 us in the kernel (1.13 times the
+// speed over 109 drawn layers, 1.11 at stride 2) where eight waves with a K step each took 1 us more, 17.6, 3 and 2.4.
+//   Vector instructions of a wave wait behind the matrix instructions of another on its SIMD, and a request behind the
+//   addition for its address: asked for by multiplying waves, or with vector addresses, requests and multiplies took turns (910 to 1020 cycles a chunk; the requests
+//   alone 380).  Hence waves that only ask, with scalar addresses and the higher priority, and one multiplying wave to a SIMD.
+//   The columns of a filter row differ by a byte in f, and it is the gradient that is shifted by it (G[f - kw] X[f + kh row_pitch] instead of
+//   G[f] X[f + kh row_pitch + kw]): two shifted fragments serve all rows, 47 instead of 71 vector instructions a chunk.
+//
+// Only aligned 16-byte reads are fast (the reads of a chunk by eight waves: 145 ns in dwords, 110 to 130 in aligned pieces, 300 to 1300
+// in unaligned ones), so a window is the one or two pieces it lies in, and its place in them, Q = row shift mod 16, is a constant of the
+// loop: sixteen of them, chosen once.  Slot column c of row r holds the row's piece c ^ (r % 16) (the four last columns of the strided
+// form's rows of twenty c ^ (r % 4)), so that the lanes of a read fall into different banks.
+template <bool S2>
+struct Ring32 {
+    static constexpr int PL = S2 ? 4 : 1;              // staged rows per input channel
+    static constexpr int UP = S2 ? 20 : 32;            // 16-byte slots of a staged activation row
+    static constexpr int D = S2 ? 3 : 6;               // stage buffers
+    static constexpr int NEXT = S2 ? D : D - 1;        // chunks asked for ahead of the present one
+    // requests of an asking wave for a chunk: of the gradient's pieces, of the activation's, and one (eight lanes) of the gradient's before
+    static constexpr int AREQ = 2, XREQ = PL * 32 * UP / 256, REQ = AREQ + XREQ + 1;
+    static constexpr int BEFORE = 32 * kKC, A_BYTES = BEFORE + 32 * 16, ROW = 16 * UP, STAGE = A_BYTES + PL * 32 * ROW;
+    static constexpr int LDS = D * STAGE;
+    __host__ __device__ static constexpr int slot_of(int col, int row) {
+        return S2 && col >= 16 ? 16 + ((col - 16) ^ (row & 3)) : (col & 16) | ((col & 15) ^ (row & 15));
+    }
+    // Windows of a K step: shift in rows, staged plane; first tap, the step to the next one, which takes the gradient a byte later, and how many.
+    //   unit stride: a filter row each; stride 2: planes (even, even), both shifts, (even, odd), both, (odd, even), (odd, odd)
+    static constexpr int WINDOWS = S2 ? 6 : 3;
+    struct Window { int shift, plane, tap, step, taps; };
+    __host__ __device__ static constexpr Window window(int w) {
+        constexpr Window unit[3] = {{0, 0, 0, 1, 3}, {1, 0, 3, 1, 3}, {2, 0, 6, 1, 3}};
+        constexpr Window strided[6] = {{0, 0, 0, 2, 2}, {1, 0, 6, 2, 2}, {0, 1, 1, 2, 1}, {1, 1, 7, 2, 1}, {0, 2, 3, 2, 2}, {0, 3, 4, 2, 1}};
+        return S2 ? strided[w] : unit[w % 3];
+    }
+    __host__ __device__ static constexpr int window_of(int m) { int w = 0; while (m >= window(w).taps) m -= window(w++).taps; return w; }   // of multiply m
+    __host__ __device__ static constexpr int column_of(int m) { int w = 0; while (m >= window(w).taps) m -= window(w++).taps; return m; }
+};
+// Row pitches it serves (the last window of a chunk ends with slot column UP - 1), and the slots of a row that are filled.
+template <bool S2>
+constexpr int ring32_max_pitch() { return S2 ? 54 : 123; }
+inline int ring32_units(bool s2, int row_pitch) { return 16 + (s2 ? row_pitch : 2 * row_pitch) / 16 + 1; }
+
+// Dwords FROM .. FROM + COUNT - 1 of the piece at `at` into the same places of d (three of them with the fourth).
+template <int FROM, int COUNT>
+__device__ __forceinline__ void read_piece(const int8_t* at, int* d) {
+    static_assert(FROM + COUNT == 4 || FROM == 0, "the end or the beginning of a piece");
+    if constexpr (COUNT == 1) {
+        d[FROM] = *reinterpret_cast<const int*>(at + 4 * FROM);
+    } else if constexpr (COUNT == 2) {
+        const v2i v = *reinterpret_cast<const v2i*>(at + 4 * FROM);
+        d[FROM] = v[0]; d[FROM + 1] = v[1];
+    } else {
+        const v4i v = *reinterpret_cast<const v4i*>(at);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) d[i] = v[i];
+    }
+}
+// Piece K of the one or two that bytes Q .. Q + 15 lie in, dword by dword.
+template <int Q, int K>
+__device__ __forceinline__ void read_window(const int8_t* at, int (&d)[8]) {
+    constexpr int first = Q / 4, last = (Q + 15) / 4;
+    if constexpr (K == 0) read_piece<first, 4 - first>(at, d);
+    else if constexpr (last >= 4) read_piece<0, last - 3>(at, d + 4);
+}
+// The window itself.  The fourth dword of a piece of which three are used counts as used here as well (otherwise its register is given to
+// a later read of the same batch, which then waits for the whole batch before it), and whole dwords of two pieces are put together here
+// (left to itself the compiler copies them where they are read, and waits there).
+template <int Q>
+__device__ __forceinline__ v4i window(const int (&d)[8]) {
+    if constexpr (Q / 4 == 1) asm volatile("" ::"v"(d[0]));
+    if constexpr ((Q + 15) / 4 == 6) asm volatile("" ::"v"(d[7]));
+    v4i x = window_at<Q>(d);
+    if constexpr (Q % 4 == 0 && Q != 0) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) asm volatile("v_mov_b32 %0, %1" : "=v"(x[e]) : "v"(d[Q / 4 + e]));
+    }
+    return x;
+}
+
+// The K loop of a multiplying wave over n chunks.
+template <bool S2, int Q>
+__device__ __forceinline__ void ring32_loop(const int n, const int kq, const int l32, const int lh, const int row_pitch, v16i (&acc)[kT]) {
+    using R = Ring32<S2>;
+    extern __shared__ __align__(16) int8_t lds[];
+    int at_g[2], at_before[2], at_x[2][3][2];   // by K step; by row shift and piece
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+        const int u = 2 * (kq + 4 * i) + lh;
+        at_g[i] = l32 * kKC + 16 * (u ^ (l32 & 15));
+        at_before[i] = (u == 0 ? R::BEFORE + 16 * l32 : l32 * kKC + 16 * ((u - 1) ^ (l32 & 15))) + 12;
+#pragma unroll
+        for (int s = 0; s < 3; ++s)
+#pragma unroll
+            for (int k = 0; k < 2; ++k) at_x[i][s][k] = R::A_BYTES + l32 * R::ROW + 16 * R::slot_of(u + k + s * row_pitch / 16, l32);
+    }
+    struct Raw {
+        int before;   // the four bytes before g
+        v4i g;
+        int x[R::WINDOWS][8];
+    };
+    // read k of K step I: the gradient, then the windows, two pieces each at most
+    constexpr int READS = 2 + 2 * R::WINDOWS;
+    auto read = [&](Raw& r, const int8_t* S, auto I, auto k) {
+        if constexpr (k == 0) r.g = *reinterpret_cast<const v4i*>(S + at_g[I]);
+        else if constexpr (k == 1) r.before = *reinterpret_cast<const int*>(S + at_before[I]);
+        else {
+            constexpr int w = (k - 2) / 2;
+            constexpr auto win = R::window(w);
+            read_window<win.shift * Q % 16, k % 2>(S + win.plane * 32 * R::ROW + at_x[I][win.shift][k % 2], r.x[w]);
+        }
+    };
+    v4i g[3], x;   // the gradient's bytes, and those one and two before; the window
+    auto mul = [&](const Raw& r, auto m) {
+        constexpr int w = R::window_of(m), c = R::column_of(m);
+        constexpr auto win = R::window(w);
+        if constexpr (m == 0) g[0] = r.g;
+        if constexpr (w == 0 && c > 0) {
+            const int d[5] = {r.before, r.g[0], r.g[1], r.g[2], r.g[3]};
+            g[c] = window_at<4 - c>(d);
+        }
+        if constexpr (c == 0) x = window<win.shift * Q % 16>(r.x[w]);
+        acc[win.tap + c * win.step] = __builtin_amdgcn_mfma_i32_32x32x32_i8(g[c], x, acc[win.tap + c * win.step], 0, 0, 0);
+    };
+    // Multiplies the K step in `now` and reads step I of the chunk at S into `next`, the reads one by one between the multiplies: in a
+    // row they wait for one another, and the multiplies behind them with them.
+    auto half = [&](const Raw& now, Raw& next, const int8_t* S, auto I) {
+        ring_round<kT>([&](auto m) {
+            __builtin_amdgcn_sched_barrier(0);
+            mul(now, m);
+            ring_round<READS>([&](auto k) {
+                if constexpr (k * (kT - 1) / READS == m) read(next, S, I, k);
+            });
+        });
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    constexpr std::integral_constant<int, 0> first;
+    constexpr std::integral_constant<int, 1> second;
+
+    Raw r0, r1;
+    __builtin_amdgcn_s_barrier();           // chunk 0 has landed
+    ring_round<READS>([&](auto k) { read(r0, lds, first, k); });
+    for (int i = 0, buf = 0; i < n; ++i) {
+        half(r0, r1, lds + buf * R::STAGE, second);
+        if constexpr (S2) asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // chunk i is read out, its place is the next to be taken
+        __builtin_amdgcn_s_barrier();       // chunk i + 1 has landed
+        buf = buf + 1 == R::D ? 0 : buf + 1;
+        half(r1, r0, lds + buf * R::STAGE, first);
+    }
+}
+
+template <bool S2>
+__device__ __forceinline__ void dw32_ring_role(Dw32Args& p, const int bid) {
+    using R = Ring32<S2>;
+    extern __shared__ __align__(16) int8_t lds[];
+    __shared__ float l_scale[32];
+
+    dw_depth(p, kT);
+    const int tid = threadIdx.x, lane = tid % kWave;
+    const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
+    const int l32 = lane & 31, lh = lane >> 5;
+
+    int split, tile;
+    if (!dw_block_map(p, bid, split, tile)) return;   // uniform
+    const int tn = tile % p.tiles_n, tm = tile / p.tiles_n;
+    const int co0 = tm * 32, ci0 = tn * 32;
+    const int per = p.nchunks / p.splits, rem = p.nchunks % p.splits;
+    const int c_begin = split * per + min(split, rem);
+    const int n = per + (split < rem ? 1 : 0);
+
+    v16i acc[kT];
+    if (wave >= 4) {   // uniform: asks
+        __builtin_amdgcn_s_setprio(3);
+        // piece by piece of the stacked slots, the gradient's [32][16] and the activation's [32 * PL][UP], 64 at a time
+        const __amdgpu_buffer_rsrc_t rs_g = tile_rsrc(p.g + (int64_t)co0 * p.klen), rs_x = tile_rsrc(p.x + (int64_t)ci0 * p.x_chan_pitch);
+        uint32_t from[R::REQ];
+#pragma unroll
+        for (int j = 0; j < R::REQ; ++j) {
+            const int u = (j * 4 + wave - 4) * 64 + lane;
+            if (j == R::REQ - 1) {   // the pieces before the chunk
+                const int row = 8 * (wave - 4) + lane;
+                from[j] = (uint32_t)((int64_t)(co0 + row < p.Cout ? row : 0) * p.klen);   // (of the first eight lanes)
+            } else if (j < R::AREQ) {   // rows past Cout / Cin recompute the first one and are never stored
+                const int row = u >> 4;
+                from[j] = (uint32_t)((int64_t)(co0 + row < p.Cout ? row : 0) * p.klen + 16 * ((u & 15) ^ (row & 15)));
+            } else {
+                const int row = (u - 512) / R::UP, slot = (u - 512) - row * R::UP;   // staged row = plane * 32 + channel of the tile
+                const int col = R::slot_of(slot, row), ci = row % 32;                // (its own inverse)
+                from[j] = (uint32_t)((int64_t)(ci0 + ci < p.Cin ? ci : 0) * p.x_chan_pitch + (int64_t)(row / 32) * p.x_plane_pitch + 16 * col);
+                if (col >= p.b_units) from[j] = kNoByte;
+            }
+        }
+        // a chunk is REQ requests a wave (past the end the last chunk again, into a buffer nobody reads), so that the
+        // count of outstanding requests in the waits is a constant
+        auto ask = [&](int i, int buf) {
+            const uint32_t k0 = (uint32_t)(c_begin + min(i, n - 1)) * (uint32_t)kKC;
+            int8_t* const stage = lds + buf * R::STAGE;
+            ring_round<R::AREQ>([&](auto j) { load_to_lds(rs_g, from[j], k0, stage + 1024 * (j * 4 + wave - 4)); });
+            // (a plane begins with zeros: they stand for what is before its first byte)
+            if (lane < 8) load_to_lds(rs_g, from[R::REQ - 1], k0 == 0 ? 0u : k0 - 16u, stage + R::BEFORE + 128 * (wave - 4));
+            ring_round<R::XREQ>([&](auto j) {
+                load_to_lds(rs_x, from[R::AREQ + j], k0, stage + R::A_BYTES + 1024 * (j * 4 + wave - 4));
+            });
+        };
+        ask(0, 0);
+        ask(1, 1);
+        asm volatile("s_waitcnt vmcnt(%0)" ::"n"(R::REQ) : "memory");   // chunk 0 has landed
+        __builtin_amdgcn_s_barrier();   // (the plain barrier: __syncthreads would wait for all requests)
+        for (int s = 2; s < R::NEXT; ++s) ask(s, s);
+        for (int i = 0, buf = 0; i < n; ++i) {
+            asm volatile("s_waitcnt vmcnt(%0)" ::"n"((R::NEXT - 2) * R::REQ) : "memory");   // chunk i + 1 has landed
+            __builtin_amdgcn_s_barrier();
+            ask(i + R::NEXT, S2 ? buf : buf == 0 ? R::D - 1 : buf - 1);   // where chunk i was (S2), or the one before it, which is multiplied
+            buf = buf + 1 == R::D ? 0 : buf + 1;
+        }
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // the requests past the end have landed before LDS is put to other use
+        __builtin_amdgcn_s_setprio(0);
+    } else {
+#pragma unroll
+        for (int t = 0; t < kT; ++t)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) acc[t][r] = 0;
+        switch (p.row_pitch & 15) {   // uniform
+#define DAQ_RING32(Q) case Q: ring32_loop<S2, Q>(n, wave, l32, lh, p.row_pitch, acc); break;
+            DAQ_RING32(0) DAQ_RING32(1) DAQ_RING32(2) DAQ_RING32(3) DAQ_RING32(4) DAQ_RING32(5) DAQ_RING32(6) DAQ_RING32(7)
+            DAQ_RING32(8) DAQ_RING32(9) DAQ_RING32(10) DAQ_RING32(11) DAQ_RING32(12) DAQ_RING32(13) DAQ_RING32(14) DAQ_RING32(15)
+#undef DAQ_RING32
+        }
+    }
+
+    // ---- combine the four multiplying waves.  Of the 36 quads of slots (four consecutive registers of a tap: one 16-byte LDS access a
+    // lane) a pair of waves w, w + 4 owns nine: wave w sums five, three hand-overs and its own part, wave w + 4 four, all handed over;
+    // area [owner][quad][source][lane] ----
+    // register r of a 32 x 32 tile: row (co) 8*(r/4) + 4*lh + r%4, column (ci) l32; slot = tap*16 + r
+    // A complete tile: dW[co][ci][t] has the 32 ci x 9 taps of one co contiguous (1152 bytes), but a lane holds one
+    // ci and a register one (co, t).  The tile is transposed through LDS so that the global stores are row runs.
+    constexpr int SLOTS = kT * 16, OWN = kT, FIRST = 5, PAIR = 3 * FIRST + 4 * (OWN - FIRST);   // quads of a pair, of its first wave; entries
+    constexpr int COLS = 32 * kT, ROWW = COLS + 4;   // ints per co row in LDS
+    static_assert(4 * PAIR * 1024 <= R::LDS && 32 * ROWW * 4 <= R::LDS, "fits");
+    v4i* area = reinterpret_cast<v4i*>(lds);
+    int* red = reinterpret_cast<int*>(lds);
+    int32_t* dst = p.part + ((int64_t)tile * p.splits + split) * SLOTS * kWave + lane;
+    auto quad = [&](int q) { return v4i{acc[q / 4][4 * (q % 4)], acc[q / 4][4 * (q % 4) + 1], acc[q / 4][4 * (q % 4) + 2], acc[q / 4][4 * (q % 4) + 3]}; };
+    __syncthreads();   // the staging buffers are dead from here on
+    if (wave < 4) {
+#pragma unroll
+        for (int q = 0; q < 4 * OWN; ++q) {
+            const int w = q / OWN, j = q % OWN;
+            if (j >= FIRST) area[(w * PAIR + 3 * FIRST + 4 * (j - FIRST) + wave) * kWave + lane] = quad(q);
+            else if (w != wave) area[(w * PAIR + 3 * j + (wave < w ? wave : wave - 1)) * kWave + lane] = quad(q);   // uniform
+        }
+    } else if (tid < 256 + 32) {
+        l_scale[tid - 256] = (*p.s_x / 127.0f) * (p.s_chan[min(co0 + tid - 256, p.Cout - 1)] / 127.0f);
+    }
+    __syncthreads();
+    v4i sum[4][OWN];   // (of one of the four pairs, the wave's part of the nine)
+#pragma unroll
+    for (int w = 0; w < 4; ++w) {
+        const v4i* from = area + w * PAIR * kWave + lane;
+        if (wave == w) {   // uniform
+#pragma unroll
+            for (int j = 0; j < FIRST; ++j) sum[w][j] = quad(w * OWN + j) + from[3 * j * kWave] + from[(3 * j + 1) * kWave] + from[(3 * j + 2) * kWave];
+        } else if (wave == w + 4) {   // uniform
+#pragma unroll
+            for (int j = 0; j < OWN - FIRST; ++j) {
+                const v4i* f = from + (3 * FIRST + 4 * j) * kWave;
+                sum[w][FIRST + j] = f[0] + f[kWave] + f[2 * kWave] + f[3 * kWave];
+            }
+        }
+    }
+    if (p.splits == 1) __syncthreads();   // everyone is done reading the hand-over area
+#pragma unroll
+    for (int w = 0; w < 4; ++w)
+#pragma unroll
+        for (int j = 0; j < OWN; ++j) {
+            if (wave != w + (j < FIRST ? 0 : 4)) continue;   // uniform
+            const int q = w * OWN + j;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const int r = 4 * (q % 4) + e;
+                if (p.splits > 1) __builtin_nontemporal_store(sum[w][j][e], &dst[(4 * q + e) * kWave]);   // uniform; read next by other CUs, not by this one
+                else red[(8 * (r >> 2) + 4 * lh + (r & 3)) * ROWW + l32 * kT + q / 4] = sum[w][j][e];
+            }
+        }
+    if (p.splits > 1) return;
+    __syncthreads();
+    const int ncol = min(32, p.Cin - ci0) * kT, nrow = min(32, p.Cout - co0);   // valid ints of a row, valid rows
+    const int64_t first = ((int64_t)co0 * p.Cin + ci0) * p.taps_all;
+    const int row_step = p.Cin * p.taps_all;   // (below 2^31 over the rows of dW)
+    if (ncol == COLS && p.taps_all == kT && p.Cin % 4 == 0 && ((uintptr_t)p.dW & (p.bf16 ? 7 : 15)) == 0 && !p.acc_out) {   // uniform
+        // four results a thread at a time (one at a time, with an address for each, this took 2.3 us)
+        constexpr int V = COLS / 4;
+        int row = tid / V, col = tid - row * V;
+#pragma unroll
+        for (int k = 0; k < (32 * V + 511) / 512; ++k) {
+            if (row < nrow) {
+                const v4i v = *reinterpret_cast<const v4i*>(red + row * ROWW + 4 * col);
+                const float sc = l_scale[row];
+                store_result4(p.dW, first + row * row_step + 4 * col, (float)v[0] * sc, (float)v[1] * sc, (float)v[2] * sc, (float)v[3] * sc, p.bf16, 0);
+            }
+            const int c = col + 512 % V;
+            row += 512 / V + (c >= V);
+            col = c >= V ? c - V : c;
+        }
+        return;
+    }
+    int row = tid / COLS, col = tid - row * COLS;
+    for (int k = 0; k < 32 * COLS / 512; ++k) {
+        if (row < nrow && col < ncol) {
+            // (3-D: a depth tap's nine results, then the next input channel's)
+            const int64_t at = first + row * row_step + (p.taps_all == kT ? col : (col / kT) * p.taps_all + col % kT);
+            const int v = red[row * ROWW + col];
+            store_result(p.dW, at, (float)v * l_scale[row], p.bf16);
+            if (p.acc_out) p.acc_out[at] = v;
+        }
+        const int c = col + 512 % COLS;
+        row += 512 / COLS + (c >= COLS);
+        col = c >= COLS ? c - COLS : c;
     }
 }
 
@@ -475,7 +675,6 @@ __device__ __forceinline__ void dw11_role(Dw32Args& p, const int bid) {
 
     if constexpr (DMA) {
         static_assert(WM == 1 && WN == 1 && WK == 8 && CH == 1, "the direct-to-LDS form is the eight-wave one");
-        typedef __attribute__((address_space(3))) void* lds_ptr;
         constexpr int D = 4;                     // stage buffers
         constexpr int SB = (BM + BN) * kKC;      // bytes of a stage
         // request i of wave w fills rows 16w + 4i .. + 3 of the stage: lane l -> row + l / 16, slot column l % 16
@@ -498,7 +697,7 @@ __device__ __forceinline__ void dw11_role(Dw32Args& p, const int bid) {
             const int64_t k0 = (int64_t)min(chunk, c_last) * kKC;
 #pragma unroll
             for (int i = 0; i < 4; ++i)
-                __builtin_amdgcn_global_load_lds(src[i] + k0, (lds_ptr)(lds + buf * SB + (16 * wave + 4 * i) * kKC), 16, 0, 0);
+                    load_to_lds(src[i] + k0, lds + buf * SB + (16 * wave + 4 * i) * kKC);
         };
 #pragma unroll
         for (int st = 0; st < D - 1; ++st) issue(c_begin + st, st);

@@ -27,6 +27,12 @@ def test_filter_gradient_ring_remainders(batch, stride):
     on_random_codes(wl.Layer("ring", batch, 20, 7 * stride, 7 * stride, 24, 3, 3, stride, 1), 40 + batch)
 
 
+@pytest.mark.parametrize("stride,width", [(1, w) for w in (*range(14, 30), 1, 2, 3, 121, 122, 123)] + [(2, w) for w in (*range(28, 60, 2), 1, 3, 105, 106, 107)])
+def test_filter_gradient_row_pitches(stride, width):
+    """3 x 3: rows of every length modulo 16 (a loop of its own each), the shortest, and the longest that the staged rows hold and one more."""
+    on_random_codes(wl.Layer("pitch", 2, 35, 6 * stride, width, 33, 3, 3, stride, 1), 300 + width)
+
+
 @pytest.mark.parametrize("layer", [
     wl.Layer("t3x5", 6, 160, 20, 20, 96, 3, 3, 1, 1),        # 15 tiles: 17 splits fill the chip, 18 would need a second round
     wl.Layer("t1x1_odd", 5, 200, 17, 17, 344, 1, 1, 1, 0),   # 24 tiles of 64 x 64
