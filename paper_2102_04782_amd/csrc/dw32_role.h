@@ -60,12 +60,8 @@ constexpr int kKC = 256;        // K bytes staged per chunk (8 MFMA K-steps of 3
 constexpr int kPA = kKC + 16;   // LDS pitch of a gradient row: 16-byte aligned, rotates banks between rows
 constexpr int kT = 9;
 
-// 16 bytes of every lane, from its own address to 64 consecutive slots of LDS from `dst` on (lane l: slot l), without registers in between.
-__device__ __forceinline__ void load_to_lds(const int8_t* src, int8_t* dst) {
-    __builtin_amdgcn_global_load_lds(src, (__attribute__((address_space(3))) void*)dst, 16, 0, 0);
-}
-
-// The same with the address as a descriptor's base, a constant of the lane and a scalar: a request then takes no vector instruction, which
+// 16 bytes of every lane to 64 consecutive slots of LDS from `dst` on (lane l: slot l), without registers in between, the address being a
+// descriptor's base, a constant of the lane and a scalar.  A request so takes no vector instruction, which
 // matters beside matrix instructions (a CU whose other waves multiply, 960 requests of 1 KiB: 12.9 us of the 19.2 that the multiplies take;
 // with an addition for each address none before the multiplies were through).  kNoByte: no address, the lane's slot is cleared.
 constexpr uint32_t kNoByte = 0xFFFFFFF0u;
@@ -677,27 +673,24 @@ __device__ __forceinline__ void dw11_role(Dw32Args& p, const int bid) {
         static_assert(WM == 1 && WN == 1 && WK == 8 && CH == 1, "the direct-to-LDS form is the eight-wave one");
         constexpr int D = 4;                     // stage buffers
         constexpr int SB = (BM + BN) * kKC;      // bytes of a stage
-        // request i of wave w fills rows 16w + 4i .. + 3 of the stage: lane l -> row + l / 16, slot column l % 16
-        const int8_t* src[4];
+        // request i of wave w fills rows 16w + 4i .. + 3 of the stage: lane l -> row + l / 16, slot column l % 16; the first four waves the
+        // gradient's rows, the others the activation's
+        const bool grad = wave < 4;   // uniform
+        const __amdgpu_buffer_rsrc_t rs = tile_rsrc(grad ? p.g + (int64_t)co0 * p.klen : p.x + (int64_t)ci0 * p.x_chan_pitch);
+        uint32_t from[4];
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const int row = 16 * wave + 4 * i + lane / 16;
+        for (int i = 0; i < 4; ++i) {   // rows past Cout / Cin recompute the first one and are never stored
+            const int row = 16 * (wave % 4) + 4 * i + lane / 16;
             const int col = (lane % 16) ^ (row & 15);
-            if (row < BM) {   // rows past Cout / Cin recompute row 0 and are never stored
-                const int co = co0 + row;
-                src[i] = p.g + (int64_t)(co < p.Cout ? co : 0) * p.klen + 16 * col;
-            } else {
-                const int ci = ci0 + row - BM;
-                src[i] = p.x + (int64_t)(ci < p.Cin ? ci : 0) * p.x_chan_pitch + 16 * col;
-            }
+            const bool live = row < (grad ? p.Cout - co0 : p.Cin - ci0);
+            from[i] = (uint32_t)((int64_t)(live ? row : 0) * (grad ? p.klen : p.x_chan_pitch) + 16 * col);
         }
         // every call issues four requests (past the end the last chunk again, into a buffer nobody reads), so that the
         // count of outstanding requests below is a constant
         auto issue = [&](int chunk, int buf) {
-            const int64_t k0 = (int64_t)min(chunk, c_last) * kKC;
+            const uint32_t k0 = (uint32_t)min(chunk, c_last) * (uint32_t)kKC;
 #pragma unroll
-            for (int i = 0; i < 4; ++i)
-                    load_to_lds(src[i] + k0, lds + buf * SB + (16 * wave + 4 * i) * kKC);
+            for (int i = 0; i < 4; ++i) load_to_lds(rs, from[i], k0, lds + buf * SB + (16 * wave + 4 * i) * kKC);
         };
 #pragma unroll
         for (int st = 0; st < D - 1; ++st) issue(c_begin + st, st);
