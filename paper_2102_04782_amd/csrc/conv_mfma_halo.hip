@@ -46,7 +46,7 @@ struct HaloArgs {
     int stride;           // 1, or 2 (parity classes)
     int TH, TW, NI;       // destination tile, in pixels of one parity class
     int SH, SW;           // source window per image (the largest over the classes)
-    int tiles_h, tiles_w, groups;
+    int tiles_h, tiles_w, groups, row_tiles;
     int units;            // 16-byte window units per thread
     int double_buffer;    // more than one contraction chunk: two window buffers
     int zfill;            // stride 2, only parity class (0, 0) has taps: its workgroups also write the zeros of the other three
@@ -55,7 +55,7 @@ struct HaloArgs {
     // 32-bit entries: a uniform index then costs a scalar load, not a vector-memory round trip
     int tap_slot[kMaxPhases][kMaxTaps];  // slot offset a tap adds inside the window
     int tap_id[kMaxPhases][kMaxTaps];    // kh*kW + kw of the tap
-    FastDiv div_tw, div_thw, div_sw, div_si, div_tiles_w, div_tiles_hw, div_ptiles;
+    FastDiv div_tw, div_thw, div_sw, div_si, div_tiles_w, div_tiles_hw, div_row_tiles;
     const float* s_a;
     const float* s_b;
     float* out;           // fp32 [N][Crow][Hd][Wd]
@@ -107,21 +107,22 @@ __device__ __forceinline__ void halo_role(const HaloArgs& p, const uint32_t bid)
     const int tid = threadIdx.x, wave = tid / kWave, lane = tid % kWave;
     const int l32 = lane & 31, lh = lane >> 5;
     const int wr = wave % WR, wp = wave / WR;
-    // block -> (row tile, parity class, image group, tile row, tile column)
-    const int per_phase = p.groups * p.tiles_h * p.tiles_w;
-    const int ptiles = (ST > 1 && !p.zfill) ? ((per_phase + 7) & ~7) * (ST * ST) : per_phase;
-    const int tr = (int)fdiv(bid, p.div_ptiles);
-    int tp = (int)bid - tr * ptiles;
+    // block -> (image group, tile row, tile column, row tile, parity class)
+    // Blocks i, i + 8, i + 16, ... run on one XCD: it takes an eighth of that list, in its order.  Neighbouring tiles share lines of the
+    // result (a row of a tile seldom ends with a line), and the four parity classes of a tile interleave in memory pixel by pixel: their
+    // pieces meet in one L2 instead of going to memory one by one, and a window is fetched into one L2 for all row tiles.  (Dealt out tile by
+    // tile, row tile after row tile: data gradient of 384 <- 129, 1 x 1 at stride 2, 86 x 86, batch 94, 210 us and 154 here; of 128 <- 128, 3 x 3 at
+    // stride 2, 56 x 56, batch 64, 60.8 and 51; 1.10 times the speed over 50 drawn layers, of which every twelfth is slower, by up to 6 %: 256 <-
+    // 512, 1 x 1 at stride 2, 56 x 56, batch 64, 59.8 and 63.  An XCD's tiles 4 or 16 at a time, or its row tiles one after the other, were slower.)
+    const uint32_t xcd = bid % kXcd, each = (uint32_t)p.main_blocks / kXcd, more = (uint32_t)p.main_blocks % kXcd;
+    uint32_t at = bid / kXcd + xcd * each + min(xcd, more);
     int phase = 0;
     if (ST > 1 && !p.zfill) {
-        // The four parity classes of a tile interleave in memory (every other pixel of every other row), so each of them
-        // writes partial cache lines.  Their workgroups sit 8 blocks apart in groups of 32: same XCD (block i runs on
-        // XCD i % 8), dispatched together, and the partial lines meet in one L2 instead of going to memory one by one.
-        const int g8 = tp >> 5, r = tp & 31;
-        phase = r >> 3;
-        tp = g8 * 8 + (r & 7);
-        if (tp >= per_phase) return;   // uniform: padding of the last group of eight tiles
+        phase = (int)(at % (ST * ST));
+        at /= ST * ST;
     }
+    const int tp = (int)fdiv(at, p.div_row_tiles);
+    const int tr = (int)at - tp * p.row_tiles;
     const int pa = phase / ST, pb = phase % ST;
     const int grp = (int)fdiv((uint32_t)tp, p.div_tiles_hw);
     const int trem = tp - grp * p.tiles_h * p.tiles_w;
@@ -739,12 +740,9 @@ __global__ __launch_bounds__(256) void k_dx_1x1_stream(StreamArgs p) {
     }
 }
 
-// Workgroups of one row tile: one per pixel tile, times the parity classes of a strided data gradient (whose tiles are
-// padded to groups of eight, see the kernel's block decoding).
+// Workgroups of one row tile: one per pixel tile, times the parity classes of a strided data gradient.
 int64_t blocks_per_row_tile(const HaloArgs& a) {
-    const int64_t per_phase = (int64_t)a.groups * a.tiles_h * a.tiles_w;
-    if (a.stride > 1 && !a.zfill) return round_up(per_phase, 8) * a.stride * a.stride;
-    return per_phase;
+    return (int64_t)a.groups * a.tiles_h * a.tiles_w * (a.stride > 1 && !a.zfill ? a.stride * a.stride : 1);
 }
 
 // floor division for possibly negative numerators
@@ -877,7 +875,8 @@ Geometry plan(bool backward, int N, int Hs, int Ws, int cp, int Hd, int Wd, int 
     // room for the workgroups of a deferred filter-gradient reduction (at most 4096, dw_tail_worthwhile) is kept here,
     // so that the grid-size test of the launch cannot fail once an entry point has started launching
     if (pt * ceil_div(Crow, 64) >= ((int64_t)1 << 31) - 4096) return g;
-    a.div_ptiles = make_fastdiv((uint32_t)pt);
+    a.row_tiles = (int)ceil_div(Crow, g.rows);
+    a.div_row_tiles = make_fastdiv((uint32_t)a.row_tiles);
     g.ok = true;
     return g;
 }
@@ -1098,6 +1097,8 @@ Plan3 plan3(bool backward, const daq_conv3d_desc& d) {
     if (!g.ok || g.a.zfill) return pl;
     if (g.rows == 128 && g.a.stride == 2) {   // no such 3-D form
         g.rows = 64;
+        g.a.row_tiles = (int)ceil_div(g.a.Crow, 64);
+        g.a.div_row_tiles = make_fastdiv((uint32_t)g.a.row_tiles);
     }
     HaloArgs& a = g.a;
     a.src_bytes = (uint32_t)src_bytes;
@@ -1194,7 +1195,9 @@ static OtherKernel as_other(const Geometry& g) {
     for (int c = 1; c < a.stride * a.stride; ++c) taps = std::max(taps, a.ph_taps[c]);
     const TileForm form = ring1_applies(g) ? TileForm::kRing1 : taps9_applies(g) ? TileForm::kTaps9 : g.rows == 128 ? TileForm::kRows128
                           : a.Crow <= 32   ? TileForm::kNarrow : TileForm::kTaps;
-    return OtherKernel{form, a.stride > 1, blocks_per_row_tile(a) * ceil_div(a.Crow, g.rows), taps * (int)ceil_div(a.cp, kKc)};
+    // (the prices were fitted to a strided layer's tiles dealt out by the eight)
+    const int64_t tiles = a.stride > 1 && !a.zfill ? round_up((int64_t)a.groups * a.tiles_h * a.tiles_w, 8) * a.stride * a.stride : blocks_per_row_tile(a);
+    return OtherKernel{form, a.stride > 1, tiles * ceil_div(a.Crow, g.rows), taps * (int)ceil_div(a.cp, kKc)};
 }
 
 bool bwd_data_halo_supported(const daq_conv_desc& d) { return plan_bwd(d).ok; }

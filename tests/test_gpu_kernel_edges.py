@@ -225,3 +225,8 @@ def test_depthwise_filter_gradient_at_stride_2(batch, size, channels):
     """Row pitches of every residue, one slab and several."""
     for w in range(size, size + 4):
         on_random_codes(wl.Layer("dws2", batch, channels, size, 2 * w, channels, 3, 3, 2, 1, groups=channels), 80 + w)
+
+
+@pytest.mark.parametrize("batch,stride", [(1, 1), (3, 1), (5, 1), (7, 1), (1, 2), (3, 2)])
+def test_tiles_dealt_to_the_xcds_with_remainders(batch, stride):
+    on_random_codes(wl.Layer("deal", batch, 90, 11, 13, 70, 3, 3, stride, 1), 83)
