@@ -3,7 +3,7 @@
 //
 //     C[row channel][pixel] = sum over (tap, k)  Wp[tap][row][k] * P[src_pixel(pixel, tap)][k]
 //
-// A workgroup owns NI images x (TH x TW) destination pixels (<= 256) and 64 or 128 row channels.
+// A workgroup owns NI images x (TH x TW) destination pixels (<= 256) and 64 row channels (128 in one form).
 // Per 64-byte chunk of the contraction axis it stages the SOURCE WINDOW of its tile in LDS once -
 // (TH + reach) x (TW + reach) pixel slots of 64 channel bytes - and every filter tap reads that
 // window at a shifted slot, so no pixel is staged more than once and the loop over the taps has no
@@ -34,6 +34,8 @@ constexpr int kMaxTaps = 49;
 constexpr int kMaxUnits = 8;       // 16-byte units of the window a thread stages: up to 512 slots
 constexpr int kMaxPhases = 4;
 constexpr int kRingA = 4;          // filter tiles are requested kRingA - 1 steps ahead of their use
+// Workgroups from which the waves take 32 rows x 128 pixels instead of 64 x 64 (see halo_role): with a run-time tap list, and of 1 x 1 filters.
+constexpr int kWideBlocks = 512, kWideBlocks1 = 2048;
 constexpr uint32_t kOob = 0x80000000u;  // a buffer offset past every extent: such a load returns zeros
 
 struct HaloArgs {
@@ -74,26 +76,34 @@ __device__ __forceinline__ v4i buffer_load16(__amdgpu_buffer_rsrc_t rsrc, uint32
     return __builtin_amdgcn_raw_buffer_load_b128(rsrc, (int)voffset, (int)soffset, 0);
 }
 
-// WR = waves along the row (output channel) axis, WAVES = waves per workgroup.  (1, 4): 64 rows x 256 pixels with
-// 64 x 64 wave tiles.  (2, 4): 128 rows x 256 pixels with 64 x 128 wave tiles.  (2, 8): the same workgroup tile with
-// 64 x 64 wave tiles on eight waves - two per SIMD, so that the LDS reads of one overlap the multiplies of the other.
+// WR = waves along the row (output channel) axis, WAVES = waves per workgroup; a wave owns 32 * NX rows (64 with WR = 1) and an equal share of
+// the PX pixels.  On four waves: (WR 1, NX 2) 64 rows x 64 pixels each, (WR 2, NX 1) 32 x 128 (PX = 256) or 32 x 64 (PX = 128).  On eight:
+// (WR 2, NX 2) 64 x 64, a workgroup of 128 rows.
+//   Filter tiles come through the vector memory pipe, 64 bytes a clock for the whole CU, pixels from LDS, 128 bytes a clock.  With waves of 64 x 64 each of the
+// four asks for the same 4 KiB of filter a step, 256 clocks for 256 of multiplies, and registers allow one workgroup to a CU, so that its prologue, its
+// barriers and its stores show.  With 32 x 128 a wave asks for 2 KiB, LDS delivers twice as much, and two workgroups fit (3 x 3: 245 registers for 310).
+// Data gradient, operands from memory: 312 <- 80, 3 x 3 at 41 x 41, batch 40, 63.6 us and 41.7; 400 <- 16 at 49 x 49, batch 53, 62 and 49; 451 <- 368 at 15 x 15,
+// batch 66, 47 and 38; 1.13 times the speed over 24 drawn 3 x 3 layers.  128-pixel tiles of 3 x 3 filters: 512 <- 512 at 7 x 7, batch 64, 16.6 us with 64 x 32,
+// 13.8 with 32 x 64.  What is left is where a step with fewer reads of LDS is the shorter one, hardly a workgroup to a CU or hardly any arithmetic:
+// 64 x 64 up to 512 workgroups with a run-time tap list (80 <- 992, 5 x 5 at 34 x 34, batch 37, 141 us and 154), up to 2048 of 1 x 1 filters (512 <-
+// 1024 at 14 x 14, batch 64, 22.5 and 23.5; beyond, 912 <- 560 at stride 2, 81 x 81, batch 75, 650 and 601), 64 x 32 for 128-pixel tiles of 1 x 1 filters (2048 <- 512 at
+// 7 x 7, batch 64, 18.2 and 21.5).
 // DB = the contraction axis has more than one 64-byte chunk (two window buffers, restaged per chunk).
 // ST = stride (1 or 2): with one parity class its tables are indexed with constants.
 // TAPS > 0 (unit stride; TAPS = 1 also stride 2 with a single live parity class): the number of filter taps is this constant.  The loop over the taps of a chunk is
 // then unrolled, the ring of filter tiles has one slot per tap (slot = tap, so each tile is requested TAPS - 1
 // steps before its use), the tap tables are read once, and the pixel fragments of the next tap are read from LDS
-// before the multiplies of the current one: with a single wave per SIMD nothing else hides those latencies.
-// NX = 32-row blocks of a wave that can hold result rows: 1 for results of at most 32 channels (the data gradient of a
-// network's first layer), whose second block would only multiply zeros - dynamic-tap form on 64-row tiles only.
-// PX = destination pixels per workgroup: 128 (a wave then owns 64 rows x 32 pixels) for 1 x 1 layers with so few
-// pixels that 256-pixel tiles would leave CUs without a workgroup.
+// before the multiplies of the current one: with one or two waves per SIMD little else hides those latencies.
+// NX = 32-row blocks of a wave that can hold result rows; WR = 1, NX = 1 is for results of at most 32 channels (the data gradient of a
+// network's first layer), whose second block would only multiply zeros - dynamic-tap form only.
+// PX = destination pixels per workgroup: 128 for layers with so few pixels that 256-pixel tiles would leave CUs without a workgroup.
 // D3: a 3-D layer.  Its frames are the images of the tile; a depth tap kd of the filter reads the same window of another
 // frame of the sample (zeros where there is none), so the depth taps are further chunks of the contraction axis - chunk
 // kd * nkc_frame + kc - and nothing else in the loop changes; the filter copy is in the same order (k_frag3 writes it).
-// (3 x 3 x 3, 64 -> 64, 8 x 56 x 56, batch 8, data gradient: 365 us with dot products, 49 us here, 0.9 POP/s.)
+// (3 x 3 x 3, 64 -> 64, 8 x 56 x 56, batch 8, data gradient: 365 us with dot products, 36 us here.)
 template <int WR, bool DB, int ST, int WAVES, int TAPS, int NX, int PX, bool D3>
 __device__ __forceinline__ void halo_role(const HaloArgs& p, const uint32_t bid) {
-    constexpr int ROWS = 64 * WR;
+    constexpr int RW = WR == 1 ? 64 : 32 * NX, ROWS = RW * WR;   // result rows of a wave, of the workgroup
     constexpr int WPX = WAVES / WR;
     constexpr int SPT = 16 * WAVES;   // window slots one pass of the workgroup stages (four lanes per slot)
     constexpr int PXW = PX / WPX;
@@ -202,7 +212,7 @@ __device__ __forceinline__ void halo_role(const HaloArgs& p, const uint32_t bid)
     for (int x = 0; x < NX; ++x)
 #pragma unroll
         for (int sub = 0; sub < 2; ++sub) {
-            const int rb = (row0 + wr * 64) / 32 + x;
+            const int rb = (row0 + wr * RW) / 32 + x;
             aoff[x][sub] = rb < p.RB ? (uint32_t)((rb * 2 + sub) * 1024 + lane * 16) : kOob;
         }
     v4i ra[kRingA][2][2];   // [ring slot][x][sub]
@@ -406,7 +416,7 @@ __device__ __forceinline__ void halo_role(const HaloArgs& p, const uint32_t bid)
     const FastDiv div_thw = p.div_thw, div_tw = p.div_tw;
     float* const out = p.out;
     int32_t* const acc_out = p.acc_out;
-    const int rowbase = row0 + wr * 64 + 4 * lh;
+    const int rowbase = row0 + wr * RW + 4 * lh;
     const int HWd = Hd * Wd;
     const int CS = D3 ? p.Dd * HWd : HWd;   // elements from a result channel to the next
     const bool full_rows = row0 + ROWS <= Crow;
@@ -754,6 +764,7 @@ struct Geometry {
     size_t lds_bytes;
     int rows;
     int px;   // destination pixels per workgroup
+    bool priced128;   // as_other
 };
 
 // 1 x 1 filters with several contraction chunks, on 64-row tiles: the form with rings of chunks.  Unit stride, or
@@ -854,17 +865,12 @@ Geometry plan(bool backward, int N, int Hs, int Ws, int cp, int Hd, int Wd, int 
     a.double_buffer = cp > kKc || depth;   // (depth: the 3-D forms exist with two window buffers only)
     g.lds_bytes = (size_t)(a.double_buffer ? 2 : 1) * S * kPitch;
     if (g.lds_bytes > 150 * 1024) return g;
-    // 128-row tiles reuse each pixel fragment twice as often, but only pay off when they still fill the chip
+    // Tiles of 64 rows, two workgroups to a CU; of 128 rows, one to a CU, only for a single chunk by parity classes, where they fill the chip (384 <- 16
+    // at 59 x 59, batch 78: 130 us and 163 on 64 rows; elsewhere the other way round, up to 1.7 times: 192 <- 110, 5 x 5, 26 x 26, batch 53, 46.6 and 28.5).
     const int64_t blocks128 = (int64_t)a.groups * a.tiles_h * a.tiles_w * (a.zfill ? 1 : s * s) * ceil_div(Crow, 128);
-    g.rows = (Crow > 64 && blocks128 >= 256 && px == kPxWg) ? 128 : 64;
-    // 1 x 1 filters with several contraction chunks do hardly any arithmetic per chunk, so a workgroup is as fast as its
-    // requests come back: the ring form (64-row tiles, chunks requested three ahead, two workgroups per CU) was
-    // measured faster than 128-row tiles up to a thousand of those (ResNet-50's 128 -> 512 at 28 x 28 and 1024 -> 512
-    // at 14 x 14, N = 64: 19.9 -> 18.2 and 29.7 -> 23.2 us), slower beyond (256 -> 512 at 56 x 56: 103 -> 120 us)
-    if (g.rows == 128 && blocks128 <= 1024) {
-        g.rows = 64;
-        if (!ring1_applies(g)) g.rows = 128;
-    }
+    const bool fills128 = Crow > 64 && blocks128 >= 256 && px == kPxWg;
+    g.rows = fills128 && s == 2 && !a.double_buffer ? 128 : 64;
+    g.priced128 = fills128 && !(ring1_applies(g) && blocks128 <= 1024);
     a.div_tw = make_fastdiv((uint32_t)a.TW);
     a.div_thw = make_fastdiv((uint32_t)(a.TH * a.TW));
     a.div_sw = make_fastdiv((uint32_t)a.SW);
@@ -892,8 +898,8 @@ constexpr HaloNames kFwdNames{"conv_fwd_halo", "conv_fwd_halo", "conv_fwd_halo_r
 // layers of a classification network: few pixels, long contraction) is cut into 128-pixel tiles instead.  Measured
 // on ResNet-50's last stages, N = 64: 512 -> 2048 at 7 x 7 (104 tiles) 23.3 -> 17.2 us, 256 -> 1024 at 14 x 14 (256
 // tiles) 14.6 -> 14.5 us cold and 12.4 -> 11.6 us warm, 2048 -> 512 at 7 x 7 (416 tiles) 14.0 -> 15.1 us: not there.
-// The constant-tap 3 x 3 form (one workgroup per CU at 256 pixels) takes 128-pixel tiles below 192 tiles: 512 -> 512
-// at 7 x 7, N = 64, has 104.
+// The constant-tap 3 x 3 form takes 128-pixel tiles where 256-pixel tiles are fewer than the CUs: 512 -> 512 at 7 x 7, batch 128 (208 tiles),
+// 25.6 -> 23.5 us; 256 -> 256 at 14 x 14, batch 48 (192), 15.7 -> 15.1; batch 64 (256) 14.4 -> 14.9: not there.
 bool taps9_applies(const Geometry& g) {
     const HaloArgs& a = g.a;
     return a.stride == 1 && a.ph_taps[0] == 9 && a.double_buffer && g.rows == 64;
@@ -907,7 +913,7 @@ Geometry plan_small(Geometry g, Plan replan) {
         Geometry s = replan(128);
         return s.ok && ring1_applies(s) ? s : g;
     }
-    if (taps9_applies(g) && blocks < 192) {
+    if (taps9_applies(g) && blocks < 256) {
         Geometry s = replan(128);
         return s.ok && taps9_applies(s) ? s : g;
     }
@@ -923,30 +929,22 @@ daq_status launch(Geometry& g, hipStream_t st, const HaloNames& names) {
     g.a.main_blocks = (int)(blocks - a.tail.blocks);
     if (a.tail.blocks > 0) g.lds_bytes = std::max<size_t>(g.lds_bytes, 8 * kWave * sizeof(int32_t));   // the role's scratch
     const dim3 grid((unsigned)blocks);
-#define DAQ_HALO_CASE(WRV, DBV, WV)                                                                                  \
-    {                                                                                                                \
-        auto kern = a.stride == 2 ? k_conv_halo<WRV, DBV, 2, WV> : k_conv_halo<WRV, DBV, 1, WV>;                     \
-        if (!allow_lds((const void*)kern, g.lds_bytes))                                                                                              \
-            return DAQ_ERR_HIP;                                                                                      \
-        DAQ_LAUNCH(name, st, hipLaunchKernelGGL(kern, grid, dim3(64 * WV), g.lds_bytes, st, a));                     \
-    }
-    // Layers with several contraction chunks and 3 x 3 filters at unit stride, on 64-row tiles: the form with a
-    // constant tap count.  (With a single chunk the kernel is all prologue and epilogue, and the dynamic form, which
-    // needs fewer registers, lets more workgroups overlap theirs; 128-row tiles stay on the eight-wave form.)
-    // 1 x 1 filters with several contraction chunks, on 64-row tiles: the form with rings of chunks
-    // (on 128-row tiles, which are chosen when the grid is large, it measured no better than the dynamic form)
+    // Layers with several contraction chunks and 3 x 3 filters at unit stride: the form with a constant tap count.  (With a single chunk the
+    // kernel is all prologue and epilogue, and the dynamic form, which needs fewer registers, lets more workgroups overlap theirs.)
+    // 1 x 1 filters with several contraction chunks: the form with rings of chunks
     const bool ring1 = ring1_applies(g);
     if (g.px != kPxWg && !ring1 && !taps9_applies(g)) return DAQ_ERR_UNSUPPORTED;   // small tiles exist in these two forms only (see plan_small)
     if (ring1) {
-        auto kern = a.stride == 2 ? (g.px == kPxWg ? k_conv_halo<1, true, 2, 4, 1> : k_conv_halo<1, true, 2, 4, 1, 2, 128>)
-                                  : (g.px == kPxWg ? k_conv_halo<1, true, 1, 4, 1> : k_conv_halo<1, true, 1, 4, 1, 2, 128>);
+        const bool wide = g.a.main_blocks > kWideBlocks1;
+        auto kern = a.stride == 2 ? (g.px != kPxWg ? k_conv_halo<1, true, 2, 4, 1, 2, 128> : wide ? k_conv_halo<2, true, 2, 4, 1, 1> : k_conv_halo<1, true, 2, 4, 1>)
+                                  : (g.px != kPxWg ? k_conv_halo<1, true, 1, 4, 1, 2, 128> : wide ? k_conv_halo<2, true, 1, 4, 1, 1> : k_conv_halo<1, true, 1, 4, 1>);
         if (!allow_lds((const void*)kern, g.lds_bytes))
             return DAQ_ERR_HIP;
         DAQ_LAUNCH(names.k1, st, hipLaunchKernelGGL(kern, grid, dim3(256), g.lds_bytes, st, a));
         return DAQ_OK;
     }
     if (taps9_applies(g)) {
-        auto kern = g.px == kPxWg ? k_conv_halo<1, true, 1, 4, 9> : k_conv_halo<1, true, 1, 4, 9, 2, 128>;
+        auto kern = g.px == kPxWg ? k_conv_halo<2, true, 1, 4, 9, 1> : k_conv_halo<2, true, 1, 4, 9, 1, 128>;
         if (!allow_lds((const void*)kern, g.lds_bytes))
             return DAQ_ERR_HIP;
         DAQ_LAUNCH(names.k9, st, hipLaunchKernelGGL(kern, grid, dim3(256), g.lds_bytes, st, a));
@@ -955,8 +953,9 @@ daq_status launch(Geometry& g, hipStream_t st, const HaloNames& names) {
     if (g.rows == 128) {
         HaloArgs a8 = g.a;   // eight waves stage the window in half as many passes
         a8.units = (int)ceil_div((int64_t)g.a.NI * g.a.SH * g.a.SW, 128);
-        const HaloArgs& a = a8;
-        if (a.double_buffer) DAQ_HALO_CASE(2, true, 8) else DAQ_HALO_CASE(2, false, 8)
+        auto kern = k_conv_halo<2, false, 2, 8>;
+        if (!allow_lds((const void*)kern, g.lds_bytes)) return DAQ_ERR_HIP;
+        DAQ_LAUNCH(name, st, hipLaunchKernelGGL(kern, grid, dim3(512), g.lds_bytes, st, a8));
     } else if (a.Crow <= 32) {
 #define DAQ_HALO_NARROW(DBV)                                                                                         \
     {                                                                                                                \
@@ -968,9 +967,15 @@ daq_status launch(Geometry& g, hipStream_t st, const HaloNames& names) {
         if (a.double_buffer) DAQ_HALO_NARROW(true) else DAQ_HALO_NARROW(false)
 #undef DAQ_HALO_NARROW
     } else {
-        if (a.double_buffer) DAQ_HALO_CASE(1, true, 4) else DAQ_HALO_CASE(1, false, 4)
+        // (many workgroups: waves of 32 rows x 128 pixels, as above)
+        const bool wide = g.a.main_blocks > kWideBlocks;
+        auto kern = wide ? (a.double_buffer ? (a.stride == 2 ? k_conv_halo<2, true, 2, 4, 0, 1> : k_conv_halo<2, true, 1, 4, 0, 1>)
+                                            : (a.stride == 2 ? k_conv_halo<2, false, 2, 4, 0, 1> : k_conv_halo<2, false, 1, 4, 0, 1>))
+                         : (a.double_buffer ? (a.stride == 2 ? k_conv_halo<1, true, 2, 4> : k_conv_halo<1, true, 1, 4>)
+                                            : (a.stride == 2 ? k_conv_halo<1, false, 2, 4> : k_conv_halo<1, false, 1, 4>));
+        if (!allow_lds((const void*)kern, g.lds_bytes)) return DAQ_ERR_HIP;
+        DAQ_LAUNCH(name, st, hipLaunchKernelGGL(kern, grid, dim3(256), g.lds_bytes, st, a));
     }
-#undef DAQ_HALO_CASE
     return DAQ_OK;
 }
 
@@ -1032,7 +1037,7 @@ __global__ __launch_bounds__(512, 1) void k_bwd_both(Dw32Args w, HaloArgs x, int
     if (threadIdx.x >= 256) return;   // (a barrier waits for the waves that are still there)
     const uint32_t bid = (uint32_t)(b - x_first);
     if constexpr (FORM == kBothRing1) halo_role<1, true, 1, 4, 1, 2, 128, false>(x, bid);
-    else if constexpr (FORM == kBothTaps9) halo_role<1, true, 1, 4, 9, 2, 128, false>(x, bid);
+    else if constexpr (FORM == kBothTaps9) halo_role<2, true, 1, 4, 9, 1, 128, false>(x, bid);
     else if constexpr (FORM == kBothOneChunk) halo_role<1, false, 1, 4, 0, 2, kPxWg, false>(x, bid);
     else if constexpr (FORM == kBothNarrow) halo_role<1, false, 1, 4, 0, 1, kPxWg, false>(x, bid);
     else halo_role<1, true, 2, 4, 1, 2, 128, false>(x, bid);
@@ -1095,11 +1100,6 @@ Plan3 plan3(bool backward, const daq_conv3d_desc& d) {
     };
     Geometry g = plan_small(make(kPxWg), make);
     if (!g.ok || g.a.zfill) return pl;
-    if (g.rows == 128 && g.a.stride == 2) {   // no such 3-D form
-        g.rows = 64;
-        g.a.row_tiles = (int)ceil_div(g.a.Crow, 64);
-        g.a.div_row_tiles = make_fastdiv((uint32_t)g.a.row_tiles);
-    }
     HaloArgs& a = g.a;
     a.src_bytes = (uint32_t)src_bytes;
     a.wfrag_bytes = (uint32_t)pl.frag_bytes;
@@ -1118,17 +1118,16 @@ daq_status launch3(Plan3& pl, const int8_t* filter, void* frag, const char* name
     DAQ_LAUNCH("frag_w3", st, hipLaunchKernelGGL(k_frag3, dim3((unsigned)ceil_div(units, 256)), dim3(256), 0, st, filter, pl.rows, pl.kp, a.T, a.RB,
                                                  a.nkc_frame, units, (v4i*)frag));
     a.wfrag = (const int8_t*)frag;
-    const bool r128 = pl.g.rows == 128;
-    if (r128) a.units = (int)ceil_div((int64_t)a.NI * a.SH * a.SW, 128);   // eight waves stage the window in half as many passes
-    const int64_t blocks = blocks_per_row_tile(a) * ceil_div(a.Crow, pl.g.rows);
+    const int64_t blocks = blocks_per_row_tile(a) * ceil_div(a.Crow, 64);
     a.main_blocks = (int)blocks;
+    const bool wide = blocks > kWideBlocks;
     auto kern = a.stride == 2 ? (a.Crow <= 32 ? k_conv_halo<1, true, 2, 4, 0, 1, kPxWg, true> : k_conv_halo<1, true, 2, 4, 0, 2, kPxWg, true>)
-                : r128        ? k_conv_halo<2, true, 1, 8, 0, 2, kPxWg, true>
                 : a.Crow <= 32 && pl.g.px == kPxWg ? k_conv_halo<1, true, 1, 4, 0, 1, kPxWg, true>
-                : taps9_applies(pl.g) ? (pl.g.px == kPxWg ? k_conv_halo<1, true, 1, 4, 9, 2, kPxWg, true> : k_conv_halo<1, true, 1, 4, 9, 2, 128, true>)
+                : taps9_applies(pl.g) ? (pl.g.px == kPxWg ? k_conv_halo<2, true, 1, 4, 9, 1, kPxWg, true> : k_conv_halo<2, true, 1, 4, 9, 1, 128, true>)
+                : wide                ? k_conv_halo<2, true, 1, 4, 0, 1, kPxWg, true>
                                       : k_conv_halo<1, true, 1, 4, 0, 2, kPxWg, true>;
     if (!allow_lds((const void*)kern, pl.g.lds_bytes)) return DAQ_ERR_HIP;
-    DAQ_LAUNCH(name, st, hipLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3(r128 ? 512 : 256), pl.g.lds_bytes, st, a));
+    DAQ_LAUNCH(name, st, hipLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3(256), pl.g.lds_bytes, st, a));
     return DAQ_OK;
 }
 
@@ -1193,11 +1192,16 @@ static OtherKernel as_other(const Geometry& g) {
     const HaloArgs& a = g.a;
     int taps = a.ph_taps[0];
     for (int c = 1; c < a.stride * a.stride; ++c) taps = std::max(taps, a.ph_taps[c]);
-    const TileForm form = ring1_applies(g) ? TileForm::kRing1 : taps9_applies(g) ? TileForm::kTaps9 : g.rows == 128 ? TileForm::kRows128
-                          : a.Crow <= 32   ? TileForm::kNarrow : TileForm::kTaps;
-    // (the prices were fitted to a strided layer's tiles dealt out by the eight)
-    const int64_t tiles = a.stride > 1 && !a.zfill ? round_up((int64_t)a.groups * a.tiles_h * a.tiles_w, 8) * a.stride * a.stride : blocks_per_row_tile(a);
-    return OtherKernel{form, a.stride > 1, tiles * ceil_div(a.Crow, g.rows), taps * (int)ceil_div(a.cp, kKc)};
+    // The prices are those of the forms and grids they were fitted to: tiles of 128 rows where those would fill the chip, a strided layer's tiles
+    // by the eight.  (Such products have become 1.1 to 1.7 times faster since.)
+    const TileForm form = g.priced128         ? TileForm::kRows128
+                          : ring1_applies(g)  ? TileForm::kRing1
+                          : taps9_applies(g)  ? TileForm::kTaps9
+                          : a.Crow <= 32      ? TileForm::kNarrow
+                                              : TileForm::kTaps;
+    const bool classes = a.stride > 1 && !a.zfill;
+    const int64_t tiles = classes ? round_up((int64_t)a.groups * a.tiles_h * a.tiles_w, 8) * a.stride * a.stride : blocks_per_row_tile(a);
+    return OtherKernel{form, a.stride > 1, tiles * ceil_div(a.Crow, g.priced128 ? 128 : 64), taps * (int)ceil_div(a.cp, kKc)};
 }
 
 bool bwd_data_halo_supported(const daq_conv_desc& d) { return plan_bwd(d).ok; }

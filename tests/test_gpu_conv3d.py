@@ -38,6 +38,7 @@ LAYERS = {
     "mc_no_pad": ((2, 64, 7, 14, 13, 48, 3, 3, 3, 1, 1, 1, 0, 0, 0, 1, 1, 1, 1), 0),    # output volume smaller than the input's
     "mc_deep_pad": ((2, 48, 4, 12, 12, 56, 3, 3, 3, 1, 1, 1, 2, 1, 1, 2, 1, 1, 1), 0),  # depth dilation 2
     "mc_s2": ((4, 64, 5, 17, 16, 80, 3, 3, 3, 1, 2, 2, 1, 1, 1, 1, 1, 1, 1), 0),        # stride 2 in height and width: parity classes, phase planes
+    "mc_wide": ((11, 1009, 3, 9, 15, 80, 2, 1, 3, 1, 1, 1, 0, 0, 1, 1, 1, 1, 1), 0),     # more than 512 workgroups with a run-time tap list
     "mc_depth_s2": ((2, 64, 9, 14, 12, 64, 3, 3, 3, 2, 1, 1, 1, 1, 1, 1, 1, 1, 1), 0),  # stride 2 in depth only
     "mc_all_s2": ((4, 64, 8, 18, 18, 96, 3, 3, 3, 2, 2, 2, 1, 1, 1, 1, 1, 1, 1), 0),    # in all three
     "mc_taps15": ((2, 64, 5, 14, 14, 48, 3, 5, 3, 1, 1, 1, 1, 2, 1, 1, 1, 1, 1), 0),    # run-time tap list in the data gradient

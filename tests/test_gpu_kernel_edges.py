@@ -230,3 +230,20 @@ def test_depthwise_filter_gradient_at_stride_2(batch, size, channels):
 @pytest.mark.parametrize("batch,stride", [(1, 1), (3, 1), (5, 1), (7, 1), (1, 2), (3, 2)])
 def test_tiles_dealt_to_the_xcds_with_remainders(batch, stride):
     on_random_codes(wl.Layer("deal", batch, 90, 11, 13, 70, 3, 3, stride, 1), 83)
+
+
+@pytest.mark.parametrize("layer", [
+    wl.Layer("w1", 33, 4065, 9, 15, 272, 1, 1, 1, 0),          # 2112 workgroups of one 256-pixel tile each: waves of 32 rows x 128 pixels
+    wl.Layer("w1_less", 32, 4065, 9, 15, 272, 1, 1, 1, 0),     # 2048: 64 x 64
+    wl.Layer("w1_s2", 33, 4065, 17, 29, 272, 1, 1, 2, 0),
+    wl.Layer("wt", 33, 1009, 9, 15, 80, 1, 3, 1, 0),           # run-time tap list, several chunks: 528
+    wl.Layer("wt_less", 32, 1009, 9, 15, 80, 1, 3, 1, 0),      # 512: 64 x 64
+    wl.Layer("wt_one", 33, 1009, 9, 15, 40, 3, 3, 1, 1),       # one chunk
+    wl.Layer("wt_s2", 9, 1009, 17, 29, 80, 3, 3, 2, 1),        # parity classes: 576
+    wl.Layer("r128", 9, 1009, 17, 29, 40, 3, 3, 2, 1),         # one chunk by parity class: 128-row tiles
+    wl.Layer("t9_256", 16, 1009, 9, 15, 80, 3, 3, 1, 1),       # constant taps: 256 workgroups, 256-pixel tiles
+    wl.Layer("t9_128", 15, 1009, 9, 15, 80, 3, 3, 1, 1),       # fewer: 128-pixel tiles
+], ids=lambda l: l.name)
+def test_forms_of_the_halo_kernel(layer):
+    """Both sides of the lines between the tile kernel's forms, result channels off every block."""
+    on_random_codes(layer, 83)
