@@ -599,6 +599,8 @@ struct StreamArgs {
     int cp, Crow, RB, HW;
     int RP, S;            // pairs of row blocks; pixel-group phases, a multiple of four (a wave takes groups s, s + S, ...)
     uint32_t total_px, groups;
+    uint32_t deal, dealt;   // blocks that an XCD takes in a row; the blocks dealt out that way, whole turns of the XCDs
+    FastDiv div_deal;
     FastDiv div_rp, div_hw;
     const float* s_a;
     const float* s_b;
@@ -627,8 +629,13 @@ __global__ __launch_bounds__(256) void k_dx_1x1_stream(StreamArgs p) {
     const int lane = threadIdx.x % kWave, l32 = lane & 31, lh = lane >> 5;
     // the four waves of a workgroup take four neighbouring pixel groups of one pair of row blocks: together they
     // write 512 consecutive bytes of each of the pair's 64 planes
-    const uint32_t quad = fdiv(blockIdx.x, p.div_rp);
-    const int rp = (int)(blockIdx.x - quad * (uint32_t)p.RP);
+    uint32_t at = blockIdx.x;
+    if (at < p.dealt) {   // uniform: stream_deal
+        const uint32_t i = at / kXcd, turn = fdiv(i, p.div_deal);
+        at = (turn * (kXcd - 1) + at % kXcd) * p.deal + i;
+    }
+    const uint32_t quad = fdiv(at, p.div_rp);
+    const int rp = (int)(at - quad * (uint32_t)p.RP);
     const uint32_t s = quad * 4u + threadIdx.x / kWave;
     if (s >= (uint32_t)p.S) return;   // uniform per wave
     // (a wave takes groups s, s + S, ...: all waves together advance through the pixels as one window.  Giving every
@@ -1138,6 +1145,18 @@ bool stream_applies(const daq_conv_desc& d, const daq_layout& Lg) {
            ceil_div(std::max(d.Cin, d.Cout), 64) <= 4096;
 }
 
+// Blocks of the streaming form that an XCD takes in a row (0: block by block).  A pair of row blocks of four pixel groups is a block, 512 bytes of each of
+// its planes.  Where planes are no multiple of 64 bytes neighbouring blocks share lines, which then meet in one L2: an eighth of
+// the blocks each (64 <- 384 at 14 x 14, batch 128, operands from memory, 16.9 us dealt out one by one, 13.0; 16 <- 48 at 45 x 45, batch 86, 14.4 and
+// 11.9) or, of large results, which lose the order of their pages that way, eight quads (16 <- 320 at 61 x 61, batch 34, 57.4, 52.5 by
+// eighths, 49.8; 32 <- 244 at 79 x 75, batch 27, 56, 53 and 48).  On other planes only the source is shared, among the pairs of row blocks: four quads from
+// four pairs and 128 bytes a pixel on (512 <- 256 at 28 x 28, batch 64, 35.1 and 26.1; 144 <- 24 at 56 x 56, batch 128, three pairs, 44.8 and 45.4, 336 <- 32 at
+// 52 x 52, batch 50, 39.6 and 42.6: not there).
+int64_t stream_deal(int64_t out_bytes, int64_t plane_bytes, int cp, int pairs, int64_t blocks) {
+    if (plane_bytes % 64 == 0) return pairs >= 4 && cp >= 128 ? 4 * pairs : 0;
+    return out_bytes <= (48 << 20) ? blocks / kXcd : 8 * pairs;
+}
+
 // src: the NHWC operand (layout Ls); wfrag: the fragment-order filter copy whose rows are the result's `rows` channels
 daq_status launch_stream(const char* name, const daq_conv_desc& d, const daq_layout& Ls, const int8_t* src,
                          const int8_t* wfrag, int64_t wfrag_bytes, int rows, const float* s_a, const float* s_b, float* out,
@@ -1168,6 +1187,10 @@ daq_status launch_stream(const char* name, const daq_conv_desc& d, const daq_lay
     a.main_blocks = (int)wgs;
     const dim3 grid((unsigned)(wgs + a.tail.blocks));
     const int64_t out_bytes = (int64_t)d.N * rows * a.HW * (bf16 ? 2 : 4);
+    const int64_t deal = stream_deal(out_bytes, (int64_t)a.HW * (bf16 ? 2 : 4), a.cp, a.RP, wgs);
+    a.deal = (uint32_t)std::max<int64_t>(deal, 1);
+    a.dealt = (uint32_t)(deal ? wgs / (kXcd * deal) * (kXcd * deal) : 0);
+    a.div_deal = make_fastdiv(a.deal);
     const int store = acc || out_bytes >= ((int64_t)1 << 31) || (bf16 && (a.HW & 1)) ? 0 : bf16 ? 2 : 1;
     const bool nt = stream_result(out_bytes, (int64_t)a.HW * (bf16 ? 2 : 4));
     a.out_bytes = store ? (uint32_t)out_bytes : 0u;

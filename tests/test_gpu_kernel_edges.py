@@ -247,3 +247,15 @@ def test_tiles_dealt_to_the_xcds_with_remainders(batch, stride):
 def test_forms_of_the_halo_kernel(layer):
     """Both sides of the lines between the tile kernel's forms, result channels off every block."""
     on_random_codes(layer, 83)
+
+
+@pytest.mark.parametrize("layer", [
+    wl.Layer("eighths", 9, 70, 13, 13, 40, 1, 1, 1, 0),     # 96 blocks (two pairs of row blocks), an eighth for each XCD
+    wl.Layer("eighths_few", 1, 30, 5, 5, 20, 1, 1, 1, 0),   # fewer blocks than XCDs
+    wl.Layer("turns", 12, 250, 8, 8, 130, 1, 1, 1, 0),      # planes of whole lines, four pairs: 16 blocks a turn, some left over
+    wl.Layer("plain", 12, 130, 8, 8, 40, 1, 1, 1, 0),       # three pairs
+    wl.Layer("large", 9, 250, 75, 75, 20, 1, 1, 1, 0),      # more than 48 MiB: eight quads a turn
+], ids=lambda l: l.name)
+def test_blocks_of_the_streaming_form(layer):
+    """Orders in which the XCDs take the blocks, with remainders."""
+    on_random_codes(layer, 85)
