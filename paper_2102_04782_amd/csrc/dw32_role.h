@@ -355,18 +355,20 @@ __device__ __forceinline__ void read_window(const int8_t* at, int (&d)[8]) {
     else if constexpr (last >= 4) read_piece<0, last - 3>(at, d + 4);
 }
 // The window itself.  The fourth dword of a piece of which three are used counts as used here as well (otherwise its register is given to
-// a later read of the same batch, which then waits for the whole batch before it), and whole dwords of two pieces are put together here
-// (left to itself the compiler copies them where they are read, and waits there).
+// a later read of the same batch, which then waits for the whole batch before it), and whole dwords of two pieces are put together here, by a
+// shift of no bytes (plain copies the compiler makes where they are read, and waits there; moves in inline assembly it does not see: a matrix
+// instruction may read a register no sooner than two wait states after a vector instruction wrote it, and the compiler counts those only
+// from instructions that it knows).
 template <int Q>
 __device__ __forceinline__ v4i window(const int (&d)[8]) {
     if constexpr (Q / 4 == 1) asm volatile("" ::"v"(d[0]));
     if constexpr ((Q + 15) / 4 == 6) asm volatile("" ::"v"(d[7]));
-    v4i x = window_at<Q>(d);
     if constexpr (Q % 4 == 0 && Q != 0) {
-#pragma unroll
-        for (int e = 0; e < 4; ++e) asm volatile("v_mov_b32 %0, %1" : "=v"(x[e]) : "v"(d[Q / 4 + e]));
+        constexpr int j = Q / 4;
+        return v4i{alignbyte(d[j], d[j], 0), alignbyte(d[j + 1], d[j + 1], 0), alignbyte(d[j + 2], d[j + 2], 0), alignbyte(d[j + 3], d[j + 3], 0)};
+    } else {
+        return window_at<Q>(d);
     }
-    return x;
 }
 
 // The K loop of a multiplying wave over n chunks.
