@@ -66,9 +66,9 @@ __global__ __launch_bounds__(512) void k_dw32_ring(Dw32Args p) {
     dw32_ring_role<S2>(p, (int)blockIdx.x);
 }
 
-template <int WM, int WN, int WK, int PF, int CH, bool DMA = false>
+template <int WM, int WN, int WK, int PF, int CH, bool DMA = false, bool LONG = false>
 __global__ __launch_bounds__(64 * WM * WN * WK) void k_dw11(Dw32Args p) {
-    dw11_role<WM, WN, WK, PF, CH, DMA>(p, (int)blockIdx.x);
+    dw11_role<WM, WN, WK, PF, CH, DMA, LONG>(p, (int)blockIdx.x);
 }
 
 // K splits across workgroups.  A workgroup fills a CU (its stage buffers are 100 to 150 KB of LDS), so a launch of more than 256 runs in
@@ -146,6 +146,12 @@ void choose_bands(Plan32& pl, int bm, int bn, int depth = 1) {
 }
 
 }  // namespace
+
+// 1 x 1: from how many chunks of a workgroup on its requests are addressed by vector instructions.  Operands from memory, scalar and vector
+// addresses: 512 -> 2048 at 7 x 7, batch 128, 25 chunks, 19.8 and 19.4 us; 512 -> 1024 at stride 2, 28 x 28, batch 128, 50 chunks, 37.8 and 36.4;
+// 32 -> 1312 at stride 2, 70 x 70, batch 3, 15 chunks, 9.7 and 10.3; 64 -> 384 at 14 x 14, batch 64, 9.1 and 9.3.  By chunks, over 182 layers: below 9
+// 0.987 of the time with scalar addresses, 9 to 19 0.994, 20 to 33 1.008, from 34 on 1.013.
+bool dw11_long(int64_t chunks) { return chunks >= 20; }
 
 Plan32 make_plan32(const daq_conv_desc& d, int depth) {
     Plan32 pl{};
@@ -322,7 +328,7 @@ daq_status conv_bwd_filter_lds(const daq_conv_desc& d, const Plan32& plan, const
                 return DAQ_ERR_HIP;
             DAQ_LAUNCH("conv_bwd_filter_dw11", st, hipLaunchKernelGGL(kern, grid, dim3(256), pl.lds_bytes, st, a));
         } else {
-            auto kern = k_dw11<1, 1, 8, 3, 1, true>;
+            auto kern = dw11_long(ceil_div(pl.nchunks, pl.splits)) ? k_dw11<1, 1, 8, 3, 1, true, true> : k_dw11<1, 1, 8, 3, 1, true>;
             if (!allow_lds((const void*)kern, pl.lds_bytes))
                 return DAQ_ERR_HIP;
             DAQ_LAUNCH("conv_bwd_filter_dw11", st, hipLaunchKernelGGL(kern, grid, dim3(512), pl.lds_bytes, st, a));

@@ -254,6 +254,7 @@ struct Plan32 {
 };
 // depth: depth taps of a 3-D layer (its frames are the images of `d`); the launch has that many times the tiles
 Plan32 make_plan32(const daq_conv_desc& d, int depth = 1);
+bool dw11_long(int64_t chunks);   // 1 x 1: whether a workgroup of so many chunks addresses its requests by vector instructions
 size_t bwd_filter_lds_ws_bytes(const Plan32& pl, int depth = 1);
 int64_t bwd_filter_lds_row_bytes(const Plan32& pl);   // read of an activation row, from its start on
 // With `defer`, a K-split launch leaves its last stage (sum of the partial tiles, de-quantization) undone and

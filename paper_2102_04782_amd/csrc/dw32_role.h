@@ -617,13 +617,15 @@ __device__ __forceinline__ void dw32_ring_role(Dw32Args& p, const int bid) {
 //     acc[co][ci] = sum_f  G[co][f] * X[ci][f] ,
 // with both operands staged the same way (rows of 256 + 16 bytes, aligned 16-byte fragment reads).
 // A wave owns 64 (co) x 64 (ci): four 32 x 32 tiles, so every fragment it reads feeds two multiplies.
-// Same ring, K-split and wave-combine scheme as above.
+// K splits, and waves that share a tile combined through LDS, as above.
 // ---------------------------------------------------------------------------------------------
-// DMA (the eight-wave form): the operands go from global memory straight into LDS (global_load_lds_dwordx4, the 64
-// lanes' 16-byte pieces land in 64 consecutive slots), four stage buffers of unpadded 256-byte rows, three stages on
+// DMA (the eight-wave form): the operands go from global memory straight into LDS (the 64 lanes' 16-byte pieces land in 64
+// consecutive slots), four stage buffers of unpadded 256-byte rows, three stages on
 // their way; no staging registers, no LDS stores, one barrier per chunk.  Slot column c of row r holds the row's
 // 16-byte column c ^ (r % 16), so that the 16 lanes of a fragment read still fall into different banks.
-template <int WM, int WN, int WK, int PF, int CH, bool DMA>
+// LONG: the requests' addresses are made by vector instructions (64 bits a lane) instead of scalar ones, which lets them go out behind the
+// multiplies of the chunk before.  A workgroup of many chunks is the faster for it, a short one the slower (dw11_long).
+template <int WM, int WN, int WK, int PF, int CH, bool DMA, bool LONG = false>
 __device__ __forceinline__ void dw11_role(Dw32Args& p, const int bid) {
     constexpr int WAVES = WM * WN * WK, NT = 64 * WAVES;
     static_assert(WAVES == 4 || WAVES == 8, "four or eight waves");
@@ -680,19 +682,28 @@ __device__ __forceinline__ void dw11_role(Dw32Args& p, const int bid) {
         const bool grad = wave < 4;   // uniform
         const __amdgpu_buffer_rsrc_t rs = tile_rsrc(grad ? p.g + (int64_t)co0 * p.klen : p.x + (int64_t)ci0 * p.x_chan_pitch);
         uint32_t from[4];
+        const int8_t* src[4];
 #pragma unroll
         for (int i = 0; i < 4; ++i) {   // rows past Cout / Cin recompute the first one and are never stored
             const int row = 16 * (wave % 4) + 4 * i + lane / 16;
             const int col = (lane % 16) ^ (row & 15);
             const bool live = row < (grad ? p.Cout - co0 : p.Cin - ci0);
             from[i] = (uint32_t)((int64_t)(live ? row : 0) * (grad ? p.klen : p.x_chan_pitch) + 16 * col);
+            if constexpr (LONG) {   // (one base a lane: with a base for the wave the compiler keeps the addresses scalar)
+                const int g_row = 16 * wave + 4 * i + lane / 16;
+                src[i] = g_row < BM ? p.g + (int64_t)(live ? co0 + row : 0) * p.klen + 16 * col : p.x + (int64_t)(live ? ci0 + row : 0) * p.x_chan_pitch + 16 * col;
+            }
         }
         // every call issues four requests (past the end the last chunk again, into a buffer nobody reads), so that the
         // count of outstanding requests below is a constant
         auto issue = [&](int chunk, int buf) {
             const uint32_t k0 = (uint32_t)min(chunk, c_last) * (uint32_t)kKC;
 #pragma unroll
-            for (int i = 0; i < 4; ++i) load_to_lds(rs, from[i], k0, lds + buf * SB + (16 * wave + 4 * i) * kKC);
+            for (int i = 0; i < 4; ++i) {
+                int8_t* const dst = lds + buf * SB + (16 * wave + 4 * i) * kKC;
+                if constexpr (LONG) __builtin_amdgcn_global_load_lds(src[i] + k0, (__attribute__((address_space(3))) void*)dst, 16, 0, 0);
+                else load_to_lds(rs, from[i], k0, dst);
+            }
         };
 #pragma unroll
         for (int st = 0; st < D - 1; ++st) issue(c_begin + st, st);
