@@ -18,6 +18,7 @@
 // workgroup handles one class and issues only the taps that are live for it - no multiplies by
 // stride-skipped zeros.
 #include <algorithm>
+#include <cstddef>
 
 #include "daq_internal.h"
 #include "dw32_role.h"
@@ -593,24 +594,29 @@ __global__ __launch_bounds__(64 * WAVES, (TAPS == 1 || NX == 1 || PX < kPxWg) ? 
 // Waves of a workgroup hold neighbouring row blocks of the same pixel groups.
 // ---------------------------------------------------------------------------------------------
 struct StreamArgs {
+    // What a block finds its place by fills the first 64 bytes, what it loads and stores by the next: arguments arrive in lines of that size,
+    // 0.25 us each when one is asked for behind another (64 -> 64 at 42 x 42, batch 14: 5.30 us with the dealing's fields in a third line).
+    int main_blocks;
+    uint32_t deal, dealt;   // blocks that an XCD takes in a row; the blocks dealt out that way, whole turns of the XCDs
+    FastDiv div_deal;
+    FastDiv div_rp;
+    int RP, S;            // pairs of row blocks; pixel-group phases, a multiple of four (a wave takes groups s, s + S, ...)
+    int cp, Crow, RB, HW;
+    int bf16;             // the result is bfloat16 storage
     const int8_t* src;    // NHWC gradient, [pixels][cp]
     const int8_t* wfrag;  // filter in fragment order (one tap): [cp/64][RB][2][1024]
     uint32_t src_bytes, wfrag_bytes;
-    int cp, Crow, RB, HW;
-    int RP, S;            // pairs of row blocks; pixel-group phases, a multiple of four (a wave takes groups s, s + S, ...)
     uint32_t total_px, groups;
-    uint32_t deal, dealt;   // blocks that an XCD takes in a row; the blocks dealt out that way, whole turns of the XCDs
-    FastDiv div_deal;
-    FastDiv div_rp, div_hw;
     const float* s_a;
     const float* s_b;
     float* out;
     uint32_t out_bytes;   // STORE 1 and 2
+    FastDiv div_hw;
     int32_t* acc_out;
     DwTail tail;          // tail.blocks > 0: that many workgroups behind the first main_blocks finish a deferred filter gradient
-    int main_blocks;
-    int bf16;             // the result is bfloat16 storage
 };
+
+static_assert(offsetof(StreamArgs, src) == 64 && offsetof(StreamArgs, out_bytes) <= 124, "a block's place in the first line, its operands in the second");
 
 // KS = 32-byte contraction steps (cp <= 32 * KS)
 // STORE: how the results leave.  1 (fp32) and 2 (bfloat16, even planes): through a buffer descriptor, an offset past its extent
@@ -622,7 +628,7 @@ struct StreamArgs {
 template <int KS, int STORE, bool NT>
 __global__ __launch_bounds__(256) void k_dx_1x1_stream(StreamArgs p) {
     __shared__ int32_t l_role[256];
-    if (p.tail.blocks > 0 && (int)blockIdx.x >= p.main_blocks) {   // uniform
+    if ((int)blockIdx.x >= p.main_blocks) {   // uniform
         dw_reduce_role(p.tail, (int)blockIdx.x - p.main_blocks, l_role);
         return;
     }
