@@ -26,6 +26,28 @@
 
 namespace daq {
 
+// Blocks of the streaming form that an XCD takes in a row (0: block by block).  A pair of row blocks of four pixel groups is a block, 512 bytes of each of
+// its planes.  Where planes are no multiple of 64 bytes neighbouring blocks share lines, which then meet in one L2: an eighth of
+// the blocks each (384 <- 64 at 14 x 14, batch 128, operands from memory, 16.9 us dealt out one by one, 13.0; 48 <- 16 at 45 x 45, batch 86, 14.4 and
+// 11.9) or, of large results, which lose the order of their pages that way, eight quads (320 <- 16 at 61 x 61, batch 34, 57.4, 52.5 by
+// eighths, 49.8; 244 <- 32 at 79 x 75, batch 27, 56, 53 and 48), or two where a wave of many channels leaves few blocks to deal (1368 <- 192 at 75 x 75,
+// batch 12, 168 and 161; four pairs and fewer are enough for eight: 240 <- 256 at 45 x 44, batch 84, 62.9 and 61.1).  On other planes only the source is shared, among the pairs of row blocks: four quads from
+// four pairs and 128 bytes a pixel on (512 <- 256 at 28 x 28, batch 64, 35.1 and 26.1; 144 <- 24 at 56 x 56, batch 128, three pairs, 44.8 and 45.4, 336 <- 32 at
+// 52 x 52, batch 50, 39.6 and 42.6: not there) up to sixteen pairs (1776 <- 128 at 24 x 26, batch 18, 28 pairs, 21.5 and 23.9).
+//   Lines shared and a multiple of eight pairs: one by one, an XCD has the same row blocks of every quad, neighbours meet anyway, and the pages keep their order
+// (1499 <- 59 at 43 x 43, batch 50, 180 us and 208 dealt; 512 <- 16 at 22 x 22, batch 44, 12.3 and 14.1), but for eight pairs of many
+// channels, whose source counts too (480 <- 256 at 50 x 51, batch 65, 143 us and 132).  So it nearly is with 27 pairs and more, and what
+// is won is less than the order of large results (1936 <- 48 at 20 x 18, batch 53, 31 pairs, 45.4 and 50.6; 26 pairs: 1616 <- 56 at 67 x 67, batch 4,
+// 35.4 and 32.9; 1664 <- 24 at 72 x 73, batch 11, 129.5 and 131.8).
+int64_t stream_deal(int64_t out_bytes, int64_t plane_bytes, int cp, int pairs, int64_t blocks) {
+    if (plane_bytes % 64 == 0) return pairs >= 4 && pairs <= 16 && cp >= 128 ? 4 * pairs : 0;
+    const bool large = out_bytes > (48 << 20), many = cp > 128;
+    if (pairs % kXcd == 0 && !(large && many && pairs == kXcd)) return 0;
+    if (!large) return blocks / kXcd;
+    if (many) return (pairs >= 5 ? 2 : 8) * pairs;
+    return pairs >= 27 ? 0 : 8 * pairs;
+}
+
 namespace {
 
 constexpr int kPxWg = 256;         // destination pixels per workgroup (128 in the small-tile form of 1 x 1 filters)
@@ -1149,18 +1171,6 @@ bool stream_applies(const daq_conv_desc& d, const daq_layout& Lg) {
     return d.groups == 1 && d.kH == 1 && d.kW == 1 && d.strideH == 1 && d.strideW == 1 && d.padH == 0 && d.padW == 0 &&
            Lg.kind == DAQ_LAYOUT_NHWC && Lg.c_pitch <= 256 && (int64_t)d.N * d.Hin * d.Win < ((int64_t)1 << 31) - 64 &&
            ceil_div(std::max(d.Cin, d.Cout), 64) <= 4096;
-}
-
-// Blocks of the streaming form that an XCD takes in a row (0: block by block).  A pair of row blocks of four pixel groups is a block, 512 bytes of each of
-// its planes.  Where planes are no multiple of 64 bytes neighbouring blocks share lines, which then meet in one L2: an eighth of
-// the blocks each (64 <- 384 at 14 x 14, batch 128, operands from memory, 16.9 us dealt out one by one, 13.0; 16 <- 48 at 45 x 45, batch 86, 14.4 and
-// 11.9) or, of large results, which lose the order of their pages that way, eight quads (16 <- 320 at 61 x 61, batch 34, 57.4, 52.5 by
-// eighths, 49.8; 32 <- 244 at 79 x 75, batch 27, 56, 53 and 48).  On other planes only the source is shared, among the pairs of row blocks: four quads from
-// four pairs and 128 bytes a pixel on (512 <- 256 at 28 x 28, batch 64, 35.1 and 26.1; 144 <- 24 at 56 x 56, batch 128, three pairs, 44.8 and 45.4, 336 <- 32 at
-// 52 x 52, batch 50, 39.6 and 42.6: not there).
-int64_t stream_deal(int64_t out_bytes, int64_t plane_bytes, int cp, int pairs, int64_t blocks) {
-    if (plane_bytes % 64 == 0) return pairs >= 4 && cp >= 128 ? 4 * pairs : 0;
-    return out_bytes <= (48 << 20) ? blocks / kXcd : 8 * pairs;
 }
 
 // src: the NHWC operand (layout Ls); wfrag: the fragment-order filter copy whose rows are the result's `rows` channels

@@ -27,8 +27,23 @@ static void long_filter_gradients() {
     EXPECT(!is_long(layer(3, 32, 70, 70, 1312, 1, 2)) && !is_long(layer(64, 64, 14, 14, 384, 1, 1)) && !is_long(layer(64, 512, 7, 7, 2048, 1, 1)));
 }
 
+// Streaming 1 x 1 products: the blocks that an XCD takes in a row.
+static void dealt_blocks() {
+    auto deal = [](int N, int rows, int H, int W, int cp, int64_t blocks) {
+        return stream_deal((int64_t)N * rows * H * W * 4, (int64_t)H * W * 4, cp, (int)ceil_div(rows, 64), blocks);
+    };
+    EXPECT(deal(50, 1499, 43, 43, 64, 2064) == 0 && deal(122, 1015, 22, 22, 16, 2048) == 0 && deal(44, 512, 22, 22, 16, 672) == 0);   // a multiple of eight pairs
+    EXPECT(deal(53, 1936, 20, 18, 48, 2046) == 0 && deal(106, 1952, 29, 28, 32, 2046) == 0);                                       // nearly
+    EXPECT(deal(18, 1776, 24, 26, 128, 1036) == 0 && deal(2, 1880, 72, 72, 128, 1020) == 0);                                       // whole lines, many pairs
+    EXPECT(deal(12, 1368, 75, 75, 192, 528) == 2 * 22 && deal(51, 1304, 50, 51, 192, 525) == 2 * 21);                              // few blocks
+    EXPECT(deal(65, 480, 50, 51, 256, 512) == 2 * 8 && deal(84, 240, 45, 44, 256, 512) == 8 * 4 && deal(10, 2048, 13, 14, 160, 256) == 0);
+    EXPECT(deal(34, 320, 61, 61, 16, 2000) == 8 * 5 && deal(64, 512, 28, 28, 256, 512) == 4 * 8 && deal(64, 448, 28, 28, 256, 504) == 4 * 7);
+    EXPECT(deal(110, 311, 27, 23, 48, 1000) == 8 * 5 && deal(128, 384, 14, 14, 64, 1024) == 128 && deal(86, 48, 45, 45, 16, 1024) == 128);
+}
+
 int main() {
     long_filter_gradients();
+    dealt_blocks();
     std::printf("%d failures\n", fails);
     return fails != 0;
 }
