@@ -62,38 +62,49 @@ constexpr int kWideBlocks = 512, kWideBlocks1 = 2048;
 constexpr uint32_t kOob = 0x80000000u;  // a buffer offset past every extent: such a load returns zeros
 
 struct HaloArgs {
+    // What a workgroup finds its tile by, in one line of 64 bytes: arguments arrive in such lines, a quarter of a microsecond each when one is asked for
+    // behind another.  Then what it needs up to its first loads.
+    int main_blocks;      // the product's workgroups; those behind them finish a deferred filter gradient (tail)
+    int row_tiles;
+    int groups;
+    int tiles_h, tiles_w;
+    int zfill;            // stride 2, only parity class (0, 0) has taps: its workgroups also write the zeros of the other three
+    FastDiv div_row_tiles, div_tiles_hw, div_tiles_w;
+    int NI;
+    int TH, TW;           // destination tile, NI images, in pixels of one parity class
+    int SH, SW;           // source window per image (the largest over the classes)
+    int N, Hs, Ws, cp;
+    int units;            // 16-byte window units per thread
+    FastDiv div_si, div_sw;
+    int T;                // kH*kW
     const int8_t* src;    // pixel operand, NHWC [N][Hs][Ws][cp]
     const int8_t* wfrag;  // filter operand in fragment order
     uint32_t src_bytes, wfrag_bytes;
-    int N, Hs, Ws, cp;
-    int Hd, Wd;
-    int Crow, RB, T;      // result channels, 32-row blocks of the filter copy, kH*kW
-    int stride;           // 1, or 2 (parity classes)
-    int TH, TW, NI;       // destination tile, in pixels of one parity class
-    int SH, SW;           // source window per image (the largest over the classes)
-    int tiles_h, tiles_w, groups, row_tiles;
-    int units;            // 16-byte window units per thread
-    int double_buffer;    // more than one contraction chunk: two window buffers
-    int zfill;            // stride 2, only parity class (0, 0) has taps: its workgroups also write the zeros of the other three
-    // per parity class: live taps, window origin relative to the tile's first pixel
-    int ph_taps[kMaxPhases], ph_org_h[kMaxPhases], ph_org_w[kMaxPhases];
-    // 32-bit entries: a uniform index then costs a scalar load, not a vector-memory round trip
-    int tap_slot[kMaxPhases][kMaxTaps];  // slot offset a tap adds inside the window
-    int tap_id[kMaxPhases][kMaxTaps];    // kh*kW + kw of the tap
-    FastDiv div_tw, div_thw, div_sw, div_si, div_tiles_w, div_tiles_hw, div_row_tiles;
     const float* s_a;
     const float* s_b;
-    float* out;           // fp32 [N][Crow][Hd][Wd]
-    int32_t* acc_out;
-    DwTail tail;          // tail.blocks > 0: that many workgroups behind the first main_blocks finish a deferred filter
-    int main_blocks;      // gradient instead (they are dispatched last and fill the slots this kernel's own tiles leave)
+    int RB;               // 32-row blocks of the filter copy
+    // per parity class: live taps, window origin relative to the tile's first pixel
+    int ph_taps[kMaxPhases], ph_org_h[kMaxPhases], ph_org_w[kMaxPhases];
+    FastDiv div_tw, div_thw;
+    int double_buffer;    // more than one contraction chunk: two window buffers
+    int Hd, Wd;
+    int Crow;             // result channels
+    int stride;           // 1, or 2 (parity classes)
     int bf16;             // the result is stored as bfloat16 (round to nearest even) instead of fp32
     int nt;               // the result is large: streaming stores, so that it does not push the next kernels' operands out of the caches
+    float* out;           // fp32 [N][Crow][Hd][Wd]
+    int32_t* acc_out;
     // 3-D layers: an "image" is one frame of a sample, N counts frames, and the contraction runs over kD depth taps of nkc_frame
     // chunks each (see D3 below)
     int Dd, Ds, kD, sD_log2, pD, dD, fwd, nkc_frame;
     FastDiv div_dd, div_nkc;
+    DwTail tail;          // tail.blocks > 0: that many workgroups behind the first main_blocks finish a deferred filter
+                          // gradient instead (they are dispatched last and fill the slots this kernel's own tiles leave)
+    // 32-bit entries: a uniform index then costs a scalar load, not a vector-memory round trip
+    int tap_slot[kMaxPhases][kMaxTaps];  // slot offset a tap adds inside the window
+    int tap_id[kMaxPhases][kMaxTaps];    // kh*kW + kw of the tap
 };
+static_assert(offsetof(HaloArgs, NI) == 60 && offsetof(HaloArgs, src) == 128 && offsetof(HaloArgs, ph_org_h) <= 192, "lines of arguments");
 
 __device__ __forceinline__ v4i buffer_load16(__amdgpu_buffer_rsrc_t rsrc, uint32_t voffset, uint32_t soffset) {
     return __builtin_amdgcn_raw_buffer_load_b128(rsrc, (int)voffset, (int)soffset, 0);
@@ -133,8 +144,15 @@ __device__ __forceinline__ void halo_role(const HaloArgs& p, const uint32_t bid)
     constexpr int BF = PXW / 32;
     extern __shared__ __align__(16) int8_t lds[];   // one or two window buffers of S slots
 
-    if (p.tail.blocks > 0 && (int)bid >= p.main_blocks) {   // uniform
-        dw_reduce_role(p.tail, (int)bid - p.main_blocks, reinterpret_cast<int32_t*>(lds));
+    // (kept whole by the empty statement: the compiler would ask piece by piece, with a wait for each)
+    uint32_t main_blocks = (uint32_t)p.main_blocks, row_tiles = (uint32_t)p.row_tiles;
+    int tiles_h = p.tiles_h, tiles_w = p.tiles_w, zfill = p.zfill, NI = p.NI;
+    FastDiv div_row_tiles = p.div_row_tiles, div_tiles_hw = p.div_tiles_hw, div_tiles_w = p.div_tiles_w;
+    asm volatile("" : "+s"(main_blocks), "+s"(row_tiles), "+s"(tiles_h), "+s"(tiles_w), "+s"(zfill), "+s"(NI), "+s"(div_row_tiles.mul),
+                      "+s"(div_row_tiles.shift), "+s"(div_row_tiles.one), "+s"(div_tiles_hw.mul), "+s"(div_tiles_hw.shift), "+s"(div_tiles_hw.one),
+                      "+s"(div_tiles_w.mul), "+s"(div_tiles_w.shift), "+s"(div_tiles_w.one) : "s"(p.TH), "s"(p.src));   // (and the next two lines are on their way)
+    if (bid >= main_blocks) {   // uniform
+        dw_reduce_role(p.tail, (int)(bid - main_blocks), reinterpret_cast<int32_t*>(lds));
         return;
     }
     const int tid = threadIdx.x, wave = tid / kWave, lane = tid % kWave;
@@ -147,23 +165,23 @@ __device__ __forceinline__ void halo_role(const HaloArgs& p, const uint32_t bid)
     // tile, row tile after row tile: data gradient of 384 <- 129, 1 x 1 at stride 2, 86 x 86, batch 94, 210 us and 154 here; of 128 <- 128, 3 x 3 at
     // stride 2, 56 x 56, batch 64, 60.8 and 51; 1.10 times the speed over 50 drawn layers, of which every twelfth is slower, by up to 6 %: 256 <-
     // 512, 1 x 1 at stride 2, 56 x 56, batch 64, 59.8 and 63.  An XCD's tiles 4 or 16 at a time, or its row tiles one after the other, were slower.)
-    const uint32_t xcd = bid % kXcd, each = (uint32_t)p.main_blocks / kXcd, more = (uint32_t)p.main_blocks % kXcd;
+    const uint32_t xcd = bid % kXcd, each = main_blocks / kXcd, more = main_blocks % kXcd;
     uint32_t at = bid / kXcd + xcd * each + min(xcd, more);
     int phase = 0;
-    if (ST > 1 && !p.zfill) {
+    if (ST > 1 && !zfill) {
         phase = (int)(at % (ST * ST));
         at /= ST * ST;
     }
-    const int tp = (int)fdiv(at, p.div_row_tiles);
-    const int tr = (int)at - tp * p.row_tiles;
+    const int tp = (int)fdiv(at, div_row_tiles);
+    const int tr = (int)(at - (uint32_t)tp * row_tiles);
     const int pa = phase / ST, pb = phase % ST;
-    const int grp = (int)fdiv((uint32_t)tp, p.div_tiles_hw);
-    const int trem = tp - grp * p.tiles_h * p.tiles_w;
-    const int tih = (int)fdiv((uint32_t)trem, p.div_tiles_w);
-    const int tiw = trem - tih * p.tiles_w;
+    const int grp = (int)fdiv((uint32_t)tp, div_tiles_hw);
+    const int trem = tp - grp * tiles_h * tiles_w;
+    const int tih = (int)fdiv((uint32_t)trem, div_tiles_w);
+    const int tiw = trem - tih * tiles_w;
     const int row0 = tr * ROWS;
-    const int n0 = grp * p.NI, h0 = tih * p.TH, w0 = tiw * p.TW;
-    const int SI = p.SH * p.SW, S = p.NI * SI;
+    const int n0 = grp * NI, h0 = tih * p.TH, w0 = tiw * p.TW;
+    const int SI = p.SH * p.SW, S = NI * SI;
     const int halo_bytes = S * kPitch;
     const int nkc = D3 ? p.kD * p.nkc_frame : (p.cp + kKc - 1) / kKc;
     const int taps = p.ph_taps[phase];
@@ -262,7 +280,7 @@ __device__ __forceinline__ void halo_role(const HaloArgs& p, const uint32_t bid)
         const int rem = q - img * p.TH * p.TW;
         const int th = (int)fdiv((uint32_t)rem, p.div_tw);
         const int tw = rem - th * p.TW;
-        bslot[y] = (img < p.NI) ? img * SI + th * p.SW + tw : 0;
+        bslot[y] = (img < NI) ? img * SI + th * p.SW + tw : 0;
     }
 
     v16i acc[2][BF];
@@ -435,7 +453,7 @@ __device__ __forceinline__ void halo_role(const HaloArgs& p, const uint32_t bid)
     // epilogue: register r of tile (x, y) is row 32x + 8*(r/4) + 4*lh + r%4, destination pixel q = wp*PXW + 32y + l32
     // (Copies of the fields: behind a store the compiler takes p, a reference, for changed, and would fetch a field again and wait for
     // it before each of the next stores: 1 x 1 stride 2 with odd rows, 258 -> 193 at 19 x 15, batch 9, 9.5 us against 8.7.)
-    const int Hd = p.Hd, Wd = p.Wd, Crow = p.Crow, N = p.N, NI = p.NI, TH = p.TH, TW = p.TW, zfill = p.zfill, bf16 = p.bf16, nt = p.nt;
+    const int Hd = p.Hd, Wd = p.Wd, Crow = p.Crow, N = p.N, TH = p.TH, TW = p.TW, bf16 = p.bf16, nt = p.nt;
     const FastDiv div_thw = p.div_thw, div_tw = p.div_tw;
     float* const out = p.out;
     int32_t* const acc_out = p.acc_out;
