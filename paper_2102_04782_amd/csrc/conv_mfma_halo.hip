@@ -48,6 +48,18 @@ int64_t stream_deal(int64_t out_bytes, int64_t plane_bytes, int cp, int pairs, i
     return pairs >= 27 ? 0 : 8 * pairs;
 }
 
+// 1 x 1 products on 128-pixel tiles, whose workgroups all run at once: where no two tiles share a line of the result - tiles of whole images, or
+// of whole rows that begin and end with one - only the filter is left to share, and the blocks go out one by one, row tile after row tile, all tiles of
+// one filter tile together.  (Operands from memory, tile after tile and so: 512 <- 2048 at 7 x 7, batch 128, 24.0 us and 23.4; 256 <- 768 at 48 x 48,
+// batch 4, 1.12 times the speed; 105 layers at stride 2 1.018, 12 at unit stride with cut images 1.03.)  Not with many tiles that are no multiple of eight:
+// the row tiles of one then lie on several XCDs, each of which fetches its window (512 <- 80 at stride 2, 24 x 24, batch 33, 66 tiles, 13.8 and 15.3;
+// 928 <- 1104 at 7 x 7, batch 82, 41 tiles, 22.3 and 24.2).
+bool tiles_by_rows(int TH, int tiles_h, int tiles_w, int stride, int Hd, int Wd, int bytes, int64_t tiles, int row_tiles) {
+    if (tiles % kXcd != 0 && tiles >= 32 && row_tiles > 3) return false;
+    if (tiles_h * tiles_w == 1) return true;
+    return tiles_w == 1 && (int64_t)stride * TH * Wd * bytes % 64 == 0 && (int64_t)Hd * Wd * bytes % 64 == 0;
+}
+
 namespace {
 
 constexpr int kPxWg = 256;         // destination pixels per workgroup (128 in the small-tile form of 1 x 1 filters)
@@ -65,8 +77,8 @@ struct HaloArgs {
     // What a workgroup finds its tile by, in one line of 64 bytes: arguments arrive in such lines, a quarter of a microsecond each when one is asked for
     // behind another.  Then what it needs up to its first loads.
     int main_blocks;      // the product's workgroups; those behind them finish a deferred filter gradient (tail)
-    int row_tiles;
-    int groups;
+    int by_rows;          // tiles_by_rows
+    int row_tiles;        // (by_rows: the tiles of a row tile)
     int tiles_h, tiles_w;
     int zfill;            // stride 2, only parity class (0, 0) has taps: its workgroups also write the zeros of the other three
     FastDiv div_row_tiles, div_tiles_hw, div_tiles_w;
@@ -90,6 +102,7 @@ struct HaloArgs {
     int Hd, Wd;
     int Crow;             // result channels
     int stride;           // 1, or 2 (parity classes)
+    int groups;
     int bf16;             // the result is stored as bfloat16 (round to nearest even) instead of fp32
     int nt;               // the result is large: streaming stores, so that it does not push the next kernels' operands out of the caches
     float* out;           // fp32 [N][Crow][Hd][Wd]
@@ -145,10 +158,10 @@ __device__ __forceinline__ void halo_role(const HaloArgs& p, const uint32_t bid)
     extern __shared__ __align__(16) int8_t lds[];   // one or two window buffers of S slots
 
     // (kept whole by the empty statement: the compiler would ask piece by piece, with a wait for each)
-    uint32_t main_blocks = (uint32_t)p.main_blocks, row_tiles = (uint32_t)p.row_tiles;
+    uint32_t main_blocks = (uint32_t)p.main_blocks, row_tiles = (uint32_t)p.row_tiles, rows_first = (uint32_t)p.by_rows;
     int tiles_h = p.tiles_h, tiles_w = p.tiles_w, zfill = p.zfill, NI = p.NI;
     FastDiv div_row_tiles = p.div_row_tiles, div_tiles_hw = p.div_tiles_hw, div_tiles_w = p.div_tiles_w;
-    asm volatile("" : "+s"(main_blocks), "+s"(row_tiles), "+s"(tiles_h), "+s"(tiles_w), "+s"(zfill), "+s"(NI), "+s"(div_row_tiles.mul),
+    asm volatile("" : "+s"(main_blocks), "+s"(row_tiles), "+s"(rows_first), "+s"(tiles_h), "+s"(tiles_w), "+s"(zfill), "+s"(NI), "+s"(div_row_tiles.mul),
                       "+s"(div_row_tiles.shift), "+s"(div_row_tiles.one), "+s"(div_tiles_hw.mul), "+s"(div_tiles_hw.shift), "+s"(div_tiles_hw.one),
                       "+s"(div_tiles_w.mul), "+s"(div_tiles_w.shift), "+s"(div_tiles_w.one) : "s"(p.TH), "s"(p.src));   // (and the next two lines are on their way)
     if (bid >= main_blocks) {   // uniform
@@ -166,14 +179,15 @@ __device__ __forceinline__ void halo_role(const HaloArgs& p, const uint32_t bid)
     // stride 2, 56 x 56, batch 64, 60.8 and 51; 1.10 times the speed over 50 drawn layers, of which every twelfth is slower, by up to 6 %: 256 <-
     // 512, 1 x 1 at stride 2, 56 x 56, batch 64, 59.8 and 63.  An XCD's tiles 4 or 16 at a time, or its row tiles one after the other, were slower.)
     const uint32_t xcd = bid % kXcd, each = main_blocks / kXcd, more = main_blocks % kXcd;
-    uint32_t at = bid / kXcd + xcd * each + min(xcd, more);
+    const bool by_rows = TAPS == 1 && PX == 128 && rows_first != 0;   // tiles_by_rows: the blocks' own order, row tile after row tile
+    uint32_t at = by_rows ? bid : bid / kXcd + xcd * each + min(xcd, more);
     int phase = 0;
     if (ST > 1 && !zfill) {
         phase = (int)(at % (ST * ST));
         at /= ST * ST;
     }
-    const int tp = (int)fdiv(at, div_row_tiles);
-    const int tr = (int)(at - (uint32_t)tp * row_tiles);
+    const int quot = (int)fdiv(at, div_row_tiles), left = (int)(at - (uint32_t)quot * row_tiles);   // (by rows: of the tiles of a row tile)
+    const int tp = by_rows ? left : quot, tr = by_rows ? quot : left;
     const int pa = phase / ST, pb = phase % ST;
     const int grp = (int)fdiv((uint32_t)tp, div_tiles_hw);
     const int trem = tp - grp * tiles_h * tiles_w;
@@ -988,6 +1002,11 @@ daq_status launch(Geometry& g, hipStream_t st, const HaloNames& names) {
     const bool ring1 = ring1_applies(g);
     if (g.px != kPxWg && !ring1 && !taps9_applies(g)) return DAQ_ERR_UNSUPPORTED;   // small tiles exist in these two forms only (see plan_small)
     if (ring1) {
+        if (g.px != kPxWg && tiles_by_rows(a.TH, a.tiles_h, a.tiles_w, a.stride, a.Hd, a.Wd, a.bf16 ? 2 : 4, ptiles, a.row_tiles)) {
+            g.a.by_rows = 1;
+            g.a.row_tiles = (int)ptiles;
+            g.a.div_row_tiles = make_fastdiv((uint32_t)ptiles);
+        }
         const bool wide = g.a.main_blocks > kWideBlocks1;
         auto kern = a.stride == 2 ? (g.px != kPxWg ? k_conv_halo<1, true, 2, 4, 1, 2, 128> : wide ? k_conv_halo<2, true, 2, 4, 1, 1> : k_conv_halo<1, true, 2, 4, 1>)
                                   : (g.px != kPxWg ? k_conv_halo<1, true, 1, 4, 1, 2, 128> : wide ? k_conv_halo<2, true, 1, 4, 1, 1> : k_conv_halo<1, true, 1, 4, 1>);

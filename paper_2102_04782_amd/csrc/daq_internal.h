@@ -286,7 +286,9 @@ daq_status conv3d_bwd_data_halo(const daq_conv3d_desc& d, const int8_t* qg, cons
 daq_status conv3d_fwd_halo(const daq_conv3d_desc& d, const int8_t* qx, const int8_t* w_fwd, const float* s_x, const float* s_w, float* Y,
                            int32_t* acc, void* frag, hipStream_t st);
 
-// conv_mfma_halo.hip, streaming 1 x 1 products: blocks that an XCD takes in a row, 0: one by one
+// conv_mfma_halo.hip, 1 x 1 products on 128-pixel tiles: whether their workgroups go row tile after row tile
+bool tiles_by_rows(int TH, int tiles_h, int tiles_w, int stride, int Hd, int Wd, int bytes, int64_t tiles, int row_tiles);
+// streaming 1 x 1 products: blocks that an XCD takes in a row, 0: one by one
 int64_t stream_deal(int64_t out_bytes, int64_t plane_bytes, int cp, int pairs, int64_t blocks);
 
 // conv_mfma_direct.hip: the same products for layers of few tiles, operands straight from global memory.  `other` is what would serve

@@ -41,9 +41,19 @@ static void dealt_blocks() {
     EXPECT(deal(110, 311, 27, 23, 48, 1000) == 8 * 5 && deal(128, 384, 14, 14, 64, 1024) == 128 && deal(86, 48, 45, 45, 16, 1024) == 128);
 }
 
+// 1 x 1 products on 128-pixel tiles: one by one where no two tiles share a line of the result.
+static void order_of_tiles() {
+    EXPECT(tiles_by_rows(7, 1, 1, 1, 7, 7, 4, 64, 8) && tiles_by_rows(7, 1, 1, 1, 7, 7, 2, 64, 8));        // whole images: 512 <- 2048, batch 128
+    EXPECT(!tiles_by_rows(7, 1, 1, 1, 7, 7, 4, 41, 15) && tiles_by_rows(7, 1, 1, 1, 7, 7, 4, 4, 28));      // many tiles, no multiple of eight
+    EXPECT(tiles_by_rows(2, 24, 1, 1, 48, 48, 4, 96, 4) && !tiles_by_rows(2, 24, 1, 1, 47, 47, 4, 96, 4)); // whole rows, on lines and off them
+    EXPECT(!tiles_by_rows(9, 2, 1, 1, 14, 14, 4, 128, 1) && !tiles_by_rows(1, 64, 2, 1, 64, 128, 4, 128, 1));
+    EXPECT(tiles_by_rows(4, 7, 1, 2, 56, 56, 4, 56, 8) && !tiles_by_rows(1, 7, 1, 1, 56, 56, 2, 56, 8));
+}
+
 int main() {
     long_filter_gradients();
     dealt_blocks();
+    order_of_tiles();
     std::printf("%d failures\n", fails);
     return fails != 0;
 }
