@@ -1,8 +1,12 @@
 """Forms that a rule on sizes chooses, at both sides of it, against the oracle (integers exactly, see test_gpu_parity)."""
+import numpy as np
 import pytest
+import torch
 
+from paper_2102_04782_amd import binding as daq
 from paper_2102_04782_amd import workloads as wl
 from test_gpu_kernel_edges import on_random_codes
+from test_gpu_parity import close, descs, dev, ref, t
 
 pytestmark = pytest.mark.gpu
 by_name = dict(ids=lambda l: l.name)
@@ -40,3 +44,41 @@ def test_blocks_of_the_streaming_form(layer):
 ], **by_name)
 def test_order_of_128_pixel_tiles(layer):
     on_random_codes(layer, 93)
+
+
+def codes_of(layer, seed):
+    rng = np.random.default_rng(seed)
+    q = [rng.integers(-127, 128, shape).astype(np.int8) for shape in (layer.x_shape, layer.w_shape, layer.y_shape)]
+    return (*q, (10.0 ** rng.uniform(-4, -1, layer.Cout)).astype(np.float32))
+
+
+@pytest.mark.parametrize("layer", [
+    wl.Layer("w1", 33, 4065, 9, 15, 272, 1, 1, 1, 0),        # 2112 workgroups of a 1 x 1 filter: waves of 32 rows x 128 pixels
+    wl.Layer("wt", 33, 1009, 9, 15, 20, 1, 3, 1, 0),         # run-time tap list, one chunk
+    wl.Layer("wt_chunks", 33, 1009, 9, 15, 80, 1, 3, 1, 0),
+    wl.Layer("t9_256", 16, 1009, 9, 15, 80, 3, 3, 1, 1),
+], **by_name)
+def test_bf16_results_of_the_wide_waves(layer):
+    d, rd = descs(layer)
+    _, qW, qG, _ = codes_of(layer, 94)
+    s_g, s_w = (torch.tensor([v], dtype=torch.float32, device=dev()) for v in (0.03, 0.11))
+    got = torch.full(d.x_shape, float("nan"), dtype=torch.bfloat16, device=dev())
+    daq.conv_bwd_data_int8_bf16(d, t(daq.layout_qg(d).pack(qG)), s_g, t(daq.layout_qw(d).pack(d, qW)), s_w, dX=got)
+    torch.cuda.synchronize()
+    want = ref.conv_bwd_data_int8_bf16(rd, qG, 0.03, qW, 0.11)
+    assert np.array_equal(got.view(torch.int16).cpu().numpy().view(np.uint16), want)
+
+
+@pytest.mark.parametrize("shift", [0, 1, 2, 3])
+@pytest.mark.parametrize("stride", [1, 2])
+def test_filter_gradient_results_at_any_element(shift, stride):
+    """3 x 3, complete tiles of a channel count that allows four results at a time: only where the result begins on 16 bytes."""
+    layer = wl.Layer("dW", 1, 64, 7 * stride, 7 * stride, 40, 3, 3, stride, 1)
+    d, rd = descs(layer)
+    qX, _, qG, s_c = codes_of(layer, 95)
+    buf = torch.full((shift + int(np.prod(layer.w_shape)) + 4,), 7.0, device=dev())
+    dW = buf[shift:shift + int(np.prod(layer.w_shape))].view(layer.w_shape)
+    daq.conv_bwd_filter_int8(d, t(daq.layout_qx_cnhw(d).pack(qX)), torch.tensor([2.5], device=dev()), t(daq.layout_vq(d).pack(qG)), t(s_c), dW=dW)
+    torch.cuda.synchronize()
+    close(dW.cpu().numpy(), ref.conv_bwd_filter_int8(rd, qX, 2.5, qG, s_c)[0], "dW")
+    assert bool((buf[:shift] == 7).all()) and bool((buf[shift + dW.numel():] == 7).all())
