@@ -60,6 +60,12 @@ bool tiles_by_rows(int TH, int tiles_h, int tiles_w, int stride, int Hd, int Wd,
     return tiles_w == 1 && (int64_t)stride * TH * Wd * bytes % 64 == 0 && (int64_t)Hd * Wd * bytes % 64 == 0;
 }
 
+// A run-time tap list: whether the waves take 32 rows x 128 pixels instead of 64 x 64 (see halo_role), from 512 workgroups on.  Not with several
+// chunks of many taps, 28 steps (tap x chunk) and more: beginning and end, which a second workgroup on the CU hides, are little of those, and a step
+// of 64 x 64 reads LDS half as often (848 <- 144 forward, 5 x 5 at 24 x 24, batch 34, with the quantizers 149 us wide, 140; 723 <- 376, 5 x 5, 18 x 18, batch 37, 0.945 of the time; 45 layers
+// 0.97, of fewer steps 1.01, of one chunk 1.06).
+bool wide_waves(int64_t blocks, int chunks, int taps) { return blocks > 512 && !(chunks > 1 && chunks * taps >= 28); }
+
 namespace {
 
 constexpr int kPxWg = 256;         // destination pixels per workgroup (128 in the small-tile form of 1 x 1 filters)
@@ -69,8 +75,7 @@ constexpr int kMaxTaps = 49;
 constexpr int kMaxUnits = 8;       // 16-byte units of the window a thread stages: up to 512 slots
 constexpr int kMaxPhases = 4;
 constexpr int kRingA = 4;          // filter tiles are requested kRingA - 1 steps ahead of their use
-// Workgroups from which the waves take 32 rows x 128 pixels instead of 64 x 64 (see halo_role): with a run-time tap list, and of 1 x 1 filters.
-constexpr int kWideBlocks = 512, kWideBlocks1 = 2048;
+constexpr int kWideBlocks1 = 2048;   // 1 x 1 filters: workgroups from which the waves take 32 rows x 128 pixels instead of 64 x 64 (see halo_role)
 constexpr uint32_t kOob = 0x80000000u;  // a buffer offset past every extent: such a load returns zeros
 
 struct HaloArgs {
@@ -132,7 +137,7 @@ __device__ __forceinline__ v4i buffer_load16(__amdgpu_buffer_rsrc_t rsrc, uint32
 // Data gradient, operands from memory: 312 <- 80, 3 x 3 at 41 x 41, batch 40, 63.6 us and 41.7; 400 <- 16 at 49 x 49, batch 53, 62 and 49; 451 <- 368 at 15 x 15,
 // batch 66, 47 and 38; 1.13 times the speed over 24 drawn 3 x 3 layers.  128-pixel tiles of 3 x 3 filters: 512 <- 512 at 7 x 7, batch 64, 16.6 us with 64 x 32,
 // 13.8 with 32 x 64.  What is left is where a step with fewer reads of LDS is the shorter one, hardly a workgroup to a CU or hardly any arithmetic:
-// 64 x 64 up to 512 workgroups with a run-time tap list (80 <- 992, 5 x 5 at 34 x 34, batch 37, 141 us and 154), up to 2048 of 1 x 1 filters (512 <-
+// 64 x 64 up to 512 workgroups with a run-time tap list or with many steps (wide_waves; 80 <- 992, 5 x 5 at 34 x 34, batch 37, 141 us and 154), up to 2048 of 1 x 1 filters (512 <-
 // 1024 at 14 x 14, batch 64, 22.5 and 23.5; beyond, 912 <- 560 at stride 2, 81 x 81, batch 75, 650 and 601), 64 x 32 for 128-pixel tiles of 1 x 1 filters (2048 <- 512 at
 // 7 x 7, batch 64, 18.2 and 21.5).
 // DB = the contraction axis has more than one 64-byte chunk (two window buffers, restaged per chunk).
@@ -822,6 +827,9 @@ int64_t blocks_per_row_tile(const HaloArgs& a) {
     return (int64_t)a.groups * a.tiles_h * a.tiles_w * (a.stride > 1 && !a.zfill ? a.stride * a.stride : 1);
 }
 
+// Taps of the parity class that has most.
+int max_taps(const HaloArgs& a) { return *std::max_element(a.ph_taps, a.ph_taps + a.stride * a.stride); }
+
 // floor division for possibly negative numerators
 int floor_div(int a, int b) { return a >= 0 ? a / b : -((-a + b - 1) / b); }
 
@@ -1040,7 +1048,7 @@ daq_status launch(Geometry& g, hipStream_t st, const HaloNames& names) {
 #undef DAQ_HALO_NARROW
     } else {
         // (many workgroups: waves of 32 rows x 128 pixels, as above)
-        const bool wide = g.a.main_blocks > kWideBlocks;
+        const bool wide = wide_waves(g.a.main_blocks, (int)ceil_div(a.cp, kKc), max_taps(a));
         auto kern = wide ? (a.double_buffer ? (a.stride == 2 ? k_conv_halo<2, true, 2, 4, 0, 1> : k_conv_halo<2, true, 1, 4, 0, 1>)
                                             : (a.stride == 2 ? k_conv_halo<2, false, 2, 4, 0, 1> : k_conv_halo<2, false, 1, 4, 0, 1>))
                          : (a.double_buffer ? (a.stride == 2 ? k_conv_halo<1, true, 2, 4> : k_conv_halo<1, true, 1, 4>)
@@ -1192,7 +1200,7 @@ daq_status launch3(Plan3& pl, const int8_t* filter, void* frag, const char* name
     a.wfrag = (const int8_t*)frag;
     const int64_t blocks = blocks_per_row_tile(a) * ceil_div(a.Crow, 64);
     a.main_blocks = (int)blocks;
-    const bool wide = blocks > kWideBlocks;
+    const bool wide = wide_waves(blocks, 1, 1);
     auto kern = a.stride == 2 ? (a.Crow <= 32 ? k_conv_halo<1, true, 2, 4, 0, 1, kPxWg, true> : k_conv_halo<1, true, 2, 4, 0, 2, kPxWg, true>)
                 : a.Crow <= 32 && pl.g.px == kPxWg ? k_conv_halo<1, true, 1, 4, 0, 1, kPxWg, true>
                 : taps9_applies(pl.g) ? (pl.g.px == kPxWg ? k_conv_halo<2, true, 1, 4, 9, 1, kPxWg, true> : k_conv_halo<2, true, 1, 4, 9, 1, 128, true>)
@@ -1266,8 +1274,7 @@ daq_status launch_stream(const char* name, const daq_conv_desc& d, const daq_lay
 
 static OtherKernel as_other(const Geometry& g) {
     const HaloArgs& a = g.a;
-    int taps = a.ph_taps[0];
-    for (int c = 1; c < a.stride * a.stride; ++c) taps = std::max(taps, a.ph_taps[c]);
+    const int taps = max_taps(a);
     // The prices are those of the forms and grids they were fitted to: tiles of 128 rows where those would fill the chip, a strided layer's tiles
     // by the eight.  (Such products have become 1.1 to 1.7 times faster since.)
     const TileForm form = g.priced128         ? TileForm::kRows128

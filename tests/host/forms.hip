@@ -50,10 +50,17 @@ static void order_of_tiles() {
     EXPECT(tiles_by_rows(4, 7, 1, 2, 56, 56, 4, 56, 8) && !tiles_by_rows(1, 7, 1, 1, 56, 56, 2, 56, 8));
 }
 
+// The tile kernel with a run-time tap list.
+static void waves_of_tiles() {
+    EXPECT(wide_waves(4932, 1, 25) && wide_waves(513, 2, 9) && wide_waves(3920, 3, 2) && wide_waves(4320, 1, 49));
+    EXPECT(!wide_waves(512, 1, 25) && !wide_waves(1428, 3, 25) && !wide_waves(912, 3, 25) && !wide_waves(888, 6, 25) && !wide_waves(1053, 4, 7));
+}
+
 int main() {
     long_filter_gradients();
     dealt_blocks();
     order_of_tiles();
+    waves_of_tiles();
     std::printf("%d failures\n", fails);
     return fails != 0;
 }
