@@ -66,6 +66,11 @@ bool tiles_by_rows(int TH, int tiles_h, int tiles_w, int stride, int Hd, int Wd,
 // 0.97, of fewer steps 1.01, of one chunk 1.06).
 bool wide_waves(int64_t blocks, int chunks, int taps) { return blocks > 512 && !(chunks > 1 && chunks * taps >= 28); }
 
+// The same of 1 x 1 filters, 256-pixel tiles: from 2048 workgroups on, and at stride 2 on rows of odd length, whose results leave element by
+// element: two workgroups to a CU then hide that (64 x 64 and wide: 1128 <- 64 at 17 x 17, batch 25, 25.7 us and 21.3; 1146 <- 192 at 41 x 41, batch 13, 60.2 and 52.7; 80 <- 192
+// at 49 x 49, batch 72, 1.13 times the speed; 24 layers 1.08, none slower.  On rows of even length 0.90 to 1.10, 29 layers 1.00).
+bool wide_waves1(int64_t blocks, int stride, int Wd) { return blocks > 2048 || (stride == 2 && (Wd & 1)); }
+
 namespace {
 
 constexpr int kPxWg = 256;         // destination pixels per workgroup (128 in the small-tile form of 1 x 1 filters)
@@ -75,7 +80,6 @@ constexpr int kMaxTaps = 49;
 constexpr int kMaxUnits = 8;       // 16-byte units of the window a thread stages: up to 512 slots
 constexpr int kMaxPhases = 4;
 constexpr int kRingA = 4;          // filter tiles are requested kRingA - 1 steps ahead of their use
-constexpr int kWideBlocks1 = 2048;   // 1 x 1 filters: workgroups from which the waves take 32 rows x 128 pixels instead of 64 x 64 (see halo_role)
 constexpr uint32_t kOob = 0x80000000u;  // a buffer offset past every extent: such a load returns zeros
 
 struct HaloArgs {
@@ -137,7 +141,7 @@ __device__ __forceinline__ v4i buffer_load16(__amdgpu_buffer_rsrc_t rsrc, uint32
 // Data gradient, operands from memory: 312 <- 80, 3 x 3 at 41 x 41, batch 40, 63.6 us and 41.7; 400 <- 16 at 49 x 49, batch 53, 62 and 49; 451 <- 368 at 15 x 15,
 // batch 66, 47 and 38; 1.13 times the speed over 24 drawn 3 x 3 layers.  128-pixel tiles of 3 x 3 filters: 512 <- 512 at 7 x 7, batch 64, 16.6 us with 64 x 32,
 // 13.8 with 32 x 64.  What is left is where a step with fewer reads of LDS is the shorter one, hardly a workgroup to a CU or hardly any arithmetic:
-// 64 x 64 up to 512 workgroups with a run-time tap list or with many steps (wide_waves; 80 <- 992, 5 x 5 at 34 x 34, batch 37, 141 us and 154), up to 2048 of 1 x 1 filters (512 <-
+// 64 x 64 up to 512 workgroups with a run-time tap list or with many steps (wide_waves; 80 <- 992, 5 x 5 at 34 x 34, batch 37, 141 us and 154), up to 2048 of 1 x 1 filters (wide_waves1; 512 <-
 // 1024 at 14 x 14, batch 64, 22.5 and 23.5; beyond, 912 <- 560 at stride 2, 81 x 81, batch 75, 650 and 601), 64 x 32 for 128-pixel tiles of 1 x 1 filters (2048 <- 512 at
 // 7 x 7, batch 64, 18.2 and 21.5).
 // DB = the contraction axis has more than one 64-byte chunk (two window buffers, restaged per chunk).
@@ -1015,7 +1019,7 @@ daq_status launch(Geometry& g, hipStream_t st, const HaloNames& names) {
             g.a.row_tiles = (int)ptiles;
             g.a.div_row_tiles = make_fastdiv((uint32_t)ptiles);
         }
-        const bool wide = g.a.main_blocks > kWideBlocks1;
+        const bool wide = wide_waves1(g.a.main_blocks, a.stride, a.Wd);
         auto kern = a.stride == 2 ? (g.px != kPxWg ? k_conv_halo<1, true, 2, 4, 1, 2, 128> : wide ? k_conv_halo<2, true, 2, 4, 1, 1> : k_conv_halo<1, true, 2, 4, 1>)
                                   : (g.px != kPxWg ? k_conv_halo<1, true, 1, 4, 1, 2, 128> : wide ? k_conv_halo<2, true, 1, 4, 1, 1> : k_conv_halo<1, true, 1, 4, 1>);
         if (!allow_lds((const void*)kern, g.lds_bytes))

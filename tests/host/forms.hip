@@ -50,9 +50,10 @@ static void order_of_tiles() {
     EXPECT(tiles_by_rows(4, 7, 1, 2, 56, 56, 4, 56, 8) && !tiles_by_rows(1, 7, 1, 1, 56, 56, 2, 56, 8));
 }
 
-// The tile kernel with a run-time tap list.
+// The tile kernel with a run-time tap list, and of 1 x 1 filters.
 static void waves_of_tiles() {
     EXPECT(wide_waves(4932, 1, 25) && wide_waves(513, 2, 9) && wide_waves(3920, 3, 2) && wide_waves(4320, 1, 49));
+    EXPECT(wide_waves1(396, 2, 11) && wide_waves1(2049, 1, 56) && !wide_waves1(2048, 1, 11) && !wide_waves1(520, 2, 40));
     EXPECT(!wide_waves(512, 1, 25) && !wide_waves(1428, 3, 25) && !wide_waves(912, 3, 25) && !wide_waves(888, 6, 25) && !wide_waves(1053, 4, 7));
 }
 

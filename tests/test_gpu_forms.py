@@ -82,3 +82,12 @@ def test_filter_gradient_results_at_any_element(shift, stride):
     torch.cuda.synchronize()
     close(dW.cpu().numpy(), ref.conv_bwd_filter_int8(rd, qX, 2.5, qG, s_c)[0], "dW")
     assert bool((buf[:shift] == 7).all()) and bool((buf[shift + dW.numel():] == 7).all())
+
+
+@pytest.mark.parametrize("layer", [
+    wl.Layer("odd", 33, 700, 17, 19, 70, 1, 1, 2, 0),
+    wl.Layer("odd_columns", 12, 1000, 34, 37, 65, 1, 1, 2, 0),
+    wl.Layer("odd_lines", 12, 1000, 37, 34, 65, 1, 1, 2, 0),
+], **by_name)
+def test_strided_1x1_products_on_odd_rows(layer):
+    on_random_codes(layer, 96)
