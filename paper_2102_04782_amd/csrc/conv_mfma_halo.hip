@@ -48,16 +48,31 @@ int64_t stream_deal(int64_t out_bytes, int64_t plane_bytes, int cp, int pairs, i
     return pairs >= 27 ? 0 : 8 * pairs;
 }
 
-// 1 x 1 products on 128-pixel tiles, whose workgroups all run at once: where no two tiles share a line of the result - tiles of whole images, or
-// of whole rows that begin and end with one - only the filter is left to share, and the blocks go out one by one, row tile after row tile, all tiles of
-// one filter tile together.  (Operands from memory, tile after tile and so: 512 <- 2048 at 7 x 7, batch 128, 24.0 us and 23.4; 256 <- 768 at 48 x 48,
+// Whether two tiles of a 1 x 1 product share a 64-byte line of the result: not where they are whole images, or whole rows or pieces of rows that begin and
+// end with a line.
+static bool tiles_share_lines(int TH, int TW, int tiles_h, int tiles_w, int stride, int Hd, int Wd, int bytes) {
+    if (tiles_h * tiles_w == 1) return false;
+    if (tiles_w > 1) return (int64_t)stride * TW * bytes % 64 != 0 || (int64_t)Wd * bytes % 64 != 0;
+    return (int64_t)stride * TH * Wd * bytes % 64 != 0 || (int64_t)Hd * Wd * bytes % 64 != 0;
+}
+
+// 1 x 1 products on 128-pixel tiles, whose workgroups all run at once: where no two tiles share a line of the result
+// only the filter is left to share, and the blocks go out one by one, row tile after row tile, all tiles of one filter tile together.  (Operands from memory, tile after tile and so: 512 <- 2048 at 7 x 7, batch 128, 24.0 us and 23.4; 256 <- 768 at 48 x 48,
 // batch 4, 1.12 times the speed; 105 layers at stride 2 1.018, 12 at unit stride with cut images 1.03.)  Not with many tiles that are no multiple of eight:
 // the row tiles of one then lie on several XCDs, each of which fetches its window (512 <- 80 at stride 2, 24 x 24, batch 33, 66 tiles, 13.8 and 15.3;
 // 928 <- 1104 at 7 x 7, batch 82, 41 tiles, 22.3 and 24.2).
-bool tiles_by_rows(int TH, int tiles_h, int tiles_w, int stride, int Hd, int Wd, int bytes, int64_t tiles, int row_tiles) {
+bool tiles_by_rows(int TH, int TW, int tiles_h, int tiles_w, int stride, int Hd, int Wd, int bytes, int64_t tiles, int row_tiles) {
     if (tiles % kXcd != 0 && tiles >= 32 && row_tiles > 3) return false;
-    if (tiles_h * tiles_w == 1) return true;
-    return tiles_w == 1 && (int64_t)stride * TH * Wd * bytes % 64 == 0 && (int64_t)Hd * Wd * bytes % 64 == 0;
+    return !tiles_share_lines(TH, TW, tiles_h, tiles_w, stride, Hd, Wd, bytes);
+}
+
+// 1 x 1 products at unit stride on 256-pixel tiles that share no line: an eighth of the result to each XCD has them write eight places at once whose
+// distance may be one of the memory channels' (48 x 48: 512 <- 320, batch 58, 148 us; 256 <- 320, batch 62, 82).  An XCD has
+// every eighth tile instead, still with all its row tiles, and the chip writes one place (118 and 71; 1.05 times the speed over 25 layers of more
+// than 1000 workgroups, worst 0.98).  Of fewer workgroups only where that leaves no tile over (1024 <- 384 at 20 x 20, batch 19, 38 tiles, 0.89 times the speed).
+bool tiles_spread(int TH, int TW, int tiles_h, int tiles_w, int Hd, int Wd, int bytes, int64_t tiles, int row_tiles) {
+    if (tiles % kXcd != 0 && tiles * row_tiles <= 1000) return false;
+    return !tiles_share_lines(TH, TW, tiles_h, tiles_w, 1, Hd, Wd, bytes);
 }
 
 // A run-time tap list: whether the waves take 32 rows x 128 pixels instead of 64 x 64 (see halo_role), from 512 workgroups on.  Not with several
@@ -91,19 +106,18 @@ struct HaloArgs {
     int tiles_h, tiles_w;
     int zfill;            // stride 2, only parity class (0, 0) has taps: its workgroups also write the zeros of the other three
     FastDiv div_row_tiles, div_tiles_hw, div_tiles_w;
-    int NI;
-    int TH, TW;           // destination tile, NI images, in pixels of one parity class
+    int spread;           // tiles_spread: the workgroups of whole eights of tiles
+    int NI, TH, TW;       // destination tile, NI images, in pixels of one parity class
     int SH, SW;           // source window per image (the largest over the classes)
     int N, Hs, Ws, cp;
     int units;            // 16-byte window units per thread
     FastDiv div_si, div_sw;
-    int T;                // kH*kW
     const int8_t* src;    // pixel operand, NHWC [N][Hs][Ws][cp]
     const int8_t* wfrag;  // filter operand in fragment order
     uint32_t src_bytes, wfrag_bytes;
     const float* s_a;
     const float* s_b;
-    int RB;               // 32-row blocks of the filter copy
+    int RB, T;            // 32-row blocks of the filter copy, kH*kW
     // per parity class: live taps, window origin relative to the tile's first pixel
     int ph_taps[kMaxPhases], ph_org_h[kMaxPhases], ph_org_w[kMaxPhases];
     FastDiv div_tw, div_thw;
@@ -126,7 +140,7 @@ struct HaloArgs {
     int tap_slot[kMaxPhases][kMaxTaps];  // slot offset a tap adds inside the window
     int tap_id[kMaxPhases][kMaxTaps];    // kh*kW + kw of the tap
 };
-static_assert(offsetof(HaloArgs, NI) == 60 && offsetof(HaloArgs, src) == 128 && offsetof(HaloArgs, ph_org_h) <= 192, "lines of arguments");
+static_assert(offsetof(HaloArgs, NI) == 64 && offsetof(HaloArgs, src) == 128 && offsetof(HaloArgs, ph_org_h) <= 192, "lines of arguments");
 
 __device__ __forceinline__ v4i buffer_load16(__amdgpu_buffer_rsrc_t rsrc, uint32_t voffset, uint32_t soffset) {
     return __builtin_amdgcn_raw_buffer_load_b128(rsrc, (int)voffset, (int)soffset, 0);
@@ -167,12 +181,13 @@ __device__ __forceinline__ void halo_role(const HaloArgs& p, const uint32_t bid)
     extern __shared__ __align__(16) int8_t lds[];   // one or two window buffers of S slots
 
     // (kept whole by the empty statement: the compiler would ask piece by piece, with a wait for each)
-    uint32_t main_blocks = (uint32_t)p.main_blocks, row_tiles = (uint32_t)p.row_tiles, rows_first = (uint32_t)p.by_rows;
-    int tiles_h = p.tiles_h, tiles_w = p.tiles_w, zfill = p.zfill, NI = p.NI;
+    uint32_t main_blocks = (uint32_t)p.main_blocks, row_tiles = (uint32_t)p.row_tiles, rows_first = (uint32_t)p.by_rows, spread = (uint32_t)p.spread;
+    int tiles_h = p.tiles_h, tiles_w = p.tiles_w, zfill = p.zfill;
     FastDiv div_row_tiles = p.div_row_tiles, div_tiles_hw = p.div_tiles_hw, div_tiles_w = p.div_tiles_w;
-    asm volatile("" : "+s"(main_blocks), "+s"(row_tiles), "+s"(rows_first), "+s"(tiles_h), "+s"(tiles_w), "+s"(zfill), "+s"(NI), "+s"(div_row_tiles.mul),
+    asm volatile("" : "+s"(main_blocks), "+s"(row_tiles), "+s"(rows_first), "+s"(spread), "+s"(tiles_h), "+s"(tiles_w), "+s"(zfill), "+s"(div_row_tiles.mul),
                       "+s"(div_row_tiles.shift), "+s"(div_row_tiles.one), "+s"(div_tiles_hw.mul), "+s"(div_tiles_hw.shift), "+s"(div_tiles_hw.one),
                       "+s"(div_tiles_w.mul), "+s"(div_tiles_w.shift), "+s"(div_tiles_w.one) : "s"(p.TH), "s"(p.src));   // (and the next two lines are on their way)
+    const int NI = p.NI;
     if (bid >= main_blocks) {   // uniform
         dw_reduce_role(p.tail, (int)(bid - main_blocks), reinterpret_cast<int32_t*>(lds));
         return;
@@ -189,14 +204,16 @@ __device__ __forceinline__ void halo_role(const HaloArgs& p, const uint32_t bid)
     // 512, 1 x 1 at stride 2, 56 x 56, batch 64, 59.8 and 63.  An XCD's tiles 4 or 16 at a time, or its row tiles one after the other, were slower.)
     const uint32_t xcd = bid % kXcd, each = main_blocks / kXcd, more = main_blocks % kXcd;
     const bool by_rows = TAPS == 1 && PX == 128 && rows_first != 0;   // tiles_by_rows: the blocks' own order, row tile after row tile
-    uint32_t at = by_rows ? bid : bid / kXcd + xcd * each + min(xcd, more);
+    constexpr bool kSpread = TAPS == 1 && PX == kPxWg && ST == 1;
+    const bool dealt = kSpread && bid < spread;   // tiles_spread: of every eight tiles an XCD has one, with all its row tiles; what is left over, block by block
+    uint32_t at = by_rows || (kSpread && spread > 0 && !dealt) ? bid : bid / kXcd + (dealt ? 0u : xcd * each + min(xcd, more));
     int phase = 0;
     if (ST > 1 && !zfill) {
         phase = (int)(at % (ST * ST));
         at /= ST * ST;
     }
     const int quot = (int)fdiv(at, div_row_tiles), left = (int)(at - (uint32_t)quot * row_tiles);   // (by rows: of the tiles of a row tile)
-    const int tp = by_rows ? left : quot, tr = by_rows ? quot : left;
+    const int tp = by_rows ? left : dealt ? quot * kXcd + (int)xcd : quot, tr = by_rows ? quot : left;
     const int pa = phase / ST, pb = phase % ST;
     const int grp = (int)fdiv((uint32_t)tp, div_tiles_hw);
     const int trem = tp - grp * tiles_h * tiles_w;
@@ -1014,11 +1031,13 @@ daq_status launch(Geometry& g, hipStream_t st, const HaloNames& names) {
     const bool ring1 = ring1_applies(g);
     if (g.px != kPxWg && !ring1 && !taps9_applies(g)) return DAQ_ERR_UNSUPPORTED;   // small tiles exist in these two forms only (see plan_small)
     if (ring1) {
-        if (g.px != kPxWg && tiles_by_rows(a.TH, a.tiles_h, a.tiles_w, a.stride, a.Hd, a.Wd, a.bf16 ? 2 : 4, ptiles, a.row_tiles)) {
+        if (g.px != kPxWg && tiles_by_rows(a.TH, a.TW, a.tiles_h, a.tiles_w, a.stride, a.Hd, a.Wd, a.bf16 ? 2 : 4, ptiles, a.row_tiles)) {
             g.a.by_rows = 1;
             g.a.row_tiles = (int)ptiles;
             g.a.div_row_tiles = make_fastdiv((uint32_t)ptiles);
         }
+        if (g.px == kPxWg && a.stride == 1 && tiles_spread(a.TH, a.TW, a.tiles_h, a.tiles_w, a.Hd, a.Wd, a.bf16 ? 2 : 4, ptiles, a.row_tiles))
+            g.a.spread = (int)(ptiles / kXcd * kXcd * a.row_tiles);
         const bool wide = wide_waves1(g.a.main_blocks, a.stride, a.Wd);
         auto kern = a.stride == 2 ? (g.px != kPxWg ? k_conv_halo<1, true, 2, 4, 1, 2, 128> : wide ? k_conv_halo<2, true, 2, 4, 1, 1> : k_conv_halo<1, true, 2, 4, 1>)
                                   : (g.px != kPxWg ? k_conv_halo<1, true, 1, 4, 1, 2, 128> : wide ? k_conv_halo<2, true, 1, 4, 1, 1> : k_conv_halo<1, true, 1, 4, 1>);

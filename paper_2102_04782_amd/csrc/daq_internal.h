@@ -287,7 +287,9 @@ daq_status conv3d_fwd_halo(const daq_conv3d_desc& d, const int8_t* qx, const int
                            int32_t* acc, void* frag, hipStream_t st);
 
 // conv_mfma_halo.hip, 1 x 1 products on 128-pixel tiles: whether their workgroups go row tile after row tile
-bool tiles_by_rows(int TH, int tiles_h, int tiles_w, int stride, int Hd, int Wd, int bytes, int64_t tiles, int row_tiles);
+bool tiles_by_rows(int TH, int TW, int tiles_h, int tiles_w, int stride, int Hd, int Wd, int bytes, int64_t tiles, int row_tiles);
+// of 256-pixel tiles at unit stride: whether an XCD has every eighth tile instead of an eighth of them
+bool tiles_spread(int TH, int TW, int tiles_h, int tiles_w, int Hd, int Wd, int bytes, int64_t tiles, int row_tiles);
 bool wide_waves(int64_t blocks, int chunks, int taps);   // a run-time tap list: waves of 32 rows x 128 pixels instead of 64 x 64
 bool wide_waves1(int64_t blocks, int stride, int Wd);           // the same of 1 x 1 filters
 // streaming 1 x 1 products: blocks that an XCD takes in a row, 0: one by one

@@ -43,11 +43,13 @@ static void dealt_blocks() {
 
 // 1 x 1 products on 128-pixel tiles: one by one where no two tiles share a line of the result.
 static void order_of_tiles() {
-    EXPECT(tiles_by_rows(7, 1, 1, 1, 7, 7, 4, 64, 8) && tiles_by_rows(7, 1, 1, 1, 7, 7, 2, 64, 8));        // whole images: 512 <- 2048, batch 128
-    EXPECT(!tiles_by_rows(7, 1, 1, 1, 7, 7, 4, 41, 15) && tiles_by_rows(7, 1, 1, 1, 7, 7, 4, 4, 28));      // many tiles, no multiple of eight
-    EXPECT(tiles_by_rows(2, 24, 1, 1, 48, 48, 4, 96, 4) && !tiles_by_rows(2, 24, 1, 1, 47, 47, 4, 96, 4)); // whole rows, on lines and off them
-    EXPECT(!tiles_by_rows(9, 2, 1, 1, 14, 14, 4, 128, 1) && !tiles_by_rows(1, 64, 2, 1, 64, 128, 4, 128, 1));
-    EXPECT(tiles_by_rows(4, 7, 1, 2, 56, 56, 4, 56, 8) && !tiles_by_rows(1, 7, 1, 1, 56, 56, 2, 56, 8));
+    EXPECT(tiles_by_rows(7, 7, 1, 1, 1, 7, 7, 4, 64, 8) && tiles_by_rows(7, 7, 1, 1, 1, 7, 7, 2, 64, 8));          // whole images: 512 <- 2048, batch 128
+    EXPECT(!tiles_by_rows(7, 7, 1, 1, 1, 7, 7, 4, 41, 15) && tiles_by_rows(7, 7, 1, 1, 1, 7, 7, 4, 4, 28));        // many tiles, no multiple of eight
+    EXPECT(tiles_by_rows(2, 48, 24, 1, 1, 48, 48, 4, 96, 4) && !tiles_by_rows(2, 47, 24, 1, 1, 47, 47, 4, 96, 4)); // whole rows, on lines and off them
+    EXPECT(tiles_by_rows(8, 16, 8, 4, 1, 64, 64, 4, 160, 4) && !tiles_by_rows(8, 12, 8, 4, 1, 64, 48, 4, 160, 4)); // pieces of rows
+    EXPECT(!tiles_by_rows(9, 14, 2, 1, 1, 14, 14, 4, 128, 1) && tiles_by_rows(4, 28, 7, 1, 2, 56, 56, 4, 56, 8) && !tiles_by_rows(1, 56, 56, 1, 1, 56, 56, 2, 56, 8));
+    EXPECT(tiles_spread(16, 16, 3, 3, 48, 48, 4, 522, 8) && tiles_spread(16, 16, 3, 3, 48, 48, 4, 558, 4) && tiles_spread(16, 16, 3, 3, 48, 48, 4, 216, 2));
+    EXPECT(!tiles_spread(12, 20, 2, 1, 20, 20, 4, 38, 16) && !tiles_spread(3, 74, 25, 1, 74, 74, 4, 144, 7) && tiles_spread(14, 14, 1, 1, 14, 14, 4, 128, 16));
 }
 
 // The tile kernel with a run-time tap list, and of 1 x 1 filters.

@@ -46,6 +46,17 @@ def test_order_of_128_pixel_tiles(layer):
     on_random_codes(layer, 93)
 
 
+@pytest.mark.parametrize("layer", [
+    wl.Layer("eights", 16, 1600, 16, 16, 260, 1, 1, 1, 0),   # sixteen tiles of an image
+    wl.Layer("left_over", 44, 1500, 14, 14, 260, 1, 1, 1, 0),   # 44 tiles, 1056 workgroups: five eights and four
+    wl.Layer("rows", 5, 1500, 48, 32, 260, 1, 1, 1, 0),      # tiles of eight whole rows
+    wl.Layer("pieces", 2, 1500, 48, 48, 260, 1, 1, 1, 0),    # nine tiles of 16 x 16 an image
+    wl.Layer("few", 18, 1500, 14, 14, 260, 1, 1, 1, 0),      # 18 tiles, 432 workgroups: an eighth to each XCD
+], **by_name)
+def test_order_of_256_pixel_tiles(layer):
+    on_random_codes(layer, 97)
+
+
 def codes_of(layer, seed):
     rng = np.random.default_rng(seed)
     q = [rng.integers(-127, 128, shape).astype(np.int8) for shape in (layer.x_shape, layer.w_shape, layer.y_shape)]
