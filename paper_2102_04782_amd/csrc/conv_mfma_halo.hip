@@ -151,7 +151,7 @@ __device__ __forceinline__ v4i buffer_load16(__amdgpu_buffer_rsrc_t rsrc, uint32
 // (WR 2, NX 2) 64 x 64, a workgroup of 128 rows.
 //   Filter tiles come through the vector memory pipe, 64 bytes a clock for the whole CU, pixels from LDS, 128 bytes a clock.  With waves of 64 x 64 each of the
 // four asks for the same 4 KiB of filter a step, 256 clocks for 256 of multiplies, and registers allow one workgroup to a CU, so that its prologue, its
-// barriers and its stores show.  With 32 x 128 a wave asks for 2 KiB, LDS delivers twice as much, and two workgroups fit (3 x 3: 245 registers for 310).
+// barriers and its stores show.  With 32 x 128 a wave asks for 2 KiB, LDS delivers twice as much, and two workgroups fit (3 x 3: 245 registers for 310, 250 in 3-D).
 // Data gradient, operands from memory: 312 <- 80, 3 x 3 at 41 x 41, batch 40, 63.6 us and 41.7; 400 <- 16 at 49 x 49, batch 53, 62 and 49; 451 <- 368 at 15 x 15,
 // batch 66, 47 and 38; 1.13 times the speed over 24 drawn 3 x 3 layers.  128-pixel tiles of 3 x 3 filters: 512 <- 512 at 7 x 7, batch 64, 16.6 us with 64 x 32,
 // 13.8 with 32 x 64.  What is left is where a step with fewer reads of LDS is the shorter one, hardly a workgroup to a CU or hardly any arithmetic:
@@ -236,7 +236,9 @@ __device__ __forceinline__ void halo_role(const HaloArgs& p, const uint32_t bid)
     // ---- window staging: unit i of a thread is chunk (tid & 3) of slot (tid >> 2) + SPT*i ----
     const int sc = tid & 3;
     uint32_t hoff[kMaxUnits];
-    int hz[D3 ? kMaxUnits : 1];   // D3: the destination frame's depth; hoff is then the offset in frame 0 of the sample
+    // D3: the destination frame's depth (below 65536, plan3), two in a register where those are scarce; hoff is then the offset in frame 0 of the sample
+    constexpr bool kPacked = D3 && TAPS == 9 && PX == kPxWg;
+    uint32_t hz[D3 ? kPacked ? kMaxUnits / 2 : kMaxUnits : 1] = {};
 #pragma unroll
     for (int i = 0; i < kMaxUnits; ++i) {
         hoff[i] = kOob;
@@ -250,7 +252,9 @@ __device__ __forceinline__ void halo_role(const HaloArgs& p, const uint32_t bid)
             const bool ok = slot < S && n < p.N && (unsigned)hs < (unsigned)p.Hs && (unsigned)ws < (unsigned)p.Ws;
             if constexpr (D3) {
                 const int smp = (int)fdiv((uint32_t)n, p.div_dd);
-                hz[i] = n - smp * p.Dd;
+                const uint32_t z = (uint32_t)(n - smp * p.Dd);
+                if constexpr (kPacked) hz[i / 2] |= z << 16 * (i % 2);
+                else hz[i] = z;
                 if (ok) hoff[i] = (uint32_t)(((smp * p.Ds * p.Hs + hs) * p.Ws + ws) * p.cp + 16 * sc);
             } else {
                 if (ok) hoff[i] = (uint32_t)(((n * p.Hs + hs) * p.Ws + ws) * p.cp + 16 * sc);
@@ -263,10 +267,12 @@ __device__ __forceinline__ void halo_role(const HaloArgs& p, const uint32_t bid)
             const int kd = (int)fdiv((uint32_t)kci, p.div_nkc), kc = kci - kd * p.nkc_frame;
             const bool kok = kci < nkc && kc * kKc + 16 * sc < p.cp;
             const uint32_t frame = (uint32_t)(p.Hs * p.Ws * p.cp);
+            if constexpr (kPacked) asm volatile("" : "+v"(hz[0]), "+v"(hz[1]), "+v"(hz[2]), "+v"(hz[3]));   // (unpacked ahead of the loop they would spill)
 #pragma unroll
             for (int i = 0; i < kMaxUnits; ++i)
                 if (i < p.units) {   // uniform
-                    const int t = p.fwd ? (hz[i] << p.sD_log2) + kd * p.dD - p.pD : hz[i] + p.pD - kd * p.dD;
+                    const int z = (int)(kPacked ? hz[i / 2] >> 16 * (i % 2) & 0xFFFFu : hz[kPacked ? 0 : i]);
+                    const int t = p.fwd ? (z << p.sD_log2) + kd * p.dD - p.pD : z + p.pD - kd * p.dD;
                     const int zs = p.fwd ? t : t >> p.sD_log2;   // arithmetic shift: a negative t stays negative
                     const bool zok = (unsigned)zs < (unsigned)p.Ds && (p.fwd || (zs << p.sD_log2) == t);
                     rh[i] = buffer_load16(rs_src, kok && zok && hoff[i] != kOob ? hoff[i] + (uint32_t)zs * frame : kOob, (uint32_t)(kc * kKc));
@@ -1196,7 +1202,7 @@ Plan3 plan3(bool backward, const daq_conv3d_desc& d) {
     const int64_t src_bytes = round_up((int64_t)d.N * Ds * Hs * Ws * pl.kp, 256);
     const int nkc_frame = (int)ceil_div(pl.kp, kKc), taps = d.kH * d.kW;
     pl.frag_bytes = (int64_t)d.kD * nkc_frame * taps * ceil_div(rows, 32) * 2048;
-    if (src_bytes >= ((int64_t)1 << 31) || pl.frag_bytes >= ((int64_t)1 << 31) || (int64_t)d.N * Dd >= ((int64_t)1 << 31)) return pl;
+    if (src_bytes >= ((int64_t)1 << 31) || pl.frag_bytes >= ((int64_t)1 << 31) || (int64_t)d.N * Dd >= ((int64_t)1 << 31) || Dd > 65535) return pl;
     auto make = [&](int px) {
         return plan(backward, d.N * Dd, Hs, Ws, pl.kp, Hd, Wd, rows, d.kH, d.kW, d.strideH, d.strideW, d.padH, d.padW, d.dilH, d.dilW, px,
                     true);

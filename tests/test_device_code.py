@@ -70,3 +70,17 @@ def test_matrix_instructions_wait_for_what_vector_instructions_wrote(code_object
             del recent[:-4]
     assert seen > 1000
     assert not bad, (len(bad), bad[:5])
+
+
+def test_kernels_of_products_keep_their_registers(code_objects):
+    """No kernel that multiplies matrices keeps vector registers in memory: forms and launch bounds are chosen so that they fit."""
+    kernels, bad = 0, []
+    for path in code_objects:
+        for block in _tool("llvm-readelf", "--notes", path).split(".agpr_count")[1:]:
+            name = re.search(r"\.name:\s+(\S+)", block)[1]
+            spilled = int(re.search(r"\.vgpr_spill_count:\s+(\d+)", block)[1])
+            if re.search("k_conv_|k_dw|k_dx_|k_bwd_both|k_nhwc", name):
+                kernels += 1
+                if spilled:
+                    bad.append((name, spilled))
+    assert kernels > 50 and not bad, bad
