@@ -866,7 +866,6 @@ struct Geometry {
     size_t lds_bytes;
     int rows;
     int px;   // destination pixels per workgroup
-    bool priced128;   // as_other
 };
 
 // 1 x 1 filters with several contraction chunks, on 64-row tiles: the form with rings of chunks.  Unit stride, or
@@ -970,9 +969,7 @@ Geometry plan(bool backward, int N, int Hs, int Ws, int cp, int Hd, int Wd, int 
     // Tiles of 64 rows, two workgroups to a CU; of 128 rows, one to a CU, only for a single chunk by parity classes, where they fill the chip (384 <- 16
     // at 59 x 59, batch 78: 130 us and 163 on 64 rows; elsewhere the other way round, up to 1.7 times: 192 <- 110, 5 x 5, 26 x 26, batch 53, 46.6 and 28.5).
     const int64_t blocks128 = (int64_t)a.groups * a.tiles_h * a.tiles_w * (a.zfill ? 1 : s * s) * ceil_div(Crow, 128);
-    const bool fills128 = Crow > 64 && blocks128 >= 256 && px == kPxWg;
-    g.rows = fills128 && s == 2 && !a.double_buffer ? 128 : 64;
-    g.priced128 = fills128 && !(ring1_applies(g) && blocks128 <= 1024);
+    g.rows = Crow > 64 && blocks128 >= 256 && px == kPxWg && s == 2 && !a.double_buffer ? 128 : 64;
     a.div_tw = make_fastdiv((uint32_t)a.TW);
     a.div_thw = make_fastdiv((uint32_t)(a.TH * a.TW));
     a.div_sw = make_fastdiv((uint32_t)a.SW);
@@ -1304,16 +1301,8 @@ daq_status launch_stream(const char* name, const daq_conv_desc& d, const daq_lay
 static OtherKernel as_other(const Geometry& g) {
     const HaloArgs& a = g.a;
     const int taps = max_taps(a);
-    // The prices are those of the forms and grids they were fitted to: tiles of 128 rows where those would fill the chip, a strided layer's tiles
-    // by the eight.  (Such products have become 1.1 to 1.7 times faster since.)
-    const TileForm form = g.priced128         ? TileForm::kRows128
-                          : ring1_applies(g)  ? TileForm::kRing1
-                          : taps9_applies(g)  ? TileForm::kTaps9
-                          : a.Crow <= 32      ? TileForm::kNarrow
-                                              : TileForm::kTaps;
-    const bool classes = a.stride > 1 && !a.zfill;
-    const int64_t tiles = classes ? round_up((int64_t)a.groups * a.tiles_h * a.tiles_w, 8) * a.stride * a.stride : blocks_per_row_tile(a);
-    return OtherKernel{form, a.stride > 1, tiles * ceil_div(a.Crow, g.priced128 ? 128 : 64), taps * (int)ceil_div(a.cp, kKc)};
+    const TileForm form = ring1_applies(g) ? TileForm::kRing1 : taps9_applies(g) ? TileForm::kTaps9 : a.Crow <= 32 ? TileForm::kNarrow : TileForm::kTaps;
+    return OtherKernel{form, a.stride > 1, blocks_per_row_tile(a) * ceil_div(a.Crow, 64), taps * (int)ceil_div(a.cp, kKc)};
 }
 
 bool bwd_data_halo_supported(const daq_conv_desc& d) { return plan_bwd(d).ok; }

@@ -299,7 +299,7 @@ int64_t stream_deal(int64_t out_bytes, int64_t plane_bytes, int cp, int pairs, i
 // the layer otherwise, with its workgroups and the steps (tap x 64 channels) of each; false: that is the faster one by the two's cost
 // models, or these kernels do not serve the layer, and nothing was launched.
 struct DwTail;
-enum class TileForm { kTaps9, kRows128, kNarrow, kTaps, kRing1, kNhwc };
+enum class TileForm { kTaps9, kNarrow, kTaps, kRing1, kNhwc };
 struct OtherKernel {
     TileForm form;
     bool classes;      // a strided data gradient, by parity class

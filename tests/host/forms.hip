@@ -59,11 +59,21 @@ static void waves_of_tiles() {
     EXPECT(!wide_waves(512, 1, 25) && !wide_waves(1428, 3, 25) && !wide_waves(912, 3, 25) && !wide_waves(888, 6, 25) && !wide_waves(1053, 4, 7));
 }
 
+// Products of few tiles: the kernel without staging or the tile kernel, as that is now.
+static void few_tiles() {
+    auto fwd = [](const daq_conv_desc& d) { return product_direct_waves(false, d, false) > 0; };
+    auto bwd = [](const daq_conv_desc& d) { return product_direct_waves(true, d, false) > 0; };
+    EXPECT(!bwd(layer(2, 208, 27, 27, 637, 3, 1)) && !bwd(layer(9, 32, 35, 35, 288, 3, 1)) && !bwd(layer(4, 112, 23, 23, 240, 3, 1)));   // 1.15 to 1.35 times the time
+    EXPECT(bwd(layer(4, 48, 31, 31, 554, 1, 1)) && bwd(layer(10, 240, 9, 9, 528, 1, 1)));                                                // 1.2 the other way
+    EXPECT(fwd(layer(16, 224, 12, 12, 400, 5, 1)) && fwd(layer(13, 176, 11, 11, 480, 5, 1)) && fwd(layer(1, 368, 6, 6, 808, 3, 1)));
+}
+
 int main() {
     long_filter_gradients();
     dealt_blocks();
     order_of_tiles();
     waves_of_tiles();
+    few_tiles();
     std::printf("%d failures\n", fails);
     return fails != 0;
 }
