@@ -105,8 +105,9 @@ int choose_splits(const Plan32& pl, int depth) {
     return s;
 }
 
-// The split where a later kernel takes the reduction along, from 33 splits on (dw_tail_worthwhile): its launch, 2.8 of its 3.3 us, is
-// saved.  (7 -> 106, 3 x 3 on 99 x 12, batch 30, both gradients: 23 us with 25 splits and a reduction, 21 with 64.)
+// The split where a later kernel takes the reduction along, from 33 splits on (dw_tail_worthwhile): 2.8 us for its launch are
+// saved.  (Whatever the model charges for launch and reduction together: 150 layers, both gradients, with 2.2 and 1.5 up to 0.87 of the speed at
+// stride 2, 3.5 and 5 within 0.1 %.  7 -> 106, 3 x 3 on 99 x 12, batch 30, both gradients: 23 us with 25 splits and a reduction, 21 with 64.)
 int choose_splits_tail(const Plan32& pl) {
     const SplitModel m = split_model(pl, 1);
     const int64_t top = std::min(m.limit, m.n);

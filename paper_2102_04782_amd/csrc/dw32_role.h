@@ -47,6 +47,7 @@ struct DwBeside {
 };
 bool bwd_filter_beside(const daq_conv_desc& d, Plan32 pl, const int8_t* qx, const float* s_x, const int8_t* vq, const float* s_chan, float* dW,
                        int32_t* acc, void* ws, int max_blocks, double other_us, bool other_streams, DwBeside& out);
+double beside_data_us(bool nine_taps, int chunks);   // conv_mfma_halo.hip: time of the data gradient's part of that launch
 
 namespace {
 

@@ -68,12 +68,24 @@ static void few_tiles() {
     EXPECT(fwd(layer(16, 224, 12, 12, 400, 5, 1)) && fwd(layer(13, 176, 11, 11, 480, 5, 1)) && fwd(layer(1, 368, 6, 6, 808, 3, 1)));
 }
 
+// Both gradients in one launch: the filter gradient's splits by the time of the data gradient's part as it is now.
+static void joint_launch() {
+    auto splits = [](const daq_conv_desc& d, int blocks_left, int chunks) {
+        DwBeside w;
+        const Plan32 pl = make_plan32(d);
+        if (!bwd_filter_beside(d, pl, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, reinterpret_cast<void*>(256), blocks_left, beside_data_us(true, chunks), false, w)) return 0;
+        return w.a.splits;
+    };
+    EXPECT(splits(layer(26, 112, 11, 11, 80, 3, 1), 204, 2) > 1 && splits(layer(8, 16, 17, 17, 80, 3, 1), 238, 2) > 1 && splits(layer(4, 36, 28, 28, 128, 3, 1), 224, 2) > 1);
+}
+
 int main() {
     long_filter_gradients();
     dealt_blocks();
     order_of_tiles();
     waves_of_tiles();
     few_tiles();
+    joint_launch();
     std::printf("%d failures\n", fails);
     return fails != 0;
 }
