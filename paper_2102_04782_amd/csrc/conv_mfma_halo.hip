@@ -97,7 +97,7 @@ constexpr int kMaxPhases = 4;
 constexpr int kRingA = 4;          // filter tiles are requested kRingA - 1 steps ahead of their use
 constexpr uint32_t kOob = 0x80000000u;  // a buffer offset past every extent: such a load returns zeros
 
-struct HaloArgs {
+struct alignas(64) HaloArgs {
     // What a workgroup finds its tile by, in one line of 64 bytes: arguments arrive in such lines, a quarter of a microsecond each when one is asked for
     // behind another.  Then what it needs up to its first loads.
     int main_blocks;      // the product's workgroups; those behind them finish a deferred filter gradient (tail)
@@ -1132,7 +1132,8 @@ enum BothForm { kBothRing1, kBothTaps9, kBothOneChunk, kBothNarrow, kBothRing1S2
 constexpr int kBothBlocks = 256;
 
 template <bool K11, int FORM>
-__global__ __launch_bounds__(512, 1) void k_bwd_both(Dw32Args w, HaloArgs x, int w_blocks, int x_first) {
+__global__ __launch_bounds__(512, 1) void k_bwd_both(int w_blocks, int x_first, Dw32Args w, HaloArgs x) {
+    asm volatile("" ::"s"(w_blocks), "s"(w.part), "s"(w.x_frame), "s"(x.main_blocks));   // the first lines of arguments of either part, asked for at once
     const int b = (int)blockIdx.x;
     if (b < x_first) {   // uniform
         if (b >= w_blocks) return;
@@ -1374,7 +1375,7 @@ bool conv_bwd_both_small(const daq_conv_desc& d, const Plan32& plan_w, const int
     if (w.k11 == K && form == F) {                                                                                   \
         auto kern = k_bwd_both<K, F>;                                                                                \
         if (!allow_lds((const void*)kern, lds)) return DAQ_ERR_HIP;                                                  \
-        DAQ_LAUNCH("conv_bwd_both", st, hipLaunchKernelGGL(kern, grid, dim3(512), lds, st, w.a, a, w.blocks, x_first)); \
+        DAQ_LAUNCH("conv_bwd_both", st, hipLaunchKernelGGL(kern, grid, dim3(512), lds, st, w.blocks, x_first, w.a, a)); \
         return w.tail.blocks > 0 ? launch_dw_reduce(w.tail, 1, st) : DAQ_OK;                                         \
     }
         DAQ_BOTH(false, kBothTaps9) DAQ_BOTH(false, kBothOneChunk) DAQ_BOTH(false, kBothNarrow)
