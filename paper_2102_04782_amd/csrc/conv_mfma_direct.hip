@@ -236,35 +236,39 @@ DirectPlan plan_direct(bool backward, const daq_conv_desc& d) {
     return g;
 }
 
-// Both sides' costs in us, one launch between events, fitted to products of random layers (here to 992, there to 680 as the forms are now); MB of result included:
+// Both sides' costs in us, one launch between events, fitted to products of random layers (here and the last two columns there to 992, the others to 680 as
+// the forms are now); MB of result included:
 //     here   7.6 + 0.13 * steps of a wave + 27 * thousands of steps a CU + 0.27 * MB (by parity class, every other pixel of a line: 0.55)
 //            + 0.09 * (tiles a CU beyond 40) + 0.28 * (MB of source beyond 16, which the L2s no longer hold)
 //     there  fixed + (step + turn * max(1, workgroups / 256)) * steps of a workgroup + mb * MB
-// These kernels are taken where they are 3 % faster by that (not for 1 x 1 layers of many workgroups): of the 680 products 44 then go to the form
-// that is more than 2 % slower, 0.991 of the speed of the better one on average.  E.g. 768 -> 52, 5 x 5, 6 images of 5 x 5, 97 us there and 14 here; 3 -> 96, 7 x 7
-// stride 2, 23 of 16 x 16, 46 and 7; 256 -> 304, 5 x 5, 3 of 15 x 15, 37 and 20; but 208 <- 637, 3 x 3, 2 of 27 x 27, 13.8 and 18.6.
+// These kernels are taken where they are 3 % faster by that, 20 % from 60 us on, where few were fitted (1280 <- 824, 5 x 5, 17 of 7 x 7, 102 us there and 134
+// here): of 1080 products 80 then go to the form that is more than 2 % slower (114 with the prices of the
+// forms before: 208 <- 637, 3 x 3, 2 of 27 x 27, went here, 18.6 us, 13.8 there).  E.g. 768 -> 52, 5 x 5, 6 images of 5 x 5, 97 us there and 14 here; 3 -> 96, 7 x 7
+// stride 2, 23 of 16 x 16, 46 and 7; 256 -> 304, 5 x 5, 3 of 15 x 15, 37 and 20.
+//   The model holds less well for the 1 x 1 ring form, several workgroups of which share a CU, and the re-staging form (13 to 20 % off: 512 <- 2048 at 7 x 7, batch 128,
+// 23.4 us there, 47 here): against those these have to be 7 % faster, 20 % from 30 us on, and not for 1 x 1 layers of many workgroups; and forward
+// + 2 * MB of filter, which the launch before has just written, count here (against the other forms that sent 400 <- 224, 5 x 5, 16 of 12 x 12, there, with
+// the quantizers 61 us, 49.5 here; of 120 forward products 12 to the slower form, 3 without it).
 // The line about large tensors came from products of 5 to 130 MB of source: 1219 -> 16 1 x 1, 16 of 63 x 50, 27 there and 35
 // here, 1093 -> 16, 64 of 31 x 17, 17 and 23; 7 -> 4 3 x 3, 71 of 135 x 135, 36 and 49; 5 <- 10 5 x 5 stride 2, 101 of 123 x 123, 45 and 57.  It does
-// not count against the re-staging form, whose own cost such products are further above its fit (3 -> 96 3 x 3 stride 2, 39 of 133 x 133, 56 there and 32 here);
-// against that form these have to be 7 % faster, 20 % from 30 us on, where its fit is worse, and forward + 2 * MB of filter, which the launch before has just
-// written, count here (against the tile kernel as it is now that cost both: 3 instead of 12 of 120 forward products then go to the slower form; 400 <- 224, 5 x 5,
-// 16 of 12 x 12, with the quantizers 61 us there and 49.5 here).
+// not count against the re-staging form, whose own cost such products are further above its fit (3 -> 96 3 x 3 stride 2, 39 of 133 x 133, 56 there and 32 here).
 bool faster(const DirectPlan& g, const OtherKernel& o, int classes, bool bf16) {
     struct Cost { double fixed, step, turn, mb; };
     //                             3 x 3                       32 rows at most            any taps                    1 x 1, ring                  re-staging
-    static const Cost kUnit[] = {{6.74, -0.089, 0.195, 0.303}, {7.04, 0.061, 0.187, 0.17}, {7.95, 0.1, 0.205, 0.242}, {6.12, -0.355, 0.679, 0.257}, {11.6, -1.53, 2.13, 0.4}};
-    static const Cost kClasses[] = {{0, 0, 0, 0}, {7.21, 0.275, 0.007, 0.328}, {8.0, 0.095, 0.26, 0.285}, {7.12, 0.429, 0.0, 0.236}, {0, 0, 0, 0}};
+    static const Cost kUnit[] = {{6.74, -0.089, 0.195, 0.303}, {7.04, 0.061, 0.187, 0.17}, {7.95, 0.1, 0.205, 0.242}, {5.6, -0.35, 0.69, 0.32}, {11.6, -1.53, 2.13, 0.4}};
+    static const Cost kClasses[] = {{0, 0, 0, 0}, {7.21, 0.275, 0.007, 0.328}, {8.0, 0.095, 0.26, 0.285}, {8.0, 0.1, 0.1, 0.2}, {0, 0, 0, 0}};
     const DirectArgs& a = g.a;
     const double mb = (double)a.N * a.Crow * a.Hd * a.Wd * (bf16 ? 2 : 4) * 1e-6;
     const double steps = (double)ceil_div((int64_t)a.T * a.upt, 2 * classes), tiles = (double)a.tiles * classes;
+    const bool rough = o.form == TileForm::kRing1 || o.form == TileForm::kNhwc;
     const double here = 7.6 + 0.13 * steps / g.ks + 27.0 * tiles * steps / 256e3 + (classes > 1 ? 0.55 : 0.27) * mb +
-                        (a.fwd && o.form == TileForm::kNhwc ? 2e-6 * a.wfrag_bytes : 0.0);
+                        (a.fwd && rough ? 2e-6 * a.wfrag_bytes : 0.0);
     const double read = 1e-6 * a.src_bytes / (a.fwd && a.T == 1 ? a.sH * a.sW : 1);
     const double large = o.form == TileForm::kNhwc ? 0.0 : 0.09 * std::max(0.0, tiles / 256.0 - 40.0) + 0.28 * std::max(0.0, read - 16.0);
     const Cost& c = (o.classes ? kClasses : kUnit)[(int)o.form];
     const double held = o.form == TileForm::kNhwc ? 512.0 : 256.0;
     const double there = c.fixed + (c.step + c.turn * std::max(1.0, (double)o.blocks / held)) * o.steps + c.mb * mb;
-    const double margin = o.form != TileForm::kNhwc ? 0.97 : there < 30.0 ? 0.93 : 0.8;
+    const double margin = there > (rough ? 30.0 : 60.0) ? 0.8 : rough ? 0.93 : 0.97;
     return (o.form != TileForm::kRing1 || o.blocks <= 512) && here + large < margin * there;
 }
 

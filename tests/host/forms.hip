@@ -64,7 +64,9 @@ static void few_tiles() {
     auto fwd = [](const daq_conv_desc& d) { return product_direct_waves(false, d, false) > 0; };
     auto bwd = [](const daq_conv_desc& d) { return product_direct_waves(true, d, false) > 0; };
     EXPECT(!bwd(layer(2, 208, 27, 27, 637, 3, 1)) && !bwd(layer(9, 32, 35, 35, 288, 3, 1)) && !bwd(layer(4, 112, 23, 23, 240, 3, 1)));   // 1.15 to 1.35 times the time
-    EXPECT(bwd(layer(4, 48, 31, 31, 554, 1, 1)) && bwd(layer(10, 240, 9, 9, 528, 1, 1)));                                                // 1.2 the other way
+    EXPECT(bwd(layer(8, 896, 29, 29, 16, 7, 1)) && bwd(layer(64, 272, 9, 9, 129, 7, 1)) && bwd(layer(3, 168, 56, 56, 960, 3, 2)));        // 1.1 to 1.45 the other way
+    EXPECT(!bwd(layer(17, 1280, 7, 7, 824, 5, 1)) && !bwd(layer(6, 976, 64, 64, 765, 3, 2)));                                              // large ones, 1.05 to 1.3
+    EXPECT(!bwd(layer(128, 512, 7, 7, 2048, 1, 1)) && !product_direct_waves(true, layer(128, 512, 7, 7, 2048, 1, 1), true) && !bwd(layer(64, 320, 7, 7, 1280, 1, 1)));   // twice
     EXPECT(fwd(layer(16, 224, 12, 12, 400, 5, 1)) && fwd(layer(13, 176, 11, 11, 480, 5, 1)) && fwd(layer(1, 368, 6, 6, 808, 3, 1)));
 }
 
