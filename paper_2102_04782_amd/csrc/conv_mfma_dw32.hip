@@ -200,7 +200,7 @@ Plan32 make_plan32(const daq_conv_desc& d, int depth) {
     if (Lx.row_pitch > (pl.s2 ? ring32_max_pitch<true>() : ring32_max_pitch<false>())) return pl;
     const int64_t t64 = ceil_div(d.Cout, 64) * ceil_div(d.Cin, 64);
     if (t64 >= 256 && !pl.s2) { pl.wm = 2; pl.wn = 2; pl.wk = 1; }
-    else { pl.wm = 1; pl.wn = 1; pl.wk = 8; }   // eight waves: two per SIMD, so that one's LDS phase overlaps the other's MFMAs
+    else { pl.wm = 1; pl.wn = 1; pl.wk = 8; }   // the ring: one tile of 32 x 32 to a workgroup, eight waves (dw32_ring_role)
     const int bm = 32 * pl.wm, bn = 32 * pl.wn;
     pl.tiles_m = (int)ceil_div(d.Cout, bm);
     pl.tiles_n = (int)ceil_div(d.Cin, bn);

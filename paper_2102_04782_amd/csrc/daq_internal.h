@@ -245,7 +245,8 @@ struct Plan32 {
     bool ok;              // these kernels serve the layer; an entry point makes its plan once and hands it on
     bool k11;             // 1 x 1 filter: the plain GEMM kernel
     bool s2;              // 3 x 3 filter at stride 2: four stride-phase planes per input channel
-    int wm, wn, wk, splits, tiles_m, tiles_n, nchunks, pb, b_units, ch;
+    int wm, wn, wk;       // tiles of a workgroup along co and ci; waves that share them: 1, or 8 (1 x 1: a K step each; 3 x 3: four multiply and four ask)
+    int splits, tiles_m, tiles_n, nchunks, pb, b_units, ch;
     int splits_tail;      // K splits where the reduction can ride along in the next kernel (with `defer`)
     int bands_m, bands_n, band_m, band_n;   // rectangles of the tile grid per K split when there are 1, 2 or 4 splits (else 0)
     int64_t blocks;       // workgroups of the launch

@@ -328,7 +328,8 @@ struct Ring32 {
     __host__ __device__ static constexpr int window_of(int m) { int w = 0; while (m >= window(w).taps) m -= window(w++).taps; return w; }   // of multiply m
     __host__ __device__ static constexpr int column_of(int m) { int w = 0; while (m >= window(w).taps) m -= window(w++).taps; return m; }
 };
-// Row pitches it serves (the last window of a chunk ends with slot column UP - 1), and the slots of a row that are filled.
+// Row pitches it serves (slot column UP - 1, with which the last window of a chunk may end, is reached at 63 and 127 only; longer rows than these
+// have always gone to the tap-table kernel, and were not timed here), and the slots of a row that are filled.
 template <bool S2>
 constexpr int ring32_max_pitch() { return S2 ? 54 : 123; }
 inline int ring32_units(bool s2, int row_pitch) { return 16 + (s2 ? row_pitch : 2 * row_pitch) / 16 + 1; }
@@ -816,7 +817,7 @@ __device__ __forceinline__ void dw11_role(Dw32Args& p, const int bid) {
     constexpr int SLOTS = 64;
     v4i own[2];   // WK = 8: the two quads of slots (four consecutive registers of one tile) this wave owns
     if constexpr (WK > 1) {
-        // parallel combine of the eight waves as in k_dw32, in one round: 16 quads, two per wave,
+        // parallel combine of the eight waves, each of which has a part of the whole tile, in one round: 16 quads, two per wave,
         // hand-over area [quad][source wave][lane] of 16-byte entries
         static_assert(WK == 8, "the combine below is laid out for eight waves");
         v4i* red4 = reinterpret_cast<v4i*>(lds);
